@@ -31,6 +31,9 @@ def algo_bytes_iter(db):
 def phase_bytes(db):
     """Compulsory bytes per voxel of each phase (every array it reads or
     writes, once), duals and the y4 intermediate in db bytes."""
+    if db == 4:
+        # one sweep does the whole iteration: every state word once each way, v
+        return {"sweep_a": algo_bytes_iter(4)}
     return {
         # reads u, w1 (6), w2 (6), v, s, t (FP32) and y1 (2), y2 (2), y4, y3
         # (steps 1, 4, 5, 11, 12, the u' part of 14 and the inputs of the l1
@@ -123,7 +126,7 @@ def copy_ceiling():
 
 
 def read_traffic(path, cube):
-    """HBM bytes per launch of sweep A from the stored counter summary, or None
+    """HBM bytes per launch of the (first) sweep from the stored counter summary, or None
     when it is missing, for another cube, or taken from other kernel sources."""
     if not os.path.exists(path):
         return None

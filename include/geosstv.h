@@ -163,6 +163,12 @@ int geo_step(geo_dims dims, const geo_params *p, const float *v,
  * iteration on `stream` (instrumentation for benchmarks; the events add a
  * few microseconds per iteration). phase_ms (host, GEO_NPHASE doubles)
  * receives the summed GPU time of each phase over the call:
+ * With FP32 duals:
+ *   0 the fused sweep (steps 1-14)
+ *   1 the histogram passes of l1-ball thresholds whose search missed
+ *   2 the end of the iteration: the l2-ball factor of step 15, the stopping
+ *              rule, and the exact soft-threshold search of the next iteration
+ * With BF16 duals:
  *   0 sweep A  (steps 1, 4, 5, 11, 12 and the u' part of 14 fused, plus the
  *              inputs of the threshold search)
  *   1 the exact soft-threshold search of the two l1-ball projections

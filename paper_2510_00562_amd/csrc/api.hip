@@ -25,7 +25,6 @@ Layout make_layout(int n1, int n2, int n3, int dual_storage)
     const size_t fd = N * db;
     L.dual_bytes = db;
     L.max_tiles = max_tiles(n1, n2, n3);
-    L.n_part = 2 * L.max_tiles + sweep_b_blocks((int64_t)N);
     L.cap = (int64_t)N / 16 > 65536 ? (int64_t)N / 16 : 65536;
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -34,14 +33,15 @@ Layout make_layout(int n1, int n2, int n3, int dual_storage)
         return at;
     };
     L.scalars = take(sizeof(DevScalars));
-    L.partials = take(sizeof(double) * (size_t)L.n_part);
+    // partial sums: 3 per tile, or 2 per tile and one per sweep B block (BF16)
+    L.partials = take(sizeof(double) * (3 * (size_t)L.max_tiles + (db == 2 ? sweep_b_blocks((int64_t)N) : 0)));
     L.hist = take(6 * sizeof(Hist));  // 3 radix levels x 2 fields
     L.rec = take(6 * sizeof(FbRec));
-    L.y4p = take(fd);
-    L.winpart = take(sizeof(double) * 2 * 3 * (size_t)L.max_tiles);
-    L.cand = take(sizeof(float) * 2 * (size_t)L.cap);
+    if (db == 2) L.y4p = take(fd);
+    L.winpart = take(sizeof(double) * 2 * 4 * (size_t)L.max_tiles);
+    L.cand = take((db == 2 ? sizeof(float) : sizeof(float4)) * 2 * (size_t)L.cap);
+    if (db == 2) L.zbuf = take(2 * f4);
     L.ccount = take(sizeof(uint32_t) * 2 * (size_t)L.max_tiles);
-    L.zbuf = take(2 * f4);
     L.table = take(table_bytes(1));
     for (int p = 0; p < 2; ++p) {
         L.u[p] = take(f4);
@@ -263,8 +263,8 @@ int geo_state_init(geo_dims dims, const geo_params *p, const float *v, void *ws,
 
 // One solver call over n cubes (n = 1: the single-cube entry points). The
 // launch table (host image `ent`, device copy at `table`) is written once;
-// each launch slot (sweep A, search, the three histogram passes of a missed
-// window, sweep B, finalize) completes one iteration of every busy cube.
+// each launch slot (the three histogram passes of a missed window, the sweep,
+// the search) completes one iteration of every busy cube.
 // With a tolerance the host reads the stopping flags every check_every
 // slots; the device idles a cube once it has met its rule or done n_iter
 // iterations.
@@ -295,15 +295,14 @@ static int run_cubes(int n, const geo_dims *dims, const geo_params *p, const flo
     sh.ncubes = n;
     for (int c = 0; c < n; ++c) {
         int nt = 0, nb = 0;
-        cube_entry(&ent[c], to_dims(dims[c]), v[c], ws[c], L[c], p[c].omega, p[c].mu_lo, p[c].mu_hi,
-                   p[c].band_chunk, sh.total_tiles, sh.total_b, &nt, &nb);
+        cube_entry(&ent[c], to_dims(dims[c]), v[c], ws[c], L[c], &p[c], n_iter, sh.total_tiles, sh.total_b, &nt, &nb);
         // the workspace's per-tile regions hold every chunk band_chunk gives
         // (make_layout); this only guards that invariant
         if (nt > L[c].max_tiles) return GEO_EWORKSPACE;
         sh.total_tiles += nt;
         sh.total_b += nb;
+        sh.b_kinds |= sweep_b_cpt(dims[c].n2) == 4 ? 2 : 1;
         sh.shape_tiles[tile_shape(dims[c].n1, dims[c].n2, L[c].dual_bytes)] += nt;
-        sh.b_kinds |= sweep_b_cpt(dims[c].n2, L[c].dual_bytes) == 4 ? 2 : 1;
     }
     sh.grid_a = sweep_a_grid(L[0].dual_bytes, sh.total_tiles);
     sh.fb_grid = fallback_grid();
@@ -313,8 +312,7 @@ static int run_cubes(int n, const geo_dims *dims, const geo_params *p, const flo
     std::vector<unsigned char> img(table_bytes(n), 0);
     memcpy(img.data(), ent.data(), (size_t)n * sizeof(CubeEntry));
     int rc = hip_status(hipMemcpyAsync(table, img.data(), img.size(), hipMemcpyHostToDevice, st));
-    for (int c = 0; c < n && !rc; ++c)
-        rc = hip_status(launch_begin_call(ws[c], L[c], p[c].tol, p[c].alpha, p[c].beta, n_iter, st));
+    if (!rc) rc = hip_status(launch_begin(table, (int)sizeof(CubeEntry), n, st));
     if (rc) return rc;
     const int nev = nph == 1 ? 2 : 4;
     // calls shorter than the sampling period time every slot
@@ -397,7 +395,8 @@ static int run_cubes(int n, const geo_dims *dims, const geo_params *p, const flo
                     float ms = 0.f;
                     rc = hip_status(hipEventElapsedTime(&ms, ev[(size_t)nev * q + ph],
                                                         ev[(size_t)nev * q + ph + 1]));
-                    phase_ms[ph] += ms;
+                    // FP32, in the order of its launches: passes (phase 1), sweep (0), search (2)
+                    phase_ms[nph == 1 || ph == 2 || L[0].dual_bytes == 2 ? ph : 1 - ph] += ms;
                 }
         behind = 0;
         for (int c = 0; c < n; ++c) {
@@ -420,12 +419,13 @@ static int run_cubes(int n, const geo_dims *dims, const geo_params *p, const flo
             o.converged = (p[c].tol > 0.0 && x.stop && !x.nonfinite) ? 1 : 0;
             o.rel_change = x.rel;
             o.r = x.r;
-            o.tau_s = x.sel[0].tau;
-            o.tau_t = x.sel[1].tau;
+            const bool ahead = L[c].dual_bytes == 4;
+            o.tau_s = ahead ? x.tau_used[0] : x.sel[0].tau;
+            o.tau_t = ahead ? x.tau_used[1] : x.sel[1].tau;
             o.total_iters = (int32_t)x.iter;
-            o.fallback_passes = (int32_t)x.fallback;
-            o.cand_s = (int32_t)x.sel[0].cand_count;
-            o.cand_t = (int32_t)x.sel[1].cand_count;
+            o.fallback_passes = (int32_t)(ahead ? x.missed[0] + x.missed[1] : x.fallback);
+            o.cand_s = (int32_t)(ahead ? x.cand_used[0] : x.sel[0].cand_count);
+            o.cand_t = (int32_t)(ahead ? x.cand_used[1] : x.sel[1].cand_count);
             o.slots = (int32_t)slots;
         }
         const int own = x.nonfinite ? GEO_ENONFINITE : (p[c].tol > 0.0 && !x.stop ? GEO_MAXITER : GEO_OK);

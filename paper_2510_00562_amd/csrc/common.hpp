@@ -118,6 +118,116 @@ __device__ __forceinline__ float ld_nt(const bf16 *p)
     return __uint_as_float(((uint32_t)__builtin_nontemporal_load(&p->bits)) << 16);
 }
 
+// Value as stored (FP32 or rounded to BF16).
+__device__ __forceinline__ float as_stored(const float *, float x) { return x; }
+__device__ __forceinline__ float as_stored(const bf16 *, float x)
+{
+    bf16 b;
+    st(&b, x);
+    return ld(&b);
+}
+
+// Soft threshold of the l1-ball projections.
+__device__ __forceinline__ float soft(float z, double tau)
+{
+    const double m = fabs((double)z) - tau;
+    return m > 0.0 ? copysignf((float)m, z) : 0.0f;
+}
+
+// One band of an array through the buffer path: a resource over the band
+// (uniform base and size) and a 32-bit byte offset per lane. A lane whose
+// offset lies past the band (kNoPix of any element size) loads zeros and
+// stores nothing, so code full of edge conditions stays straight-line: no
+// branches around the accesses, one 32-bit offset for every array of an
+// element size, and the compiler knows exactly how many loads are in flight
+// when one of them is needed.
+using BandRsrc = __amdgpu_buffer_rsrc_t;
+constexpr uint32_t kNoPix = 0x0c000000u;  // times 2, 4, 8, 16: past any band (< 2^27 bytes)
+template <typename T>
+__device__ __forceinline__ BandRsrc band_of(const T *p, int64_t first, uint32_t count)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(p + first), 0, (int)(count * (uint32_t)sizeof(T)), 0x00020000);
+}
+constexpr int kNT = 2;  // the nontemporal hint of a buffer access
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <int AUX = 0>
+__device__ __forceinline__ float bld(const float *, BandRsrc r, uint32_t pix)
+{
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, pix * 4u, 0, AUX));
+}
+template <int AUX = 0>
+__device__ __forceinline__ float bld(const bf16 *, BandRsrc r, uint32_t pix)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, pix * 2u, 0, AUX) << 16);
+}
+__device__ __forceinline__ u32x2 bld_raw(const float2 *, BandRsrc r, uint32_t pix)
+{
+    return __builtin_amdgcn_raw_buffer_load_b64(r, pix * 8u, 0, 0);
+}
+__device__ __forceinline__ uint32_t bld_raw(const bf16x2 *, BandRsrc r, uint32_t pix)
+{
+    return __builtin_amdgcn_raw_buffer_load_b32(r, pix * 4u, 0, 0);
+}
+__device__ __forceinline__ u32x4 bld_raw(const float4 *, BandRsrc r, uint32_t pix)
+{
+    return __builtin_amdgcn_raw_buffer_load_b128(r, pix * 16u, 0, 0);
+}
+// the pair in a raw word or two
+__device__ __forceinline__ float2 pair_of(u32x2 x) { return make_float2(__uint_as_float(x.x), __uint_as_float(x.y)); }
+__device__ __forceinline__ float2 pair_of(uint32_t b)
+{
+    return make_float2(__uint_as_float(b << 16), __uint_as_float(b & 0xffff0000u));
+}
+__device__ __forceinline__ void bst(const float *, BandRsrc r, uint32_t pix, float x)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, pix * 4u, 0, 0);
+}
+__device__ __forceinline__ void bst_nt(const float *, BandRsrc r, uint32_t pix, float x)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, pix * 4u, 0, kNT);
+}
+__device__ __forceinline__ void bst_nt(const bf16 *, BandRsrc r, uint32_t pix, float x)
+{
+    bf16 b;
+    st(&b, x);
+    __builtin_amdgcn_raw_buffer_store_b16(b.bits, r, pix * 2u, 0, kNT);
+}
+__device__ __forceinline__ void bst_nt(const float2 *, BandRsrc r, uint32_t pix, float2 x)
+{
+    u32x2 v;
+    v.x = __float_as_uint(x.x);
+    v.y = __float_as_uint(x.y);
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, pix * 8u, 0, kNT);
+}
+__device__ __forceinline__ void bst_nt(const bf16x2 *, BandRsrc r, uint32_t pix, float2 x)
+{
+    bf16 a, b;
+    st(&a, x.x);
+    st(&b, x.y);
+    __builtin_amdgcn_raw_buffer_store_b32((uint32_t)a.bits | ((uint32_t)b.bits << 16), r, pix * 4u, 0, kNT);
+}
+__device__ __forceinline__ void bst_nt(const float4 *, BandRsrc r, uint32_t pix, float4 x)
+{
+    u32x4 v;
+    v.x = __float_as_uint(x.x);
+    v.y = __float_as_uint(x.y);
+    v.z = __float_as_uint(x.z);
+    v.w = __float_as_uint(x.w);
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, pix * 16u, 0, kNT);
+}
+// one component (c = 0 first, 1 second) of a stored pair
+__device__ __forceinline__ void bst_comp_nt(const float2 *, BandRsrc r, uint32_t pix, int c, float x)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, pix * 8u + 4u * (uint32_t)c, 0, kNT);
+}
+__device__ __forceinline__ void bst_comp_nt(const bf16x2 *, BandRsrc r, uint32_t pix, int c, float x)
+{
+    bf16 b;
+    st(&b, x);
+    __builtin_amdgcn_raw_buffer_store_b16(b.bits, r, pix * 4u + 2u * (uint32_t)c, 0, kNT);
+}
+
 struct Dims {
     int n1, n2, n3;
     int64_t plane;  // N = n1*n2*n3 (distance between planes of a field)
@@ -143,12 +253,33 @@ __device__ __forceinline__ void shrink2(float &a, float &b, float thr)
     b *= f;
 }
 
-// Wavefront-wide sum of a double (64 lanes).
+// x moved between lanes by a DPP control (lanes without a source get 0).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_double(double x)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xf, true);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Wavefront-wide sum of a double (64 lanes), the same in every lane: within
+// rows of 16 lanes by shifts of 1, 2, 4, 8, then across the rows, by DPP moves
+// of the vector unit. As cross-lane LDS moves (six dependent round trips, two
+// moves each, queueing on one unit per CU) the sums of eleven values by the 16
+// wavefronts of a sweep tile took about 4 us.
 __device__ __forceinline__ double wave_sum(double x)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
+    x += dpp_double<0x111, 0xf>(x);  // row_shr:1
+    x += dpp_double<0x112, 0xf>(x);  // row_shr:2
+    x += dpp_double<0x114, 0xf>(x);  // row_shr:4
+    x += dpp_double<0x118, 0xf>(x);  // row_shr:8: lane 15 of a row holds its sum
+    x += dpp_double<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+    x += dpp_double<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3: lane 63
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
 // Block-wide sum for blocks of up to 1024 threads; result valid in thread 0.
@@ -187,22 +318,36 @@ __device__ __forceinline__ uint32_t lvl_exponent(int level, uint32_t prefix, int
 }
 
 // The inputs of the two l1-ball projections (steps 2 and 3 of Alg. 1) and
-// y4, written with explicit rounding operations so that every kernel that
-// evaluates them (both sweeps and the fallback threshold search) gets
-// bit-identical values. y4 is stored as q = 5 y4' - v, the residual of the
-// fidelity ball before step 15 rescales it, and read as y4 = a q with a
-// device factor a (max(0, 1 - eps/||q||) / 5 after an iteration).
-__device__ __forceinline__ float y4_of(float q, float a) { return __fmul_rn(a, q); }
-__device__ __forceinline__ float zs_of(float s, float y4) { return __fsub_rn(s, y4); }
-// y3m = y3 at (i-1) (0 on the first row), y3c = y3 at i masked by m_v(i),
-// step the step size of t (1/3 here; 1/5 for the comparison regularizers)
+// y4, with every rounding fixed (contraction off, the one fused operation
+// written as such), so that every kernel that evaluates them (the sweeps, the
+// search and the histogram passes) gets bit-identical values: the rounding
+// intrinsics alone do not keep the compiler from fusing them with what
+// follows. y4 is stored as q = 5 y4' - v, the residual of the fidelity ball
+// before step 15 rescales it, and read as y4 = a q with a device factor a
+// (max(0, 1 - eps/||q||) / 5 after an iteration).
+__device__ __forceinline__ float y4_of(float q, float a)
+{
+#pragma clang fp contract(off)
+    return a * q;
+}
+__device__ __forceinline__ float zs_of(float s, float y4)
+{
+#pragma clang fp contract(off)
+    return s - y4;
+}
+// e = y3 at (i-1) (0 on the first row) minus y3 at i masked by m_v(i), step
+// the step size of t (1/3 here; 1/5 for the comparison regularizers)
+__device__ __forceinline__ float zt_of(float t, float e, float y4, float step)
+{
+#pragma clang fp contract(off)
+    const float x = e + y4;
+    return __builtin_fmaf(-step, x, t);
+}
 __device__ __forceinline__ float zt_of(float t, float y3m, float y3c, float y4, float step)
 {
-    return __fsub_rn(t, __fmul_rn(step, __fadd_rn(__fsub_rn(y3m, y3c), y4)));
-}
-__device__ __forceinline__ float zt_of(float t, float y3m, float y3c, float y4)
-{
-    return zt_of(t, y3m, y3c, y4, kStepT);
+#pragma clang fp contract(off)
+    const float e = y3m - y3c;
+    return zt_of(t, e, y4, step);
 }
 
 }  // namespace geo

@@ -1,10 +1,11 @@
-// Exact l1-ball thresholds whose predicted window missed, found inside the
-// same launch slot: three histogram passes over the field (the radix levels
-// of radix.hpp), one launch each, between the window search and sweep B.
-//
+// Exact l1-ball thresholds whose predicted window missed, found inside one
+// launch slot: three histogram passes over the field (the radix levels of
+// radix.hpp), one launch each, before the sweep that needs the thresholds (FP32
+// duals: the search at the end of the slot before left them pending) or between
+// the window search and sweep B or the dual kernel (BF16 duals, comparison
+// regularizers).
 // Each launch is a no-op (its blocks read one flag of the launch and leave)
-// unless the window search of this slot left a field of some working cube
-// pending. The blocks then split the voxels of the cubes with a pending
+// unless a search left a field of some working cube pending. The blocks then split the voxels of the cubes with a pending
 // field evenly, read z_s and z_t where sweep A stored them in this
 // iteration, or else evaluate them from the state exactly as sweep A does
 // (the same rounding operations, so the values are bit-identical), keep the
@@ -247,6 +248,10 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
                         o.prefix = pk.prefix;
                         o.done = pk.done ? 1u : 0u;
                         a.c.rec[level * 2 + f] = o;
+                        // what the sweep of this slot reads of the threshold (no
+                        // pass reads it; the comparison regularizers' dual
+                        // kernel reads the records)
+                        if (o.done) sc->in.set(f, resolved(sc->sel[f], a.c.rec, f, a.c.d.plane));
                     }
                 }
                 __syncthreads();

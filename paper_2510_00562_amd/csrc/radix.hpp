@@ -174,13 +174,24 @@ __device__ RadixPick radix_chain_block(const Hist *hist, int f, double radius, i
     return pk;
 }
 
+// Empty histograms (the three radix levels) of field f, by a block of NT threads.
+template <int NT>
+__device__ __forceinline__ void clear_hist(Hist *hist, int f)
+{
+    for (int q = threadIdx.x; q < 3 * kHistBins; q += NT) {
+        Hist &h = hist[(q / kHistBins) * 2 + f];
+        h.count[q % kHistBins] = 0u;
+        h.msum[q % kHistBins] = 0ull;
+    }
+}
+
 // Append val to this block's slice of a field's candidate list. The slot
 // comes from an LDS counter (wavefront-aggregated), so sweep A never waits on
 // a global atomic; entries past the slice's capacity are counted but
 // dropped, which the search detects as an overflow. Every lane of the
 // wavefront must call it.
-__device__ __forceinline__ void wave_append(bool want, float val, float *slice, uint32_t *lds_count,
-                                            int capb)
+template <typename T>
+__device__ __forceinline__ void wave_append(bool want, const T &val, T *slice, uint32_t *lds_count, int capb)
 {
     const unsigned long long m = __ballot(want);
     if (m == 0ull) return;
@@ -196,12 +207,14 @@ __device__ __forceinline__ void wave_append(bool want, float val, float *slice, 
 // Candidates a window is widened to when the density of |z| near tau is
 // known: the search handles that many in LDS at almost the same cost as a
 // few, and a wider window misses less. Once the windows have held for
-// kCalmNarrow iterations in a row (tau moves smoothly) the narrower fill
-// saves sweep A's appends and the search's bins (256 x 256 x 128: 0.362 ms
-// per iteration at 16384 candidates, 0.357 at 8192, 0.3555 at 4096); from
-// the start it would miss more.
+// kCalmNarrow iterations in a row (tau moves smoothly, and the half-width that
+// the prediction errors ask for is a small part of this) the narrower fill
+// saves the sweep's appends and the search's loads: one batch of 16 per
+// thread instead of two (256 x 256 x 128, search 19 us at 4096 candidates,
+// 13 us at 2048; before that 0.362 ms per iteration at 16384 and 0.3555 at
+// 4096); from the start it would miss more.
 constexpr double kWindowFill = 16384.0;
-constexpr double kWindowFillCalm = 4096.0;
+constexpr double kWindowFillCalm = 2048.0;
 constexpr uint32_t kCalmNarrow = 8;
 
 // Window of |z| that sweep A collects for the next iteration. tau is
@@ -256,6 +269,60 @@ __device__ inline void set_window(SelState &o, bool missed, double budget, doubl
     o.tau_prev3 = h2 ? t2 : 0.0;
     o.tau_prev2 = h1 ? t1 : 0.0;
     o.tau_prev = tau;
+}
+
+// The search state of field f as this slot's sweep and search use it: a
+// field whose window missed takes its threshold from the slot's histogram
+// passes, and the window of the iteration after it follows from that.
+__host__ __device__ inline double window_budget(int64_t n);
+__device__ inline SelState resolved(const SelState &s, const FbRec *rec, int f, int64_t n)
+{
+    if (s.done) return s;
+    SelState o = s;
+    o.tau = fb_final(rec, f).tau;
+    o.dens = rec[f].dens;
+    o.done = 1u;
+    o.full = 0u;
+    set_window(o, true, window_budget(n));
+    return o;
+}
+
+// The interval in which the next a4 (y4 = a4 q) is expected, after a4 of this
+// iteration: extrapolated like the thresholds, with a half-width of 2.5 times
+// the larger of the last prediction's error and half of the one before it
+// (an error that happens to cross zero says nothing) plus 5e-5 a4. Without a
+// history, every value a4 can take: gy4 max(0, 1 - eps/r) lies in [0, gy4].
+struct A4History {
+    double p1, p2, p3;  // a4 of the iterations before
+    double err;         // error of the last prediction
+    uint32_t n;         // how many of them there are
+};
+__device__ inline A4History a4_history(const DevScalars *sc)
+{
+    return {sc->a_prev[0], sc->a_prev[1], sc->a_prev[2], sc->a_err, sc->a_n};
+}
+__device__ inline void predict_a4(DevScalars *sc, const A4History &h, double gy4, double a)
+{
+    double lo = 0.0, hi = gy4, c = 0.5 * gy4;
+    if (h.n >= 2u) {
+        const bool quad = h.n >= 3u;
+        c = quad ? 3.0 * (a - h.p1) + h.p2 : 2.0 * a - h.p1;
+        const double err = quad ? fabs(a - (3.0 * (h.p1 - h.p2) + h.p3))
+                                : fabs(a - (2.0 * h.p1 - h.p2)) + fabs(a - h.p1);
+        const double w = 2.5 * fmax(err, 0.5 * h.err) + 5e-5 * a;
+        sc->a_err = err;
+        lo = fmax(0.0, c - w);
+        hi = fmin(gy4, c + w);
+        if (!(lo <= hi)) lo = 0.0, hi = gy4;
+        c = fmin(fmax(c, lo), hi);
+    }
+    sc->in.a_lo = __double2float_rd(lo);
+    sc->in.a_hi = __double2float_ru(hi);
+    sc->in.a_c = (float)c;
+    sc->a_prev[2] = h.p2;
+    sc->a_prev[1] = h.p1;
+    sc->a_prev[0] = a;
+    sc->a_n = h.n < 3u ? h.n + 1u : 3u;
 }
 
 // Candidate budget of a cube's window: what LDS holds with room for the

@@ -361,7 +361,7 @@ __global__ __launch_bounds__(kWinThreads) void k_select_window(const char *table
     Hist *hist = cc.hist;
     const double *winpart = cc.winpart;
     const int grid_a = cc.ntiles;  // candidate slices: one per tile
-    const float *cand = cc.cand;
+    const float *cand = cc.vcand;
     const uint32_t *ccount = cc.ccount;
     const int capb = cc.capt;
     uint32_t *fallback_counter = &sc->fallback;

@@ -35,6 +35,8 @@ struct SelState {
     uint32_t cand_count;   // candidates in the window (search bookkeeping)
     double dens;           // values of |z| per unit near tau in the last
                            // iteration (sizes the next window)
+    uint32_t calm;         // windows in a row that held tau
+    uint32_t pad_;
 };
 
 constexpr int kHistBins = 2048;  // bins of radix level 0 (levels 1 and 2 use 1024)
@@ -86,6 +88,38 @@ struct DevScalars {
     uint32_t zstore;     // sweep A of this iteration stores z_s and z_t
     uint32_t calm;       // iterations in a row whose windows all held tau
     double gy4;          // step of y4: after an iteration y4 = gy4 c4 q
+    // Search-ahead form (sweep.hip, search.hip). sel[f].tau is the threshold
+    // of the NEXT iteration; the sweep gathers the inputs of the one after it
+    // for every a4 in [a_lo, a_hi], since the factor is known only once the
+    // sweep's residual norm is.
+    double tau_used[2];    // thresholds of the last iteration done
+    double a_prev[3];      // a4 of the iterations before, newest first
+    double a_err;          // error of the last prediction of a4
+    uint32_t cand_used[2]; // values inside the windows that gave tau_used
+    uint32_t missed[2];    // per field: full searches in the current call
+    uint32_t a_n;          // valid entries of a_prev
+    // what the next sweep reads: written by the search, or by the histogram
+    // pass that found a missed threshold (fallback.hip)
+    struct SweepIn {
+        double tau[2];
+        float lo[2], hi[2];  // windows
+        uint32_t on[2];
+        float a4;
+        float a_lo, a_hi, a_c;  // interval of the a4 after this one, its centre
+        __host__ __device__ void set(int f, const SelState &s)
+        {
+            tau[f] = s.tau;
+            lo[f] = s.win_lo;
+            hi[f] = s.win_hi;
+            on[f] = s.win_on;
+        }
+    } in;
+    // what the search of a slot reads of the state it rewrites (its two
+    // blocks of a cube run in any order): copied by the sweep of the slot
+    struct View {
+        float a_lo, a_hi, a_c;
+        uint32_t idle;
+    } view;
 };
 
 // Iterations in which a threshold window is likely to miss store the inputs
@@ -112,7 +146,6 @@ struct Layout {
     size_t y1[2], y2[2], y3[2], y4[2];      // duals (FP32 or BF16), ping-pong
     size_t total;
     int dual_bytes;
-    int n_part;     // FP64 partial-sum slots: 2 per tile, then sweep B blocks
     int max_tiles;  // most sweep A tiles of any band chunk the library may use
     int64_t cap;    // candidate capacity per field
 };
@@ -281,18 +314,24 @@ struct CubeCommon {
     Dims d;
     const float *v;
     DevScalars *sc;
-    double *part;       // [2 * ntiles] tile partials (du2, u2), then sweep B blocks
-    double *winpart;    // [2][ntiles][3] count above, sum above, sum of |z|
+    double *part;       // [3 * ntiles] tile partials (du2, u2, r2); two-sweep form:
+                        // [2 * ntiles] (du2, u2), then the blocks of the second
+    double *winpart;    // [2][ntiles][4] count above, sum above, its slope in a4,
+                        // count inside the window; two-sweep form:
+                        // [2][ntiles][3] count above, sum above, sum of |z|
     Hist *hist;         // [3 levels][2 fields] histograms of the full threshold search
     FbRec *rec;         // [3 levels][2 fields] their outcomes
-    float *cand;        // [2][ntiles][capt] candidate slices of the tiles
+    float4 *cand;       // [2][ntiles][capt] candidate slices of the tiles: (x, e, q)
+    float *vcand;       // two-sweep form: candidates |z|
     uint32_t *ccount;   // [2][ntiles] candidates appended by each tile
-    float *zbuf;        // [2][N] z_s, z_t of an iteration that stores them
+    float *zbuf;        // two-sweep form: [2][N] z_s, z_t of an iteration that
+                        // stores them
     int capt;           // candidate capacity of one tile slice
     int ntiles;
     SweepGrid g;
     int tile0;          // first tile of this cube in the launch's full tile list
-    int b0, nb;         // sweep B blocks of this cube: first, count
+    int b0, nb;         // sweep B blocks of this cube (BF16): first, count; dual
+                        // kernel blocks (regularizers)
     float thr1;         // omega * step of w1
     float zt_step;      // step size of t in z_t (the histogram passes evaluate z_t)
     float mu_lo, mu_hi;
@@ -300,12 +339,16 @@ struct CubeCommon {
     // and their sizes, for the cache prefetch that runs beside the search
     const void *bin[2][5];
     size_t bin_bytes[5];
+    // the call: stopping tolerance, radii of the l1 balls, iteration limit
+    double tol, alpha, beta;
+    uint32_t limit;
+    uint32_t ahead;     // thresholds searched one iteration ahead (FP32 duals)
 };
 template <typename DT>
 struct CubeArgs {
     CubeCommon c;
     Side<DT> side[2];
-    DT *y4p;            // 5 y4 + u' - v: step 14 before s', t'
+    DT *y4p;            // 5 y4 + u' - v: step 14 before s', t' (BF16)
 };
 
 // Read-only view of a launch table through the constant address space: its
@@ -344,22 +387,18 @@ __device__ __forceinline__ Dims load_dims(const4<Dims> &d)
 struct LaunchShape {
     int ncubes;
     int total_tiles;  // sweep A tiles over all cubes
-    int grid_a;       // persistent sweep A blocks
-    int total_b;      // sweep B blocks over all cubes
+    int grid_a;       // persistent sweep blocks
+    int total_b;      // sweep B blocks over all cubes (BF16)
+    int b_kinds;      // sweep B forms present: 1 one or two columns per thread, 2 four
     int shape_tiles[kTileShapes];  // sweep A tiles of the cubes of each tile shape
     int shape_grid[kTileShapes];   // persistent blocks of the sweep A launch of each shape
     int fb_grid;      // blocks of each fallback histogram pass
-    int b_kinds;      // sweep B forms present: 1 one or two columns per thread, 2 four
 };
 
 // Columns per sweep B thread for a row length: four when it is a multiple of
 // 4 (16-byte FP32 and 8-byte BF16 accesses), else two when it is even, else
-// one. dual_bytes: storage of the duals (the same rule for both).
-__host__ __device__ inline int sweep_b_cpt(int n2, int dual_bytes)
-{
-    (void)dual_bytes;
-    return (n2 & 1) ? 1 : ((n2 & 3) == 0 ? 4 : 2);
-}
+// one.
+__host__ __device__ inline int sweep_b_cpt(int n2) { return (n2 & 1) ? 1 : ((n2 & 3) == 0 ? 4 : 2); }
 
 // Host image of one cube's table entry (FP32 or BF16 duals: same size).
 struct CubeEntry {
@@ -388,19 +427,24 @@ __host__ __device__ inline size_t table_bytes(int ncubes) { return table_flags_o
 // ---- launchers (kernels in sweep.hip / select.hip / ops.hip) ----
 hipError_t launch_init(const Dims &d, const float *v, void *ws, const Layout &L, double eps,
                        double tol, double alpha, double beta, hipStream_t st);
-hipError_t launch_begin_call(void *ws, const Layout &L, double tol, double alpha, double beta,
-                             int call_limit, hipStream_t st);
-// Fill e for the cube (d, v, ws) with band chunk kc; tile0/b0 place it in
-// the launch; returns its tile and sweep B block counts.
-void cube_entry(CubeEntry *e, const Dims &d, const float *v, void *ws, const Layout &L, double omega,
-                double mu_lo, double mu_hi, int kc, int tile0, int b0, int *ntiles, int *nb);
+// Fill e for the cube (d, v, ws) with band chunk kc and the call's
+// parameters; tile0/b0 place it in the launch; returns its tile and sweep B
+// block counts.
+void cube_entry(CubeEntry *e, const Dims &d, const float *v, void *ws, const Layout &L, const geo_params *p,
+                 int n_iter, int tile0, int b0, int *ntiles, int *nb);
 int sweep_a_grid(int dual_bytes, int total_tiles);
 // One launch slot over the table (device copy of the entries). ev (may be
-// null): nev = 4 events recorded at the phase boundaries (before sweep A,
-// after sweep A, after the threshold search, after sweep B and the
-// finalize), or nev = 2 around sweep A only.
+// null): nev = 4 events recorded at the phase boundaries (FP32: before and
+// after the histogram passes, after the sweep, after the search; BF16: before
+// and after sweep A, after the search and the passes, after sweep B and the
+// finalize), or nev = 2 around the (first) sweep only.
 hipError_t launch_slot(const void *table, int dual_bytes, const LaunchShape &sh, hipStream_t st,
                        hipEvent_t *ev = nullptr, int nev = 4);
+// Start of a call over the table; the end of an iteration with the search of
+// the next thresholds; the reset after a state load (search.hip).
+hipError_t launch_begin(const void *table, int stride, int ncubes, hipStream_t st);
+hipError_t launch_search(const void *table, int stride, int ncubes, hipStream_t st);
+hipError_t launch_loaded(DevScalars *sc, Hist *hist, int var, hipStream_t st);
 // out != null: copy the variable out (FP32); otherwise load it from in.
 hipError_t launch_state_io(const Dims &d, void *ws, const Layout &L, int var, const float *v,
                            float *out, const float *in, hipStream_t st);
@@ -422,6 +466,8 @@ hipError_t launch_soft(const float *x, int64_t n, const SelState *sel, float *ou
 // memory-side cache meanwhile (prefetch_blocks, 0 = none).
 hipError_t launch_select_window(const void *table, int stride, int ncubes, int prefetch_blocks,
                                 hipStream_t st);
+// Sweep B of the two-sweep form (sweep_b.hip).
+hipError_t launch_sweep_b(const void *table, const LaunchShape &sh, hipStream_t st);
 
 // The histogram pass of radix level `level` (0..2) for the thresholds whose
 // window missed in this slot (fallback.hip); a no-op when none did.

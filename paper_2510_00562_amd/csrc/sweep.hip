@@ -1,27 +1,39 @@
-// One iteration of Alg. 1 (problem (20)) as HBM-streaming sweeps for gfx950.
+// One iteration of Alg. 1 (problem (20)) as one HBM-streaming sweep for gfx950.
 //
-//   sweep A  (fused, LDS-tiled): steps 1, 4, 5, the extrapolations 6 and 9-10,
-//            steps 11 and 12 and the u' part of step 14; it also evaluates the
-//            inputs z_s, z_t of the two l1-ball projections (steps 2, 3) and
-//            feeds the threshold search (count and sum above a predicted
-//            window, values inside it), plus the FP64 partial sums of the
-//            stopping rule (eq. (28)).
-//   search   (select.hip, fallback.hip): exact soft-threshold levels tau_s,
-//            tau_t from the window candidates, or, for a window that
-//            missed, from three histogram passes in the same slot.
-//   sweep B  (pointwise): steps 2, 3, 7, 8, 13, the rest of step 14 and the
-//            FP64 partial sums of the l2-ball distance of step 15.
-//   finalize (one block): the l2-ball factor of step 15 (applied lazily when
-//            y4 is next read), the stopping test and the iteration counter.
+// FP32 duals:
+//   passes   (fallback.hip): the thresholds tau_s, tau_t of this iteration
+//            whose search missed at the end of the last one; no-ops otherwise.
+//   sweep    (LDS-tiled): steps 1-14, with the thresholds and the factor
+//            a4 of y4 known from the end of the last iteration; the FP64 partial
+//            sums of the stopping rule (eq. (28)) and of the l2-ball distance of
+//            step 15; and what the search of the next thresholds needs of the
+//            new state (search.hip).
+//   search   (search.hip): the l2-ball factor of step 15 (applied lazily when
+//            y4 is next read), the stopping test, the iteration counter, and
+//            the next thresholds.
 //
-// Sweep A keeps the w1/w2 extrapolations (12 of the 21 state words per voxel)
+// Every state word is read and written once per iteration (172 bytes per
+// voxel with FP32 duals). What bounds the sweep is HBM streaming: 290 us for
+// 256 x 256 x 128 and 2040 us for 512 x 512 x 224 are 4.97 and 4.95 TB/s on those
+// bytes, 0.94 of what a plain copy reaches. In two sweeps with the search
+// between them (the second read s, t, y3, y4 and an intermediate again, 36
+// bytes) the iteration took 354 and 2350 us, now 313 and 2080.
+//
+// Two things let the loads of a band stay in flight for a whole band. They go
+// through the buffer path (common.hpp: band_of), so no branch stands between a
+// load and its use and the compiler waits for exactly that load; with branches
+// it waited for everything outstanding, at four points of a band. And the edge
+// masks of y are applied when it is stored to LDS, not when it is loaded. (The
+// BF16 sweep, the same otherwise: 400 -> 352 us at 256 x 256 x 190.)
+//
+// The sweep keeps the w1/w2 extrapolations (12 of the 21 state words per voxel)
 // out of HBM: a workgroup owns a TI x TJ pixel tile and marches through a
 // chunk of bands. Per band it stages the masked dual edge fields y1, y2 with
-// a 2-pixel halo in LDS, recomputes w' on a 1-pixel ring and u' on the
-// (i+1, j+1) ring, and updates y1, y2 from LDS; the D_s coupling of
-// neighbouring bands is carried in LDS. Global loads of band k+1 (w) and
-// k+2 (y, u, v, y4, s, t, y3) are issued while band k is computed, so the
-// memory latency overlaps the arithmetic.
+// a 2-pixel halo in LDS, recomputes w' on a 1-pixel ring, u' on the
+// (i+1, j+1) ring and t' on the rows above and below, and updates y1, y2, y3
+// from LDS; the D_s coupling of neighbouring bands is carried in LDS. Global
+// loads of band k+1 (w) and k+2 (y, u, v, y4, s, t, y3) are issued while band
+// k is computed, so the memory latency overlaps the arithmetic.
 //
 // Every state array is ping-ponged: iteration k reads side (k & 1) and writes
 // side ((k + 1) & 1), so halo reads never race with writes. The side comes
@@ -60,18 +72,10 @@ struct TileOf {
     (void)H2; (void)W2; (void)S2; (void)H1; (void)W1; (void)S1;                          \
     (void)HU; (void)WU; (void)SU; (void)NY; (void)RING1; (void)RINGU
 constexpr int NPT = 256;  // threads of the pointwise kernels
+using lds_f = __attribute__((address_space(3))) float;
 
 template <typename DT>
 using Table = const CubeArgs<DT> *__restrict__;
-
-// Value as stored (FP32 or rounded to BF16), for the l2-ball distance.
-__device__ __forceinline__ float as_stored(const float *, float x) { return x; }
-__device__ __forceinline__ float as_stored(const bf16 *, float x)
-{
-    bf16 b;
-    st(&b, x);
-    return ld(&b);
-}
 
 // XCD-aware persistent tile order: the 8 XCDs take contiguous tile ranges so
 // that the halos shared by neighbouring tiles meet in the same L2.
@@ -87,37 +91,50 @@ __device__ __forceinline__ int tile_at(int b, int G, int T, int r)
     return t < T ? t : -1;
 }
 
-// Sums of 8 FP64 values over the block; result valid in thread 0.
-__device__ __forceinline__ void block_sum8(double (&x)[8], double *red /* 8 * NT/64 */)
+// Sums of K FP64 values over the block; result valid in thread 0.
+template <int K>
+__device__ __forceinline__ void block_sums(double (&x)[K], double *red /* K * NT/64 */)
 {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) x[q] = wave_sum(x[q]);
+    for (int q = 0; q < K; ++q) x[q] = wave_sum(x[q]);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     if (lane == 0)
 #pragma unroll
-        for (int q = 0; q < 8; ++q) red[q * (NT / 64) + wid] = x[q];
+        for (int q = 0; q < K; ++q) red[q * (NT / 64) + wid] = x[q];
     __syncthreads();
     if (threadIdx.x == 0)
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
+        for (int q = 0; q < K; ++q) {
             double t = 0.0;
             for (int w = 0; w < NT / 64; ++w) t += red[q * (NT / 64) + w];
             x[q] = t;
         }
 }
 
-template <typename DT, int S>
-__global__ __launch_bounds__(NT, 4) void k_sweep_a(Table<DT> cubes, LaunchShape sh)
+// FUSED (FP32 duals): the whole iteration, thresholds known beforehand.
+// Otherwise (BF16 duals) the first of two sweeps: steps 1, 4, 5, 11, 12 and the
+// u' part of step 14, the inputs z_s, z_t of steps 2 and 3 with their window
+// statistics; the search and sweep B (sweep_b.hip) follow in the same slot.
+// With BF16 duals a change of 1e-10 in a threshold (the search-ahead form sums
+// |z| by its slope in a4, not the rounded values) grows to 4e-4 of s within 40
+// iterations, so that storage keeps the form whose sums are over the values
+// themselves.
+template <typename DT, int S, bool FUSED>
+__global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh)
 {
     GEO_TILE_GEOMETRY(S);
     using P = typename PairOf<DT>::type;
-    // [band parity][y1v, y1h, y2v, y2h] masked | u' by band parity |
-    // w1', w2' planes read by neighbours (ud_h, lr_v, c_v, c_h)
-    __shared__ __align__(16) float smem[2 * 4 * S2 + 2 * SU + 2 * 4 * S1];
-    float(*sY)[4][S2] = reinterpret_cast<float(*)[4][S2]>(smem);
-    float(*sU)[SU] = reinterpret_cast<float(*)[SU]>(smem + 2 * 4 * S2);
-    float(*sW)[4][S1] = reinterpret_cast<float(*)[4][S1]>(smem + 2 * 4 * S2 + 2 * SU);
-    __shared__ double red[8 * (NT / 64)];
+    // three bands of masked [y1v, y1h, y2v, y2h] | u' by band parity | w1', w2'
+    // planes read by neighbours (ud_h, lr_v, c_v, c_h)
+    __shared__ __align__(16) float smem[3 * 4 * S2 + 2 * SU + 2 * 4 * S1];
+    // u' and w' start here
+    constexpr int U0 = 3 * 4 * S2, W0 = U0 + 2 * SU;
+    // t' with the rows above and below the tile; what a point keeps between the
+    // phases of a band (t+, q+, y3, y3 of the row above)
+    __shared__ float sT[FUSED ? (TI + 2) * TJ : 1];
+    __shared__ float4 keep[FUSED ? NT : 1];
+    constexpr int NS = FUSED ? 11 : 8;  // FP64 partials of a tile
+    __shared__ double red[NS * (NT / 64)];
     __shared__ uint32_t ncand[2];
     __shared__ int tile0[kMaxBatch + 1];
 
@@ -138,23 +155,42 @@ __global__ __launch_bounds__(NT, 4) void k_sweep_a(Table<DT> cubes, LaunchShape 
         }
         if (c < sh.ncubes) tile0[c + 1] = x;
         if (c == 0) tile0[0] = 0;
+        // the first block copies what the search of this slot reads of the
+        // state it rewrites, and lowers the flag of the histogram passes
+        if (FUSED && blockIdx.x == 0) {
+            if (c < sh.ncubes) {
+                DevScalars *sc = cubes[c].c.sc;
+                sc->view = {sc->in.a_lo, sc->in.a_hi, sc->in.a_c, idle(sc) ? 1u : 0u};
+            }
+            if (c == 0) *slot_flags(cubes, sh.ncubes) = 0u;
+        }
     }
     __syncthreads();
     const int tid = threadIdx.x;
     const int oti = tid / TJ, otj = tid % TJ;  // the thread's own point in the tile
 
-    // ring coordinates (R1-local for w', RU-local for u')
+    // Ring roles: the w' ring (its first RING1 threads) and, apart from each
+    // other so that each wavefront has one, the u' ring (the first RINGU) and
+    // the t' ring: the rows above and below the tile (threads T0 on).
     int rwi = 0, rwj = 0, rui = 0, ruj = 0;
-    if (tid < RING1) {
+    const bool ring_w = tid < RING1, ring_u = tid < RINGU;
+    if (ring_w) {
         if (tid < W1) { rwi = 0; rwj = tid; }
         else if (tid < 2 * W1) { rwi = H1 - 1; rwj = tid - W1; }
         else { const int s = tid - 2 * W1; rwi = 1 + (s >> 1); rwj = (s & 1) ? W1 - 1 : 0; }
     }
-    if (tid < RINGU) {
+    if (ring_u) {
         if (tid < WU) { rui = TI; ruj = tid; }
         else { rui = tid - WU; ruj = TJ; }
     }
-    const bool ring_w = tid < RING1, ring_u = tid < RINGU;
+    constexpr int T0 = NT / 2;
+    static_assert(T0 >= RINGU && T0 % 64 == 0 && TJ % 64 == 0 && T0 + 2 * TJ <= NT, "one ring role per wavefront");
+    const bool wave_t = FUSED && __builtin_amdgcn_readfirstlane(tid) >= T0 &&
+                        __builtin_amdgcn_readfirstlane(tid) < T0 + 2 * TJ;
+    if (wave_t) {
+        rui = tid - T0 < TJ ? -1 : TI;
+        ruj = (tid - T0) % TJ;
+    }
 
     for (int r = 0;; ++r) {
         // (the working cubes' tile count is read from LDS at each tile rather
@@ -167,661 +203,417 @@ __global__ __launch_bounds__(NT, 4) void k_sweep_a(Table<DT> cubes, LaunchShape 
         cube = __builtin_amdgcn_readfirstlane(cube);
         const int lt = __builtin_amdgcn_readfirstlane(t - tile0[cube]);  // tile within the cube
         const4<CubeArgs<DT>> &a = ((const4<CubeArgs<DT>> *)cubes)[cube];
-        DevScalars *sc = a.c.sc;
-        // Never taken (an idle cube has no tiles in the list); without it the
-        // register allocation of one of the sweep's forms spills.
-        if (idle(sc)) continue;
+        const4<DevScalars> &sc = *(const4<DevScalars> *)a.c.sc;  // this launch does not write what it reads of it
+        // Each phase reads the pointers and windows it needs with scalar loads
+        // of its own: kept live through the march (as the compiler would, since
+        // they never change) they overflow the scalar registers, and the spills
+        // take vector registers and a fifth of the vector instructions.
+        const4<CubeArgs<DT>> *ent = &a;
+        const4<DevScalars> *scp = &sc;
+        // LDS pointers are formed where they are used, for the same reason: one
+        // base, the planes at constant offsets from it.
+        auto at = [](float *p) {
+            lds_f *q = (lds_f *)p;
+            asm volatile("" : "+v"(q));
+            return q;
+        };
+        auto fresh = [&]() {
+            asm volatile("" : "+s"(ent), "+s"(scp));
+            __builtin_amdgcn_sched_barrier(0);
+        };
         const SweepGrid g{a.c.g.tj, a.c.g.ti, a.c.g.tk, a.c.g.kc, S};
         const int tj = lt % g.tj, rest = lt / g.tj;
         const int j0 = tj * TJ, i0 = (rest % g.ti) * TI, kb = (rest / g.ti) * g.kc;
-        const Dims d = load_dims(a.c.d);
-        const int n1 = d.n1, n2 = d.n2, n3 = d.n3;
+        const int n1 = a.c.d.n1, n2 = a.c.d.n2, n3 = a.c.d.n3;
         const int ke = min(kb + g.kc, n3);
+        const int64_t N = a.c.d.plane;
+        const uint32_t np = (uint32_t)n1 * (uint32_t)n2;  // pixels of a band
 
-        const uint32_t N = (uint32_t)d.plane;
         if (tid < 2) ncand[tid] = 0u;  // published by the first barrier of the march
-        const int par = (int)(sc->iter & 1u);
-        const Side<DT> src = load_side(a.side[par]), dst = load_side(a.side[par ^ 1]);
-        const float a4 = (float)sc->a4;
-        auto vox32 = [&](int k, int i, int j) {
-            return ((uint32_t)k * (uint32_t)n1 + (uint32_t)i) * (uint32_t)n2 + (uint32_t)j;
+        const int par = (int)(sc.iter & 1u);
+        const float a4 = FUSED ? sc.in.a4 : (float)sc.a4;
+        const bool zst = !FUSED && sc.zstore != 0u;
+        double du2 = 0.0, u2 = 0.0, r2 = 0.0;
+        // |z| above the window: sum, count (of the wavefront), slope in a4
+        // (FUSED) or sum of all |z|; values inside it at the centre a4
+        double sum[2] = {0.0, 0.0}, all[2] = {0.0, 0.0};
+        uint32_t cnt[2] = {0u, 0u}, inw[2] = {0u, 0u};
+        float slope[2] = {0.f, 0.f};
+
+        // pixels of this thread in a band (kNoPix outside the cube)
+        auto pixel = [&](int i, int j) {
+            return i >= 0 && i < n1 && j >= 0 && j < n2 ? (uint32_t)i * (uint32_t)n2 + (uint32_t)j : kNoPix;
         };
-        const bool zst = sc->zstore != 0u;
-        float wlo[2], whi[2];
-        bool won[2];
-        for (int f = 0; f < 2; ++f) {
-            won[f] = sc->sel[f].win_on != 0u;
-            wlo[f] = sc->sel[f].win_lo;
-            whi[f] = sc->sel[f].win_hi;
-        }
-        double du2 = 0.0, u2 = 0.0;
-        double s_hi[2] = {0.0, 0.0}, s_all[2] = {0.0, 0.0};
-        float c_hi[2] = {0.f, 0.f};
         const int oi = i0 + oti, oj = j0 + otj;
-        const bool own_in = oi < n1 && oj < n2;
+        const uint32_t po = pixel(oi, oj);
+        const bool own_in = po != kNoPix;
+        const uint32_t pr = ring_u || wave_t ? pixel(i0 + rui, j0 + ruj) : kNoPix;
+        const uint32_t pw = ring_w ? pixel(i0 - 1 + rwi, j0 - 1 + rwj) : kNoPix;
+        uint32_t py[NY];
+        // masks of the staged y: bit 2n vertical, 2n + 1 horizontal of point n;
+        // of the own point: bits 16, 17; of the w' ring point: 18, 19
+        uint32_t keepm = 0u;
+#pragma unroll
+        for (int n = 0; n < NY; ++n) {
+            const int p = tid + NT * n, i = i0 - 2 + p / W2, j = j0 - 2 + p % W2;
+            py[n] = p < S2 ? pixel(i, j) : kNoPix;
+            keepm |= (i <= n1 - 2 ? 1u : 0u) << (2 * n) | (j <= n2 - 2 ? 2u : 0u) << (2 * n);
+        }
+        const float mv = mask_le(oi, n1), mh = mask_le(oj, n2);
+        const float rmv = mask_le(i0 - 1 + rwi, n1), rmh = mask_le(j0 - 1 + rwj, n2);
 
         // ---------------- register staging of global loads ----------------
-        float2 ry1[NY], ry2[NY];
-        auto loadY = [&](int k) {
+        // band k of an array; no bytes when the band is not wanted
+        auto band = [&](auto *p, int k, bool want) { return band_of(p, (int64_t)k * np, want ? np : 0u); };
+#define SRC (ent->side[par])
+#define DST (ent->side[par ^ 1])
+        using Raw = decltype(bld_raw((const P *)nullptr, BandRsrc(), 0u));
+        auto loadY = [&](int k, bool want, Raw (&q1)[NY], Raw (&q2)[NY]) {
+            const BandRsrc b1 = band(SRC.y1, k, want), b2 = band(SRC.y2, k, want);
 #pragma unroll
             for (int n = 0; n < NY; ++n) {
-                const int p = tid + NT * n;
-                const int li = p / W2, lj = p - li * W2;
-                const int i = i0 - 2 + li, j = j0 - 2 + lj;
-                float2 y1 = make_float2(0.f, 0.f), y2 = y1;
-                if (p < S2 && k >= 0 && k < n3 && i >= 0 && i < n1 && j >= 0 && j < n2) {
-                    const uint32_t q = vox32(k, i, j);
-                    y1 = ld2(src.y1 + q);
-                    y2 = ld2(src.y2 + q);
-                    if (i > n1 - 2) y1.x = y2.x = 0.f;  // masked: last row (vertical)
-                    if (j > n2 - 2) y1.y = y2.y = 0.f;  // masked: last column (horizontal)
-                }
-                ry1[n] = y1;
-                ry2[n] = y2;
+                q1[n] = bld_raw((const P *)nullptr, b1, py[n]);
+                q2[n] = bld_raw((const P *)nullptr, b2, py[n]);
             }
         };
-        auto storeY = [&](int buf) {
+        auto storeY = [&](float *buf, const Raw (&q1)[NY], const Raw (&q2)[NY]) {
+            lds_f *o = at(buf + tid);
 #pragma unroll
             for (int n = 0; n < NY; ++n) {
-                const int p = tid + NT * n;
-                if (p < S2) {
-                    sY[buf][0][p] = ry1[n].x;
-                    sY[buf][1][p] = ry1[n].y;
-                    sY[buf][2][p] = ry2[n].x;
-                    sY[buf][3][p] = ry2[n].y;
+                const bool v = keepm >> (2 * n) & 1u, h = keepm >> (2 * n + 1) & 1u;
+                const float2 y1 = pair_of(q1[n]), y2 = pair_of(q2[n]);
+                if (NT * (n + 1) <= S2 || tid + NT * n < S2) {
+                    o[NT * n] = v ? y1.x : 0.f;           // masked: last row (vertical)
+                    o[NT * n + S2] = h ? y1.y : 0.f;      // last column (horizontal)
+                    o[NT * n + 2 * S2] = v ? y2.x : 0.f;
+                    o[NT * n + 3 * S2] = h ? y2.y : 0.f;
                 }
             }
         };
-        // u, y4 (stored) at the own point and the u' ring point; v, s, t,
-        // y3 (row and row above) at the own point
-        float ru_u, ru_y4, ru_v, ru_s, ru_t, ru_y3c, ru_y3m, rr_u, rr_y4;
-        auto loadRU = [&](int kk) {
-            ru_u = ru_y4 = ru_v = ru_s = ru_t = ru_y3c = ru_y3m = 0.f;
-            if (kk < n3 && own_in) {
-                const uint32_t q = vox32(kk, oi, oj);
-                ru_u = src.u[q];
-                ru_y4 = ld(src.y4 + q);
-                ru_v = ld_nt(a.c.v + q);
-                ru_s = ld_nt(src.s + q);
-                ru_t = ld_nt(src.t + q);
-                ru_y3c = oi <= n1 - 2 ? ld(src.y3 + q) : 0.f;
-                ru_y3m = oi >= 1 ? ld(src.y3 + q - n2) : 0.f;
-            }
-            rr_u = rr_y4 = 0.f;
-            const int i = i0 + rui, j = j0 + ruj;
-            if (ring_u && kk < n3 && i < n1 && j < n2) {
-                const uint32_t q = vox32(kk, i, j);
-                rr_u = src.u[q];
-                rr_y4 = ld(src.y4 + q);
+        Raw ry1[NY], ry2[NY];
+        // u, y4 (stored), v, s, t, y3 (row and row above) at the own point; u
+        // and y4 at the u' ring point, or t, y4 and both y3 at the t' ring point
+        float ru_u, ru_y4, ru_v, ru_s, ru_t, ru_y3c, ru_y3m, rr_u, rr_y4, rr_y3c = 0.f, rr_y3m = 0.f;
+        auto loadRU = [&](int k, bool want, bool own) {
+            const BandRsrc bu = band(SRC.u, k, want), b4 = band(SRC.y4, k, want);
+            const BandRsrc bt = band(SRC.t, k, own), b3 = band(SRC.y3, k, own);
+            ru_u = bld((const float *)nullptr, bu, po);
+            ru_y4 = bld((const DT *)nullptr, b4, po);
+            ru_s = bld<kNT>((const float *)nullptr, band(SRC.s, k, own), po);
+            ru_t = bld<FUSED ? 0 : kNT>((const float *)nullptr, bt, po);
+            ru_y3c = bld((const DT *)nullptr, b3, po);
+            ru_y3m = bld((const DT *)nullptr, b3, po - (uint32_t)n2);  // row -1: past the band, 0
+            ru_v = bld<kNT>((const float *)nullptr, band(ent->c.v, k, own), po);
+            rr_u = bld((const float *)nullptr, wave_t ? bt : bu, pr);
+            rr_y4 = bld((const DT *)nullptr, wave_t ? band(SRC.y4, k, own) : b4, pr);
+            if constexpr (FUSED) {
+                const BandRsrc br = band(SRC.y3, k, own && wave_t);
+                rr_y3c = bld((const DT *)nullptr, br, pr);
+                rr_y3m = bld((const DT *)nullptr, br, pr - (uint32_t)n2);
             }
         };
         // w1, w2 (3 pairs each) at the own point and the w' ring point
-        float2 rw[2][2][3];  // [own, ring][field][grid]
-        auto loadW = [&](int k) {
+        u32x4 rwa[2][2];  // [own, ring][field]: ud, lr
+        u32x2 rwc[2][2];  // c
+        auto loadW = [&](int k, bool want) {
 #pragma unroll
-            for (int o = 0; o < 2; ++o) {
-                const int i = o == 0 ? oi : i0 - 1 + rwi, j = o == 0 ? oj : j0 - 1 + rwj;
-                const bool in = (o == 0 ? true : ring_w) && i >= 0 && i < n1 && j >= 0 && j < n2 && k < n3;
-                const uint32_t q = in ? vox32(k, i, j) : 0u;
+            for (int o = 0; o < 2; ++o)
 #pragma unroll
                 for (int f = 0; f < 2; ++f) {
-                    const float2 *w = f ? src.w2 : src.w1;
-                    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-                    float2 c = make_float2(0.f, 0.f);
-                    if (in) {
-                        a = w_udlr(w)[q];
-                        c = w_c(w, N)[q];
-                    }
-                    rw[o][f][0] = make_float2(a.x, a.y);
-                    rw[o][f][1] = make_float2(a.z, a.w);
-                    rw[o][f][2] = c;
+                    const float2 *w = f ? SRC.w2 : SRC.w1;
+                    rwa[o][f] = bld_raw((const float4 *)nullptr, band(w_udlr(w), k, want), o ? pw : po);
+                    rwc[o][f] = bld_raw((const float2 *)nullptr, band(w_c(w, N), k, want), o ? pw : po);
                 }
-            }
         };
 
+        auto won = [&](int f) { return FUSED ? scp->in.on[f] != 0u : scp->sel[f].win_on != 0u; };
+        auto wlo = [&](int f) { return FUSED ? scp->in.lo[f] : scp->sel[f].win_lo; };
+        auto whi = [&](int f) { return FUSED ? scp->in.hi[f] : scp->sel[f].win_hi; };
+
         // ---------------- phases ----------------
-        auto dT = [&](int buf, int pv, int c) {
-            const float *yv = sY[buf][pv], *yh = sY[buf][pv + 1];
-            return (yv[c - W2] - yv[c]) + (yh[c - 1] - yh[c]);
+        // D^T of planes pv (vertical) and pv + 1 of a staged band; y: its point
+        auto dT = [&](const lds_f *y, int pv) {
+            const lds_f *yv = y + pv * S2, *yh = yv + S2;
+            return (yv[-W2] - yv[0]) + (yh[-1] - yh[0]);
         };
-        // u+ of step 1 and u' at one point of band kk
-        auto u_at = [&](int kk, int ui, int uj, float uo, float y4s, float &y4) {
-            const int buf = kk & 1;
+        // u+ of step 1 at one point of band kk (yc: its y; yp: the band before)
+        auto u_at = [&](int kk, float *yc, float *yp, int ui, int uj, float uo, float y4s) {
             const int c = (ui + 2) * W2 + (uj + 2);
-            float g = dT(buf, 0, c);                  // D^T y1
-            if (kk <= n3 - 2) g -= dT(buf, 2, c);      // D_s^T D^T y2
-            if (kk >= 1) g += dT(buf ^ 1, 2, c);
-            y4 = y4_of(y4s, a4);
-            const float x = uo - kStepU * (g + y4);
-            return x < a.c.mu_lo ? a.c.mu_lo : (x > a.c.mu_hi ? a.c.mu_hi : x);
+            const lds_f *y = at(yc + c - W2) + W2;       // immediate offsets are unsigned
+            float g = dT(y, 0);                          // D^T y1
+            if (kk <= n3 - 2) g -= dT(y, 2);             // D_s^T D^T y2
+            if (kk >= 1) g += dT(at(yp + c - W2) + W2, 2);
+            const float x = __builtin_fmaf(-kStepU, __builtin_fmaf(a4, y4s, g), uo);
+            return x < ent->c.mu_lo ? ent->c.mu_lo : (x > ent->c.mu_hi ? ent->c.mu_hi : x);
         };
-        // step 1 (u+), u' and the z inputs of steps 2, 3 for band kk
-        auto uphase = [&](int kk, bool own_band) {
-            const int buf = kk & 1;
-            float up = 0.f, zs = 0.f, zt = 0.f;
-            bool wr = false;
-            if (kk < n3 && own_in) {
-                float y4;
-                const float un = u_at(kk, oti, otj, ru_u, ru_y4, y4);
-                up = 2.f * un - ru_u;
-                if (own_band) {
-                    wr = true;
-                    const uint32_t q = vox32(kk, oi, oj);
-                    st_nt(dst.u + q, un);
-                    // 5 (y4 + u'/5) - v: step 14 without s', t', times 5, minus v
-                    st_nt(a.y4p + q, (5.f * y4 + up) - ru_v);
-                    const double dl = (double)un - (double)ru_u;
-                    du2 += dl * dl;
-                    u2 += (double)ru_u * (double)ru_u;
-                    zs = zs_of(ru_s, y4);
-                    zt = zt_of(ru_t, ru_y3m, ru_y3c, y4);
-                    if (zst) {
-                        a.c.zbuf[q] = zs;
-                        a.c.zbuf[N + q] = zt;
-                    }
-                }
+        // FUSED: one value of the next search (search.hip), z = x - g (e + a4 q)
+        // over the interval of a4. Every lane of the wavefront takes part.
+        auto gather = [&](int f, bool in, float x, float e, float g, float q) {
+            const float zl = zt_of(x, e, y4_of(q, scp->in.a_lo), g);
+            const float zh = zt_of(x, e, y4_of(q, scp->in.a_hi), g);
+            if (!won(f)) {
+                // inside the ball so far: sum |z| at both ends
+                sum[f] += in ? (double)fabsf(zl) : 0.0;
+                slope[f] += in ? fabsf(zh) : 0.f;
+                return;
             }
-            sU[buf][oti * WU + otj] = up;
-            if (ring_u) {
-                float upr = 0.f;
-                if (kk < n3 && i0 + rui < n1 && j0 + ruj < n2) {
-                    float y4;
-                    const float un = u_at(kk, rui, ruj, rr_u, rr_y4, y4);
-                    upr = 2.f * un - rr_u;
-                }
-                sU[buf][rui * WU + ruj] = upr;
-            }
-            // threshold-search inputs (every lane takes part)
-#pragma unroll
-            for (int f = 0; f < 2; ++f) {
-                const float av = fabsf(f ? zt : zs);
-                bool cand = false;
-                if (wr) {
-                    s_all[f] += (double)av;
-                    if (won[f]) {
-                        if (av > whi[f]) {
-                            c_hi[f] += 1.f;
-                            s_hi[f] += (double)av;
-                        } else if (av >= wlo[f]) {
-                            cand = true;
-                        }
-                    }
-                }
-                wave_append(cand, av, a.c.cand + ((int64_t)f * a.c.ntiles + lt) * a.c.capt,
-                            &ncand[f], a.c.capt);
-            }
+            const float zmin = fminf(zl, zh), zmax = fmaxf(zl, zh);
+            const float zc = zt_of(x, e, y4_of(q, scp->in.a_c), g);
+            const bool above = in && (zmin > whi(f) || zmax < -whi(f));
+            const bool below = zmin > -wlo(f) && zmax < wlo(f);
+            cnt[f] += (uint32_t)__popcll(__ballot(above));
+            inw[f] += (uint32_t)__popcll(__ballot(in && fabsf(zc) >= wlo(f) && fabsf(zc) <= whi(f)));
+            sum[f] += above ? (double)fabsf(zc) : 0.0;
+            slope[f] += above ? copysignf(1.f, zc) * q : 0.f;
+            wave_append(in && !above && !below, make_float4(x, e, q, 0.f),
+                        ent->c.cand + ((int64_t)f * ent->c.ntiles + lt) * ent->c.capt, &ncand[f], ent->c.capt);
         };
-        // steps 4, 5 and the w extrapolations (9, 10) at one point of band k;
-        // own: also writes w+ and returns the own-only planes ud_v', lr_h'
+        // otherwise: one value of this slot's search
+        auto collect = [&](int f, bool in, float z) {
+            const float av = fabsf(z);
+            const bool above = in && won(f) && av > whi(f);
+            all[f] += in ? (double)av : 0.0;
+            cnt[f] += (uint32_t)__popcll(__ballot(above));
+            sum[f] += above ? (double)av : 0.0;
+            wave_append(in && won(f) && !above && av >= wlo(f), av,
+                        ent->c.vcand + ((int64_t)f * ent->c.ntiles + lt) * ent->c.capt, &ncand[f], ent->c.capt);
+        };
+        // step 1 and u' for band kk; for an own band also (FUSED) steps 2, 3, 6, 7,
+        // 8, 14 and the s values of the next search: u+, s+, t+ and
+        // q+ = 5 y4' - v (step 15: r = ||q+||); otherwise z_s, z_t and the
+        // intermediate of step 14
+        auto uphase = [&](int kk, bool own, float *yc, float *yp) {
+            float *su = smem + U0 + (kk & 1) * SU;
+            const float y4 = y4_of(ru_y4, a4);
+            const float un = u_at(kk, yc, yp, oti, otj, ru_u, ru_y4);
+            const float up = 2.f * un - ru_u;
+            *at(su + oti * WU + otj) = up;
+            bst_nt((const float *)nullptr, band(DST.u, kk, own), po, un);
+            const bool wr = own && own_in;
+            const double dl = (double)un - (double)ru_u, uo = (double)ru_u;
+            if (wr) {
+                du2 += dl * dl;
+                u2 += uo * uo;
+            }
+            const float zs = zs_of(ru_s, y4);
+            const float zt = zt_of(ru_t, ru_y3m, oi <= n1 - 2 ? ru_y3c : 0.f, y4, kStepT);
+            // 5 (y4 + u'/5) - v, rounded as the duals are stored
+            const float y4p = as_stored((const DT *)nullptr, (5.f * y4 + up) - ru_v);
+            if constexpr (FUSED) {
+                const float sn = soft(zs, scp->in.tau[0]), tn = soft(zt, scp->in.tau[1]);
+                bst_nt((const float *)nullptr, band(DST.s, kk, own), po, sn);
+                bst_nt((const float *)nullptr, band(DST.t, kk, own), po, tn);
+                const float sp = 2.f * sn - ru_s, tp = 2.f * tn - ru_t;
+                const float qn = as_stored((const DT *)nullptr, y4p + (sp + tp));
+                bst_nt((const DT *)nullptr, band(DST.y4, kk, own), po, qn);
+                if (wr) r2 += (double)qn * (double)qn;
+                *at(sT + TJ + tid) = tp;  // the own point: TJ * (oti + 1) + otj
+                keep[tid] = make_float4(tn, qn, ru_y3c, ru_y3m);
+                if (wave_t) {
+                    const float x = soft(zt_of(rr_u, rr_y3m, i0 + rui <= n1 - 2 ? rr_y3c : 0.f, y4_of(rr_y4, a4), kStepT),
+                                         scp->in.tau[1]);
+                    *at(sT + (rui + 1) * TJ + ruj) = 2.f * x - rr_u;
+                }
+                if (own) gather(0, wr, sn, 0.f, 1.f, qn);
+            } else {
+                bst_nt((const DT *)nullptr, band(ent->y4p, kk, own), po, y4p);
+                if (zst) {
+                    bst((const float *)nullptr, band(ent->c.zbuf, kk, own), po, zs);
+                    bst((const float *)nullptr, band(ent->c.zbuf + N, kk, own), po, zt);
+                }
+                if (own) {
+                    collect(0, wr, zs);
+                    collect(1, wr, zt);
+                }
+            }
+            if (ring_u) *at(su + rui * WU + ruj) = 2.f * u_at(kk, yc, yp, rui, ruj, rr_u, rr_y4) - rr_u;
+        };
+        // steps 4, 5 and the w extrapolations (9, 10) at one point of band k; the
+        // own point also writes w+ and keeps the own-only planes ud_v', lr_h'
         float wk[2][2];
-        auto w_at = [&](int k, int o, int wi, int wj, bool act) {
-            const int buf = k & 1;
-            const int i = i0 - 1 + wi, j = j0 - 1 + wj;
-            const bool in = act && i >= 0 && i < n1 && j >= 0 && j < n2;
-            const float mv = mask_le(i, n1), mh = mask_le(j, n2);
-            const int c = (wi + 1) * W2 + (wj + 1), c1 = wi * W1 + wj;
+        auto w_at = [&](int k, float *yb, int o, int wi, int wj, float v, float h) {
+            const lds_f *y = at(yb + wi * W2 + (wj + 1)) + W2;
+            lds_f *wo_at = at(smem + W0 + wi * W1 + wj);
+            constexpr int c = 0;
 #pragma unroll
             for (int f = 0; f < 2; ++f) {
-                float o6[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                if (in) {
-                    const float *yv = sY[buf][2 * f], *yh = sY[buf][2 * f + 1];
-                    float L[6];
-                    L[0] = mv * yv[c];
-                    L[1] = mv * 0.25f * ((yh[c] + yh[c - 1]) + (yh[c + W2] + yh[c + W2 - 1]));
-                    L[2] = mh * 0.25f * ((yv[c] + yv[c - W2]) + (yv[c + 1] + yv[c - W2 + 1]));
-                    L[3] = mh * yh[c];
-                    L[4] = 0.5f * (yv[c] + yv[c - W2]);
-                    L[5] = 0.5f * (yh[c] + yh[c - 1]);
-                    const float thr = f ? kStepW : a.c.thr1;
-                    float wo[6], wn[6];
+                const lds_f *yv = y + 2 * f * S2, *yh = yv + S2;
+                float L[6], wo[6], wn[6], o6[6];
+                L[0] = v * yv[c];
+                L[1] = v * 0.25f * ((yh[c] + yh[c - 1]) + (yh[c + W2] + yh[c + W2 - 1]));
+                L[2] = h * 0.25f * ((yv[c] + yv[c - W2]) + (yv[c + 1] + yv[c - W2 + 1]));
+                L[3] = h * yh[c];
+                L[4] = 0.5f * (yv[c] + yv[c - W2]);
+                L[5] = 0.5f * (yh[c] + yh[c - 1]);
+                const float thr = f ? kStepW : ent->c.thr1;
+                const u32x4 wa = rwa[o][f];
+                const u32x2 wc = rwc[o][f];
+                wo[0] = __uint_as_float(wa.x);
+                wo[1] = __uint_as_float(wa.y);
+                wo[2] = __uint_as_float(wa.z);
+                wo[3] = __uint_as_float(wa.w);
+                wo[4] = __uint_as_float(wc.x);
+                wo[5] = __uint_as_float(wc.y);
 #pragma unroll
-                    for (int g = 0; g < 3; ++g) {
-                        wo[2 * g] = rw[o][f][g].x;
-                        wo[2 * g + 1] = rw[o][f][g].y;
-                    }
-#pragma unroll
-                    for (int cc = 0; cc < 6; ++cc) wn[cc] = wo[cc] + kStepW * L[cc];
-                    shrink2(wn[0], wn[1], thr);
-                    shrink2(wn[2], wn[3], thr);
-                    shrink2(wn[4], wn[5], thr);
-                    if (o == 0) {
-                        const uint32_t q = vox32(k, i, j);
-                        float2 *wd = f ? dst.w2 : dst.w1;
-                        st_nt(w_udlr(wd) + q, make_float4(wn[0], wn[1], wn[2], wn[3]));
-                        st_nt(w_c(wd, N) + q, make_float2(wn[4], wn[5]));
-                    }
-#pragma unroll
-                    for (int cc = 0; cc < 6; ++cc) o6[cc] = 2.f * wn[cc] - wo[cc];
-                    o6[0] *= mv;
-                    o6[1] *= mv;
-                    o6[2] *= mh;
-                    o6[3] *= mh;
+                for (int cc = 0; cc < 6; ++cc) wn[cc] = wo[cc] + kStepW * L[cc];
+                shrink2(wn[0], wn[1], thr);
+                shrink2(wn[2], wn[3], thr);
+                shrink2(wn[4], wn[5], thr);
+                if (o == 0) {
+                    float2 *wd = f ? DST.w2 : DST.w1;
+                    bst_nt((const float4 *)nullptr, band(w_udlr(wd), k, true), po, make_float4(wn[0], wn[1], wn[2], wn[3]));
+                    bst_nt((const float2 *)nullptr, band(w_c(wd, N), k, true), po, make_float2(wn[4], wn[5]));
                 }
-                if (act) {
-                    sW[f][0][c1] = o6[1];
-                    sW[f][1][c1] = o6[2];
-                    sW[f][2][c1] = o6[4];
-                    sW[f][3][c1] = o6[5];
-                }
+#pragma unroll
+                for (int cc = 0; cc < 6; ++cc) o6[cc] = 2.f * wn[cc] - wo[cc];
+                o6[0] *= v;
+                o6[1] *= v;
+                o6[2] *= h;
+                o6[3] *= h;
+                wo_at[(4 * f + 0) * S1] = o6[1];
+                wo_at[(4 * f + 1) * S1] = o6[2];
+                wo_at[(4 * f + 2) * S1] = o6[4];
+                wo_at[(4 * f + 3) * S1] = o6[5];
                 if (o == 0) {
                     wk[f][0] = o6[0];
                     wk[f][1] = o6[3];
                 }
             }
         };
-        auto wphase = [&](int k) {
-            w_at(k, 0, oti + 1, otj + 1, true);
-            if (ring_w) w_at(k, 1, rwi, rwj, true);
-        };
         // steps 11, 12 for band k at the own point
-        auto yphase = [&](int k) {
-            if (!own_in) return;
+        auto yphase = [&](int k, float *yb) {
             const float msk = k <= n3 - 2 ? 1.f : 0.f;
-            const int buf = k & 1;
-            const float mv = mask_le(oi, n1), mh = mask_le(oj, n2);
-            const int c1 = (oti + 1) * W1 + (otj + 1);
-            const int c2 = (oti + 2) * W2 + (otj + 2);
-            const int cu = oti * WU + otj;
-            const float *u0 = sU[buf], *u1 = sU[buf ^ 1];
+            constexpr int c1 = W1 + 1, c2 = 0, cu = 0;
+            const lds_f *w0 = at(smem + W0 + oti * W1 + otj), *yc = at(yb + (oti + 2) * W2 + (otj + 2));
+            const lds_f *u0 = at(smem + U0 + (k & 1) * SU + oti * WU + otj);
+            const lds_f *u1 = at(smem + U0 + ((k & 1) ^ 1) * SU + oti * WU + otj);
             const float du_v = mv * (u0[cu + WU] - u0[cu]), du_h = mh * (u0[cu + 1] - u0[cu]);
             const float dn_v = mv * (u1[cu + WU] - u1[cu]), dn_h = mh * (u1[cu + 1] - u1[cu]);
-            const uint32_t q = vox32(k, oi, oj);
+            // A masked entry (vertical component on the last row, horizontal on
+            // the last column) keeps its value, and both sides hold the same
+            // one: it is not written at all.
+            const bool mx = oi > n1 - 2, my = oj > n2 - 2;
+            const uint32_t pp = mx || my ? kNoPix : po;
+            const bool edge = __ballot(own_in && (mx != my)) != 0ull;
 #pragma unroll
             for (int f = 0; f < 2; ++f) {
-                const float(*W)[S1] = sW[f];
-                const float pv = mv * (wk[f][0] + 0.25f * ((W[1][c1] + W[1][c1 + W1]) + (W[1][c1 - 1] + W[1][c1 + W1 - 1]))
-                                       + 0.5f * (W[2][c1] + W[2][c1 + W1]));
-                const float ph = mh * (wk[f][1] + 0.25f * ((W[0][c1] + W[0][c1 + 1]) + (W[0][c1 - W1] + W[0][c1 - W1 + 1]))
-                                       + 0.5f * (W[3][c1] + W[3][c1 + 1]));
-                P *yd = f ? dst.y2 : dst.y1;
-                const float2 y = make_float2(sY[buf][2 * f][c2], sY[buf][2 * f + 1][c2]);
+                const lds_f *A = w0 + 4 * f * S1, *B = A + S1, *C = B + S1, *E = C + S1;  // ud_h, lr_v, c_v, c_h
+                const float pv = mv * (wk[f][0] + 0.25f * ((B[c1] + B[c1 + W1]) + (B[c1 - 1] + B[c1 + W1 - 1]))
+                                       + 0.5f * (C[c1] + C[c1 + W1]));
+                const float ph = mh * (wk[f][1] + 0.25f * ((A[c1] + A[c1 + 1]) + (A[c1 - W1] + A[c1 - W1 + 1]))
+                                       + 0.5f * (E[c1] + E[c1 + 1]));
+                const float2 y = make_float2(yc[2 * f * S2 + c2], yc[(2 * f + 1) * S2 + c2]);
                 const float gv = f ? msk * (dn_v - du_v) : du_v;
                 const float gh = f ? msk * (dn_h - du_h) : du_h;
                 const float2 yn = make_float2(y.x + kStepY * (gv - pv), y.y + kStepY * (gh - ph));
-                // A masked entry (vertical component on the last row,
-                // horizontal on the last column) keeps its value, and both
-                // sides hold the same one: it is not written at all.
-                const bool mx = oi > n1 - 2, my = oj > n2 - 2;
-                if (!mx && !my) st2_nt(yd + q, yn);
-                else if (!mx) st_comp_nt(yd + q, 0, yn.x);
-                else if (!my) st_comp_nt(yd + q, 1, yn.y);
+                const BandRsrc b = band(f ? DST.y2 : DST.y1, k, true);
+                bst_nt((const P *)nullptr, b, pp, yn);
+                if (edge) {
+                    bst_comp_nt((const P *)nullptr, b, !mx && my ? po : kNoPix, 0, yn.x);
+                    bst_comp_nt((const P *)nullptr, b, mx && !my ? po : kNoPix, 1, yn.y);
+                }
+            }
+        };
+        // FUSED: step 13 (y3+ = y3 + D_v t'/5) and the t values of the next search
+        // for band kk, once the t' of the rows next to a point are in LDS
+        auto tphase = [&](int kk) {
+            if constexpr (FUSED) {
+                const float4 o = keep[tid];
+                const lds_f *tr = at(sT + tid);  // t' of the row above, this one, the row below
+                const float tp = tr[TJ];
+                const bool ei = oi <= n1 - 2;
+                const float yc = as_stored((const DT *)nullptr, ei ? __builtin_fmaf(kStepY, tr[2 * TJ] - tp, o.z) : o.z);
+                bst_nt((const DT *)nullptr, band(DST.y3, kk, true), po, yc);
+                const float ym = as_stored((const DT *)nullptr, __builtin_fmaf(kStepY, tp - tr[0], o.w));
+                gather(1, own_in, o.x, (oi >= 1 ? ym : 0.f) - (ei ? yc : 0.f), kStepT, o.y);
             }
         };
 
         // ---------------- march through the band chunk ----------------
-        if (kb >= 1) {
-            loadY(kb - 1);
-            storeY((kb - 1) & 1);
+        // Bands b - 1, b, b + 1, b + 2 of y sit in three buffers in turn; band
+        // k + 2 goes from registers to LDS in the interval in which band k is
+        // finished, and band k + 3 is requested then.
+        float *yA = smem, *yB = smem + 4 * S2, *yC = smem + 8 * S2;  // bands k, k + 1, k + 2 (and k - 1)
+        {
+            Raw p1[NY], p2[NY], q1[NY], q2[NY];
+            loadY(kb - 1, kb >= 1, p1, p2);
+            loadY(kb, true, q1, q2);
+            loadY(kb + 1, kb + 1 <= ke && kb + 1 < n3, ry1, ry2);
+            loadRU(kb, true, true);
+            storeY(yC, p1, p2);
+            storeY(yA, q1, q2);
+            storeY(yB, ry1, ry2);
         }
-        loadY(kb);
-        loadRU(kb);
-        storeY(kb & 1);
         __syncthreads();
-        uphase(kb, true);
-        loadY(kb + 1);
-        loadRU(kb + 1);
-        loadW(kb);
+        uphase(kb, true, yA, yC);
+        loadY(kb + 2, kb + 2 <= ke && kb + 2 < n3, ry1, ry2);
+        loadRU(kb + 1, kb + 1 < n3, kb + 1 < ke);
+        loadW(kb, true);
         __syncthreads();
-        storeY((kb + 1) & 1);
+        tphase(kb);
         __syncthreads();
-        for (int k = kb; k < ke; ++k) {
+        int k = kb;
+        do {
             const bool more = k + 1 < ke;
-            if (more) loadY(k + 2);
-            uphase(k + 1, more);
-            if (more) loadRU(k + 2);
-            wphase(k);
-            if (more) loadW(k + 1);
+            storeY(yC, ry1, ry2);  // band k + 2
+            fresh();
+            loadY(k + 3, k + 3 <= ke && k + 3 < n3, ry1, ry2);
+            fresh();
+            uphase(k + 1, more, yB, yA);
+            fresh();
+            loadRU(k + 2, k + 2 <= ke && k + 2 < n3, k + 2 < ke);
+            fresh();
+            w_at(k, yA, 0, oti + 1, otj + 1, mv, mh);
+            fresh();
+            if (ring_w) w_at(k, yA, 1, rwi, rwj, rmv, rmh);
+            fresh();
+            loadW(k + 1, more);
             __syncthreads();
-            yphase(k);
+            fresh();
+            yphase(k, yA);
+            fresh();
+            if (more) tphase(k + 1);
             __syncthreads();
-            if (more) storeY(k & 1);
-            __syncthreads();
-        }
+            float *const y = yA;
+            yA = yB;
+            yB = yC;
+            yC = y;
+        } while (++k < ke);
 
-        // the tile's FP64 partials: stopping sums, window statistics
-        double acc[8] = {du2, u2, (double)c_hi[0], s_hi[0], s_all[0], (double)c_hi[1], s_hi[1], s_all[1]};
-        block_sum8(acc, red);
+#undef SRC
+#undef DST
+        // the tile's FP64 partials: stopping sums; the residual's norm and the
+        // values above the windows, or the window statistics of the search
+        const bool one = (tid & 63) == 0;
+        const int nt = a.c.ntiles;
+        if constexpr (FUSED) {
+            double acc[NS] = {du2, u2, r2,
+                              one ? (double)cnt[0] : 0.0, sum[0], (double)slope[0], one ? (double)inw[0] : 0.0,
+                              one ? (double)cnt[1] : 0.0, sum[1], (double)slope[1], one ? (double)inw[1] : 0.0};
+            block_sums(acc, red);
+            if (tid == 0) {
+                for (int q = 0; q < 3; ++q) a.c.part[3 * lt + q] = acc[q];
+                for (int q = 0; q < 4; ++q) {
+                    a.c.winpart[4 * lt + q] = acc[3 + q];
+                    a.c.winpart[4 * (nt + lt) + q] = acc[7 + q];
+                }
+            }
+        } else {
+            double acc[NS] = {du2, u2, one ? (double)cnt[0] : 0.0, sum[0], all[0],
+                              one ? (double)cnt[1] : 0.0, sum[1], all[1]};
+            block_sums(acc, red);
+            if (tid == 0) {
+                a.c.part[2 * lt] = acc[0];
+                a.c.part[2 * lt + 1] = acc[1];
+                for (int f = 0; f < 2; ++f)
+                    for (int q = 0; q < 3; ++q) a.c.winpart[((int64_t)f * nt + lt) * 3 + q] = acc[2 + 3 * f + q];
+            }
+        }
         if (tid == 0) {
-            const int nt = a.c.ntiles;
             a.c.ccount[lt] = ncand[0];
             a.c.ccount[nt + lt] = ncand[1];
-            a.c.part[2 * lt] = acc[0];
-            a.c.part[2 * lt + 1] = acc[1];
-            for (int f = 0; f < 2; ++f)
-                for (int q = 0; q < 3; ++q) a.c.winpart[((int64_t)f * nt + lt) * 3 + q] = acc[2 + 3 * f + q];
         }
         __syncthreads();  // red and ncand are reused by the next tile
-    }
-}
-
-__device__ __forceinline__ float soft(float z, double tau)
-{
-    const double m = fabs((double)z) - tau;
-    return m > 0.0 ? copysignf((float)m, z) : 0.0f;
-}
-
-constexpr int RB = kSweepBRows;  // rows per sweep B strip
-constexpr int kPrefetchBlocks = 240;  // cache prefetch beside the search
-// CPT consecutive values of one row: one 4- or 8-byte access for a pair.
-__device__ __forceinline__ void ldv(const float *p, float (&o)[1]) { o[0] = *p; }
-__device__ __forceinline__ void ldv(const bf16 *p, float (&o)[1]) { o[0] = ld(p); }
-__device__ __forceinline__ void ldv(const float *p, float (&o)[2])
-{
-    const float2 x = *reinterpret_cast<const float2 *>(p);
-    o[0] = x.x;
-    o[1] = x.y;
-}
-__device__ __forceinline__ void ldv(const bf16 *p, float (&o)[2])
-{
-    const float2 x = ld2(reinterpret_cast<const bf16x2 *>(p));
-    o[0] = x.x;
-    o[1] = x.y;
-}
-__device__ __forceinline__ void ldv_nt(const float *p, float (&o)[1]) { o[0] = ld_nt(p); }
-__device__ __forceinline__ void ldv_nt(const bf16 *p, float (&o)[1]) { o[0] = ld_nt(p); }
-__device__ __forceinline__ void ldv_nt(const float *p, float (&o)[2])
-{
-    const f32x2 x = __builtin_nontemporal_load(reinterpret_cast<const f32x2 *>(p));
-    o[0] = x.x;
-    o[1] = x.y;
-}
-__device__ __forceinline__ void ldv_nt(const bf16 *p, float (&o)[2])
-{
-    const uint32_t b = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p));
-    o[0] = __uint_as_float(b << 16);
-    o[1] = __uint_as_float(b & 0xffff0000u);
-}
-// four columns: one 16-byte FP32 or 8-byte BF16 access
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void ldv(const float *p, float (&o)[4])
-{
-    const float4 x = *reinterpret_cast<const float4 *>(p);
-    o[0] = x.x;
-    o[1] = x.y;
-    o[2] = x.z;
-    o[3] = x.w;
-}
-__device__ __forceinline__ void ldv(const bf16 *p, float (&o)[4])
-{
-    const uint2 b = *reinterpret_cast<const uint2 *>(p);
-    o[0] = __uint_as_float(b.x << 16);
-    o[1] = __uint_as_float(b.x & 0xffff0000u);
-    o[2] = __uint_as_float(b.y << 16);
-    o[3] = __uint_as_float(b.y & 0xffff0000u);
-}
-__device__ __forceinline__ void ldv_nt(const float *p, float (&o)[4])
-{
-    const f32x4 x = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
-    o[0] = x.x;
-    o[1] = x.y;
-    o[2] = x.z;
-    o[3] = x.w;
-}
-__device__ __forceinline__ void ldv_nt(const bf16 *p, float (&o)[4])
-{
-    float a[2], b[2];
-    ldv_nt(p, a);
-    ldv_nt(p + 2, b);
-    o[0] = a[0];
-    o[1] = a[1];
-    o[2] = b[0];
-    o[3] = b[1];
-}
-template <typename T>
-__device__ __forceinline__ void stv_nt(T *p, const float (&x)[1]) { st_nt(p, x[0]); }
-__device__ __forceinline__ void stv_nt(float *p, const float (&x)[4])
-{
-    f32x4 v;
-    v.x = x[0];
-    v.y = x[1];
-    v.z = x[2];
-    v.w = x[3];
-    __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
-}
-__device__ __forceinline__ void stv_nt(bf16 *p, const float (&x)[4])
-{
-    st2_nt(reinterpret_cast<bf16x2 *>(p), make_float2(x[0], x[1]));
-    st2_nt(reinterpret_cast<bf16x2 *>(p + 2), make_float2(x[2], x[3]));
-}
-__device__ __forceinline__ void stv_nt(float *p, const float (&x)[2])
-{
-    st_nt(reinterpret_cast<float2 *>(p), make_float2(x[0], x[1]));
-}
-__device__ __forceinline__ void stv_nt(bf16 *p, const float (&x)[2])
-{
-    st2_nt(reinterpret_cast<bf16x2 *>(p), make_float2(x[0], x[1]));
-}
-
-// Steps 2, 3 (soft thresholds at the selected levels), 7, 8, 13 and 14; the
-// z inputs are evaluated again exactly as sweep A did. A thread takes a strip
-// of RB rows and CPT adjacent columns of one band and issues all of its loads
-// at once; only the rows just above and below the strip (D_v coupling of t'
-// and y3) are read twice. CPT = 2 (one access per pair) when the row length
-// is even, else 1.
-template <typename DT, int CPT>
-__device__ __forceinline__ double sweep_b_strips(const CubeArgs<DT> &a, const DevScalars *sc, int lb,
-                                                 double ts, double tt)
-{
-    const Dims d = a.c.d;
-    const int n1 = d.n1, n2 = d.n2, n3 = d.n3;
-    const int par = (int)(sc->iter & 1u);
-    const Side<DT> src = a.side[par], dst = a.side[par ^ 1];
-    const float a4 = (float)sc->a4;
-    double r2 = 0.0;
-    const uint32_t nstrip = (uint32_t)((n1 + RB - 1) / RB);
-    const uint32_t ncol = (uint32_t)(n2 / CPT);
-    const uint32_t items = (uint32_t)n3 * nstrip * ncol;
-    const uint32_t stride = (uint32_t)a.c.nb * NPT;
-    for (uint32_t w = (uint32_t)lb * NPT + threadIdx.x; w < items; w += stride) {
-        const uint32_t j = CPT * (w % ncol), rr = w / ncol;
-        const int ia = (int)(rr % nstrip) * RB, k = (int)(rr / nstrip);
-        const uint32_t q0 = ((uint32_t)k * (uint32_t)n1 + (uint32_t)ia) * (uint32_t)n2 + j;
-        // rows ia .. ia+RB-1 of the strip, and row ia+RB for the D_v coupling
-        float y3r[RB + 1][CPT], y4[RB + 1][CPT], to[RB + 1][CPT], so[RB][CPT], yp[RB][CPT];
-        float y3m0[CPT];
-        if (ia >= 1) ldv(src.y3 + q0 - n2, y3m0);
-        else
-#pragma unroll
-            for (int c = 0; c < CPT; ++c) y3m0[c] = 0.f;
-#pragma unroll
-        for (int r = 0; r <= RB; ++r) {
-            const bool in = ia + r < n1;
-            const uint32_t q = q0 + (uint32_t)(r * n2);
-            float q4[CPT];
-            if (in) {
-                ldv(src.y3 + q, y3r[r]);
-                ldv(src.y4 + q, q4);
-                ldv(src.t + q, to[r]);
-                if (r < RB) {
-                    ldv_nt(src.s + q, so[r]);
-                    ldv_nt(a.y4p + q, yp[r]);
-                }
-            } else {
-#pragma unroll
-                for (int c = 0; c < CPT; ++c) {
-                    y3r[r][c] = q4[c] = to[r][c] = 0.f;
-                    if (r < RB) so[r][c] = yp[r][c] = 0.f;
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < CPT; ++c) y4[r][c] = in ? y4_of(q4[c], a4) : 0.f;
-        }
-        float tp[RB + 1][CPT];
-#pragma unroll
-        for (int r = 0; r <= RB; ++r) {
-            const int i = ia + r;
-            float tn[CPT];
-#pragma unroll
-            for (int c = 0; c < CPT; ++c) {
-                const float y3m = r == 0 ? y3m0[c] : y3r[r - 1][c];
-                tn[c] = soft(zt_of(to[r][c], y3m, i <= n1 - 2 ? y3r[r][c] : 0.f, y4[r][c]), tt);
-                tp[r][c] = 2.f * tn[c] - to[r][c];
-            }
-            if (r < RB && i < n1) stv_nt(dst.t + q0 + (uint32_t)(r * n2), tn);
-        }
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            const int i = ia + r;
-            if (i < n1) {
-                const uint32_t q = q0 + (uint32_t)(r * n2);
-                float sn[CPT], y3n[CPT], qn[CPT];
-#pragma unroll
-                for (int c = 0; c < CPT; ++c) {
-                    sn[c] = soft(zs_of(so[r][c], y4[r][c]), ts);
-                    const float sp = 2.f * sn[c] - so[r][c];
-                    const float tp1 = i <= n1 - 2 ? tp[r + 1][c] : 0.f;
-                    y3n[c] = y3r[r][c] + kStepY * mask_le(i, n1) * (tp1 - tp[r][c]);
-                    // q+ = 5 y4' - v (step 14); r = ||q+|| (step 15)
-                    qn[c] = as_stored(dst.y4, yp[r][c] + (sp + tp[r][c]));
-                    r2 += (double)qn[c] * (double)qn[c];
-                }
-                stv_nt(dst.s + q, sn);
-                stv_nt(dst.y3 + q, y3n);
-                stv_nt(dst.y4 + q, qn);
-            }
-        }
-    }
-    return r2;
-}
-
-// WIDE: the cubes whose sweep B takes four columns per thread (a kernel of
-// their own: that form needs 104 registers, the others 73, and a kernel runs
-// at the occupancy of its largest form); otherwise the others.
-template <typename DT, bool WIDE>
-__global__ __launch_bounds__(NPT) void k_sweep_b(Table<DT> cubes, LaunchShape sh)
-{
-    __shared__ double red[NPT / 64];
-    __shared__ int cube_of_block;
-    // blocks [b0, b0 + nb) belong to one cube: the last cube whose b0 is at
-    // most this block's index, found by one wavefront (one load per lane;
-    // a scan by one thread took a memory round trip per cube of a batch)
-    static_assert(kMaxBatch <= 64, "one wavefront covers the cubes");
-    if (threadIdx.x < 64) {
-        const int c = threadIdx.x;
-        const bool le = c < sh.ncubes && cubes[c].c.b0 <= (int)blockIdx.x;
-        const unsigned long long m = __ballot(le);
-        if (c == 0) cube_of_block = 63 - __clzll((long long)m);  // cube 0 starts at block 0
-    }
-    __syncthreads();
-    const CubeArgs<DT> &a = cubes[__builtin_amdgcn_readfirstlane(cube_of_block)];
-    const DevScalars *sc = a.c.sc;
-    const int cpt = sweep_b_cpt(a.c.d.n2, (int)sizeof(DT));
-    if (idle(sc) || (cpt == 4) != WIDE) return;
-    // a missed window's threshold comes from this slot's histogram passes
-    const double ts = sc->sel[0].done ? sc->sel[0].tau : fb_final(a.c.rec, 0).tau;
-    const double tt = sc->sel[1].done ? sc->sel[1].tau : fb_final(a.c.rec, 1).tau;
-    const int lb = (int)blockIdx.x - a.c.b0;  // block within the cube
-    double r2;
-    if constexpr (WIDE)
-        r2 = sweep_b_strips<DT, 4>(a, sc, lb, ts, tt);
-    else
-        r2 = cpt == 2 ? sweep_b_strips<DT, 2>(a, sc, lb, ts, tt) : sweep_b_strips<DT, 1>(a, sc, lb, ts, tt);
-    const double tot = block_sum<NPT>(r2, red);
-    if (threadIdx.x == 0) a.c.part[2 * a.c.ntiles + lb] = tot;
-}
-
-// Fixed-order sums of the block partials of both sweeps: relative change of u
-// (stopping rule), r = ||y4'/gamma4 - v|| for the lazy scale of y4 (step 15),
-// iteration counter. A separate one-block launch: a last-block-done pattern
-// inside sweep B needs a device-scope release per block, which writes back
-// the XCD's L2 each time.
-// One block per cube of the table (entries of `stride` bytes).
-__global__ __launch_bounds__(NPT) void k_finalize(const char *table, int stride)
-{
-    // the launch table through the constant address space (scalar loads)
-    const4<CubeCommon> &cc = *(const4<CubeCommon> *)(table + (size_t)blockIdx.x * stride);
-    DevScalars *sc = cc.sc;
-    const double *part = cc.part;
-    const int grid_a = cc.ntiles, blocks_b = cc.nb;
-    __shared__ double red[3 * (NPT / 64)];
-    // the partials are read together with the flag that may make them moot
-    const bool skip = idle(sc);
-    // each thread adds its partials b = tid, tid + NPT, ... in that order,
-    // kFinUnroll of them loaded at a time
-    constexpr int kFinUnroll = 8;
-    double du2 = 0.0, u2 = 0.0, r2 = 0.0;
-    for (int b0 = threadIdx.x; b0 < grid_a; b0 += kFinUnroll * NPT) {
-        double x0[kFinUnroll], x1[kFinUnroll];
-#pragma unroll
-        for (int k = 0; k < kFinUnroll; ++k) {
-            const int b = b0 + k * NPT;
-            x0[k] = b < grid_a ? part[2 * b] : 0.0;
-            x1[k] = b < grid_a ? part[2 * b + 1] : 0.0;
-        }
-#pragma unroll
-        for (int k = 0; k < kFinUnroll; ++k)
-            if (b0 + k * NPT < grid_a) {
-                du2 += x0[k];
-                u2 += x1[k];
-            }
-    }
-    for (int b0 = threadIdx.x; b0 < blocks_b; b0 += kFinUnroll * NPT) {
-        double x2[kFinUnroll];
-#pragma unroll
-        for (int k = 0; k < kFinUnroll; ++k) {
-            const int b = b0 + k * NPT;
-            x2[k] = b < blocks_b ? part[2 * grid_a + b] : 0.0;
-        }
-#pragma unroll
-        for (int k = 0; k < kFinUnroll; ++k)
-            if (b0 + k * NPT < blocks_b) r2 += x2[k];
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *slot_flags(table, (int)gridDim.x) = 0u;
-    if (skip) return;
-    // a threshold found by this slot's histogram passes becomes the field's
-    // search state, with the window of the next iteration sized by the
-    // density of |z| around it (only this block writes the cube's state)
-    if (threadIdx.x == 0) {
-        bool missed = false;
-        for (int f = 0; f < 2; ++f)
-            if (!sc->sel[f].done) {
-                missed = true;
-                const FbRec &r = fb_final(cc.rec, f);
-                SelState o = sc->sel[f];
-                o.tau = r.tau;
-                o.done = 1u;
-                o.full = 0u;
-                o.dens = cc.rec[f].dens;
-                set_window(o, true, window_budget(cc.d.plane));
-                sc->sel[f] = o;
-            }
-        // whether the next iteration's sweep A stores z (iter counts this one)
-        const uint32_t calm = missed ? 0u : sc->calm + 1u;
-        sc->calm = calm;
-        sc->zstore = (sc->iter + 1u < kZStoreIters || calm < kZStoreCalm) ? 1u : 0u;
-    }
-    // the three block sums at once, in the order of block_sum: a butterfly
-    // within each wavefront, then the wavefronts in order (thread 0)
-    du2 = wave_sum(du2);
-    u2 = wave_sum(u2);
-    r2 = wave_sum(r2);
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (lane == 0) {
-        red[wid] = du2;
-        red[NPT / 64 + wid] = u2;
-        red[2 * (NPT / 64) + wid] = r2;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        du2 = u2 = r2 = 0.0;
-        for (int w = 0; w < NPT / 64; ++w) {
-            du2 += red[w];
-            u2 += red[NPT / 64 + w];
-            r2 += red[2 * (NPT / 64) + w];
-        }
-        const double r = sqrt(r2);
-        const double rel = u2 > 0.0 ? sqrt(du2) / sqrt(u2) : __longlong_as_double(0x7ff0000000000000ll);
-        const bool bad = !isfinite(du2) || !isfinite(u2) || !isfinite(r2);
-        sc->r = r;
-        sc->rel = rel;
-        sc->c4 = r > sc->eps ? 1.0 - sc->eps / r : 0.0;
-        sc->a4 = sc->gy4 * sc->c4;
-        sc->iter = sc->iter + 1u;
-        sc->calls_iter = sc->calls_iter + 1u;
-        if (bad) sc->nonfinite = 1u;
-        // eq. (28), from the second iteration after the initial point on: the
-        // first one (zero duals) changes u only by the box projection
-        if (bad || (sc->tol > 0.0 && sc->iter >= 2u && rel < sc->tol)) sc->stop = 1u;
     }
 }
 
@@ -859,23 +651,18 @@ __global__ __launch_bounds__(NPT) void k_init(Dims d, const float *v, Side<DT> s
         z.tol = tol;
         z.sel[0].radius = alpha;
         z.sel[1].radius = beta;
-        z.sel[0].done = z.sel[1].done = 1u;  // no search pending
-        z.zstore = 1u;
+        // z_s = z_t = 0: inside the balls, tau = 0 (radius 0: +inf)
+        for (int f = 0; f < 2; ++f) {
+            z.sel[f].done = 1u;
+            if (!(z.sel[f].radius > 0.0)) z.sel[f].tau = __longlong_as_double(0x7ff0000000000000ll);
+        }
         z.gy4 = 0.2;  // the y4 step printed after eq. (24)
+        for (int f = 0; f < 2; ++f) z.in.set(f, z.sel[f]);
+        z.zstore = 1u;
+        z.in.a4 = 1.f;
+        z.in.a_hi = __double2float_ru(z.gy4);
+        z.in.a_c = 0.1f;
         *sc = z;
-    }
-}
-
-__global__ void k_begin_call(DevScalars *sc, double tol, double alpha, double beta, uint32_t limit)
-{
-    if (threadIdx.x == 0) {
-        sc->tol = tol;
-        sc->calls_iter = 0u;
-        sc->call_limit = limit;
-        sc->fallback = 0u;
-        sc->sel[0].radius = alpha;
-        sc->sel[1].radius = beta;
-        if (!sc->nonfinite) sc->stop = 0u;
     }
 }
 
@@ -999,13 +786,13 @@ int resident_grid()
             hipDeviceProp_t prop;
             if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
         }
-        // the smaller occupancy of the tile shapes in use
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&p0, k_sweep_a<DT, 0>, NT, 0) != hipSuccess || p0 < 1)
+        // the smaller occupancy of the tile shapes in use (BF16: 8 x 128 only)
+        constexpr bool fused = sizeof(DT) == 4;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&p0, k_sweep<DT, 0, fused>, NT, 0) != hipSuccess || p0 < 1)
             p0 = 1;
         p1 = p0;
-        if constexpr (sizeof(DT) == 4)
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&p1, k_sweep_a<DT, 1>, NT, 0) != hipSuccess ||
-                p1 < 1)
+        if constexpr (fused)
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&p1, k_sweep<DT, 1, true>, NT, 0) != hipSuccess || p1 < 1)
                 p1 = 1;
         return cus * (p0 < p1 ? p0 : p1);
     }();
@@ -1013,9 +800,8 @@ int resident_grid()
 }
 
 template <typename DT>
-void cube_entry_t(CubeArgs<DT> *a, const Dims &d, const float *v, void *ws, const Layout &L,
-                  double omega, double mu_lo, double mu_hi, int kc, int tile0, int b0, int *ntiles,
-                  int *nb)
+void cube_entry_t(CubeArgs<DT> *a, const Dims &d, const float *v, void *ws, const Layout &L, const geo_params *p,
+                  int n_iter, int tile0, int b0, int *ntiles, int *nb)
 {
     char *b = (char *)ws;
     memset(a, 0, sizeof *a);
@@ -1027,83 +813,108 @@ void cube_entry_t(CubeArgs<DT> *a, const Dims &d, const float *v, void *ws, cons
     c.winpart = (double *)(b + L.winpart);
     c.hist = (Hist *)(b + L.hist);
     c.rec = (FbRec *)(b + L.rec);
-    c.cand = (float *)(b + L.cand);
-    c.zbuf = (float *)(b + L.zbuf);
+    constexpr bool fused = sizeof(DT) == 4;
+    c.ahead = fused ? 1u : 0u;
+    if (fused) {
+        c.cand = (float4 *)(b + L.cand);
+    } else {
+        c.vcand = (float *)(b + L.cand);
+        c.zbuf = (float *)(b + L.zbuf);
+    }
     c.ccount = (uint32_t *)(b + L.ccount);
     const int shape = tile_shape(d.n1, d.n2, (int)sizeof(DT));
-    c.g = sweep_grid(d.n1, d.n2, d.n3, band_chunk(d.n1, d.n2, d.n3, kc, sweep_a_grid(sizeof(DT), 1 << 30), shape),
-                     shape);
+    c.g = sweep_grid(d.n1, d.n2, d.n3,
+                     band_chunk(d.n1, d.n2, d.n3, p->band_chunk, sweep_a_grid(sizeof(DT), 1 << 30), shape), shape);
     c.ntiles = c.g.blocks();
     c.capt = (int)(L.cap / c.ntiles);
     c.tile0 = tile0;
-    {
-        // strips of RB rows and CPT columns; never more blocks than the
-        // partials hold
-        const int64_t items = (int64_t)d.n3 * ((d.n1 + RB - 1) / RB) * (d.n2 / sweep_b_cpt(d.n2, (int)sizeof(DT)));
-        const int pb = point_blocks(items);
-        c.nb = pb < kSweepBBlocks ? pb : kSweepBBlocks;
-    }
-    c.b0 = b0;
-    c.thr1 = (float)(omega * 0.25);
+    c.thr1 = (float)(p->omega * 0.25);
     c.zt_step = kStepT;
-    c.mu_lo = (float)mu_lo;
-    c.mu_hi = (float)mu_hi;
+    c.mu_lo = (float)p->mu_lo;
+    c.mu_hi = (float)p->mu_hi;
+    c.tol = p->tol;
+    c.alpha = p->alpha;
+    c.beta = p->beta;
+    c.limit = (uint32_t)n_iter;
     a->side[0] = side_of<DT>(ws, L, 0);
     a->side[1] = side_of<DT>(ws, L, 1);
-    a->y4p = (DT *)(b + L.y4p);
-    for (int p = 0; p < 2; ++p) {
-        c.bin[p][0] = a->side[p].s;
-        c.bin[p][1] = a->side[p].t;
-        c.bin[p][2] = a->side[p].y3;
-        c.bin[p][3] = a->side[p].y4;
-        c.bin[p][4] = a->y4p;
+    if (!fused) {
+        // sweep B: strips of kSweepBRows rows; never more blocks than the
+        // partials hold
+        const int64_t items = (int64_t)d.n3 * ((d.n1 + kSweepBRows - 1) / kSweepBRows) * (d.n2 / sweep_b_cpt(d.n2));
+        const int pb = point_blocks(items);
+        c.nb = pb < kSweepBBlocks ? pb : kSweepBBlocks;
+        c.b0 = b0;
+        a->y4p = (DT *)(b + L.y4p);
+        for (int p = 0; p < 2; ++p) {
+            c.bin[p][0] = a->side[p].s;
+            c.bin[p][1] = a->side[p].t;
+            c.bin[p][2] = a->side[p].y3;
+            c.bin[p][3] = a->side[p].y4;
+            c.bin[p][4] = a->y4p;
+        }
+        const size_t N = (size_t)d.plane;
+        c.bin_bytes[0] = c.bin_bytes[1] = N * sizeof(float);
+        c.bin_bytes[2] = c.bin_bytes[3] = c.bin_bytes[4] = N * sizeof(DT);
     }
-    const size_t N = (size_t)d.plane;
-    c.bin_bytes[0] = c.bin_bytes[1] = N * sizeof(float);
-    c.bin_bytes[2] = c.bin_bytes[3] = c.bin_bytes[4] = N * sizeof(DT);
     *ntiles = c.ntiles;
     *nb = c.nb;
 }
 
-template <typename DT>
-hipError_t slot_t(const void *table, const LaunchShape &sh, hipStream_t st, hipEvent_t *ev, int nev)
+constexpr int kPrefetchBlocks = 240;  // cache prefetch beside the search (BF16)
+
+hipError_t passes(const void *table, int dual_bytes, const LaunchShape &sh, hipStream_t st)
 {
-    const CubeArgs<DT> *cubes = (const CubeArgs<DT> *)table;
-    const int stride = (int)sizeof(CubeArgs<DT>);
-    if (nev >= 2) (void)hipEventRecord(ev[0], st);
+    hipError_t e = hipSuccess;
+    for (int level = 0; level < 3 && e == hipSuccess; ++level) e = launch_fallback(table, dual_bytes, sh, level, st);
+    return e;
+}
+
+hipError_t slot_fused(const void *table, const LaunchShape &sh, hipStream_t st, hipEvent_t *ev, int nev)
+{
+    const CubeArgs<float> *cubes = (const CubeArgs<float> *)table;
+    if (nev >= 4) (void)hipEventRecord(ev[0], st);
+    hipError_t e = passes(table, 4, sh, st);
+    if (e != hipSuccess) return e;
+    if (nev >= 2) (void)hipEventRecord(ev[nev >= 4 ? 1 : 0], st);
     // one persistent launch per tile shape present (each takes the tiles of
     // its cubes)
     if (sh.shape_tiles[0] > 0)
-        hipLaunchKernelGGL((k_sweep_a<DT, 0>), dim3(sh.shape_grid[0]), dim3(NT), 0, st, cubes, sh);
-    if constexpr (sizeof(DT) == 4)  // BF16 duals use 8 x 128 tiles only
-        if (sh.shape_tiles[1] > 0)
-            hipLaunchKernelGGL((k_sweep_a<DT, 1>), dim3(sh.shape_grid[1]), dim3(NT), 0, st, cubes, sh);
+        hipLaunchKernelGGL((k_sweep<float, 0, true>), dim3(sh.shape_grid[0]), dim3(NT), 0, st, cubes, sh);
+    if (sh.shape_tiles[1] > 0)
+        hipLaunchKernelGGL((k_sweep<float, 1, true>), dim3(sh.shape_grid[1]), dim3(NT), 0, st, cubes, sh);
+    if (nev >= 2) (void)hipEventRecord(ev[nev >= 4 ? 2 : 1], st);
+    e = launch_search(table, (int)sizeof(CubeEntry), sh.ncubes, st);
+    if (nev >= 4) (void)hipEventRecord(ev[3], st);
+    return e;
+}
+
+hipError_t slot_two(const void *table, const LaunchShape &sh, hipStream_t st, hipEvent_t *ev, int nev)
+{
+    const CubeArgs<bf16> *cubes = (const CubeArgs<bf16> *)table;
+    const int stride = (int)sizeof(CubeEntry);
+    if (nev >= 2) (void)hipEventRecord(ev[0], st);
+    hipLaunchKernelGGL((k_sweep<bf16, 0, false>), dim3(sh.shape_grid[0]), dim3(NT), 0, st, cubes, sh);
     if (nev >= 2) (void)hipEventRecord(ev[1], st);
     hipError_t e = launch_select_window(table, stride, sh.ncubes, kPrefetchBlocks, st);
-    for (int level = 0; level < 3 && e == hipSuccess; ++level)
-        e = launch_fallback(table, (int)sizeof(DT), sh, level, st);
+    if (e == hipSuccess) e = passes(table, 2, sh, st);
     if (e != hipSuccess) return e;
     if (nev >= 4) (void)hipEventRecord(ev[2], st);
-    if (sh.b_kinds & 1)
-        hipLaunchKernelGGL((k_sweep_b<DT, false>), dim3(sh.total_b), dim3(NPT), 0, st, cubes, sh);
-    if (sh.b_kinds & 2)
-        hipLaunchKernelGGL((k_sweep_b<DT, true>), dim3(sh.total_b), dim3(NPT), 0, st, cubes, sh);
-    hipLaunchKernelGGL(k_finalize, dim3(sh.ncubes), dim3(NPT), 0, st, (const char *)table, stride);
+    e = launch_sweep_b(table, sh, st);
+    if (e == hipSuccess) e = launch_finalize(table, stride, sh.ncubes, st);
     if (nev >= 4) (void)hipEventRecord(ev[3], st);
-    return hipGetLastError();
+    return e;
 }
 
 }  // namespace
 
-void cube_entry(CubeEntry *e, const Dims &d, const float *v, void *ws, const Layout &L, double omega,
-                double mu_lo, double mu_hi, int kc, int tile0, int b0, int *ntiles, int *nb)
+void cube_entry(CubeEntry *e, const Dims &d, const float *v, void *ws, const Layout &L, const geo_params *p,
+                int n_iter, int tile0, int b0, int *ntiles, int *nb)
 {
     if (L.dual_bytes == 2)
-        cube_entry_t<bf16>(reinterpret_cast<CubeArgs<bf16> *>(e->bytes), d, v, ws, L, omega, mu_lo,
-                           mu_hi, kc, tile0, b0, ntiles, nb);
+        cube_entry_t<bf16>(reinterpret_cast<CubeArgs<bf16> *>(e->bytes), d, v, ws, L, p, n_iter, tile0, b0, ntiles, nb);
     else
-        cube_entry_t<float>(reinterpret_cast<CubeArgs<float> *>(e->bytes), d, v, ws, L, omega, mu_lo,
-                            mu_hi, kc, tile0, b0, ntiles, nb);
+        cube_entry_t<float>(reinterpret_cast<CubeArgs<float> *>(e->bytes), d, v, ws, L, p, n_iter, tile0, b0, ntiles, nb);
 }
 
 // Persistent sweep A grid: resident blocks, at most one per tile, a multiple
@@ -1119,13 +930,7 @@ hipError_t launch_slot(const void *table, int dual_bytes, const LaunchShape &sh,
                        hipEvent_t *ev, int nev)
 {
     if (!ev) nev = 0;
-    return dual_bytes == 2 ? slot_t<bf16>(table, sh, st, ev, nev) : slot_t<float>(table, sh, st, ev, nev);
-}
-
-hipError_t launch_finalize(const void *table, int stride, int ncubes, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_finalize, dim3(ncubes), dim3(NPT), 0, st, (const char *)table, stride);
-    return hipGetLastError();
+    return dual_bytes == 2 ? slot_two(table, sh, st, ev, nev) : slot_fused(table, sh, st, ev, nev);
 }
 
 hipError_t launch_state_loaded(DevScalars *sc, int var, hipStream_t st)
@@ -1148,15 +953,6 @@ hipError_t launch_init(const Dims &d, const float *v, void *ws, const Layout &L,
     return hipGetLastError();
 }
 
-hipError_t launch_begin_call(void *ws, const Layout &L, double tol, double alpha, double beta,
-                             int call_limit, hipStream_t st)
-{
-    DevScalars *sc = (DevScalars *)((char *)ws + L.scalars);
-    hipLaunchKernelGGL(k_begin_call, dim3(1), dim3(64), 0, st, sc, tol, alpha, beta,
-                       (uint32_t)call_limit);
-    return hipGetLastError();
-}
-
 hipError_t launch_state_io(const Dims &d, void *ws, const Layout &L, int var, const float *v,
                            float *out, const float *in, hipStream_t st)
 {
@@ -1170,8 +966,10 @@ hipError_t launch_state_io(const Dims &d, void *ws, const Layout &L, int var, co
     else
         hipLaunchKernelGGL(k_state_io<float>, dim3(grid), dim3(NPT), 0, st, d,
                            side_of<float>(ws, L, 0), side_of<float>(ws, L, 1), sc, var, v, out, in);
-    if (in) hipLaunchKernelGGL(k_state_loaded, dim3(1), dim3(64), 0, st, sc, var);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !in) return e;
+    return L.dual_bytes == 2 ? launch_state_loaded(sc, var, st)
+                             : launch_loaded(sc, (Hist *)((char *)ws + L.hist), var, st);
 }
 
 }  // namespace geo

@@ -767,7 +767,7 @@ void var_table_entry(CubeEntry *e, const VarArgs &a, const VarLayout &L, void *w
     c.winpart = a.winpart;
     c.hist = (Hist *)(b + L.hist);
     c.rec = (FbRec *)(b + L.rec);
-    c.cand = a.cand;
+    c.vcand = a.cand;
     c.ccount = a.ccount;
     c.zbuf = a.z;
     c.capt = a.capt;
