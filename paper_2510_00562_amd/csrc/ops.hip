@@ -1,7 +1,7 @@
 // Standalone operators and proximal tools behind geo_apply_op and the
-// geo_project_* / geo_prox_l12 entry points. One thread per output element;
-// neighbours come through the caches. The solver itself does not use these
-// kernels: its fused sweeps (sweep.hip) stage the same stencils in LDS.
+// geo_project_* / geo_prox_l12 entry points. Neighbours come through the
+// caches. The solver itself does not use these kernels: its fused sweeps
+// (sweep.hip) stage the same stencils in LDS.
 #include "solver.hpp"
 
 namespace geo {
@@ -188,6 +188,219 @@ __global__ __launch_bounds__(NT) void k_apply(int op, int adj, Dims d, const flo
     out[g] = o;
 }
 
+// One thread per voxel and all of its output planes, for bands that the buffer
+// path takes (common.hpp: band_of; below kOpsPixels pixels). What bounds an
+// operator is HBM (K: 21 planes, 84 bytes per voxel): every plane is read from
+// HBM once, the neighbours come from the caches, and a thread's loads (37 for K)
+// are in flight together. k_apply above, one thread per output element, decodes
+// its index with 64-bit divisions and reads a plane once per output plane that
+// needs it: K and its adjoint at 256 x 256 x 128 took 324 and 543 us.
+constexpr uint32_t kOpsPixels = 1u << 26;
+
+struct OpView {
+    const float *in;
+    float *out;
+    int64_t N;
+    uint32_t np, n2, rows;  // pixels of a band, of a row, of the rows that hold a vertical edge
+    int n3, k;
+    uint32_t c0, cm, cp;    // this pixel, its left and right neighbours (kNoPix: none)
+    uint32_t h0;            // this pixel where it holds a horizontal edge
+    float mv, mh;           // 1 where the edge to the row below, the next column exists
+    bool next;              // there is a next band
+
+    __device__ __forceinline__ BandRsrc band(const float *p, int kk, uint32_t count) const
+    {
+        return band_of(p, (int64_t)kk * np, kk >= 0 && kk < n3 ? count : 0u);
+    }
+    // plane pl of the input, whole or its vertical edges only, band k + dk
+    __device__ __forceinline__ BandRsrc full(int pl, int dk = 0) const { return band(in + (int64_t)pl * N, k + dk, np); }
+    __device__ __forceinline__ BandRsrc vert(int pl, int dk = 0) const { return band(in + (int64_t)pl * N, k + dk, rows); }
+    __device__ __forceinline__ float at(BandRsrc r, uint32_t pix) const { return bld((const float *)nullptr, r, pix); }
+    __device__ __forceinline__ void put(int pl, float x) const
+    {
+        bst_nt((const float *)nullptr, band(out + (int64_t)pl * N, k, np), c0, x);
+    }
+    // x where there is a next band, else 0
+    __device__ __forceinline__ float in_band(float x) const { return next ? x : 0.f; }
+    // differences of one plane
+    __device__ __forceinline__ float dv(int pl, int dk = 0) const
+    {
+        const BandRsrc r = full(pl, dk);
+        const float x = at(r, c0 + n2) - at(r, c0);
+        return mv != 0.f ? x : 0.f;  // (a select: an infinite value stays in its own edges)
+    }
+    __device__ __forceinline__ float dh(int pl, int dk = 0) const
+    {
+        const BandRsrc r = full(pl, dk);
+        const float x = at(r, cp) - at(r, c0);
+        return mh != 0.f ? x : 0.f;
+    }
+    __device__ __forceinline__ float dvt(int pl, int dk = 0) const
+    {
+        const BandRsrc r = vert(pl, dk);
+        return at(r, c0 - n2) - at(r, c0);
+    }
+    __device__ __forceinline__ float dht(int pl, int dk = 0) const
+    {
+        const BandRsrc r = full(pl, dk);
+        return at(r, cm) - at(r, h0);
+    }
+    // D^T of the edge field in planes pl, pl + 1; D_s^T D^T of it
+    __device__ __forceinline__ float dt(int pl, int dk = 0) const { return dvt(pl, dk) + dht(pl + 1, dk); }
+    __device__ __forceinline__ float ddst(int pl) const { return dt(pl, -1) - in_band(dt(pl)); }
+    // the six components of L y, y in planes pl, pl + 1
+    __device__ __forceinline__ void interp(int pl, float (&o)[6]) const
+    {
+        const BandRsrc v = vert(pl), h = full(pl + 1);
+        const float v00 = at(v, c0), vu = at(v, c0 - n2), vr = at(v, cp), vur = at(v, cp - n2);
+        const float h00 = at(h, h0), hl = at(h, cm), hd = at(h, h0 + n2), hld = at(h, cm + n2);
+        o[0] = v00;
+        o[1] = mv * 0.25f * (h00 + hl + hd + hld);
+        o[2] = mh * 0.25f * (v00 + vu + vr + vur);
+        o[3] = h00;
+        o[4] = 0.5f * (v00 + vu);
+        o[5] = 0.5f * (h00 + hl);
+    }
+    // vertical and horizontal part of L^T w over the grids in G (bit 0 ud, 1 lr,
+    // 2 c); ud, lr, c: first plane of each grid's pair
+    template <int G>
+    __device__ __forceinline__ void interp_t(int ud, int lr, int c, float &pv, float &ph) const
+    {
+        float a = 0.f, b = 0.f;
+        if constexpr (G & 1) a += at(vert(ud), c0);
+        if constexpr (G & 2) {
+            const BandRsrc r = full(lr);
+            a += 0.25f * (at(r, h0) + at(r, h0 + n2) + at(r, cm) + at(r, cm + n2));
+            b += at(full(lr + 1), h0);
+        }
+        if constexpr (G & 1) {
+            const BandRsrc r = vert(ud + 1);
+            b += 0.25f * (at(r, c0) + at(r, cp) + at(r, c0 - n2) + at(r, cp - n2));
+        }
+        if constexpr (G & 4) {
+            const BandRsrc r = full(c), q = full(c + 1);
+            a += 0.5f * (at(r, c0) + at(r, c0 + n2));
+            b += 0.5f * (at(q, c0) + at(q, cp));
+        }
+        pv = mv * a;
+        ph = mh * b;
+    }
+};
+
+// Blocks in an order that gives each of the 8 XCDs a contiguous run of them, so
+// that the rows which neighbouring blocks share meet in one L2.
+__device__ __forceinline__ uint32_t xcd_order(uint32_t b, uint32_t n)
+{
+    const uint32_t per = n >> 3;
+    return b < 8u * per ? (b & 7u) * per + (b >> 3) : b;
+}
+
+template <int OP, bool ADJ>
+__global__ __launch_bounds__(NT) void k_op(Dims d, const float *in, float *out, uint32_t bx, uint32_t blocks)
+{
+    for (uint32_t b0 = blockIdx.x; b0 < blocks; b0 += gridDim.x) {
+        const uint32_t b = xcd_order(b0, blocks), np = (uint32_t)d.n1 * (uint32_t)d.n2, n2 = (uint32_t)d.n2;
+        OpView v;
+        v.k = (int)(b / bx);
+        const uint32_t p = (b % bx) * NT + threadIdx.x, i = p / n2, j = p - i * n2;
+        const bool ok = p < np;
+        v.in = in;
+        v.out = out;
+        v.N = d.plane;
+        v.np = np;
+        v.n2 = n2;
+        v.rows = np - n2;
+        v.n3 = d.n3;
+        v.c0 = ok ? p : kNoPix;
+        v.cm = ok && j >= 1 ? p - 1 : kNoPix;
+        v.cp = ok && j + 1 < n2 ? p + 1 : kNoPix;
+        v.h0 = ok && j + 1 < n2 ? p : kNoPix;
+        v.mv = mask_le((int)i, d.n1);
+        v.mh = mask_le((int)j, d.n2);
+        v.next = v.k <= d.n3 - 2;
+        if constexpr (!ADJ) {
+            if constexpr (OP == GEO_OP_DV) v.put(0, v.dv(0));
+            if constexpr (OP == GEO_OP_DH) v.put(0, v.dh(0));
+            if constexpr (OP == GEO_OP_DS) v.put(0, v.in_band(v.at(v.full(0, 1), v.c0) - v.at(v.full(0), v.c0)));
+            if constexpr (OP == GEO_OP_D) {
+                v.put(0, v.dv(0));
+                v.put(1, v.dh(0));
+            }
+            if constexpr (OP == GEO_OP_DDS) {
+                v.put(0, v.in_band(v.dv(0, 1) - v.dv(0)));
+                v.put(1, v.in_band(v.dh(0, 1) - v.dh(0)));
+            }
+            if constexpr (OP == GEO_OP_L_UD || OP == GEO_OP_L_LR || OP == GEO_OP_L_C || OP == GEO_OP_L) {
+                float o[6];
+                v.interp(0, o);
+                if constexpr (OP == GEO_OP_L) {
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) v.put(q, o[q]);
+                } else {
+                    constexpr int q = 2 * (OP - GEO_OP_L_UD);
+                    v.put(0, o[q]);
+                    v.put(1, o[q + 1]);
+                }
+            }
+            if constexpr (OP == GEO_OP_K) {
+                // in: u, s, t, w1 (6), w2 (6); out: y1 (2), y2 (2), y3, y4
+                float av, ah, bv, bh;
+                v.interp_t<7>(3, 5, 7, av, ah);
+                v.interp_t<7>(9, 11, 13, bv, bh);
+                const float gv = v.dv(0), gh = v.dh(0);
+                v.put(0, gv - av);
+                v.put(1, gh - ah);
+                v.put(2, v.in_band(v.dv(0, 1) - gv) - bv);
+                v.put(3, v.in_band(v.dh(0, 1) - gh) - bh);
+                v.put(4, v.dv(2));
+                v.put(5, v.at(v.full(0), v.c0) + v.at(v.full(1), v.c0) + v.at(v.full(2), v.c0));
+            }
+        } else {
+            if constexpr (OP == GEO_OP_DV) v.put(0, v.dvt(0));
+            if constexpr (OP == GEO_OP_DH) v.put(0, v.dht(0));
+            if constexpr (OP == GEO_OP_DS) v.put(0, v.at(v.full(0, -1), v.c0) - v.in_band(v.at(v.full(0), v.c0)));
+            if constexpr (OP == GEO_OP_D) v.put(0, v.dt(0));
+            if constexpr (OP == GEO_OP_DDS) v.put(0, v.ddst(0));
+            if constexpr (OP == GEO_OP_L_UD || OP == GEO_OP_L_LR || OP == GEO_OP_L_C || OP == GEO_OP_L) {
+                float pv, ph;
+                if constexpr (OP == GEO_OP_L) v.interp_t<7>(0, 2, 4, pv, ph);
+                if constexpr (OP == GEO_OP_L_UD) v.interp_t<1>(0, 0, 0, pv, ph);
+                if constexpr (OP == GEO_OP_L_LR) v.interp_t<2>(0, 0, 0, pv, ph);
+                if constexpr (OP == GEO_OP_L_C) v.interp_t<4>(0, 0, 0, pv, ph);
+                v.put(0, pv);
+                v.put(1, ph);
+            }
+            if constexpr (OP == GEO_OP_K) {
+                // in: y1 (2), y2 (2), y3, y4; out: u, s, t, w1 (6), w2 (6)
+                const float y4 = v.at(v.full(5), v.c0);
+                v.put(0, v.dt(0) + v.ddst(2) + y4);
+                v.put(1, y4);
+                v.put(2, v.dvt(4) + y4);
+                float o[6];
+                v.interp(0, o);
+#pragma unroll
+                for (int q = 0; q < 6; ++q) v.put(3 + q, -o[q]);
+                v.interp(2, o);
+#pragma unroll
+                for (int q = 0; q < 6; ++q) v.put(9 + q, -o[q]);
+            }
+        }
+    }
+}
+
+template <int OP>
+void launch_op(int adjoint, const Dims &d, const float *in, float *out, hipStream_t st)
+{
+    const int64_t np = (int64_t)d.n1 * d.n2;
+    const uint32_t bx = (uint32_t)((np + NT - 1) / NT);
+    const uint32_t blocks = bx * (uint32_t)d.n3;  // at most N / NT + n3 < 2^32
+    const dim3 grid(blocks < 1u << 30 ? blocks : 1u << 30);
+    if (adjoint)
+        hipLaunchKernelGGL((k_op<OP, true>), grid, dim3(NT), 0, st, d, in, out, bx, blocks);
+    else
+        hipLaunchKernelGGL((k_op<OP, false>), grid, dim3(NT), 0, st, d, in, out, bx, blocks);
+}
+
 // ---- l2 ball, eq. (23): two-pass FP64 norm, then the scaling ----
 __global__ __launch_bounds__(NT) void k_l2_partial(const float *x, const float *cc, int64_t n, double *part)
 {
@@ -265,6 +478,21 @@ hipError_t launch_apply_op(int op, int adjoint, const Dims &d, const float *in, 
 {
     int pin, pout;
     if (op_planes(op, adjoint, &pin, &pout)) return hipErrorInvalidValue;
+    if ((uint64_t)d.n1 * (uint64_t)d.n2 < kOpsPixels) {
+        switch (op) {
+        case GEO_OP_DV: launch_op<GEO_OP_DV>(adjoint, d, in, out, st); break;
+        case GEO_OP_DH: launch_op<GEO_OP_DH>(adjoint, d, in, out, st); break;
+        case GEO_OP_DS: launch_op<GEO_OP_DS>(adjoint, d, in, out, st); break;
+        case GEO_OP_D: launch_op<GEO_OP_D>(adjoint, d, in, out, st); break;
+        case GEO_OP_DDS: launch_op<GEO_OP_DDS>(adjoint, d, in, out, st); break;
+        case GEO_OP_L_UD: launch_op<GEO_OP_L_UD>(adjoint, d, in, out, st); break;
+        case GEO_OP_L_LR: launch_op<GEO_OP_L_LR>(adjoint, d, in, out, st); break;
+        case GEO_OP_L_C: launch_op<GEO_OP_L_C>(adjoint, d, in, out, st); break;
+        case GEO_OP_L: launch_op<GEO_OP_L>(adjoint, d, in, out, st); break;
+        default: launch_op<GEO_OP_K>(adjoint, d, in, out, st); break;
+        }
+        return hipGetLastError();
+    }
     const int64_t total = d.plane * pout;
     hipLaunchKernelGGL(k_apply, dim3((unsigned)((total + NT - 1) / NT)), dim3(NT), 0, st, op,
                        adjoint, d, in, out, pout);
