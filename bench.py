@@ -656,7 +656,7 @@ def bench_regularizer(args):
     """The benchmark cube solved with SSTV, HSSTV1 or HSSTV2 (Sec. IV-A) in
     place of GeoSSTV, through the same P-PDS (eq. (7)): voxel-iterations/s
     over the timed steps and the roofline of the variant path's dominant
-    kernel, its dual kernel (HIP events around every 8th launch)."""
+    kernel, its sweep (HIP events around every 8th launch)."""
     import numpy as np
     import torch
 
@@ -677,19 +677,16 @@ def bench_regularizer(args):
     geo.geo_step(dims, p, v, ws, args.warmup)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    res, dual_ms = geo.geo_step_timed(dims, p, v, ws, args.steps)
+    res, sweep_ms = geo.geo_step_timed(dims, p, v, ws, args.steps)
     torch.cuda.synchronize()
     el = time.perf_counter() - t0
     K = args.steps
     value = N * K / el
-    # dual kernel, per voxel: reads s, t, u+, u, the P planes of y1, y3, the
-    # y4 residual and v (z_s, z_t evaluated from them again); writes s, t+,
-    # y3, y1 and the residual
-    dual_bytes = 4 * (11 + 2 * P)
-    # the iteration's state (u, s, t, y1, y3, y4) read and written once, v read
+    # the sweep is the iteration: the state (u, s, t, the P planes of y1, y3,
+    # y4) read and written once, v read
     iter_bytes = 2 * 4 * (5 + P) + 4
-    avg_s = dual_ms / K / 1e3
-    achieved = dual_bytes * N / avg_s
+    avg_s = sweep_ms / K / 1e3
+    achieved = iter_bytes * N / avg_s
     out = {
         "metric": "P-PDS voxel-iterations/s",
         "value": value,
@@ -708,10 +705,10 @@ def bench_regularizer(args):
                                "FP32 iterates, FP64 reductions",
                    "n1": n1, "n2": n2, "n3": n3, "voxels": N, "omega": c["omega"],
                    "regularizer": args.regularizer},
-        "roofline": {"bound": "hbm", "kernel": "var_dual", "achieved": achieved / 1e9,
+        "roofline": {"bound": "hbm", "kernel": "var_sweep", "achieved": achieved / 1e9,
                      "peak": HBM_PEAK / 1e9, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK if avg_s * K <= el else None,
-                     "traffic": None, "bytes_per_voxel": dual_bytes,
+                     "traffic": None, "bytes_per_voxel": iter_bytes,
                      "avg_launch_ms": 1e3 * avg_s},
         "iteration_bytes_per_voxel": iter_bytes,
         "iteration_hbm_frac": iter_bytes * value / HBM_PEAK,

@@ -107,7 +107,7 @@ typedef struct {
                             1/(33 + 8 omega^2), s 1, t 1/5, duals 1/3. The
                             variants take GEO_STORE_F32 only, geo_workspace_
                             size, geo_state_init/get/set, geo_step,
-                            geo_step_timed (it times the dual kernel) and
+                            geo_step_timed (it times the sweep) and
                             geo_solve (not the batched or profiled entry
                             points: GEO_EINVAL), and any dims with
                             N < 2^31. Their state: u, s, t, y1 (2 planes
@@ -179,9 +179,8 @@ int geo_step_profiled(geo_dims dims, const geo_params *p, const float *v,
                       void *ws, size_t ws_bytes, int32_t n_iter, void *stream,
                       geo_result *out, double *phase_ms);
 
-/* geo_step with two HIP events around the fused sweep (for the comparison
- * regularizers: their dual kernel) of the 8th, 16th, ... iteration slot of
- * the call (the first slot follows a host synchronisation and starts from
+/* geo_step with two HIP events around the fused sweep
+ * of the 8th, 16th, ... iteration slot of the call (the first slot follows a host synchronisation and starts from
  * an idle device), or of every slot in calls of fewer than 8, on `stream`:
  * the kernel's launch time for a roofline. An event pair idles the GPU for
  * a few microseconds, so sampling keeps that cost out of 7 of 8 iterations.

@@ -173,13 +173,13 @@ int check_var_ws(geo_dims d, const geo_params *p, const void *ws, size_t ws_byte
 }
 
 int var_step_impl(geo_dims dims, const geo_params *p, const float *v, void *ws, size_t ws_bytes,
-                  int32_t n_iter, hipStream_t st, geo_result *out, double *dual_ms = nullptr)
+                  int32_t n_iter, hipStream_t st, geo_result *out, double *sweep_ms = nullptr)
 {
     int rc = check_var_ws(dims, p, ws, ws_bytes);
     if (rc) return rc;
     DevScalars x;
     int slots = 0;
-    rc = hip_status(var_step(to_dims(dims), p, v, ws, n_iter, st, &x, &slots, dual_ms));
+    rc = hip_status(var_step(to_dims(dims), p, v, ws, n_iter, st, &x, &slots, sweep_ms));
     if (rc) return rc;
     const int own = x.nonfinite ? GEO_ENONFINITE : (p->tol > 0.0 && !x.stop ? GEO_MAXITER : GEO_OK);
     if (out) {
@@ -188,12 +188,12 @@ int var_step_impl(geo_dims dims, const geo_params *p, const float *v, void *ws, 
         out->converged = (p->tol > 0.0 && x.stop && !x.nonfinite) ? 1 : 0;
         out->rel_change = x.rel;
         out->r = x.r;
-        out->tau_s = x.sel[0].tau;
-        out->tau_t = x.sel[1].tau;
+        out->tau_s = x.tau_used[0];
+        out->tau_t = x.tau_used[1];
         out->total_iters = (int32_t)x.iter;
-        out->fallback_passes = (int32_t)x.fallback;
-        out->cand_s = (int32_t)x.sel[0].cand_count;
-        out->cand_t = (int32_t)x.sel[1].cand_count;
+        out->fallback_passes = (int32_t)(x.missed[0] + x.missed[1]);
+        out->cand_s = (int32_t)x.cand_used[0];
+        out->cand_t = (int32_t)x.cand_used[1];
         out->slots = (int32_t)slots;
         out->status = own;
     }
@@ -441,7 +441,7 @@ static int step_impl(geo_dims dims, const geo_params *p, const float *v, void *w
                      int nph = GEO_NPHASE)
 {
     if (is_variant(p)) {
-        // geo_step_timed (nph = 1) times the dual kernel; no phase profile
+        // geo_step_timed (nph = 1) times the sweep; no phase profile
         if (!dims_ok(dims) || !params_ok(p) || !v || n_iter < 0 || (phase_ms && nph != 1))
             return GEO_EINVAL;
         return var_step_impl(dims, p, v, ws, ws_bytes, n_iter, S(stream), out, phase_ms);

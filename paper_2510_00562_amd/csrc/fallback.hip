@@ -2,8 +2,7 @@
 // launch slot: three histogram passes over the field (the radix levels of
 // radix.hpp), one launch each, before the sweep that needs the thresholds (FP32
 // duals: the search at the end of the slot before left them pending) or between
-// the window search and sweep B or the dual kernel (BF16 duals, comparison
-// regularizers).
+// the window search and sweep B (BF16 duals).
 // Each launch is a no-op (its blocks read one flag of the launch and leave)
 // unless a search left a field of some working cube pending. The blocks then split the voxels of the cubes with a pending
 // field evenly, read z_s and z_t where sweep A stored them in this
@@ -249,8 +248,7 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
                         o.done = pk.done ? 1u : 0u;
                         a.c.rec[level * 2 + f] = o;
                         // what the sweep of this slot reads of the threshold (no
-                        // pass reads it; the comparison regularizers' dual
-                        // kernel reads the records)
+                        // pass reads it)
                         if (o.done) sc->in.set(f, resolved(sc->sel[f], a.c.rec, f, a.c.d.plane));
                     }
                 }

@@ -185,6 +185,50 @@ __device__ __forceinline__ void clear_hist(Hist *hist, int f)
     }
 }
 
+// Sums of K FP64 values over a block of NT threads; result valid in thread 0.
+template <int K, int NT>
+__device__ __forceinline__ void block_sums(double (&x)[K], double *red /* K * NT/64 */)
+{
+#pragma unroll
+    for (int q = 0; q < K; ++q) x[q] = wave_sum(x[q]);
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    if (lane == 0)
+#pragma unroll
+        for (int q = 0; q < K; ++q) red[q * (NT / 64) + wid] = x[q];
+    __syncthreads();
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            double t = 0.0;
+            for (int w = 0; w < NT / 64; ++w) t += red[q * (NT / 64) + w];
+            x[q] = t;
+        }
+}
+
+// The scalars of a state at the initial point.
+__device__ inline void init_scalars(DevScalars *sc, double eps, double tol, double alpha, double beta, double gy4)
+{
+    DevScalars z = {};
+    z.c4 = 1.0;
+    z.a4 = 1.0;
+    z.eps = eps;
+    z.tol = tol;
+    z.sel[0].radius = alpha;
+    z.sel[1].radius = beta;
+    // z_s = z_t = 0: inside the balls, tau = 0 (radius 0: +inf)
+    for (int f = 0; f < 2; ++f) {
+        z.sel[f].done = 1u;
+        if (!(z.sel[f].radius > 0.0)) z.sel[f].tau = __longlong_as_double(0x7ff0000000000000ll);
+        z.in.set(f, z.sel[f]);
+    }
+    z.gy4 = gy4;
+    z.zstore = 1u;
+    z.in.a4 = 1.f;
+    z.in.a_hi = __double2float_ru(gy4);
+    z.in.a_c = 0.5f * (float)gy4;
+    *sc = z;
+}
+
 // Append val to this block's slice of a field's candidate list. The slot
 // comes from an LDS counter (wavefront-aggregated), so sweep A never waits on
 // a global atomic; entries past the slice's capacity are counted but
@@ -202,6 +246,39 @@ __device__ __forceinline__ void wave_append(bool want, const T &val, T *slice, u
     base = __shfl(base, leader, 64);
     const uint32_t off = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
     if (want && base + off < (uint32_t)capb) slice[base + off] = val;
+}
+
+// What a sweep sums for the search of the next thresholds (search.hip), by
+// field: |z| above the window at the interval's centre (its slope in a4, how
+// many) and the values inside it; counts are per wavefront, in scalar registers.
+struct Gathered {
+    double sum[2] = {0.0, 0.0};
+    float slope[2] = {0.f, 0.f};
+    uint32_t cnt[2] = {0u, 0u}, inside[2] = {0u, 0u};
+};
+
+// One value of the next search, z = x - g (e + a4 q), over the interval of a4.
+// in: the lane has a value. Every lane of the wavefront takes part.
+__device__ __forceinline__ void gather_ahead(Gathered &o, const4<DevScalars::SweepIn> &w, int f, bool in, float x,
+                                             float e, float g, float q, float4 *slice, uint32_t *lds_count, int capt)
+{
+    const float zl = zt_of(x, e, y4_of(q, w.a_lo), g), zh = zt_of(x, e, y4_of(q, w.a_hi), g);
+    if (!w.on[f]) {
+        // inside the ball so far: sum |z| at both ends
+        o.sum[f] += in ? (double)fabsf(zl) : 0.0;
+        o.slope[f] += in ? fabsf(zh) : 0.f;
+        return;
+    }
+    const float lo = w.lo[f], hi = w.hi[f];
+    const float zmin = fminf(zl, zh), zmax = fmaxf(zl, zh);
+    const float zc = zt_of(x, e, y4_of(q, w.a_c), g);
+    const bool above = in && (zmin > hi || zmax < -hi);
+    const bool below = zmin > -lo && zmax < lo;
+    o.cnt[f] += (uint32_t)__popcll(__ballot(above));
+    o.inside[f] += (uint32_t)__popcll(__ballot(in && fabsf(zc) >= lo && fabsf(zc) <= hi));
+    o.sum[f] += above ? (double)fabsf(zc) : 0.0;
+    o.slope[f] += above ? copysignf(1.f, zc) * q : 0.f;
+    wave_append(in && !above && !below, make_float4(x, e, q, 0.f), slice, lds_count, capt);
 }
 
 // Candidates a window is widened to when the density of |z| near tau is

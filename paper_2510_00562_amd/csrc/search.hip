@@ -476,6 +476,7 @@ __global__ __launch_bounds__(kBeginThreads) void k_begin(const char *table, int 
         if (changed[f] && rad[f] > 0.0) clear_hist<kBeginThreads>(cc.hist, f);
     if (threadIdx.x == 0) {
         sc->tol = cc.tol;
+        if (cc.set_eps) sc->eps = cc.eps;
         sc->calls_iter = 0u;
         sc->call_limit = cc.limit;
         bool pending = false;

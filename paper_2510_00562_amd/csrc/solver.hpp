@@ -330,8 +330,7 @@ struct CubeCommon {
     int ntiles;
     SweepGrid g;
     int tile0;          // first tile of this cube in the launch's full tile list
-    int b0, nb;         // sweep B blocks of this cube (BF16): first, count; dual
-                        // kernel blocks (regularizers)
+    int b0, nb;         // sweep B blocks of this cube (BF16): first, count
     float thr1;         // omega * step of w1
     float zt_step;      // step size of t in z_t (the histogram passes evaluate z_t)
     float mu_lo, mu_hi;
@@ -343,6 +342,8 @@ struct CubeCommon {
     double tol, alpha, beta;
     uint32_t limit;
     uint32_t ahead;     // thresholds searched one iteration ahead (FP32 duals)
+    uint32_t set_eps;   // the regularizers take the fidelity radius of each call
+    double eps;
 };
 template <typename DT>
 struct CubeArgs {
@@ -476,17 +477,17 @@ hipError_t launch_fallback(const void *table, int dual_bytes, const LaunchShape 
                            hipStream_t st);
 
 // The comparison regularizers (variants.hip): problem (15) with SSTV or
-// HSSTV in place of GeoSSTV, with the same device scalars, window search,
-// histogram passes and finalize as the main solver.
+// HSSTV in place of GeoSSTV, with the same device scalars, histogram passes
+// and search as the main solver's FP32 form.
 int var_planes(int regularizer);
 size_t var_workspace_bytes(int n1, int n2, int n3, int regularizer);
 hipError_t var_state_init(const Dims &d, const geo_params *p, const float *v, void *ws,
                           hipStream_t st);
 // n_iter iterations or fewer once the rule of eq. (28) holds; blocking;
-// fills *out with the device scalars. dual_ms (may be null): GPU time of the
-// dual kernel over the call, from events around a sample of launches.
+// fills *out with the device scalars. sweep_ms (may be null): GPU time of the
+// sweep over the call, from events around a sample of launches.
 hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws, int n_iter,
-                    hipStream_t st, DevScalars *out, int *slots, double *dual_ms = nullptr);
+                    hipStream_t st, DevScalars *out, int *slots, double *sweep_ms = nullptr);
 // out != null: copy the variable out; otherwise load it from in.
 hipError_t var_state_io(const Dims &d, const geo_params *p, void *ws, int var, float *out,
                         const float *in, hipStream_t st);

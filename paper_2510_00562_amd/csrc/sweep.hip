@@ -91,26 +91,6 @@ __device__ __forceinline__ int tile_at(int b, int G, int T, int r)
     return t < T ? t : -1;
 }
 
-// Sums of K FP64 values over the block; result valid in thread 0.
-template <int K>
-__device__ __forceinline__ void block_sums(double (&x)[K], double *red /* K * NT/64 */)
-{
-#pragma unroll
-    for (int q = 0; q < K; ++q) x[q] = wave_sum(x[q]);
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (lane == 0)
-#pragma unroll
-        for (int q = 0; q < K; ++q) red[q * (NT / 64) + wid] = x[q];
-    __syncthreads();
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            double t = 0.0;
-            for (int w = 0; w < NT / 64; ++w) t += red[q * (NT / 64) + w];
-            x[q] = t;
-        }
-}
-
 // FUSED (FP32 duals): the whole iteration, thresholds known beforehand.
 // Otherwise (BF16 duals) the first of two sweeps: steps 1, 4, 5, 11, 12 and the
 // u' part of step 14, the inputs z_s, z_t of steps 2 and 3 with their window
@@ -234,11 +214,11 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
         const float a4 = FUSED ? sc.in.a4 : (float)sc.a4;
         const bool zst = !FUSED && sc.zstore != 0u;
         double du2 = 0.0, u2 = 0.0, r2 = 0.0;
-        // |z| above the window: sum, count (of the wavefront), slope in a4
-        // (FUSED) or sum of all |z|; values inside it at the centre a4
+        Gathered ga;
+        // otherwise (by field): |z| above the window, sum and count (of the
+        // wavefront), and sum of all |z|
         double sum[2] = {0.0, 0.0}, all[2] = {0.0, 0.0};
-        uint32_t cnt[2] = {0u, 0u}, inw[2] = {0u, 0u};
-        float slope[2] = {0.f, 0.f};
+        uint32_t cnt[2] = {0u, 0u};
 
         // pixels of this thread in a band (kNoPix outside the cube)
         auto pixel = [&](int i, int j) {
@@ -326,9 +306,9 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
                 }
         };
 
-        auto won = [&](int f) { return FUSED ? scp->in.on[f] != 0u : scp->sel[f].win_on != 0u; };
-        auto wlo = [&](int f) { return FUSED ? scp->in.lo[f] : scp->sel[f].win_lo; };
-        auto whi = [&](int f) { return FUSED ? scp->in.hi[f] : scp->sel[f].win_hi; };
+        auto won = [&](int f) { return scp->sel[f].win_on != 0u; };
+        auto wlo = [&](int f) { return scp->sel[f].win_lo; };
+        auto whi = [&](int f) { return scp->sel[f].win_hi; };
 
         // ---------------- phases ----------------
         // D^T of planes pv (vertical) and pv + 1 of a staged band; y: its point
@@ -346,27 +326,10 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
             const float x = __builtin_fmaf(-kStepU, __builtin_fmaf(a4, y4s, g), uo);
             return x < ent->c.mu_lo ? ent->c.mu_lo : (x > ent->c.mu_hi ? ent->c.mu_hi : x);
         };
-        // FUSED: one value of the next search (search.hip), z = x - g (e + a4 q)
-        // over the interval of a4. Every lane of the wavefront takes part.
+        // FUSED: one value of the next search, z = x - g (e + a4 q)
         auto gather = [&](int f, bool in, float x, float e, float g, float q) {
-            const float zl = zt_of(x, e, y4_of(q, scp->in.a_lo), g);
-            const float zh = zt_of(x, e, y4_of(q, scp->in.a_hi), g);
-            if (!won(f)) {
-                // inside the ball so far: sum |z| at both ends
-                sum[f] += in ? (double)fabsf(zl) : 0.0;
-                slope[f] += in ? fabsf(zh) : 0.f;
-                return;
-            }
-            const float zmin = fminf(zl, zh), zmax = fmaxf(zl, zh);
-            const float zc = zt_of(x, e, y4_of(q, scp->in.a_c), g);
-            const bool above = in && (zmin > whi(f) || zmax < -whi(f));
-            const bool below = zmin > -wlo(f) && zmax < wlo(f);
-            cnt[f] += (uint32_t)__popcll(__ballot(above));
-            inw[f] += (uint32_t)__popcll(__ballot(in && fabsf(zc) >= wlo(f) && fabsf(zc) <= whi(f)));
-            sum[f] += above ? (double)fabsf(zc) : 0.0;
-            slope[f] += above ? copysignf(1.f, zc) * q : 0.f;
-            wave_append(in && !above && !below, make_float4(x, e, q, 0.f),
-                        ent->c.cand + ((int64_t)f * ent->c.ntiles + lt) * ent->c.capt, &ncand[f], ent->c.capt);
+            gather_ahead(ga, scp->in, f, in, x, e, g, q, ent->c.cand + ((int64_t)f * ent->c.ntiles + lt) * ent->c.capt,
+                         &ncand[f], ent->c.capt);
         };
         // otherwise: one value of this slot's search
         auto collect = [&](int f, bool in, float z) {
@@ -588,9 +551,11 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
         const int nt = a.c.ntiles;
         if constexpr (FUSED) {
             double acc[NS] = {du2, u2, r2,
-                              one ? (double)cnt[0] : 0.0, sum[0], (double)slope[0], one ? (double)inw[0] : 0.0,
-                              one ? (double)cnt[1] : 0.0, sum[1], (double)slope[1], one ? (double)inw[1] : 0.0};
-            block_sums(acc, red);
+                              one ? (double)ga.cnt[0] : 0.0, ga.sum[0], (double)ga.slope[0],
+                              one ? (double)ga.inside[0] : 0.0,
+                              one ? (double)ga.cnt[1] : 0.0, ga.sum[1], (double)ga.slope[1],
+                              one ? (double)ga.inside[1] : 0.0};
+            block_sums<NS, NT>(acc, red);
             if (tid == 0) {
                 for (int q = 0; q < 3; ++q) a.c.part[3 * lt + q] = acc[q];
                 for (int q = 0; q < 4; ++q) {
@@ -601,7 +566,7 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
         } else {
             double acc[NS] = {du2, u2, one ? (double)cnt[0] : 0.0, sum[0], all[0],
                               one ? (double)cnt[1] : 0.0, sum[1], all[1]};
-            block_sums(acc, red);
+            block_sums<NS, NT>(acc, red);
             if (tid == 0) {
                 a.c.part[2 * lt] = acc[0];
                 a.c.part[2 * lt + 1] = acc[1];
@@ -644,25 +609,7 @@ __global__ __launch_bounds__(NPT) void k_init(Dims d, const float *v, Side<DT> s
         st(s0.y4 + q, 0.f);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        DevScalars z = {};
-        z.c4 = 1.0;
-        z.a4 = 1.0;
-        z.eps = eps;
-        z.tol = tol;
-        z.sel[0].radius = alpha;
-        z.sel[1].radius = beta;
-        // z_s = z_t = 0: inside the balls, tau = 0 (radius 0: +inf)
-        for (int f = 0; f < 2; ++f) {
-            z.sel[f].done = 1u;
-            if (!(z.sel[f].radius > 0.0)) z.sel[f].tau = __longlong_as_double(0x7ff0000000000000ll);
-        }
-        z.gy4 = 0.2;  // the y4 step printed after eq. (24)
-        for (int f = 0; f < 2; ++f) z.in.set(f, z.sel[f]);
-        z.zstore = 1u;
-        z.in.a4 = 1.f;
-        z.in.a_hi = __double2float_ru(z.gy4);
-        z.in.a_c = 0.1f;
-        *sc = z;
+        init_scalars(sc, eps, tol, alpha, beta, 0.2);  // the y4 step printed after eq. (24)
     }
 }
 

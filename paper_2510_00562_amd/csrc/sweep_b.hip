@@ -1,9 +1,8 @@
 // The second sweep of the two-sweep form of the iteration (BF16 duals, see
 // sweep.hip), pointwise: steps 2, 3, 7, 8, 13, the rest of step 14 and the
 // FP64 partial sums of the l2-ball distance of step 15, at the thresholds that
-// the search between the sweeps found; then the finalize (one block per cube),
-// which the comparison regularizers (variants.hip) use too: the l2-ball factor
-// of step 15 (applied lazily when y4 is next read), the stopping test and the
+// the search between the sweeps found; then the finalize (one block per cube):
+// the l2-ball factor of step 15 (applied lazily when y4 is next read), the stopping test and the
 // iteration counter.
 #include "radix.hpp"
 

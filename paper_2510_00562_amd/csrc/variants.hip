@@ -9,32 +9,28 @@
 //   u 1/(||A||^2 + 1), s 1, t 1/5, y 1/3.
 //
 // One launch slot per iteration, on the caller's stream, over a one-entry
-// launch table in the workspace (the layout the main solver's search,
-// histogram passes and finalize read):
-//   primal kernel: u+ = P_box(u - g_u (A^T y1 + y4)) into the other u buffer,
-//                  the inputs z_s = s - y4 and z_t = t - g_t (D_v^T y3 + y4)
-//                  of the two l1-ball projections (stored in the iterations
-//                  in which a window is likely to miss, for the histogram
-//                  passes; otherwise they evaluate them again from the
-//                  state), and per block (a "tile" of the search) the window
-//                  statistics, the window candidates and the FP64 partials
-//                  of the stopping rule;
-//   window search and three histogram passes (select.hip, fallback.hip):
-//                  the exact thresholds tau_s, tau_t;
-//   dual kernel:   s+, t+ (soft thresholds of z_s, z_t, evaluated again from
-//                  the state with the primal kernel's operations: y3 and the
-//                  y4 residual are ping-ponged, so the rows next to a voxel
-//                  still hold their old values), the extrapolations
-//                  x' = 2 x+ - x, y1 += g_y A u' and the conjugate prox of the
-//                  regularizer (a clip to [-1, 1], or each 4-entry group
-//                  scaled into the unit l2 ball), y3 += g_y D_v t', the y4
-//                  residual and FP64 partials of its norm;
-//   finalize (sweep.hip): the fidelity-ball factor (y4 - g_y P_B(y4/g_y) =
-//                  c g_y (y4/g_y - v), c = max(0, 1 - eps/r), applied when y4
-//                  is next read), the relative change, the stopping rule, the
-//                  next windows.
-// The two streaming kernels are plain (grid-stride, the stencils read
-// through the caches); no tile fusion.
+// launch table in the workspace, as in the main solver's FP32 form:
+//   histogram passes (fallback.hip): thresholds that the last search missed;
+//   sweep:  one pass over the state. u+ = P_box(u - g_u (A^T y1 + y4)); s+ and
+//           t+ (soft thresholds of z_s = s - y4 and z_t = t - g_t (D_v^T y3 +
+//           y4)); the extrapolations x' = 2 x+ - x; y1 += g_y A u' and the
+//           conjugate prox of the regularizer (a clip to [-1, 1], or each
+//           4-entry group scaled into the unit l2 ball); y3 += g_y D_v t'; the
+//           y4 residual; the FP64 partial sums and the inputs of the next search;
+//   search (search.hip): the fidelity-ball factor (y4 - g_y P_B(y4/g_y) =
+//           c g_y (y4/g_y - v), c = max(0, 1 - eps/r), applied when y4 is next
+//           read), the stopping rule, the next thresholds.
+//
+// What bounds the sweep is HBM: 60 bytes per voxel (SSTV: 7 state words each
+// way and v) or 76 (HSSTV). A workgroup owns an 8 x 64 pixel tile and marches
+// through a chunk of bands; y1 is staged in LDS with a 1-pixel halo, three bands
+// in turn, u' with the row below and the column to the right, t' with the rows
+// above and below; the next bands' loads are in flight meanwhile (the buffer
+// path, common.hpp: band_of). In two kernels with the search between them, each
+// reading s, t, y3, y4 and y1, an iteration of 256 x 256 x 128 took 182 us (SSTV)
+// and 226 us (HSSTV2), now 132 and 166; of 64 x 64 x 16 45 us, now 31; of
+// 512 x 512 x 224 1165 and 1435 us, now 790 and 991 (the sweep alone 732 and
+// 936: 4.8 TB/s).
 #include <math.h>
 #include <string.h>
 
@@ -46,514 +42,362 @@ namespace geo {
 
 namespace {
 
-// The primal kernel's blocks are the search's tiles: few of them, so that
-// the window search scans few slices (with 4096 blocks of 256 threads it
-// took 43 instead of 32 us), and no more than the device holds at once
-// (primal_grid). The dual kernel runs up to 8192 blocks of 256 threads (228
-// instead of 165 us with 2048 blocks of 1024; 4096 blocks: 2% slower).
 constexpr int VT = 1024;          // init and copy kernels
-constexpr int VTP = 512;          // primal kernels (68 VGPRs four voxels per thread, 56 one)
-constexpr int VTD = 256;          // dual kernel
-constexpr int kVarTiles = 768;    // most primal kernel blocks (the workspace regions of the tiles)
-constexpr int kVarBBlocks = 8192; // dual kernel blocks
-
-__device__ __forceinline__ float soft_d(float z, double tau)
-{
-    const double m = fabs((double)z) - tau;
-    return m > 0.0 ? copysignf((float)m, z) : 0.0f;
-}
+constexpr int kVarBlocks = 8192;  // their blocks at most
+// The sweep's tile: 512 threads, one per point. Several blocks fit a CU, so one
+// block's barriers overlap another's loads, and 64 columns waste little of
+// ragged widths.
+constexpr int TI = 8, TJ = 64, NT = TI * TJ;
+constexpr int W2 = TJ + 2, S2 = (TI + 2) * W2, NY = (S2 + NT - 1) / NT;  // y1 with a 1-pixel halo
+constexpr int WU = TJ + 1, SU = (TI + 1) * WU, RINGU = SU - NT;           // u' with the (+1, +1) ring
+constexpr int T0 = NT / 2;                                               // first thread of the t' ring
+static_assert(T0 >= RINGU && T0 % 64 == 0 && T0 + 2 * TJ <= NT, "one ring role per wavefront");
+// Wavefronts per SIMD asked of the compiler: three blocks per CU in 80 registers.
+// With two (128 registers allowed, 91 taken) the HSSTV2 sweep of 256 x 256 x 128
+// takes 140 instead of 143 us, the SSTV sweep of 145 x 141 x 103 50 instead of 43.
+constexpr int kVarMinWaves = 6;
+// Bands of fewer pixels go through the buffer path (an 8-byte pair of any pixel
+// lies below the offset of a missing one); larger ones by 64-bit addresses.
+constexpr uint32_t kVarPixels = 1u << 27;
 
 struct VarArgs {
     Dims d;
-    int variant, P;           // P: planes of y1 (2 or 4)
+    int variant;
     float gu, gt, gy, omega;  // step sizes, balance
     float mu_lo, mu_hi;
     const float *v;
     DevScalars *sc;
-    float *u[2], *t[2];       // ping-pong by iteration parity
-    float *y3[2], *q[2];      // also (the dual kernel reads the rows next to its own)
-    float *s, *y1;
-    float *z;                 // [2][N]: z_s, z_t (read by the histogram passes)
-    double *part;             // [2 * ntiles] primal partials, then [nb] of r^2
-    double *winpart;          // [2][ntiles][3]
-    float *cand;              // [2][ntiles][capt]
-    uint32_t *ccount;         // [2][ntiles]
-    const FbRec *rec;
-    int ntiles, nb, capt;
+    float *u[2], *t[2], *y3[2], *q[2];  // ping-pong by iteration parity
+    float2 *ya[2], *yb[2];              // y1: (D_v, D_h) D_s u, and omega (D_v, D_h) u (HSSTV)
+    float *s;                           // in place (a point reads and writes only its own)
+    double *part;                       // [3 * slots]
+    double *winpart;                    // [2][slots][4]
+    float4 *cand;                       // [2][slots][capt]
+    uint32_t *ccount;                   // [2][slots]
+    uint32_t *flags;                    // of the launch table
+    int ti, tj, tk, kc;                 // tiles along i, j, band chunks; bands per chunk
+    int slots, per, capt;               // slots of the search, consecutive tiles of one, candidates of one
 };
 
-// voxel index -> (k, i, j); N < 2^31
-__device__ __forceinline__ void coords(const Dims &d, int64_t q, int &k, int &i, int &j)
-{
-    const uint32_t x = (uint32_t)q, n2 = (uint32_t)d.n2, n1 = (uint32_t)d.n1;
-    const uint32_t r = x / n2;
-    j = (int)(x - r * n2);
-    k = (int)(r / n1);
-    i = (int)(r - (uint32_t)k * n1);
-}
-
-// (D^T p)(k, i, j) for the vertical plane pv and horizontal plane ph
-__device__ __forceinline__ float dT(const Dims &d, const float *pv, const float *ph, int k, int i, int j)
-{
-    const int64_t q = vox(d, k, i, j);
-    float a = 0.f;
-    if (i >= 1) a += pv[q - d.n2];
-    if (i <= d.n1 - 2) a -= pv[q];
-    if (j >= 1) a += ph[q - 1];
-    if (j <= d.n2 - 2) a -= ph[q];
-    return a;
-}
-
-// The inputs z_s = s - y4 and z_t = t - g_t (D_v^T y3 + y4) of the two
-// l1-ball projections, y4 = a4 q, come from y4_of, zs_of and zt_of (with
-// the step g_t), the operations every kernel that evaluates them uses: the
-// primal and dual kernels here and the histogram passes of a missed window,
-// so the values are bit-identical wherever they are evaluated.
-
-// Sums of 8 FP64 values over a block of NT threads in a fixed order; valid
-// in thread 0.
-template <int NT>
-__device__ __forceinline__ void block_sum8v(double (&x)[8], double *red /* 8 * NT/64 */)
-{
-#pragma unroll
-    for (int c = 0; c < 8; ++c) x[c] = wave_sum(x[c]);
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (lane == 0)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) red[c * (NT / 64) + wid] = x[c];
-    __syncthreads();
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            double t = 0.0;
-            for (int w = 0; w < NT / 64; ++w) t += red[c * (NT / 64) + w];
-            x[c] = t;
-        }
-}
-
-__global__ __launch_bounds__(VTP) void k_var_primal(VarArgs a)
-{
-    __shared__ double red[8 * (VTP / 64)];
-    __shared__ uint32_t ncand[2];
-    DevScalars *sc = a.sc;
-    if (idle(sc)) return;
-    const Dims d = a.d;
-    const int64_t N = d.plane;
-    const int tid = threadIdx.x, b = blockIdx.x, nt = a.ntiles;
-    if (tid < 2) ncand[tid] = 0u;
-    const int par = (int)(sc->iter & 1u);
-    const float *u = a.u[par], *t = a.t[par], *y3 = a.y3[par], *qo = a.q[par];
-    float *un = a.u[par ^ 1];
-    const float a4 = (float)sc->a4;
-    const bool zst = sc->zstore != 0u;  // z kept for the histogram passes
-    const float *y1v = a.y1, *y1h = a.y1 + N;
-    float wlo[2], whi[2];
-    bool won[2];
-    for (int f = 0; f < 2; ++f) {
-        won[f] = sc->sel[f].win_on != 0u;
-        wlo[f] = sc->sel[f].win_lo;
-        whi[f] = sc->sel[f].win_hi;
-    }
-    __syncthreads();  // ncand cleared
-    double du2 = 0.0, u2 = 0.0, s_hi[2] = {0.0, 0.0}, s_all[2] = {0.0, 0.0};
-    float c_hi[2] = {0.f, 0.f};
-    // the same trip count for every lane of the block, so that whole
-    // wavefronts append candidates
-    for (int64_t q0 = (int64_t)b * VTP; q0 < N; q0 += (int64_t)nt * VTP) {
-        const int64_t q = q0 + tid;
-        const bool in = q < N;
-        float z[2] = {0.f, 0.f};
-        if (in) {
-            int k, i, j;
-            coords(d, q, k, i, j);
-            // A^T y1 = D_s^T D^T (first two planes) + omega D^T (the other two)
-            float g = 0.f;
-            if (k >= 1) g += dT(d, y1v, y1h, k - 1, i, j);
-            if (k <= d.n3 - 2) g -= dT(d, y1v, y1h, k, i, j);
-            if (a.P == 4) g += a.omega * dT(d, a.y1 + 2 * N, a.y1 + 3 * N, k, i, j);
-            const float y4 = y4_of(qo[q], a4);
-            const float uo = u[q];
-            const float x = uo - a.gu * (g + y4);
-            const float nu = fminf(fmaxf(x, a.mu_lo), a.mu_hi);
-            un[q] = nu;
-            const float y3m = i >= 1 ? y3[q - d.n2] : 0.f, y3c = i <= d.n1 - 2 ? y3[q] : 0.f;
-            z[0] = zs_of(a.s[q], y4);
-            z[1] = zt_of(t[q], y3m, y3c, y4, a.gt);
-            if (zst) {
-                a.z[q] = z[0];
-                a.z[N + q] = z[1];
-            }
-            const double dl = (double)nu - (double)uo;
-            du2 += dl * dl;
-            u2 += (double)uo * (double)uo;
-        }
-        // the window statistics and candidates of the threshold search
-#pragma unroll
-        for (int f = 0; f < 2; ++f) {
-            const float av = fabsf(z[f]);
-            bool cand = false;
-            if (in) {
-                s_all[f] += (double)av;
-                if (won[f]) {
-                    if (av > whi[f]) {
-                        c_hi[f] += 1.f;
-                        s_hi[f] += (double)av;
-                    } else if (av >= wlo[f]) {
-                        cand = true;
-                    }
-                }
-            }
-            wave_append(cand, av, a.cand + ((int64_t)f * nt + b) * a.capt, &ncand[f], a.capt);
-        }
-    }
-    double acc[8] = {du2, u2, (double)c_hi[0], s_hi[0], s_all[0], (double)c_hi[1], s_hi[1], s_all[1]};
-    block_sum8v<VTP>(acc, red);
-    if (tid == 0) {
-        a.ccount[b] = ncand[0];
-        a.ccount[nt + b] = ncand[1];
-        a.part[2 * b] = acc[0];
-        a.part[2 * b + 1] = acc[1];
-        for (int f = 0; f < 2; ++f)
-            for (int c = 0; c < 3; ++c) a.winpart[((int64_t)f * nt + b) * 3 + c] = acc[2 + 3 * f + c];
-    }
-}
-
-// ---- four voxels per thread along j (cubes with N2 % 4 == 0) ----
-// The same arithmetic as the kernels above, element by element in the same
-// order; whole 16-byte loads and stores of every array, the j - 1 and
-// j + 4 neighbours from one more scalar load.
-struct F4 {
-    float x[4];
-};
-__device__ __forceinline__ F4 ld4(const float *p)
-{
-    const float4 v = *reinterpret_cast<const float4 *>(p);
-    return F4{{v.x, v.y, v.z, v.w}};
-}
-__device__ __forceinline__ void st4(float *p, const F4 &v)
-{
-    *reinterpret_cast<float4 *>(p) = make_float4(v.x[0], v.x[1], v.x[2], v.x[3]);
-}
-
-// (D^T p)(k, i, j0 + e), e = 0..3, for the planes pv, ph
-__device__ __forceinline__ void dT4(const Dims &d, const float *pv, const float *ph, int k, int i, int j0,
-                                    float (&a)[4])
-{
-    const int64_t q = vox(d, k, i, j0);
-    F4 up = {{0.f, 0.f, 0.f, 0.f}}, cv = up;
-    if (i >= 1) up = ld4(pv + q - d.n2);
-    if (i <= d.n1 - 2) cv = ld4(pv + q);
-    const F4 h = ld4(ph + q);
-    const float hl = j0 >= 1 ? ph[q - 1] : 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int j = j0 + e;
-        float x = 0.f;
-        if (i >= 1) x += up.x[e];
-        if (i <= d.n1 - 2) x -= cv.x[e];
-        if (j >= 1) x += e ? h.x[e - 1] : hl;
-        if (j <= d.n2 - 2) x -= h.x[e];
-        a[e] = x;
-    }
-}
-
-__global__ __launch_bounds__(VTP) void k_var_primal4(VarArgs a)
-{
-    __shared__ double red[8 * (VTP / 64)];
-    __shared__ uint32_t ncand[2];
-    DevScalars *sc = a.sc;
-    if (idle(sc)) return;
-    const Dims d = a.d;
-    const int64_t N = d.plane, Q = N / 4;
-    const int tid = threadIdx.x, b = blockIdx.x, nt = a.ntiles;
-    if (tid < 2) ncand[tid] = 0u;
-    const int par = (int)(sc->iter & 1u);
-    const float *u = a.u[par], *t = a.t[par], *y3 = a.y3[par], *qo = a.q[par];
-    float *un = a.u[par ^ 1];
-    const float a4 = (float)sc->a4;
-    const bool zst = sc->zstore != 0u;  // z kept for the histogram passes
-    const float *y1v = a.y1, *y1h = a.y1 + N;
-    float wlo[2], whi[2];
-    bool won[2];
-    for (int f = 0; f < 2; ++f) {
-        won[f] = sc->sel[f].win_on != 0u;
-        wlo[f] = sc->sel[f].win_lo;
-        whi[f] = sc->sel[f].win_hi;
-    }
-    __syncthreads();  // ncand cleared
-    double du2 = 0.0, u2 = 0.0, s_hi[2] = {0.0, 0.0}, s_all[2] = {0.0, 0.0};
-    float c_hi[2] = {0.f, 0.f};
-    for (int64_t g0 = (int64_t)b * VTP; g0 < Q; g0 += (int64_t)nt * VTP) {
-        const int64_t g = g0 + tid;
-        const bool in = g < Q;
-        float z[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        if (in) {
-            const int64_t q = 4 * g;
-            int k, i, j0;
-            coords(d, q, k, i, j0);
-            float gm[4] = {0.f, 0.f, 0.f, 0.f}, gk[4] = {0.f, 0.f, 0.f, 0.f}, go[4] = {0.f, 0.f, 0.f, 0.f};
-            if (k >= 1) dT4(d, y1v, y1h, k - 1, i, j0, gm);
-            if (k <= d.n3 - 2) dT4(d, y1v, y1h, k, i, j0, gk);
-            if (a.P == 4) dT4(d, a.y1 + 2 * N, a.y1 + 3 * N, k, i, j0, go);
-            const F4 qv = ld4(qo + q), uo = ld4(u + q), sv = ld4(a.s + q), tv = ld4(t + q);
-            F4 y3m = {{0.f, 0.f, 0.f, 0.f}}, y3c = y3m;
-            if (i >= 1) y3m = ld4(y3 + q - d.n2);
-            if (i <= d.n1 - 2) y3c = ld4(y3 + q);
-            F4 nu, zs, zt;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float gg = 0.f;
-                if (k >= 1) gg += gm[e];
-                if (k <= d.n3 - 2) gg -= gk[e];
-                if (a.P == 4) gg += a.omega * go[e];
-                const float y4 = y4_of(qv.x[e], a4);
-                const float x = uo.x[e] - a.gu * (gg + y4);
-                nu.x[e] = fminf(fmaxf(x, a.mu_lo), a.mu_hi);
-                zs.x[e] = zs_of(sv.x[e], y4);
-                zt.x[e] = zt_of(tv.x[e], y3m.x[e], y3c.x[e], y4, a.gt);
-                z[0][e] = zs.x[e];
-                z[1][e] = zt.x[e];
-                const double dl = (double)nu.x[e] - (double)uo.x[e];
-                du2 += dl * dl;
-                u2 += (double)uo.x[e] * (double)uo.x[e];
-            }
-            st4(un + q, nu);
-            if (zst) {
-                st4(a.z + q, zs);
-                st4(a.z + N + q, zt);
-            }
-        }
-#pragma unroll
-        for (int f = 0; f < 2; ++f)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float av = fabsf(z[f][e]);
-                bool cand = false;
-                if (in) {
-                    s_all[f] += (double)av;
-                    if (won[f]) {
-                        if (av > whi[f]) {
-                            c_hi[f] += 1.f;
-                            s_hi[f] += (double)av;
-                        } else if (av >= wlo[f]) {
-                            cand = true;
-                        }
-                    }
-                }
-                wave_append(cand, av, a.cand + ((int64_t)f * nt + b) * a.capt, &ncand[f], a.capt);
-            }
-    }
-    double acc[8] = {du2, u2, (double)c_hi[0], s_hi[0], s_all[0], (double)c_hi[1], s_hi[1], s_all[1]};
-    block_sum8v<VTP>(acc, red);
-    if (tid == 0) {
-        a.ccount[b] = ncand[0];
-        a.ccount[nt + b] = ncand[1];
-        a.part[2 * b] = acc[0];
-        a.part[2 * b + 1] = acc[1];
-        for (int f = 0; f < 2; ++f)
-            for (int c = 0; c < 3; ++c) a.winpart[((int64_t)f * nt + b) * 3 + c] = acc[2 + 3 * f + c];
-    }
-}
-
-// u' = 2 u+ - u at (k, i, j) (the caller keeps the indexes inside the cube)
-__device__ __forceinline__ float uprime(const Dims &d, const float *un, const float *uo, int k, int i, int j)
-{
-    const int64_t q = vox(d, k, i, j);
-    return 2.f * un[q] - uo[q];
-}
-
-__global__ __launch_bounds__(VTD) void k_var_dual(VarArgs a)
-{
-    __shared__ double red[VTD / 64];
-    const DevScalars *sc = a.sc;
-    if (idle(sc)) return;
-    const Dims d = a.d;
-    const int64_t N = d.plane;
-    const int par = (int)(sc->iter & 1u);
-    const float *uo = a.u[par], *un = a.u[par ^ 1], *to = a.t[par];
-    const float *y3o = a.y3[par], *qo = a.q[par];
-    float *tn = a.t[par ^ 1], *y3n = a.y3[par ^ 1], *qn = a.q[par ^ 1];
-    // the thresholds: from the window search, or from this slot's passes
-    const double ts = sc->sel[0].done ? sc->sel[0].tau : fb_final(a.rec, 0).tau;
-    const double tt = sc->sel[1].done ? sc->sel[1].tau : fb_final(a.rec, 1).tau;
-    const float a4 = (float)sc->a4;
-    double r2 = 0.0;
-    for (int64_t q = (int64_t)blockIdx.x * VTD + threadIdx.x; q < N; q += (int64_t)gridDim.x * VTD) {
-        int k, i, j;
-        coords(d, q, k, i, j);
-        // z_s, z_t here as the primal kernel evaluated them
-        const float y4 = y4_of(qo[q], a4), y3c = y3o[q];
-        const float y3m = i >= 1 ? y3o[q - d.n2] : 0.f;
-        const float so = a.s[q], sn = soft_d(zs_of(so, y4), ts);
-        a.s[q] = sn;
-        const float sp = 2.f * sn - so;
-        const float tq = soft_d(zt_of(to[q], y3m, i <= d.n1 - 2 ? y3c : 0.f, y4, a.gt), tt);
-        tn[q] = tq;
-        const float tp = 2.f * tq - to[q];
-        // y3 += g_y D_v t' (t' one row down from its own z_t and old t); the
-        // last row keeps its value
-        float y3x = y3c;
-        if (i <= d.n1 - 2) {
-            const int64_t qd = q + d.n2;
-            const float y4d = y4_of(qo[qd], a4), y3d = i + 1 <= d.n1 - 2 ? y3o[qd] : 0.f;
-            const float ztd = zt_of(to[qd], y3c, y3d, y4d, a.gt);
-            const float tp1 = 2.f * soft_d(ztd, tt) - to[qd];
-            y3x = y3c + a.gy * (tp1 - tp);
-        }
-        y3n[q] = y3x;
-        // A u' here: D D_s u' on the edges that exist (and omega D u')
-        const float u0 = uprime(d, un, uo, k, i, j);
-        const bool ei = i <= d.n1 - 2, ej = j <= d.n2 - 2, ek = k <= d.n3 - 2;
-        const float ui = ei ? uprime(d, un, uo, k, i + 1, j) : 0.f;
-        const float uj = ej ? uprime(d, un, uo, k, i, j + 1) : 0.f;
-        float av[4] = {0.f, 0.f, 0.f, 0.f};
-        if (ek) {
-            const float s0 = uprime(d, un, uo, k + 1, i, j) - u0;
-            if (ei) av[0] = (uprime(d, un, uo, k + 1, i + 1, j) - ui) - s0;
-            if (ej) av[1] = (uprime(d, un, uo, k + 1, i, j + 1) - uj) - s0;
-        }
-        if (ei) av[2] = a.omega * (ui - u0);
-        if (ej) av[3] = a.omega * (uj - u0);
-        float y[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) y[c] = c < a.P ? a.y1[c * N + q] + a.gy * av[c] : 0.f;
-        if (a.variant == GEO_REG_HSSTV2) {
-            const float nr = sqrtf((y[0] * y[0] + y[1] * y[1]) + (y[2] * y[2] + y[3] * y[3]));
-            if (nr > 1.f) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) y[c] = y[c] / nr;
-            }
+// Loads and stores of one band of an array at a pixel (kNoPix: none): through
+// the buffer path, or (bands of kVarPixels pixels and more) by 64-bit addresses.
+template <bool BUF, typename T>
+struct Band {
+    BandRsrc r;
+    T *p;
+    bool any;
+    __device__ __forceinline__ Band(T *base, int k, uint32_t np, bool want)
+    {
+        if constexpr (BUF) {
+            r = band_of(base, (int64_t)k * np, want ? np : 0u);
         } else {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) y[c] = fminf(fmaxf(y[c], -1.f), 1.f);
+            p = base + (int64_t)k * np;
+            any = want;
         }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if (c < a.P) a.y1[c * N + q] = y[c];
-        // y4'/g_y - v = (a4/g_y) q + u' + s' + t' - v
-        const float qx = (a4 / a.gy) * qo[q] + ((u0 + sp) + tp) - a.v[q];
-        qn[q] = qx;
-        r2 += (double)qx * (double)qx;
     }
-    const double tot = block_sum<VTD>(r2, red);
-    if (threadIdx.x == 0) a.part[2 * a.ntiles + blockIdx.x] = tot;
+};
+template <bool BUF>
+__device__ __forceinline__ float bget(const Band<BUF, const float> &b, uint32_t pix)
+{
+    if constexpr (BUF) return bld((const float *)nullptr, b.r, pix);
+    else return b.any && pix != kNoPix ? b.p[pix] : 0.f;
+}
+template <bool BUF>
+__device__ __forceinline__ float2 bget(const Band<BUF, const float2> &b, uint32_t pix)
+{
+    if constexpr (BUF) return pair_of(bld_raw((const float2 *)nullptr, b.r, pix));
+    else return b.any && pix != kNoPix ? b.p[pix] : make_float2(0.f, 0.f);
+}
+template <bool BUF, typename T>
+__device__ __forceinline__ void bput(const Band<BUF, T> &b, uint32_t pix, T x)
+{
+    if constexpr (BUF) bst_nt((const T *)nullptr, b.r, pix, x);
+    else if (b.any && pix != kNoPix) b.p[pix] = x;
 }
 
-// u' = 2 u+ - u at four voxels from (k, i, j0), and at (k, i, j0 + 4)
-__device__ __forceinline__ void uprime4(const Dims &d, const float *un, const float *uo, int k, int i, int j0,
-                                        F4 &up, float &next)
+// P: planes of y1 (2 SSTV, 4 HSSTV)
+template <int P, bool BUF>
+__global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
 {
-    const int64_t q = vox(d, k, i, j0);
-    const F4 a = ld4(un + q), b = ld4(uo + q);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) up.x[e] = 2.f * a.x[e] - b.x[e];
-    next = j0 + 4 < d.n2 ? 2.f * un[q + 4] - uo[q + 4] : 0.f;
-}
+    __shared__ float sY[3 * P * S2];         // three bands of y1, planes one after another
+    __shared__ float sU[2 * SU];             // u' by band parity
+    __shared__ float sT[(TI + 2) * TJ];      // t' with the rows above and below
+    __shared__ float4 keep[NT];              // t+, q+, y3, y3 of the row above
+    __shared__ double red[11 * (NT / 64)];
+    __shared__ uint32_t ncand[2];
+    const int tid = threadIdx.x, lane = tid & 63;
+    // Each phase reads the pointers and the window with scalar loads of its own
+    // (sweep.hip does, and says why).
+    const const4<VarArgs> *ap = (const const4<VarArgs> *)__builtin_amdgcn_kernarg_segment_ptr();
+    const const4<VarArgs> &a = *ap;
+    const bool idle_now = idle(args.sc);
+    if (blockIdx.x == 0 && tid == 0) {
+        // what the search of this slot reads of the state it rewrites; the
+        // histogram passes are over
+        args.sc->view = {args.sc->in.a_lo, args.sc->in.a_hi, args.sc->in.a_c, idle_now ? 1u : 0u};
+        *args.flags = 0u;
+    }
+    if (idle_now) return;
+    const const4<DevScalars> &sc = *(const4<DevScalars> *)args.sc;
+    const const4<DevScalars> *scp = &sc;
+    auto fresh = [&]() {
+        asm volatile("" : "+s"(ap), "+s"(scp));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const int par = (int)(sc.iter & 1u);
+    const int n1 = a.d.n1, n2 = a.d.n2, n3 = a.d.n3;
+    const uint32_t np = (uint32_t)n1 * (uint32_t)n2;
+    const float a4 = sc.in.a4;
+    // blocks of one XCD take consecutive slots, whose halos meet in its L2
+    const uint32_t pern = (uint32_t)a.slots >> 3, b0 = blockIdx.x;
+    const int slot = (int)(b0 < 8u * pern ? (b0 & 7u) * pern + (b0 >> 3) : b0);
+    if (tid < 2) ncand[tid] = 0u;  // published by the first barrier of a march
+    const int oti = tid / TJ, otj = tid % TJ;
+    // ring roles: u' (the first RINGU threads) and t' (T0 on), a wavefront has one
+    int rui = 0, ruj = 0;
+    const bool ring_u = tid < RINGU;
+    const int wave0 = __builtin_amdgcn_readfirstlane(tid);
+    const bool wave_t = wave0 >= T0 && wave0 < T0 + 2 * TJ;
+    if (ring_u) {
+        rui = tid < WU ? TI : tid - WU;
+        ruj = tid < WU ? tid : TJ;
+    }
+    if (wave_t) {
+        rui = tid - T0 < TJ ? -1 : TI;
+        ruj = (tid - T0) % TJ;
+    }
+    double du2 = 0.0, u2 = 0.0, r2 = 0.0;
+    Gathered ga;
 
-__global__ __launch_bounds__(VTD) void k_var_dual4(VarArgs a)
-{
-    __shared__ double red[VTD / 64];
-    const DevScalars *sc = a.sc;
-    if (idle(sc)) return;
-    const Dims d = a.d;
-    const int64_t N = d.plane, Q = N / 4;
-    const int par = (int)(sc->iter & 1u);
-    const float *uo = a.u[par], *un = a.u[par ^ 1], *to = a.t[par];
-    const float *y3o = a.y3[par], *qo = a.q[par];
-    float *tn = a.t[par ^ 1], *y3n = a.y3[par ^ 1], *qw = a.q[par ^ 1];
-    const double ts = sc->sel[0].done ? sc->sel[0].tau : fb_final(a.rec, 0).tau;
-    const double tt = sc->sel[1].done ? sc->sel[1].tau : fb_final(a.rec, 1).tau;
-    const float a4 = (float)sc->a4;
-    double r2 = 0.0;
-    for (int64_t g = (int64_t)blockIdx.x * VTD + threadIdx.x; g < Q; g += (int64_t)gridDim.x * VTD) {
-        const int64_t q = 4 * g;
-        int k, i, j0;
-        coords(d, q, k, i, j0);
-        const bool ei = i <= d.n1 - 2, ek = k <= d.n3 - 2;
-        const F4 so = ld4(a.s + q), tov = ld4(to + q), qv = ld4(qo + q), y3c = ld4(y3o + q);
-        F4 y3m = {{0.f, 0.f, 0.f, 0.f}};
-        if (i >= 1) y3m = ld4(y3o + q - d.n2);
-        F4 sn, tq, sp, tp;
+    const int t1 = min((slot + 1) * a.per, a.ti * a.tj * a.tk);
+    for (int t = slot * a.per; t < t1; ++t) {
+        const int rest = t / a.tj;
+        const int j0 = (t % a.tj) * TJ, i0 = (rest % a.ti) * TI, kb = (rest / a.ti) * a.kc;
+        const int ke = min(kb + a.kc, n3);
+        auto pixel = [&](int i, int j) {
+            return i >= 0 && i < n1 && j >= 0 && j < n2 ? (uint32_t)i * (uint32_t)n2 + (uint32_t)j : kNoPix;
+        };
+        // (the pixel of the row above: 64-bit addresses need its bound checked,
+        // the buffer path drops a negative offset)
+        auto row_above = [&](uint32_t p, int i) {
+            return BUF ? p - (uint32_t)n2 : (p != kNoPix && i >= 1 ? p - (uint32_t)n2 : kNoPix);
+        };
+        const int oi = i0 + oti, oj = j0 + otj;
+        const uint32_t po = pixel(oi, oj), pom = row_above(po, oi);
+        const bool own_in = po != kNoPix;
+        const int ri = i0 + rui, rj = j0 + ruj;
+        const uint32_t pr = ring_u || wave_t ? pixel(ri, rj) : kNoPix, prm = row_above(pr, ri);
+        uint32_t py[NY];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            // z_s, z_t here as the primal kernel evaluated them
-            const float y4 = y4_of(qv.x[e], a4);
-            sn.x[e] = soft_d(zs_of(so.x[e], y4), ts);
-            sp.x[e] = 2.f * sn.x[e] - so.x[e];
-            tq.x[e] = soft_d(zt_of(tov.x[e], y3m.x[e], ei ? y3c.x[e] : 0.f, y4, a.gt), tt);
-            tp.x[e] = 2.f * tq.x[e] - tov.x[e];
+        for (int n = 0; n < NY; ++n) {
+            const int p = tid + NT * n;
+            py[n] = p < S2 ? pixel(i0 - 1 + p / W2, j0 - 1 + p % W2) : kNoPix;
         }
-        st4(a.s + q, sn);
-        st4(tn + q, tq);
-        // y3 += g_y D_v t' (t' one row down from its own z_t and old t); the
-        // last row keeps its value
-        F4 y3x = y3c;
-        if (ei) {
-            const int64_t qd = q + d.n2;
-            const F4 td = ld4(to + qd), qd4 = ld4(qo + qd);
-            F4 y3d = {{0.f, 0.f, 0.f, 0.f}};
-            if (i + 1 <= d.n1 - 2) y3d = ld4(y3o + qd);
+        const bool ei = oi <= n1 - 2, ej = oj <= n2 - 2;
+
+        // ---------------- loads ----------------
+        struct Y {
+            float2 a[NY], b[P == 4 ? NY : 1];
+        };
+        auto loadY = [&](int k, bool want, Y &y) {
+            const Band<BUF, const float2> ba(ap->ya[par], k, np, want);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float ztd = zt_of(td.x[e], y3c.x[e], y3d.x[e], y4_of(qd4.x[e], a4), a.gt);
-                const float tp1 = 2.f * soft_d(ztd, tt) - td.x[e];
-                y3x.x[e] = y3c.x[e] + a.gy * (tp1 - tp.x[e]);
+            for (int n = 0; n < NY; ++n) y.a[n] = bget<BUF>(ba, py[n]);
+            if constexpr (P == 4) {
+                const Band<BUF, const float2> bb(ap->yb[par], k, np, want);
+#pragma unroll
+                for (int n = 0; n < NY; ++n) y.b[n] = bget<BUF>(bb, py[n]);
             }
-        }
-        st4(y3n + q, y3x);
-        // u' on the rows (k, i), (k, i + 1), (k + 1, i), (k + 1, i + 1)
-        F4 u0, ui = {{0.f, 0.f, 0.f, 0.f}}, uk = ui, uki = ui;
-        float u0n, ukn = 0.f, dummy;
-        uprime4(d, un, uo, k, i, j0, u0, u0n);
-        if (ei) uprime4(d, un, uo, k, i + 1, j0, ui, dummy);
-        if (ek) uprime4(d, un, uo, k + 1, i, j0, uk, ukn);
-        if (ek && ei) uprime4(d, un, uo, k + 1, i + 1, j0, uki, dummy);
-        F4 yv[4];
+        };
+        auto storeY = [&](float *buf, const Y &y) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if (c < a.P) yv[c] = ld4(a.y1 + c * N + q);
-        const F4 vv = ld4(a.v + q);
-        F4 qn;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const bool ej = j0 + e <= d.n2 - 2;
-            const float uj = ej ? (e < 3 ? u0.x[e + 1] : u0n) : 0.f;
-            float av[4] = {0.f, 0.f, 0.f, 0.f};
-            if (ek) {
-                const float s0 = uk.x[e] - u0.x[e];
-                if (ei) av[0] = (uki.x[e] - ui.x[e]) - s0;
-                if (ej) av[1] = ((e < 3 ? uk.x[e + 1] : ukn) - uj) - s0;
-            }
-            if (ei) av[2] = a.omega * (ui.x[e] - u0.x[e]);
-            if (ej) av[3] = a.omega * (uj - u0.x[e]);
-            float y[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) y[c] = c < a.P ? yv[c].x[e] + a.gy * av[c] : 0.f;
-            if (a.variant == GEO_REG_HSSTV2) {
-                const float nr = sqrtf((y[0] * y[0] + y[1] * y[1]) + (y[2] * y[2] + y[3] * y[3]));
-                if (nr > 1.f) {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) y[c] = y[c] / nr;
+            for (int n = 0; n < NY; ++n) {
+                const int p = tid + NT * n;
+                if (NT * (n + 1) <= S2 || p < S2) {
+                    buf[p] = y.a[n].x;
+                    buf[S2 + p] = y.a[n].y;
+                    if constexpr (P == 4) {
+                        buf[2 * S2 + p] = y.b[n].x;
+                        buf[3 * S2 + p] = y.b[n].y;
+                    }
                 }
+            }
+        };
+        // the own point; u and q at the u' ring point, or t, q and y3 at the t' one
+        float lu, lq, lv, ls, lt, l3c, l3m, xu, xq, x3c, x3m;
+        auto loadRU = [&](int k, bool want, bool own) {
+            const Band<BUF, const float> bu(ap->u[par], k, np, want), bq(ap->q[par], k, np, want);
+            const Band<BUF, const float> bt(ap->t[par], k, np, own), b3(ap->y3[par], k, np, own);
+            lu = bget<BUF>(bu, po);
+            lq = bget<BUF>(bq, po);
+            ls = bget<BUF>(Band<BUF, const float>(ap->s, k, np, own), po);
+            lt = bget<BUF>(bt, po);
+            l3c = bget<BUF>(b3, po);
+            l3m = bget<BUF>(b3, pom);
+            lv = bget<BUF>(Band<BUF, const float>(ap->v, k, np, own), po);
+            const Band<BUF, const float> bx(wave_t ? ap->t[par] : ap->u[par], k, np, wave_t ? own : want);
+            const Band<BUF, const float> br(ap->y3[par], k, np, own && wave_t);
+            xu = bget<BUF>(bx, pr);
+            xq = bget<BUF>(bq, pr);
+            x3c = bget<BUF>(br, pr);
+            x3m = bget<BUF>(br, prm);
+        };
+
+        // ---------------- phases ----------------
+        // D^T of a staged pair of planes at the point c (v, h: its edges exist)
+        auto dT = [&](const float *y, int c, bool v, bool h) {
+            float x = y[c - W2];
+            x -= v ? y[c] : 0.f;
+            x += y[S2 + c - 1];
+            x -= h ? y[S2 + c] : 0.f;
+            return x;
+        };
+        // u+ at one point of band k (yc: its y1, yp: the band before)
+        auto u_at = [&](int k, const float *yc, const float *yp, int ui, int uj, bool v, bool h, float uo, float qo) {
+            const int c = (ui + 1) * W2 + (uj + 1);
+            float g = 0.f;
+            if (k >= 1) g += dT(yp, c, v, h);
+            if (k <= n3 - 2) g -= dT(yc, c, v, h);
+            if constexpr (P == 4) g = __builtin_fmaf(ap->omega, dT(yc + 2 * S2, c, v, h), g);
+            const float x = __builtin_fmaf(-ap->gu, g + y4_of(qo, a4), uo);
+            return fminf(fmaxf(x, ap->mu_lo), ap->mu_hi);
+        };
+        auto slice = [&](int f) { return ap->cand + ((int64_t)f * ap->slots + slot) * ap->capt; };
+        auto uphase = [&](int k, bool own, const float *yc, const float *yp) {
+            float *su = sU + (k & 1) * SU;
+            const float un = u_at(k, yc, yp, oti, otj, ei, ej, lu, lq);
+            const float u0 = 2.f * un - lu;
+            su[oti * WU + otj] = u0;
+            bput(Band<BUF, float>(ap->u[par ^ 1], k, np, own), po, un);
+            const bool wr = own && own_in;
+            const double dl = (double)un - (double)lu, ud = (double)lu;
+            if (wr) {
+                du2 += dl * dl;
+                u2 += ud * ud;
+            }
+            const float y4 = y4_of(lq, a4);
+            const float sn = soft(zs_of(ls, y4), scp->in.tau[0]);
+            const float tn = soft(zt_of(lt, l3m, ei ? l3c : 0.f, y4, ap->gt), scp->in.tau[1]);
+            bput(Band<BUF, float>(ap->s, k, np, own), po, sn);
+            bput(Band<BUF, float>(ap->t[par ^ 1], k, np, own), po, tn);
+            const float sp = 2.f * sn - ls, tp = 2.f * tn - lt;
+            // y4'/g_y - v = (a4/g_y) q + u' + s' + t' - v
+            const float qn = (a4 / ap->gy) * lq + ((u0 + sp) + tp) - lv;
+            bput(Band<BUF, float>(ap->q[par ^ 1], k, np, own), po, qn);
+            if (wr) r2 += (double)qn * (double)qn;
+            sT[TJ + tid] = tp;
+            keep[tid] = make_float4(tn, qn, l3c, l3m);
+            if (wave_t) {
+                const float x = soft(zt_of(xu, x3m, ri <= n1 - 2 ? x3c : 0.f, y4_of(xq, a4), ap->gt), scp->in.tau[1]);
+                sT[(rui + 1) * TJ + ruj] = 2.f * x - xu;
+            }
+            if (ring_u)
+                su[rui * WU + ruj] = 2.f * u_at(k, yc, yp, rui, ruj, ri <= n1 - 2, rj <= n2 - 2, xu, xq) - xu;
+            if (own) gather_ahead(ga, scp->in, 0, wr, sn, 0.f, 1.f, qn, slice(0), &ncand[0], ap->capt);
+        };
+        // y1+ of band k at the own point
+        auto yphase = [&](int k, const float *yc) {
+            const float *u = sU + (k & 1) * SU + oti * WU + otj, *w = sU + ((k & 1) ^ 1) * SU + oti * WU + otj;
+            const int c = (oti + 1) * W2 + (otj + 1);
+            const bool ek = k <= n3 - 2;
+            const float u0 = u[0], ui = ei ? u[WU] : 0.f, uj = ej ? u[1] : 0.f;
+            const float s0 = w[0] - u0;
+            float av[P], y[P];
+            av[0] = ek && ei ? (w[WU] - ui) - s0 : 0.f;
+            av[1] = ek && ej ? (w[1] - uj) - s0 : 0.f;
+            if constexpr (P == 4) {
+                av[2] = ei ? ap->omega * (ui - u0) : 0.f;
+                av[3] = ej ? ap->omega * (uj - u0) : 0.f;
+            }
+#pragma unroll
+            for (int q = 0; q < P; ++q) y[q] = __builtin_fmaf(ap->gy, av[q], yc[q * S2 + c]);
+            if (P == 4 && ap->variant == GEO_REG_HSSTV2) {
+                const float nr = sqrtf((y[0] * y[0] + y[1] * y[1]) + (y[P - 2] * y[P - 2] + y[P - 1] * y[P - 1]));
+#pragma unroll
+                for (int q = 0; q < P; ++q) y[q] = nr > 1.f ? y[q] / nr : y[q];
             } else {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) y[c] = fminf(fmaxf(y[c], -1.f), 1.f);
+                for (int q = 0; q < P; ++q) y[q] = fminf(fmaxf(y[q], -1.f), 1.f);
             }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) yv[c].x[e] = y[c];
-            qn.x[e] = (a4 / a.gy) * qv.x[e] + ((u0.x[e] + sp.x[e]) + tp.x[e]) - vv.x[e];
-            r2 += (double)qn.x[e] * (double)qn.x[e];
+            bput(Band<BUF, float2>(ap->ya[par ^ 1], k, np, true), po, make_float2(y[0], y[1]));
+            if constexpr (P == 4)
+                bput(Band<BUF, float2>(ap->yb[par ^ 1], k, np, true), po, make_float2(y[2], y[3]));
+        };
+        // y3+ = y3 + g_y D_v t' (the last row keeps its value) and the t values of
+        // the next search
+        auto tphase = [&](int k) {
+            const float4 o = keep[tid];
+            const float tp = sT[TJ + tid];
+            const float yc = ei ? __builtin_fmaf(ap->gy, sT[2 * TJ + tid] - tp, o.z) : o.z;
+            bput(Band<BUF, float>(ap->y3[par ^ 1], k, np, true), po, yc);
+            const float ym = oi >= 1 ? __builtin_fmaf(ap->gy, tp - sT[tid], o.w) : 0.f;
+            gather_ahead(ga, scp->in, 1, own_in, o.x, ym - (ei ? yc : 0.f), ap->gt, o.y, slice(1), &ncand[1], ap->capt);
+        };
+
+        // ---------------- march ----------------
+        float *yA = sY, *yB = sY + P * S2, *yC = sY + 2 * P * S2;  // bands k, k + 1, k + 2 (and k - 1)
+        Y ry;
+        {
+            Y p, q;
+            loadY(kb - 1, kb >= 1, p);
+            loadY(kb, true, q);
+            loadY(kb + 1, kb + 1 <= ke && kb + 1 < n3, ry);
+            loadRU(kb, true, true);
+            storeY(yC, p);
+            storeY(yA, q);
+            storeY(yB, ry);
         }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if (c < a.P) st4(a.y1 + c * N + q, yv[c]);
-        st4(qw + q, qn);
+        __syncthreads();
+        fresh();
+        uphase(kb, true, yA, yC);
+        fresh();
+        loadY(kb + 2, kb + 2 <= ke && kb + 2 < n3, ry);
+        loadRU(kb + 1, kb + 1 < n3, kb + 1 < ke);
+        __syncthreads();
+        fresh();
+        tphase(kb);
+        __syncthreads();
+        int k = kb;
+        do {
+            const bool more = k + 1 < ke;
+            storeY(yC, ry);  // band k + 2
+            fresh();
+            loadY(k + 3, k + 3 <= ke && k + 3 < n3, ry);
+            fresh();
+            uphase(k + 1, more, yB, yA);
+            fresh();
+            loadRU(k + 2, k + 2 <= ke && k + 2 < n3, k + 2 < ke);
+            __syncthreads();
+            fresh();
+            yphase(k, yA);
+            fresh();
+            if (more) tphase(k + 1);
+            __syncthreads();
+            float *const y = yA;
+            yA = yB;
+            yB = yC;
+            yC = y;
+        } while (++k < ke);
     }
-    const double tot = block_sum<VTD>(r2, red);
-    if (threadIdx.x == 0) a.part[2 * a.ntiles + blockIdx.x] = tot;
+
+    // the slot's FP64 partials
+    const bool one = lane == 0;
+    double acc[11] = {du2, u2, r2,
+                      one ? (double)ga.cnt[0] : 0.0, ga.sum[0], (double)ga.slope[0], one ? (double)ga.inside[0] : 0.0,
+                      one ? (double)ga.cnt[1] : 0.0, ga.sum[1], (double)ga.slope[1], one ? (double)ga.inside[1] : 0.0};
+    block_sums<11, NT>(acc, red);
+    if (tid == 0) {
+        for (int q = 0; q < 3; ++q) a.part[3 * slot + q] = acc[q];
+        for (int q = 0; q < 4; ++q) {
+            a.winpart[4 * slot + q] = acc[3 + q];
+            a.winpart[4 * (a.slots + slot) + q] = acc[7 + q];
+        }
+        a.ccount[slot] = ncand[0];
+        a.ccount[a.slots + slot] = ncand[1];
+    }
 }
 
-__global__ __launch_bounds__(VT) void k_var_init(VarArgs a, double eps, double tol, double alpha,
+__global__ __launch_bounds__(VT) void k_var_init(VarArgs a, int P, double eps, double tol, double alpha,
                                                  double beta, double gy4)
 {
     const int64_t N = a.d.plane;
@@ -563,55 +407,42 @@ __global__ __launch_bounds__(VT) void k_var_init(VarArgs a, double eps, double t
         a.s[q] = 0.f;
         a.y3[0][q] = 0.f;
         a.q[0][q] = 0.f;
-        for (int c = 0; c < a.P; ++c) a.y1[c * N + q] = 0.f;
+        a.ya[0][q] = make_float2(0.f, 0.f);
+        if (P == 4) a.yb[0][q] = make_float2(0.f, 0.f);
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        DevScalars z = {};
-        z.c4 = 1.0;
-        z.a4 = 1.0;
-        z.eps = eps;
-        z.tol = tol;
-        z.sel[0].radius = alpha;
-        z.sel[1].radius = beta;
-        z.sel[0].done = z.sel[1].done = 1u;  // no search pending
-        z.zstore = 1u;
-        z.gy4 = gy4;
-        *a.sc = z;
-    }
-}
-
-__global__ void k_var_begin_call(DevScalars *sc, double eps, double tol, double alpha, double beta,
-                                 uint32_t limit)
-{
-    if (threadIdx.x == 0) {
-        sc->eps = eps;
-        sc->tol = tol;
-        sc->calls_iter = 0u;
-        sc->call_limit = limit;
-        sc->fallback = 0u;
-        sc->sel[0].radius = alpha;
-        sc->sel[1].radius = beta;
-        sc->stop = sc->nonfinite ? 1u : 0u;
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) init_scalars(a.sc, eps, tol, alpha, beta, gy4);
 }
 
 // Copy a state variable out (out != null) or in, planes as in the C ABI.
-__global__ __launch_bounds__(VT) void k_var_io(VarArgs a, int var, float *out, const float *in)
+__global__ __launch_bounds__(VT) void k_var_io(VarArgs a, int P, int var, float *out, const float *in)
 {
     const int64_t N = a.d.plane;
     const int par = (int)(a.sc->iter & 1u);
-    const int64_t n = var == GEO_VAR_Y1 ? a.P * N : N;
     const float a4 = (float)a.sc->a4;
+    const int64_t step = (int64_t)gridDim.x * VT;
+    if (var == GEO_VAR_Y1) {
+        for (int64_t g = (int64_t)blockIdx.x * VT + threadIdx.x; g < P / 2 * N; g += step) {
+            const int h = g >= N;  // which pair
+            const int64_t q = g - (h ? N : 0);
+            float2 *y = (h ? a.yb : a.ya)[par];
+            if (out) {
+                out[2 * h * N + q] = y[q].x;
+                out[(2 * h + 1) * N + q] = y[q].y;
+            } else {
+                y[q] = make_float2(in[2 * h * N + q], in[(2 * h + 1) * N + q]);
+            }
+        }
+        return;
+    }
     float *base;
     switch (var) {
     case GEO_VAR_U: base = a.u[par]; break;
     case GEO_VAR_S: base = a.s; break;
     case GEO_VAR_T: base = a.t[par]; break;
-    case GEO_VAR_Y1: base = a.y1; break;
     case GEO_VAR_Y3: base = a.y3[par]; break;
     default: base = a.q[par]; break;
     }
-    for (int64_t g = (int64_t)blockIdx.x * VT + threadIdx.x; g < n; g += (int64_t)gridDim.x * VT) {
+    for (int64_t g = (int64_t)blockIdx.x * VT + threadIdx.x; g < N; g += step) {
         if (out)
             out[g] = var == GEO_VAR_Y4 ? a4 * base[g] : base[g];
         else
@@ -619,83 +450,96 @@ __global__ __launch_bounds__(VT) void k_var_io(VarArgs a, int var, float *out, c
     }
 }
 
-int grid_of(int64_t n, int cap, int threads = VT)
+int grid_of(int64_t n)
 {
-    const int64_t b = (n + threads - 1) / threads;
-    return (int)(b < 1 ? 1 : (b > cap ? cap : b));
+    const int64_t b = (n + VT - 1) / VT;
+    return (int)(b < 1 ? 1 : (b > kVarBlocks ? kVarBlocks : b));
 }
 
 size_t align256v(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Blocks of `kernel` that the device holds at once (queried once per kernel).
-template <typename K>
-int resident_blocks(K kernel, int threads)
+// Sweep blocks that the device holds at once (queried once per form).
+template <int P>
+int resident_blocks()
 {
-    int dev = 0, cus = 256, per = 1;
-    if (hipGetDevice(&dev) == hipSuccess) {
-        hipDeviceProp_t prop;
-        if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
+    static const int cached = [] {
+        int dev = 0, cus = 256, per = 1;
+        if (hipGetDevice(&dev) == hipSuccess) {
+            hipDeviceProp_t prop;
+            if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
+        }
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_var_sweep<P, true>, NT, 0) != hipSuccess || per < 1)
+            per = 1;
+        return cus * per;
+    }();
+    return cached;
+}
+
+// Tiles of a cube: the band chunk in 1..32 whose tiles the resident blocks
+// finish first, a tile costing its bands and kTileFixedBands more (its first
+// loads, the halo bands, the partial sums); ties to the deeper chunk. A search
+// slot is one tile, or (bands of more than kMaxTiles tiles) several.
+struct VarTiles {
+    int ti, tj, tk, kc, slots, per;
+};
+VarTiles var_tiles(const Dims &d, int blocks)
+{
+    VarTiles v;
+    v.ti = ceil_div(d.n1, TI);
+    v.tj = ceil_div(d.n2, TJ);
+    const int64_t pb = (int64_t)v.ti * v.tj;
+    v.kc = d.n3 < 32 ? d.n3 : 32;
+    double best = 0.0;
+    for (int kc = v.kc; kc >= 1; --kc) {
+        const int64_t T = pb * ceil_div(d.n3, kc);
+        if (T > kMaxTiles && best > 0.0) break;
+        const double cost = (double)ceil_div(T, blocks) * (kc + kTileFixedBands);
+        if (best == 0.0 || cost < best - 1e-9) {
+            best = cost;
+            v.kc = kc;
+        }
     }
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, 0) != hipSuccess || per < 1)
-        per = 1;
-    return cus * per;
+    // (very deep cubes: the chunk grows until the tiles fit the search)
+    while (v.kc < d.n3 && pb * ceil_div(d.n3, v.kc) > kMaxTiles) v.kc = 2 * v.kc < d.n3 ? 2 * v.kc : d.n3;
+    v.tk = ceil_div(d.n3, v.kc);
+    const int64_t T = pb * v.tk;
+    v.per = ceil_div(T, kMaxTiles);
+    v.slots = ceil_div(T, v.per);
+    return v;
 }
 
-// Primal kernel blocks for N voxels: enough for one voxel (or group of four)
-// per thread, at most what the device holds at once (three blocks per CU of
-// the four-voxel kernel, four of the one-voxel kernel) and kVarTiles (three
-// per CU of 256), so that the grid runs in one round: 1024 blocks of the
-// four-voxel kernel left a second round of 256 (iterations 2.4% (HSSTV2)
-// and 3.2% (SSTV) slower than with 768; with 512, 1.2% and 2.4%). The
-// workspace regions of the tiles sized for 1024 instead of 768 moved the
-// arrays after them and made the dual kernel 2% slower.
-int primal_grid(int64_t N, bool quads)
-{
-    static const int res1 = resident_blocks(k_var_primal, VTP), res4 = resident_blocks(k_var_primal4, VTP);
-    const int cap = quads ? res4 : res1;
-    return grid_of(quads ? N / 4 : N, cap < kVarTiles ? cap : kVarTiles, VTP);
-}
-
-// four voxels per thread when rows split into whole 16-byte groups and v is
-// 16-byte aligned (the workspace arrays are 256-byte aligned)
-bool use_quads(const Dims &d, const float *v) { return d.n2 % 4 == 0 && ((uintptr_t)v & 15u) == 0; }
-
-// Workspace: the scalars, the search's regions, the launch table, then the
-// N-float arrays.
+// Workspace: the scalars, the search's regions (sized for kMaxTiles slots: the
+// tiling follows the device), the launch table, then the arrays.
 struct VarLayout {
-    size_t sc, part, winpart, hist, rec, cand, ccount, table, u0, u1, t0, t1, s, y1, y3[2], q[2], z, total;
-    int max_tiles, nb;  // most primal blocks, dual blocks
-    int64_t cap;        // candidates per field
+    size_t sc, part, winpart, hist, rec, cand, ccount, table, u[2], t[2], s, ya[2], yb[2], y3[2], q[2], total;
+    int64_t cap;  // candidates per field
 };
 
 VarLayout var_layout(int64_t N, int P)
 {
     VarLayout L;
-    L.max_tiles = grid_of(N, kVarTiles, VTP);
-    L.nb = grid_of(N, kVarBBlocks, VTD);
+    memset(&L, 0, sizeof L);
     L.cap = N / 16 > 65536 ? N / 16 : 65536;
     size_t o = 0;
     auto take = [&](size_t b) { const size_t at = o; o = align256v(o + b); return at; };
     const size_t f = sizeof(float) * (size_t)N;
     L.sc = take(sizeof(DevScalars));
-    L.part = take(sizeof(double) * (2 * (size_t)L.max_tiles + (size_t)L.nb));
-    L.winpart = take(sizeof(double) * 2 * 3 * (size_t)L.max_tiles);
+    L.part = take(sizeof(double) * 3 * kMaxTiles);
+    L.winpart = take(sizeof(double) * 2 * 4 * kMaxTiles);
     L.hist = take(6 * sizeof(Hist));  // 3 radix levels x 2 fields
     L.rec = take(6 * sizeof(FbRec));
-    L.cand = take(sizeof(float) * 2 * (size_t)L.cap);
-    L.ccount = take(sizeof(uint32_t) * 2 * (size_t)L.max_tiles);
+    L.cand = take(sizeof(float4) * 2 * (size_t)L.cap);
+    L.ccount = take(sizeof(uint32_t) * 2 * kMaxTiles);
     L.table = take(table_bytes(1));
-    L.u0 = take(f);
-    L.u1 = take(f);
-    L.t0 = take(f);
-    L.t1 = take(f);
+    for (int p = 0; p < 2; ++p) {
+        L.u[p] = take(f);
+        L.t[p] = take(f);
+        L.y3[p] = take(f);
+        L.q[p] = take(f);
+        L.ya[p] = take(2 * f);
+        if (P == 4) L.yb[p] = take(2 * f);
+    }
     L.s = take(f);
-    L.y1 = take((size_t)P * f);
-    L.y3[0] = take(f);
-    L.y3[1] = take(f);
-    L.q[0] = take(f);
-    L.q[1] = take(f);
-    L.z = take(2 * f);
     L.total = o;
     return L;
 }
@@ -706,8 +550,8 @@ VarArgs var_args(const Dims &d, const geo_params *p, const float *v, void *ws, V
     memset(&a, 0, sizeof a);
     a.d = d;
     a.variant = p->regularizer;
-    a.P = var_planes(p->regularizer);
-    const VarLayout L = var_layout(d.plane, a.P);
+    const int P = var_planes(p->regularizer);
+    const VarLayout L = var_layout(d.plane, P);
     if (Lout) *Lout = L;
     char *b = (char *)ws;
     const double na2 = p->regularizer == GEO_REG_SSTV ? 32.0 : 32.0 + 8.0 * p->omega * p->omega;
@@ -721,42 +565,42 @@ VarArgs var_args(const Dims &d, const geo_params *p, const float *v, void *ws, V
     a.sc = (DevScalars *)(b + L.sc);
     a.part = (double *)(b + L.part);
     a.winpart = (double *)(b + L.winpart);
-    a.cand = (float *)(b + L.cand);
+    a.cand = (float4 *)(b + L.cand);
     a.ccount = (uint32_t *)(b + L.ccount);
-    a.rec = (const FbRec *)(b + L.rec);
-    a.u[0] = (float *)(b + L.u0);
-    a.u[1] = (float *)(b + L.u1);
-    a.t[0] = (float *)(b + L.t0);
-    a.t[1] = (float *)(b + L.t1);
+    a.flags = slot_flags(b + L.table, 1);
+    for (int q = 0; q < 2; ++q) {
+        a.u[q] = (float *)(b + L.u[q]);
+        a.t[q] = (float *)(b + L.t[q]);
+        a.y3[q] = (float *)(b + L.y3[q]);
+        a.q[q] = (float *)(b + L.q[q]);
+        a.ya[q] = (float2 *)(b + L.ya[q]);
+        a.yb[q] = P == 4 ? (float2 *)(b + L.yb[q]) : nullptr;
+    }
     a.s = (float *)(b + L.s);
-    a.y1 = (float *)(b + L.y1);
-    a.y3[0] = (float *)(b + L.y3[0]);
-    a.y3[1] = (float *)(b + L.y3[1]);
-    a.q[0] = (float *)(b + L.q[0]);
-    a.q[1] = (float *)(b + L.q[1]);
-    a.z = (float *)(b + L.z);
-    // the primal grid (at most max_tiles: both forms need at most N / VTP)
-    a.ntiles = primal_grid(d.plane, v && use_quads(d, v));
-    a.nb = L.nb;
-    a.capt = (int)(L.cap / a.ntiles);
+    // (one tiling for all of them, so that HSSTV1 with omega = 0 sums as SSTV does)
+    const VarTiles t = var_tiles(d, resident_blocks<4>());
+    a.ti = t.ti;
+    a.tj = t.tj;
+    a.tk = t.tk;
+    a.kc = t.kc;
+    a.slots = t.slots;
+    a.per = t.per;
+    a.capt = (int)(L.cap / a.slots);
     return a;
 }
 
-// Host image of the launch table entry: the fields the window search, the
-// histogram passes and the finalize read. The tile geometry and the sweep B
-// prefetch of the main solver stay zero. The state sides hold the arrays
-// from which the histogram passes evaluate z_s and z_t (s, t, y3, the y4
-// residual) when the primal kernel did not store them.
-void var_table_entry(CubeEntry *e, const VarArgs &a, const VarLayout &L, void *ws)
+// Host image of the launch table entry: the fields the histogram passes, the
+// search and the start of a call read.
+void var_table_entry(CubeEntry *e, const VarArgs &a, const VarLayout &L, void *ws, const geo_params *p, int n_iter)
 {
     memset(e, 0, sizeof *e);
     CubeArgs<float> *x = reinterpret_cast<CubeArgs<float> *>(e->bytes);
     char *b = (char *)ws;
-    for (int p = 0; p < 2; ++p) {
-        x->side[p].s = a.s;
-        x->side[p].t = a.t[p];
-        x->side[p].y3 = a.y3[p];
-        x->side[p].y4 = a.q[p];
+    for (int q = 0; q < 2; ++q) {
+        x->side[q].s = a.s;
+        x->side[q].t = a.t[q];
+        x->side[q].y3 = a.y3[q];
+        x->side[q].y4 = a.q[q];
     }
     CubeCommon &c = x->c;
     c.zt_step = a.gt;
@@ -767,14 +611,26 @@ void var_table_entry(CubeEntry *e, const VarArgs &a, const VarLayout &L, void *w
     c.winpart = a.winpart;
     c.hist = (Hist *)(b + L.hist);
     c.rec = (FbRec *)(b + L.rec);
-    c.vcand = a.cand;
+    c.cand = a.cand;
     c.ccount = a.ccount;
-    c.zbuf = a.z;
     c.capt = a.capt;
-    c.ntiles = a.ntiles;
-    c.nb = a.nb;
-    c.mu_lo = a.mu_lo;
-    c.mu_hi = a.mu_hi;
+    c.ntiles = a.slots;
+    c.tol = p->tol;
+    c.alpha = p->alpha;
+    c.beta = p->beta;
+    c.eps = p->eps;
+    c.set_eps = 1u;
+    c.limit = (uint32_t)n_iter;
+    c.ahead = 1u;
+}
+
+template <bool BUF>
+void launch_var_sweep(const VarArgs &a, hipStream_t st)
+{
+    if (a.variant == GEO_REG_SSTV)
+        hipLaunchKernelGGL((k_var_sweep<2, BUF>), dim3(a.slots), dim3(NT), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_var_sweep<4, BUF>), dim3(a.slots), dim3(NT), 0, st, a);
 }
 
 }  // namespace
@@ -790,41 +646,37 @@ hipError_t var_state_init(const Dims &d, const geo_params *p, const float *v, vo
 {
     const VarArgs a = var_args(d, p, v, ws);
     // y4 = gy4 c4 q after an iteration, gy4 the FP32 step the kernels use
-    hipLaunchKernelGGL(k_var_init, dim3(grid_of(d.plane, kVarBBlocks)), dim3(VT), 0, st, a, p->eps,
+    hipLaunchKernelGGL(k_var_init, dim3(grid_of(d.plane)), dim3(VT), 0, st, a, var_planes(p->regularizer), p->eps,
                        p->tol, p->alpha, p->beta, (double)a.gy);
     return hipGetLastError();
 }
 
 hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws, int n_iter,
-                    hipStream_t st, DevScalars *out, int *slots, double *dual_ms)
+                    hipStream_t st, DevScalars *out, int *slots, double *sweep_ms)
 {
     VarLayout L;
     const VarArgs a = var_args(d, p, v, ws, &L);
     void *table = (char *)ws + L.table;
-    const int stride = (int)sizeof(CubeArgs<float>);
+    const int stride = (int)sizeof(CubeEntry);
     LaunchShape sh;
     memset(&sh, 0, sizeof sh);
     sh.ncubes = 1;
     sh.fb_grid = fallback_grid();
+    const bool buf = (uint64_t)d.n1 * (uint64_t)d.n2 < kVarPixels;
     // the table image, with its launch-wide flags zeroed
     std::vector<unsigned char> img(table_bytes(1), 0);
-    var_table_entry(reinterpret_cast<CubeEntry *>(img.data()), a, L, ws);
+    var_table_entry(reinterpret_cast<CubeEntry *>(img.data()), a, L, ws, p, n_iter);
     hipError_t e = hipMemcpyAsync(table, img.data(), img.size(), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_var_begin_call, dim3(1), dim3(64), 0, st, a.sc, p->eps, p->tol, p->alpha,
-                           p->beta, (uint32_t)n_iter);
-        e = hipGetLastError();
-    }
-    // dual_ms: events around the dual kernel of the kTimedEvery-th,
-    // 2 kTimedEvery-th, ... slot of the call (every slot in calls of fewer),
-    // the mean scaled to the iterations done
+    if (e == hipSuccess) e = launch_begin(table, stride, 1, st);
+    // sweep_ms: events around the sweep of the kTimedEvery-th, 2 kTimedEvery-th,
+    // ... slot of the call (every slot in calls of fewer), the mean scaled to
+    // the iterations done
     const bool all = n_iter < kTimedEvery;
     std::vector<hipEvent_t> ev;
-    if (dual_ms && e == hipSuccess) {
+    if (sweep_ms && e == hipSuccess) {
         ev.resize(2 * (size_t)(all ? n_iter : n_iter / kTimedEvery));
         for (size_t k = 0; k < ev.size() && e == hipSuccess; ++k) e = hipEventCreate(&ev[k]);
     }
-    const bool quads = use_quads(d, v);
     // with a tolerance the host reads the stop flag every check_every slots
     const int every = p->tol > 0.0 ? (p->check_every > 0 ? p->check_every : 32) : (n_iter > 0 ? n_iter : 1);
     size_t ne = 0;
@@ -833,24 +685,18 @@ hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws
     while (issued < n_iter && e == hipSuccess) {
         const int batch = n_iter - issued < every ? n_iter - issued : every;
         for (int it = issued; it < issued + batch && e == hipSuccess; ++it) {
-            if (quads)
-                hipLaunchKernelGGL(k_var_primal4, dim3(a.ntiles), dim3(VTP), 0, st, a);
-            else
-                hipLaunchKernelGGL(k_var_primal, dim3(a.ntiles), dim3(VTP), 0, st, a);
-            e = launch_select_window(table, stride, 1, 0, st);
-            for (int level = 0; level < 3 && e == hipSuccess; ++level)
-                e = launch_fallback(table, 4, sh, level, st);
+            for (int level = 0; level < 3 && e == hipSuccess; ++level) e = launch_fallback(table, 4, sh, level, st);
             if (e != hipSuccess) break;
-            const bool timed = dual_ms && (all || it % kTimedEvery == kTimedEvery - 1) &&
+            const bool timed = sweep_ms && (all || it % kTimedEvery == kTimedEvery - 1) &&
                                ne + 2 <= ev.size();
             if (timed) e = hipEventRecord(ev[ne], st);
-            if (quads)
-                hipLaunchKernelGGL(k_var_dual4, dim3(a.nb), dim3(VTD), 0, st, a);
+            if (buf)
+                launch_var_sweep<true>(a, st);
             else
-                hipLaunchKernelGGL(k_var_dual, dim3(a.nb), dim3(VTD), 0, st, a);
+                launch_var_sweep<false>(a, st);
             if (timed && e == hipSuccess) e = hipEventRecord(ev[ne + 1], st);
             ne += timed ? 2 : 0;
-            if (e == hipSuccess) e = launch_finalize(table, stride, 1, st);
+            if (e == hipSuccess) e = launch_search(table, stride, 1, st);
         }
         issued += batch;
         if (e == hipSuccess) e = hipMemcpyAsync(out, a.sc, sizeof(DevScalars), hipMemcpyDeviceToHost, st);
@@ -863,7 +709,7 @@ hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws
         if (e == hipSuccess) e = hipStreamSynchronize(st);
     }
     *slots = issued;
-    if (e == hipSuccess && dual_ms) {
+    if (e == hipSuccess && sweep_ms) {
         double sum = 0.0;
         for (size_t k = 0; k + 1 < ne && e == hipSuccess; k += 2) {
             float ms = 0.f;
@@ -871,7 +717,7 @@ hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws
             sum += ms;
         }
         const size_t ns = ne / 2;
-        *dual_ms = ns ? sum / (double)ns * (double)out->calls_iter : 0.0;
+        *sweep_ms = ns ? sum / (double)ns * (double)out->calls_iter : 0.0;
     }
     for (hipEvent_t x : ev) (void)hipEventDestroy(x);
     return e;
@@ -880,13 +726,14 @@ hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws
 hipError_t var_state_io(const Dims &d, const geo_params *p, void *ws, int var, float *out,
                         const float *in, hipStream_t st)
 {
-    const VarArgs a = var_args(d, p, nullptr, ws);
-    const int64_t n = var == GEO_VAR_Y1 ? a.P * d.plane : d.plane;
-    hipLaunchKernelGGL(k_var_io, dim3(grid_of(n, kVarBBlocks)), dim3(VT), 0, st, a, var, out, in);
+    VarLayout L;
+    const VarArgs a = var_args(d, p, nullptr, ws, &L);
+    const int P = var_planes(p->regularizer);
+    hipLaunchKernelGGL(k_var_io, dim3(grid_of(var == GEO_VAR_Y1 ? P / 2 * d.plane : d.plane)), dim3(VT), 0, st, a, P,
+                       var, out, in);
     hipError_t e = hipGetLastError();
-    // a loaded state does not continue the previous run: y4 read with the
-    // factor 1, the threshold predictions dropped
-    if (e == hipSuccess && in) e = launch_state_loaded(a.sc, var, st);
+    // a loaded state does not continue the previous run
+    if (e == hipSuccess && in) e = launch_loaded(a.sc, (Hist *)((char *)ws + L.hist), var, st);
     return e;
 }
 
