@@ -416,7 +416,8 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
             o.tau = tau;
             const double wdt = hi - lo;
             o.dens = won && wdt > 0.0 ? (double)n_in / wdt : 0.0;
-            set_window(o, false, window_budget(cc.d.plane), s.calm >= kCalmNarrow ? kWindowFillCalm : kWindowFill);
+            set_window(o, false, window_budget(cc.d.plane), s.calm >= kCalmNarrow ? kWindowFillCalm : kWindowFill,
+                       true);
             o.calm = s.calm + 1u;
         } else {
             o.done = 0u;
@@ -514,6 +515,7 @@ __global__ __launch_bounds__(kBeginThreads) void k_loaded(DevScalars *sc, Hist *
             SelState &s = sc->sel[f];
             s.win_on = 0u;
             s.tau_prev = s.tau_prev2 = s.tau_prev3 = 0.0;
+            s.err = 0.0;
             s.calm = 0u;
             s.done = s.radius > 0.0 ? 0u : 1u;
             if (!(s.radius > 0.0)) s.tau = __longlong_as_double(0x7ff0000000000000ll);

@@ -35,6 +35,7 @@ struct SelState {
     uint32_t cand_count;   // candidates in the window (search bookkeeping)
     double dens;           // values of |z| per unit near tau in the last
                            // iteration (sizes the next window)
+    double err;            // error of the last prediction of tau (FP32 duals)
     uint32_t calm;         // windows in a row that held tau
     uint32_t pad_;
 };
@@ -55,7 +56,8 @@ struct FbRec {
     double tau;      // the threshold, when the level ended the search
     double s_above;  // sum and count of the values above the chosen bin
     double c_above;
-    double dens;     // values per unit of |z| in tau's level-0 bin (level 0)
+    double dens;     // values per unit of |z| in the chosen bin (levels 0, 1;
+                     // 0: too few to tell)
     uint32_t prefix; // bits fixed so far (the chosen bins)
     uint32_t done;   // the level ended the search
 };

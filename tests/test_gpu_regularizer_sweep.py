@@ -115,3 +115,40 @@ def check(variant, shape, scale=1.0):
         e = float((got.double() - want).abs().max())
         print(f"regularizer {variant} {shape} {name}: {e:.1e}", flush=True)
         assert e <= 6e-6, (name, e)
+
+
+@pytest.mark.parametrize("seed", [4, 11])
+def test_thresholds_of_late_iterations(seed):
+    """Late in a solve the windows narrow with the steps of the thresholds: they
+    hold, and the thresholds are those of the values (evaluated here in 64 bits from the FP32 state: 4
+    roundings of 6e-8, and tau lies among the values that have them)."""
+    announce(f"SSTV, late iterations, seed {seed}")
+    torch = torch_cuda()
+    import paper_2510_00562_amd as geo
+    from gpu_helpers import dev, f32
+    from synth.cubes import SMALL_64x64x16, like, make_cube
+    shape = (198, 120, 120)
+    c = make_cube(like(SMALL_64x64x16, n1=120, n2=120, n3=198, seed=seed, cells=20))
+    v = dev(f32(c["v"]))
+    dims = geo.dims_of(shape)
+    p = geo.params(c["eps"], c["alpha"], c["beta"], regularizer=1)
+    ws = geo.Workspace(geo.geo_workspace_size(dims, p))
+    geo.geo_state_init(dims, p, v, ws)
+    geo.geo_step(dims, p, v, ws, 900)
+    for _ in range(3):
+        assert geo.geo_step(dims, p, v, ws, 99).fallback_passes == 0
+        x = {}
+        for name in ("s", "t", "y3", "y4"):
+            x[name] = torch.empty(shape, dtype=torch.float32, device="cuda")
+            geo.geo_state_get(dims, p, ws, name, v, x[name])
+        r = geo.geo_step(dims, p, v, ws, 1)
+        x = {k: a.double() for k, a in x.items()}
+        d = -x["y3"].clone()
+        d[:, -1] = 0.0
+        d[:, 1:] += x["y3"][:, :-1]
+        want = (_threshold(torch, x["s"] - x["y4"], c["alpha"]),
+                _threshold(torch, x["t"] - 0.2 * (d + x["y4"]), c["beta"]))
+        print(f"tau {r.tau_s:.9g} {r.tau_t:.9g}, of the values {want[0]:.9g} {want[1]:.9g}; "
+              f"in the windows {r.cand_s} {r.cand_t}", flush=True)
+        assert r.tau_s == pytest.approx(want[0], rel=1e-6)
+        assert r.tau_t == pytest.approx(want[1], rel=1e-6)
