@@ -353,8 +353,12 @@ __device__ inline void set_window(SelState &o, bool missed, double budget, doubl
     double h = 2.0 * err + least;
     if (!h2 || missed) h = fmax(h, fabs(step) + 2e-4 * tau);
     if (budget > 0.0 && o.dens > 0.0) {
-        // as wide as the search's flat cost allows, narrower than the budget
-        h = fmax(h, fill / (2.0 * o.dens));
+        // as wide as the search's flat cost allows, narrower than the budget;
+        // ahead: within [0, 2 tau], or a cube of fewer than `fill` values would
+        // widen its window from iteration to iteration without end, and the
+        // search sums in units of the window's upper end
+        const double wide = fill / (2.0 * o.dens);
+        h = fmax(h, ahead ? fmin(wide, tau) : wide);
         h = fmin(h, budget / (2.0 * o.dens));
     }
     double lo = c - h, hi = c + h;
