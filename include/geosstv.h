@@ -85,11 +85,11 @@ typedef struct {
                             whatever this is, since the device stops
                             iterating on its own once the rule is met      */
     int32_t band_chunk;  /* bands each tile of the fused sweep marches
-                            through (0 = chosen per cube: the depth in 8..32
-                            whose tiles the device's persistent blocks finish
-                            first, see geo_sweep_geometry; values below 8
-                            count as 8; raised when a cube would have more
-                            than 4096 tiles). A performance knob only:
+                            through (0 = chosen per cube, together with the
+                            pixels of its tiles, for the device's persistent
+                            blocks; values below 8 count as 8; raised when a
+                            cube would have more than 4096 tiles). A
+                            performance knob only:
                             results do not depend on it beyond FP64
                             summation order.                              */
     int32_t regularizer; /* GEO_REG_GEOSSTV (0, the method of the paper) or
@@ -223,9 +223,12 @@ int geo_batch_step(int32_t n_cubes, const geo_dims *dims, const geo_params *p,
                    void *table, size_t table_bytes, int32_t n_iter, int32_t use_graph,
                    void *stream, geo_result *out);
 
-/* Launch geometry of the fused sweep (steps 1, 4, 5, 11, 12 of Alg. 1 and
- * the inputs of steps 2 and 3), for callers that model load balance, such
- * as a band-chunk autotuner. Host-side only: no GPU work.
+/* Nominal launch geometry of the fused sweep, for callers that model load
+ * balance, such as a band-chunk autotuner. Host-side only: no GPU work. With
+ * BF16 duals it is the one used. With FP32 duals the sweep marches through the
+ * bands asked for in tiles of up to 1024 pixels fitted to the cube's rows and
+ * columns (idle lanes cost time), and chooses the bands as well when none are
+ * asked for; the nominal tiles tell how requests compare.
  *   dual_storage: GEO_STORE_F32 or GEO_STORE_BF16 (as in geo_params). A
  *       tile is 8 x 128 pixels, or 16 x 64 when the cube's width fills a
  *       64-wide tile grid more than 3% better (FP32 duals only).
@@ -235,7 +238,7 @@ int geo_batch_step(int32_t n_cubes, const geo_dims *dims, const geo_params *p,
  *       (min(kc, n3) + 2), ties to the deeper one.
  *   blocks: persistent blocks the default is chosen for (geo_sweep_blocks
  *       on the device that will run the cube); read only when requested = 0.
- *   used_chunk: the bands per tile the library will use.
+ *   used_chunk: the bands per tile of that request or default.
  *   tiles: tiles of this cube at that chunk (pixel tiles x band chunks).
  *   tile_rows, tile_cols: pixel shape of a tile (n1 rows x n2 columns).
  * Errors: GEO_EINVAL for bad dims or storage type, requested < 0,

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stddef.h>
+#include <math.h>
 #include <stdint.h>
 
 #include "common.hpp"
@@ -152,9 +153,10 @@ struct Layout {
     int64_t cap;    // candidate capacity per field
 };
 
-// Tile of the fused primal/dual sweep: TI x TJ pixels (one per thread of a
-// 1024-thread workgroup), marching through a chunk of kc bands (kc chosen
-// per cube at run time). Two shapes, chosen per cube by its width:
+// Nominal tile of the fused primal/dual sweep: TI x TJ pixels (one per thread of
+// a 1024-thread workgroup), marching through a chunk of kc bands (kc chosen
+// per cube at run time). With FP32 duals cube_grid fits the tile to the cube;
+// callers' load models see the nominal one. Two shapes, by the cube's width:
 //   shape 0, 8 x 128: each band row of a tile is one 512-byte run per array;
 //     it streamed 2.5% faster than 16 x 64 in a probe of the same 22-read,
 //     18-write access pattern;
@@ -165,9 +167,11 @@ struct Layout {
 constexpr int kTileShapes = 2;
 constexpr int kShapeTI[kTileShapes] = {8, 16}, kShapeTJ[kTileShapes] = {128, 64};
 constexpr int kSweepThreads = 1024;
+constexpr int kTileRows = kShapeTI[0], kTileCols = kShapeTJ[0], kTileSpan = kTileRows + kTileCols;
 constexpr int kDefaultKC = 32;       // deepest default chunk (the rule below picks 8..32)
 constexpr int kMinKC = 8;
 constexpr int kMaxTiles = 4096;      // tiles of one cube (slices of its search)
+constexpr int kFitTiles = 512;       // that any workspace has room for
 constexpr int kMaxBatch = 64;        // cubes of one batched launch
 constexpr int kPointThreads = 256;
 constexpr int kSweepBBlocks = 2048;  // grid-stride blocks of sweep B per cube
@@ -176,7 +180,7 @@ constexpr int kTimedEvery = 8;  // geo_step_timed: events around every 8th sweep
 
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-// Tile shape of a cube: 16 x 64 when its share of tile points inside the
+// Nominal tile shape of a cube: 16 x 64 when its share of tile points inside the
 // cube beats that of 8 x 128 by more than 3% (the streaming advantage of the
 // wider tile), else 8 x 128. With BF16 duals always 8 x 128 (the 16 x 64
 // sweep spills registers in that form). A function of the cube's size and
@@ -192,18 +196,19 @@ inline int tile_shape(int n1, int n2, int dual_bytes)
 }
 struct SweepGrid {
     int tj, ti, tk, kc;  // tiles along j, i, band chunks; bands per chunk
-    int shape;           // tile shape (kShapeTI/kShapeTJ)
+    int shape;           // kernel form: 0 for tiles of 8 x 128, 1 for any others
+    int rows, cols;      // pixels of a tile
     __host__ __device__ int blocks() const { return tj * ti * tk; }
 };
 inline SweepGrid sweep_grid(int n1, int n2, int n3, int kc, int shape)
 {
     return SweepGrid{ceil_div(n2, kShapeTJ[shape]), ceil_div(n1, kShapeTI[shape]), ceil_div(n3, kc), kc,
-                     shape};
+                     shape, kShapeTI[shape], kShapeTJ[shape]};
 }
 // Fixed work of one tile (its halo band, the pipeline fill, its partial
 // sums) in band-equivalents, for the load-balance rule below.
 constexpr double kTileFixedBands = 2.0;
-// Default depth for a cube: the chunk in [kMinKC, kDefaultKC] whose tiles,
+// Nominal default depth for a cube: the chunk in [kMinKC, kDefaultKC] whose tiles,
 // taken in turn by `blocks` persistent blocks, finish first. A round of
 // tiles costs the deepest tile's bands plus the fixed work; ties keep the
 // deeper chunk (fewer tiles). A cube with few tiles gets shallower chunks,
@@ -240,8 +245,8 @@ inline bool solver_dims_fit(int n1, int n2)
         if ((int64_t)ceil_div(n2, kShapeTJ[q]) * ceil_div(n1, kShapeTI[q]) > kMaxTiles) return false;
     return true;
 }
-// Bands per tile actually used: the request (0 = the default above for
-// `blocks` persistent blocks), at least kMinKC, raised until the cube has at
+// Bands per tile of a request (0 = the default above for `blocks` persistent
+// blocks), at least kMinKC, raised until the cube has at
 // most kMaxTiles tiles (always reached for a cube that solver_dims_fit
 // takes: at kc >= n3 a cube has one band chunk).
 inline int band_chunk(int n1, int n2, int n3, int requested, int blocks, int shape)
@@ -273,9 +278,85 @@ inline int max_tiles(int n1, int n2, int n3)
                 break;
             }
         }
-    return m;
+    // (tiles of few bands of a small cube: more than any nominal chunk gives)
+    return m > kFitTiles ? m : kFitTiles;
 }
 
+// Tiles of a cube with FP32 duals: the rows x cols and, when the chunk is left to
+// the library, the bands per tile that a model of the sweep's time prefers over
+// 8 x 128 of the nominal chunk, by 3% or more. One workgroup per CU marches at a
+// time, so a round of at most `blocks` tiles takes
+//   bands * sqrt(4.7^2 + (P / 36900)^2) + 16 us,
+// P the pixels in flight: 4.7 us of instructions a band (measured on 8K pixels),
+// the state streamed at the card's rate (8.5 us at 262144), and the tile's start
+// and end. A row of a tile that ends within a row of the cube costs 15 pixels
+// more in parts of cache lines that the neighbour moves again (8 or 0 where
+// width and tile are multiples of 16 or 32). To the cube's time alone the model
+// adds its share of a chip filled by many cubes, which finer tiles raise; with a
+// chunk asked for (as a batch does) that share decides.
+// Measured (N1 x N2 x N3, sweep, us): nominal tiles against those chosen
+//   64 x 64 x 16     16 x 64, 8 bands    53.6   16 x 64, 1 band      20.8
+//   128 x 128 x 64   8 x 128, 8 bands    69.3   8 x 128, 4 bands     51.5
+//   120 x 120 x 198  8 x 128, 12 bands  117.0   the same (8 x 120: 113.2)
+//   131 x 139 x 156  16 x 64, 16 bands  240.9   14 x 70, 16 bands   150.6
+//   512 x 512 x 224  8 x 128, 32 bands   2005   8 x 128, 224 bands   1889
+//   16 uneven cubes of 64..256 by 32..190, 16 bands  1844   fitted   1723
+inline SweepGrid fitted_grid(int n1, int n2, int n3, int requested, int blocks)
+{
+    auto step = [](double px) { return sqrt(4.7 * 4.7 + px * px / (36900.0 * 36900.0)); };
+    auto time_of = [&](const SweepGrid &g) {
+        const int T = g.blocks(), kc = g.kc < n3 ? g.kc : n3;
+        const bool whole = g.tj == 1;
+        const double miss = whole ? 0.0 : (n2 % 32 == 0 && g.cols % 32 == 0) ? 0.0 : (n2 % 16 == 0 && g.cols % 16 == 0) ? 8.0 : 15.0;
+        const double px = ((double)n1 * n2 + miss * n1 * g.tj) / (g.ti * g.tj);  // pixels moved per tile and band
+        const int full = T / blocks, left = T % blocks;
+        const double round = kc * step(px * blocks) + 16.0;  // of a full chip
+        const double share = (double)T / blocks * round;
+        if (requested > 0) return share;
+        return full * round + (left ? kc * step(px * left) + 16.0 : 0.0) + share;
+    };
+    // (the form whose geometry the compiler knows, for the widths that fill it)
+    auto form = [&](int rows, int cols) { return rows == kTileRows && cols == kTileCols && n2 % kTileCols == 0 ? 0 : 1; };
+    SweepGrid best = sweep_grid(n1, n2, n3, band_chunk(n1, n2, n3, requested, blocks, 0), 0);
+    best.shape = form(best.rows, best.cols);
+    double best_time = 0.97 * time_of(best);
+    const int most = max_tiles(n1, n2, n3), best_chunk = best.kc;
+    const int s0 = ceil_div(n2, kTileCols);
+    for (int s = s0; s < s0 + 4; ++s) {
+        int cols = ceil_div(n2, s);
+        if (n2 % 16 == 0) cols = ceil_div(cols, 16) * 16;
+        int r = kSweepThreads / cols;
+        if (r > kTileSpan - cols) r = kTileSpan - cols;
+        const int nr0 = ceil_div(n1, r);
+        for (int nr = nr0; nr < nr0 + 2; ++nr) {
+            const int rows = ceil_div(n1, nr);
+            SweepGrid g{ceil_div(n2, cols), ceil_div(n1, rows), 0, 0, form(rows, cols), rows, cols};
+            const int pb = g.ti * g.tj;
+            // band chunks: one, and as many as fill 1/4, 1/2, 1, 2, ... rounds
+            for (int q = requested > 0 ? 8 : -3; q <= 8; ++q) {
+                int nk = requested > 0 ? ceil_div(n3, best_chunk) : q == -3 ? 1 : q < 0 ? (blocks >> -q) / pb : (q + 1) * blocks / pb;
+                nk = nk < 1 ? 1 : nk > n3 ? n3 : nk;
+                g.kc = requested > 0 ? best_chunk : ceil_div(n3, nk);
+                g.tk = ceil_div(n3, g.kc);
+                if (g.blocks() > most) continue;
+                const double t = time_of(g);
+                if (t < best_time) {
+                    best_time = t;
+                    best = g;
+                }
+            }
+        }
+    }
+    return best;
+}
+// The tiles of a cube: a function of its size and storage, the request and the
+// device only, so that a cube runs the same ones alone and in a batch.
+inline SweepGrid cube_grid(int n1, int n2, int n3, int requested, int blocks, int dual_bytes)
+{
+    if (dual_bytes == 4) return fitted_grid(n1, n2, n3, requested, blocks);
+    const int shape = tile_shape(n1, n2, dual_bytes);
+    return sweep_grid(n1, n2, n3, band_chunk(n1, n2, n3, requested, blocks, shape), shape);
+}
 Layout make_layout(int n1, int n2, int n3, int dual_storage);
 
 // Pointers of one ping-pong side. Inside the workspace the two components

@@ -49,28 +49,17 @@ namespace geo {
 namespace {
 
 constexpr int NT = kSweepThreads;
-// Tile geometry of shape S (kShapeTI[S] x kShapeTJ[S] pixels)
-template <int S>
-struct TileOf {
-    static constexpr int TI = kShapeTI[S], TJ = kShapeTJ[S];
-    static constexpr int H2 = TI + 4, W2 = TJ + 4, S2 = H2 * W2;  // y with a 2-pixel halo
-    static constexpr int H1 = TI + 2, W1 = TJ + 2, S1 = H1 * W1;  // w' on a 1-pixel ring
-    static constexpr int HU = TI + 1, WU = TJ + 1, SU = HU * WU;  // u' with the (+1, +1) ring
-    static constexpr int NY = (S2 + NT - 1) / NT;                  // y points per thread
-    static constexpr int RING1 = S1 - TI * TJ;                     // w' ring points
-    static constexpr int RINGU = SU - TI * TJ;                     // u' ring points
-    static_assert(TI * TJ == NT && TJ % 64 == 0, "one own point per thread, whole wavefronts per tile row");
-    static_assert(RING1 <= NT && RINGU <= NT, "at most one ring point per thread");
-};
-// the geometry of shape S under its short names, inside a kernel
-#define GEO_TILE_GEOMETRY(S)                                                              \
-    constexpr int TI = TileOf<S>::TI, TJ = TileOf<S>::TJ;                                 \
-    constexpr int H2 = TileOf<S>::H2, W2 = TileOf<S>::W2, S2 = TileOf<S>::S2;             \
-    constexpr int H1 = TileOf<S>::H1, W1 = TileOf<S>::W1, S1 = TileOf<S>::S1;             \
-    constexpr int HU = TileOf<S>::HU, WU = TileOf<S>::WU, SU = TileOf<S>::SU;             \
-    constexpr int NY = TileOf<S>::NY, RING1 = TileOf<S>::RING1, RINGU = TileOf<S>::RINGU; \
-    (void)H2; (void)W2; (void)S2; (void)H1; (void)W1; (void)S1;                          \
-    (void)HU; (void)WU; (void)SU; (void)NY; (void)RING1; (void)RINGU
+// LDS planes of a tile of TI x TJ pixels, TI * TJ <= NT and TI + TJ <= kTileSpan
+// (8 x 128 fills them): y with a 2-pixel halo, w' on a 1-pixel ring, u' with the
+// (+1, +1) ring, t' with the rows above and below. A tile of fewer than NT
+// pixels leaves the last word of each free: idle threads write there.
+constexpr int S2 = NT + 4 * kTileSpan + 16, S1 = NT + 2 * kTileSpan + 4, SU = NT + kTileSpan + 1;
+constexpr int ST = NT + 2 * kTileCols;
+constexpr int NY = (S2 + NT - 1) / NT;  // y points per thread
+constexpr int T0 = NT / 2;              // first thread of the t' ring
+static_assert(kTileRows * kTileCols == NT && kTileRows + kTileCols == kTileSpan, "the fixed tile fills the planes");
+static_assert(2 * kTileSpan + 4 <= NT && kTileSpan + 1 <= T0 && T0 + 2 * kTileCols <= NT && T0 % 64 == 0,
+              "at most one ring point of a kind per thread, one of u' and t' per wavefront");
 constexpr int NPT = 256;  // threads of the pointwise kernels
 using lds_f = __attribute__((address_space(3))) float;
 
@@ -99,10 +88,11 @@ __device__ __forceinline__ int tile_at(int b, int G, int T, int r)
 // |z| by its slope in a4, not the rounded values) grows to 4e-4 of s within 40
 // iterations, so that storage keeps the form whose sums are over the values
 // themselves.
+// S 0: tiles of 8 x 128 pixels, the geometry known to the compiler (256 x 256 x
+// 128: 289 us, in the other form 293); 1: the cube's own rows x cols.
 template <typename DT, int S, bool FUSED>
 __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh)
 {
-    GEO_TILE_GEOMETRY(S);
     using P = typename PairOf<DT>::type;
     // three bands of masked [y1v, y1h, y2v, y2h] | u' by band parity | w1', w2'
     // planes read by neighbours (ud_h, lr_v, c_v, c_h)
@@ -111,14 +101,14 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
     constexpr int U0 = 3 * 4 * S2, W0 = U0 + 2 * SU;
     // t' with the rows above and below the tile; what a point keeps between the
     // phases of a band (t+, q+, y3, y3 of the row above)
-    __shared__ float sT[FUSED ? (TI + 2) * TJ : 1];
+    __shared__ float sT[FUSED ? ST : 1];
     __shared__ float4 keep[FUSED ? NT : 1];
     constexpr int NS = FUSED ? 11 : 8;  // FP64 partials of a tile
     __shared__ double red[NS * (NT / 64)];
     __shared__ uint32_t ncand[2];
     __shared__ int tile0[kMaxBatch + 1];
 
-    // The tiles of the cubes of this tile shape that work in this slot, one
+    // The tiles of the cubes of this form that work in this slot, one
     // cube after another: a cube that idles takes none, so the persistent
     // blocks, and the XCDs, share the working cubes' tiles evenly (with the
     // full list, a batch in which a few cubes still run would leave most
@@ -147,30 +137,6 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
     }
     __syncthreads();
     const int tid = threadIdx.x;
-    const int oti = tid / TJ, otj = tid % TJ;  // the thread's own point in the tile
-
-    // Ring roles: the w' ring (its first RING1 threads) and, apart from each
-    // other so that each wavefront has one, the u' ring (the first RINGU) and
-    // the t' ring: the rows above and below the tile (threads T0 on).
-    int rwi = 0, rwj = 0, rui = 0, ruj = 0;
-    const bool ring_w = tid < RING1, ring_u = tid < RINGU;
-    if (ring_w) {
-        if (tid < W1) { rwi = 0; rwj = tid; }
-        else if (tid < 2 * W1) { rwi = H1 - 1; rwj = tid - W1; }
-        else { const int s = tid - 2 * W1; rwi = 1 + (s >> 1); rwj = (s & 1) ? W1 - 1 : 0; }
-    }
-    if (ring_u) {
-        if (tid < WU) { rui = TI; ruj = tid; }
-        else { rui = tid - WU; ruj = TJ; }
-    }
-    constexpr int T0 = NT / 2;
-    static_assert(T0 >= RINGU && T0 % 64 == 0 && TJ % 64 == 0 && T0 + 2 * TJ <= NT, "one ring role per wavefront");
-    const bool wave_t = FUSED && __builtin_amdgcn_readfirstlane(tid) >= T0 &&
-                        __builtin_amdgcn_readfirstlane(tid) < T0 + 2 * TJ;
-    if (wave_t) {
-        rui = tid - T0 < TJ ? -1 : TI;
-        ruj = (tid - T0) % TJ;
-    }
 
     for (int r = 0;; ++r) {
         // (the working cubes' tile count is read from LDS at each tile rather
@@ -201,7 +167,39 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
             asm volatile("" : "+s"(ent), "+s"(scp));
             __builtin_amdgcn_sched_barrier(0);
         };
-        const SweepGrid g{a.c.g.tj, a.c.g.ti, a.c.g.tk, a.c.g.kc, S};
+        const SweepGrid g{a.c.g.tj, a.c.g.ti, a.c.g.tk, a.c.g.kc, S, S ? a.c.g.rows : kTileRows,
+                          S ? a.c.g.cols : kTileCols};
+        const int TI = g.rows, TJ = g.cols;
+        const int W2 = TJ + 4, W1 = TJ + 2, WU = TJ + 1;  // LDS row lengths
+        const bool act = S == 0 || tid < TI * TJ;         // the thread has a point of the tile
+        const int oti = act ? tid / TJ : 0, otj = act ? tid % TJ : 0;
+        // Ring roles: the w' ring (the first threads) and, apart from each other
+        // so that each wavefront has one, the u' ring (the first threads) and the
+        // t' ring: the rows above and below the tile (threads T0 on).
+        int rwi = 0, rwj = 0, rui = 0, ruj = 0;
+        const bool ring_w = tid < 2 * (TI + TJ) + 4, ring_u = tid < TI + TJ + 1;
+        const bool ring_t = FUSED && tid >= T0 && tid < T0 + 2 * TJ;
+        const int wave0 = __builtin_amdgcn_readfirstlane(tid);
+        const bool wave_t = FUSED && wave0 >= T0 && wave0 < T0 + 2 * TJ;
+        if (ring_w) {
+            if (tid < W1) { rwi = 0; rwj = tid; }
+            else if (tid < 2 * W1) { rwi = TI + 1; rwj = tid - W1; }
+            else { const int s = tid - 2 * W1; rwi = 1 + (s >> 1); rwj = (s & 1) ? W1 - 1 : 0; }
+        }
+        if (ring_u) {
+            if (tid < WU) { rui = TI; ruj = tid; }
+            else { rui = tid - WU; ruj = TJ; }
+        }
+        if (ring_t) {
+            rui = tid - T0 < TJ ? -1 : TI;
+            ruj = tid - T0 < TJ ? tid - T0 : tid - T0 - TJ;
+        }
+        // Offsets into the LDS planes: of the own point in y (one row up), w' and
+        // u' (where an idle thread writes to the free word), of the ring points.
+        const int oy = (oti + 1) * W2 + (otj + 2), ow = oti * W1 + otj, ou = oti * WU + otj;
+        const int ow_w = act ? ow + W1 + 1 : S1 - 1, ou_w = act ? ou : SU - 1, ot_w = act ? TJ + tid : ST - 1;
+        const int ry = (rui + 1) * W2 + (ruj + 2), ru = rui * WU + ruj;
+        const int rwy = rwi * W2 + (rwj + 1), rww = rwi * W1 + rwj;
         const int tj = lt % g.tj, rest = lt / g.tj;
         const int j0 = tj * TJ, i0 = (rest % g.ti) * TI, kb = (rest / g.ti) * g.kc;
         const int n1 = a.c.d.n1, n2 = a.c.d.n2, n3 = a.c.d.n3;
@@ -225,9 +223,9 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
             return i >= 0 && i < n1 && j >= 0 && j < n2 ? (uint32_t)i * (uint32_t)n2 + (uint32_t)j : kNoPix;
         };
         const int oi = i0 + oti, oj = j0 + otj;
-        const uint32_t po = pixel(oi, oj);
+        const uint32_t po = act ? pixel(oi, oj) : kNoPix;
         const bool own_in = po != kNoPix;
-        const uint32_t pr = ring_u || wave_t ? pixel(i0 + rui, j0 + ruj) : kNoPix;
+        const uint32_t pr = ring_u || ring_t ? pixel(i0 + rui, j0 + ruj) : kNoPix;
         const uint32_t pw = ring_w ? pixel(i0 - 1 + rwi, j0 - 1 + rwj) : kNoPix;
         uint32_t py[NY];
         // masks of the staged y: bit 2n vertical, 2n + 1 horizontal of point n;
@@ -236,7 +234,7 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
 #pragma unroll
         for (int n = 0; n < NY; ++n) {
             const int p = tid + NT * n, i = i0 - 2 + p / W2, j = j0 - 2 + p % W2;
-            py[n] = p < S2 ? pixel(i, j) : kNoPix;
+            py[n] = p < (TI + 4) * W2 ? pixel(i, j) : kNoPix;
             keepm |= (i <= n1 - 2 ? 1u : 0u) << (2 * n) | (j <= n2 - 2 ? 2u : 0u) << (2 * n);
         }
         const float mv = mask_le(oi, n1), mh = mask_le(oj, n2);
@@ -311,18 +309,19 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
         auto whi = [&](int f) { return scp->sel[f].win_hi; };
 
         // ---------------- phases ----------------
-        // D^T of planes pv (vertical) and pv + 1 of a staged band; y: its point
-        auto dT = [&](const lds_f *y, int pv) {
-            const lds_f *yv = y + pv * S2, *yh = yv + S2;
-            return (yv[-W2] - yv[0]) + (yh[-1] - yh[0]);
+        // D^T of planes pv (vertical) and pv + 1 of a staged band, at the point
+        // below `up` (LDS pointers: immediate offsets are unsigned)
+        auto dT = [&](const lds_f *up, int pv) {
+            const lds_f *yv = up + pv * S2, *yh = yv + S2 + W2 - 1;
+            return (yv[0] - yv[W2]) + (yh[0] - yh[1]);
         };
-        // u+ of step 1 at one point of band kk (yc: its y; yp: the band before)
-        auto u_at = [&](int kk, float *yc, float *yp, int ui, int uj, float uo, float y4s) {
-            const int c = (ui + 2) * W2 + (uj + 2);
-            const lds_f *y = at(yc + c - W2) + W2;       // immediate offsets are unsigned
+        // u+ of step 1 at one point of band kk (yc: its y; yp: the band before;
+        // o: the offset of the point above it)
+        auto u_at = [&](int kk, float *yc, float *yp, int o, float uo, float y4s) {
+            const lds_f *y = at(yc + o);
             float g = dT(y, 0);                          // D^T y1
             if (kk <= n3 - 2) g -= dT(y, 2);             // D_s^T D^T y2
-            if (kk >= 1) g += dT(at(yp + c - W2) + W2, 2);
+            if (kk >= 1) g += dT(at(yp + o), 2);
             const float x = __builtin_fmaf(-kStepU, __builtin_fmaf(a4, y4s, g), uo);
             return x < ent->c.mu_lo ? ent->c.mu_lo : (x > ent->c.mu_hi ? ent->c.mu_hi : x);
         };
@@ -348,9 +347,9 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
         auto uphase = [&](int kk, bool own, float *yc, float *yp) {
             float *su = smem + U0 + (kk & 1) * SU;
             const float y4 = y4_of(ru_y4, a4);
-            const float un = u_at(kk, yc, yp, oti, otj, ru_u, ru_y4);
+            const float un = u_at(kk, yc, yp, oy, ru_u, ru_y4);
             const float up = 2.f * un - ru_u;
-            *at(su + oti * WU + otj) = up;
+            *at(su + ou_w) = up;
             bst_nt((const float *)nullptr, band(DST.u, kk, own), po, un);
             const bool wr = own && own_in;
             const double dl = (double)un - (double)ru_u, uo = (double)ru_u;
@@ -370,9 +369,9 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
                 const float qn = as_stored((const DT *)nullptr, y4p + (sp + tp));
                 bst_nt((const DT *)nullptr, band(DST.y4, kk, own), po, qn);
                 if (wr) r2 += (double)qn * (double)qn;
-                *at(sT + TJ + tid) = tp;  // the own point: TJ * (oti + 1) + otj
+                *at(sT + ot_w) = tp;  // the own point: TJ * (oti + 1) + otj
                 keep[tid] = make_float4(tn, qn, ru_y3c, ru_y3m);
-                if (wave_t) {
+                if (S ? ring_t : wave_t) {
                     const float x = soft(zt_of(rr_u, rr_y3m, i0 + rui <= n1 - 2 ? rr_y3c : 0.f, y4_of(rr_y4, a4), kStepT),
                                          scp->in.tau[1]);
                     *at(sT + (rui + 1) * TJ + ruj) = 2.f * x - rr_u;
@@ -389,14 +388,15 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
                     collect(1, wr, zt);
                 }
             }
-            if (ring_u) *at(su + rui * WU + ruj) = 2.f * u_at(kk, yc, yp, rui, ruj, rr_u, rr_y4) - rr_u;
+            if (ring_u) *at(su + ru) = 2.f * u_at(kk, yc, yp, ry, rr_u, rr_y4) - rr_u;
         };
         // steps 4, 5 and the w extrapolations (9, 10) at one point of band k; the
         // own point also writes w+ and keeps the own-only planes ud_v', lr_h'
         float wk[2][2];
-        auto w_at = [&](int k, float *yb, int o, int wi, int wj, float v, float h) {
-            const lds_f *y = at(yb + wi * W2 + (wj + 1)) + W2;
-            lds_f *wo_at = at(smem + W0 + wi * W1 + wj);
+        // (oy_, ow_: offsets of the point above it in y and of the point in w')
+        auto w_at = [&](int k, float *yb, int o, int oy_, int ow_, float v, float h) {
+            const lds_f *y = at(yb + oy_) + W2;
+            lds_f *wo_at = at(smem + W0 + ow_);
             constexpr int c = 0;
 #pragma unroll
             for (int f = 0; f < 2; ++f) {
@@ -446,10 +446,11 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
         // steps 11, 12 for band k at the own point
         auto yphase = [&](int k, float *yb) {
             const float msk = k <= n3 - 2 ? 1.f : 0.f;
-            constexpr int c1 = W1 + 1, c2 = 0, cu = 0;
-            const lds_f *w0 = at(smem + W0 + oti * W1 + otj), *yc = at(yb + (oti + 2) * W2 + (otj + 2));
-            const lds_f *u0 = at(smem + U0 + (k & 1) * SU + oti * WU + otj);
-            const lds_f *u1 = at(smem + U0 + ((k & 1) ^ 1) * SU + oti * WU + otj);
+            const int c1 = W1 + 1;
+            constexpr int c2 = 0, cu = 0;
+            const lds_f *w0 = at(smem + W0 + ow), *yc = at(yb + oy + W2);
+            const lds_f *u0 = at(smem + U0 + (k & 1) * SU + ou);
+            const lds_f *u1 = at(smem + U0 + ((k & 1) ^ 1) * SU + ou);
             const float du_v = mv * (u0[cu + WU] - u0[cu]), du_h = mh * (u0[cu + 1] - u0[cu]);
             const float dn_v = mv * (u1[cu + WU] - u1[cu]), dn_h = mh * (u1[cu + 1] - u1[cu]);
             // A masked entry (vertical component on the last row, horizontal on
@@ -482,7 +483,8 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
         auto tphase = [&](int kk) {
             if constexpr (FUSED) {
                 const float4 o = keep[tid];
-                const lds_f *tr = at(sT + tid);  // t' of the row above, this one, the row below
+                // t' of the row above, this one, the row below
+                const lds_f *tr = at(sT + (S ? oti * TJ + otj : tid));
                 const float tp = tr[TJ];
                 const bool ei = oi <= n1 - 2;
                 const float yc = as_stored((const DT *)nullptr, ei ? __builtin_fmaf(kStepY, tr[2 * TJ] - tp, o.z) : o.z);
@@ -526,9 +528,9 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
             fresh();
             loadRU(k + 2, k + 2 <= ke && k + 2 < n3, k + 2 < ke);
             fresh();
-            w_at(k, yA, 0, oti + 1, otj + 1, mv, mh);
+            w_at(k, yA, 0, oy, ow_w, mv, mh);
             fresh();
-            if (ring_w) w_at(k, yA, 1, rwi, rwj, rmv, rmh);
+            if (ring_w) w_at(k, yA, 1, rwy, rww, rmv, rmh);
             fresh();
             loadW(k + 1, more);
             __syncthreads();
@@ -733,7 +735,7 @@ int resident_grid()
             hipDeviceProp_t prop;
             if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
         }
-        // the smaller occupancy of the tile shapes in use (BF16: 8 x 128 only)
+        // the smaller occupancy of the forms in use (BF16: 8 x 128 only)
         constexpr bool fused = sizeof(DT) == 4;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&p0, k_sweep<DT, 0, fused>, NT, 0) != hipSuccess || p0 < 1)
             p0 = 1;
@@ -769,9 +771,7 @@ void cube_entry_t(CubeArgs<DT> *a, const Dims &d, const float *v, void *ws, cons
         c.zbuf = (float *)(b + L.zbuf);
     }
     c.ccount = (uint32_t *)(b + L.ccount);
-    const int shape = tile_shape(d.n1, d.n2, (int)sizeof(DT));
-    c.g = sweep_grid(d.n1, d.n2, d.n3,
-                     band_chunk(d.n1, d.n2, d.n3, p->band_chunk, sweep_a_grid(sizeof(DT), 1 << 30), shape), shape);
+    c.g = cube_grid(d.n1, d.n2, d.n3, p->band_chunk, sweep_a_grid(sizeof(DT), 1 << 30), (int)sizeof(DT));
     c.ntiles = c.g.blocks();
     c.capt = (int)(L.cap / c.ntiles);
     c.tile0 = tile0;
@@ -824,8 +824,7 @@ hipError_t slot_fused(const void *table, const LaunchShape &sh, hipStream_t st, 
     hipError_t e = passes(table, 4, sh, st);
     if (e != hipSuccess) return e;
     if (nev >= 2) (void)hipEventRecord(ev[nev >= 4 ? 1 : 0], st);
-    // one persistent launch per tile shape present (each takes the tiles of
-    // its cubes)
+    // one persistent launch per form present (each takes the tiles of its cubes)
     if (sh.shape_tiles[0] > 0)
         hipLaunchKernelGGL((k_sweep<float, 0, true>), dim3(sh.shape_grid[0]), dim3(NT), 0, st, cubes, sh);
     if (sh.shape_tiles[1] > 0)
