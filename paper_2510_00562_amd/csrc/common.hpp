@@ -118,6 +118,38 @@ __device__ __forceinline__ float ld_nt(const bf16 *p)
     return __uint_as_float(((uint32_t)__builtin_nontemporal_load(&p->bits)) << 16);
 }
 
+// Four consecutive floats at any 4-byte alignment (global memory takes it), and
+// a group of U of them per thread: element e of group u of thread t of a block of
+// NT threads at base + 4 (u NT + t) + e, of n.
+struct __attribute__((aligned(4))) Quad {
+    float x[4];
+};
+__device__ __forceinline__ Quad ld_quad(const float *p, int64_t q, int64_t n)
+{
+    Quad o;
+    if (q + 4 <= n) {
+        __builtin_memcpy(&o, p + q, sizeof o);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o.x[e] = q + e < n ? p[q + e] : 0.f;
+    }
+    return o;
+}
+__device__ __forceinline__ void st_quad_nt(float *p, int64_t q, int64_t n, const Quad &v)
+{
+    typedef float unaligned4 __attribute__((ext_vector_type(4), aligned(4)));
+    if (q + 4 <= n) {
+        unaligned4 w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = v.x[e];
+        __builtin_nontemporal_store(w, reinterpret_cast<unaligned4 *>(p + q));
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (q + e < n) p[q + e] = v.x[e];
+    }
+}
+
 // Value as stored (FP32 or rounded to BF16).
 __device__ __forceinline__ float as_stored(const float *, float x) { return x; }
 __device__ __forceinline__ float as_stored(const bf16 *, float x)

@@ -50,8 +50,8 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
                                                          const uint32_t *pending)
 {
     if (*pending == 0u) return;  // no window missed in this slot
-    __shared__ uint32_t hc[2][kHistBins];
-    __shared__ unsigned long long hm[2][kHistBins];
+    __shared__ uint32_t hc[2][kHistStage];
+    __shared__ unsigned long long hm[2][kHistStage];
     __shared__ int64_t seg0[kMaxBatch + 1];  // first work index of each cube
     __shared__ uint32_t fmask[kMaxBatch];    // fields of each cube at this level
     __shared__ RadixPick pick_out;
@@ -214,11 +214,23 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
         if (last) {
             // acquire: drop cached copies so that the reads see every block's atomics
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            double *bs = reinterpret_cast<double *>(&hm[0][0]);
-            uint32_t *bc = &hc[0][0];
             const int nb = lvl_bins(level);
-            for (int f = 0; f < 2; ++f) {
+            // both fields' bins, then one wavefront each
+            for (int k = tid; k < 2 * nb; k += kFbThreads) {
+                const int f = k >= nb ? 1 : 0, b = k - f * nb;
                 if (!(m >> f & 1u)) continue;
+                Hist &h = hist[level * 2 + f];
+                // read where the atomics were performed
+                const uint32_t e = lvl_exponent(level, f ? pre1 : pre0, b);
+                const unsigned long long ms = __hip_atomic_load((unsigned long long *)&h.msum[b], __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_SYSTEM);
+                reinterpret_cast<double *>(hm[f])[bin_at(b)] = (double)ms * bin_scale(e);
+                hc[f][bin_at(b)] = __hip_atomic_load((uint32_t *)&h.count[b], __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+            __syncthreads();
+            const int f = __builtin_amdgcn_readfirstlane(tid >> 6);
+            if (f < 2 && (m >> f & 1u)) {
                 RadixPick pk = {0.0, 0.0, 0.0, 0.0, 0u, level, 0};
                 if (level > 0) {
                     const FbRec &pr = rec[(level - 1) * 2 + f];
@@ -226,33 +238,20 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
                     pk.c_above = pr.c_above;
                     pk.prefix = pr.prefix;
                 }
-                Hist &h = hist[level * 2 + f];
-                for (int b = tid; b < nb; b += kFbThreads) {
-                    // read where the atomics were performed
-                    const uint32_t e = lvl_exponent(level, pk.prefix, b);
-                    const unsigned long long ms = __hip_atomic_load((unsigned long long *)&h.msum[b], __ATOMIC_RELAXED,
-                                                                    __HIP_MEMORY_SCOPE_SYSTEM);
-                    bs[b] = (double)ms * bin_scale(e);
-                    bc[b] = __hip_atomic_load((uint32_t *)&h.count[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                radix_level_wave(reinterpret_cast<double *>(hm[f]), hc[f], sc->sel[f].radius, pk);
+                if ((tid & 63) == 0) {
+                    FbRec o;
+                    o.tau = pk.tau;
+                    o.s_above = pk.s_above;
+                    o.c_above = pk.c_above;
+                    o.dens = pk.dens;
+                    o.prefix = pk.prefix;
+                    o.done = pk.done ? 1u : 0u;
+                    a.c.rec[level * 2 + f] = o;
+                    // what the sweep of this slot reads of the threshold (no
+                    // pass reads it)
+                    if (o.done) sc->in.set(f, resolved(sc->sel[f], a.c.rec, f, a.c.d.plane));
                 }
-                __syncthreads();
-                if (tid < 64) {
-                    radix_level_wave(bs, bc, sc->sel[f].radius, pk);
-                    if (tid == 0) {
-                        FbRec o;
-                        o.tau = pk.tau;
-                        o.s_above = pk.s_above;
-                        o.c_above = pk.c_above;
-                        o.dens = pk.dens;
-                        o.prefix = pk.prefix;
-                        o.done = pk.done ? 1u : 0u;
-                        a.c.rec[level * 2 + f] = o;
-                        // what the sweep of this slot reads of the threshold (no
-                        // pass reads it)
-                        if (o.done) sc->in.set(f, resolved(sc->sel[f], a.c.rec, f, a.c.d.plane));
-                    }
-                }
-                __syncthreads();
             }
             if (tid == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }

@@ -36,10 +36,16 @@ struct RadixPick {
 
 __device__ __forceinline__ double bin_scale(uint32_t e) { return ldexp(1.0, (int)(e ? e : 1u) - 150); }
 
+// Where bin b is staged: a lane reads 32 (or 16) bins in a row, and with one word
+// left out after every 32 the lanes' reads fall into different banks. (All in
+// one bank, the pick took 3 us longer.)
+constexpr int kHistStage = kHistBins + kHistBins / 32;
+__device__ __forceinline__ int bin_at(int b) { return b + (b >> 5); }
+
 // One level for one field from its histogram staged in LDS (bin sums as
-// doubles in bs, counts in bc), by wavefront lanes 0..63 of the caller (every
-// lane must call; all lanes return the same result). nb/64 bins per lane,
-// lane 0 the top ones.
+// doubles in bs, counts in bc, bin b at bin_at(b)), by wavefront lanes 0..63 of
+// the caller (every lane must call; all lanes return the same result). nb/64
+// bins per lane, lane 0 the top ones.
 __device__ __forceinline__ void radix_level_wave(const double *bs, const uint32_t *bc, double radius,
                                                  RadixPick &pk)
 {
@@ -51,9 +57,10 @@ __device__ __forceinline__ void radix_level_wave(const double *bs, const uint32_
     const int btop = nb - 1 - per * lane;
     // this lane's bins, top down
     double ls = 0.0, lc = 0.0;
+#pragma unroll 8
     for (int q = 0; q < per; ++q) {
-        ls += bs[btop - q];
-        lc += (double)bc[btop - q];
+        ls += bs[bin_at(btop - q)];
+        lc += (double)bc[bin_at(btop - q)];
     }
     // inclusive scan over the lanes, lane 0 first
     double xs = ls, xc = lc;
@@ -74,7 +81,7 @@ __device__ __forceinline__ void radix_level_wave(const double *bs, const uint32_
     double mS = 0.0, mC = 0.0, mbs = 0.0, mbc = 0.0, mfb = 0.0;
     for (int q = 0; q < per; ++q) {
         const int b = btop - q;
-        const double vs = bs[b], vc = (double)bc[b];
+        const double vs = bs[bin_at(b)], vc = (double)bc[bin_at(b)];
         const float eb = __uint_as_float(base | ((uint32_t)b << shift));
         const double fb = (S + vs) - (double)eb * (C + vc);
         if (fb >= radius) {
@@ -148,35 +155,6 @@ __device__ __forceinline__ void radix_level_wave(const double *bs, const uint32_
         pk.c_above = mC;
     }
     pk.level = pk.done ? 3 : level + 1;
-}
-
-// The levels below `upto` (0..3) of field f of a cube, from its histograms
-// (hist[level * 2 + f]), by a block of NT threads: every thread stages the
-// level's bins into LDS (bs: 2048 doubles, bc: 2048 words), wavefront 0
-// decides. Every thread must call; every thread returns the result.
-template <int NT>
-__device__ RadixPick radix_chain_block(const Hist *hist, int f, double radius, int upto, double *bs,
-                                       uint32_t *bc, RadixPick *out)
-{
-    RadixPick pk = {0.0, 0.0, 0.0, 0.0, 0u, 0, 0};
-    while (!pk.done && pk.level < upto) {
-        const int level = pk.level, nb = level == 0 ? 2048 : 1024;
-        const Hist &h = hist[level * 2 + f];
-        for (int b = threadIdx.x; b < nb; b += NT) {
-            const uint32_t e = level == 0 ? (uint32_t)(b >> 3) : (level == 1 ? (pk.prefix >> 3) : (pk.prefix >> 13));
-            bs[b] = (double)h.msum[b] * bin_scale(e);
-            bc[b] = h.count[b];
-        }
-        __syncthreads();
-        if (threadIdx.x < 64) {
-            radix_level_wave(bs, bc, radius, pk);
-            if (threadIdx.x == 0) *out = pk;
-        }
-        __syncthreads();
-        pk = *out;
-        __syncthreads();  // out and the staging are rewritten by the next level
-    }
-    return pk;
 }
 
 // Empty histograms (the three radix levels) of field f, by a block of NT threads.

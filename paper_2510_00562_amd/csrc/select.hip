@@ -20,147 +20,139 @@ namespace geo {
 
 namespace {
 
-constexpr int kSelThreads = 256;
-constexpr int kHistUnroll = 8;  // values per thread in flight in a histogram pass
-// Histogram passes: large blocks, about one per CU and field. Every block
-// adds its LDS histogram into the field's global one with atomics, and the
-// blocks' atomics on a common bin (values cluster in a few bins) are
-// performed one after another: fewer, larger blocks shorten that chain.
+// The standalone projection: a launch that empties the search, per radix level a
+// histogram pass and a block that picks the bin, and the soft threshold. What
+// bounds a pass is the reading of x, at level 0 the LDS atomics on the few bins
+// in which the values cluster (one 64-bit atomic adds a value's count, bits 40
+// up, and its significand, whose sum over a block's at most 2^16 values stays
+// below 2^40, into one of kHistCopies copies by lane), and at level 1 the
+// atomics of all blocks on every global bin (so one block per CU). 256 x 256 x
+// 128 floats: passes 15, 15 and 6 us, picks 6, 4 and 4; with two atomics a value
+// into one copy and scalar loads 27, 18 and 15, with the picks' LDS reads in one
+// bank 11, 7 and 6. The last block to finish a pass as its picker, without a
+// launch of its own, made the passes 23, 19 and 14 us: 256 blocks wait for their
+// atomics and queue on one counter.
 constexpr int kHistThreads = 1024;
+constexpr int kHistCopies = 8;
+constexpr int kHistUnroll = 8;                 // groups of four values per thread in flight
+constexpr int kHistMost = 1 << 16;             // values of a block at most
+constexpr int kSoftThreads = 256, kSoftUnroll = 2;  // 13.5 -> 10.8 us, as ops.hip
 
-
-__global__ __launch_bounds__(kSelThreads) void k_select_begin(SelState *sel, int nfields, double r0,
-                                                              double r1, Hist *hist,
-                                                              const uint32_t *stop)
+__global__ __launch_bounds__(kHistThreads) void k_select_begin(SelState *sel, double radius, Hist *hist)
 {
-    if (stop && *stop) return;
-    const int f = blockIdx.x;
-    if (f >= nfields) return;
-    for (int b = threadIdx.x; b < kHistBins; b += kSelThreads) {
-        hist[f].count[b] = 0u;
-        hist[f].msum[b] = 0ull;
+    for (int b = threadIdx.x; b < kHistBins; b += kHistThreads) {
+        hist->count[b] = 0u;
+        hist->msum[b] = 0ull;
     }
     if (threadIdx.x == 0) {
-        SelState s;
-        s.radius = f == 0 ? r0 : r1;
-        s.s_above = 0.0;
-        s.c_above = 0ull;
-        s.prefix = 0u;
-        s.level = 0u;
-        s.done = s.radius <= 0.0 ? 1u : 0u;
-        s.tau = s.radius <= 0.0 ? __longlong_as_double(0x7ff0000000000000ll) : 0.0;
-        s.tau_prev = 0.0;
-        s.tau_prev2 = 0.0;
-        s.tau_prev3 = 0.0;
+        SelState s = {};
+        s.radius = radius;
+        s.done = radius <= 0.0 ? 1u : 0u;
+        s.tau = radius <= 0.0 ? __longlong_as_double(0x7ff0000000000000ll) : 0.0;
         s.full = 1u;
-        s.win_lo = s.win_hi = 0.f;
-        s.win_on = 0u;
-        s.cand_count = 0u;
-        sel[f] = s;
+        *sel = s;
     }
 }
 
-// Values of |z| come either from arrays (standalone projection) or are
-// evaluated from the solver state exactly as the sweeps evaluate them.
-struct ArraySrc {
-    const float *z[2];
-    __device__ __forceinline__ void begin() const {}
-    __device__ __forceinline__ float get(int f, int64_t q) const { return z[f][q]; }
-};
-
-// Histogram of the pattern bits of one radix level, restricted to values
-// whose higher bits equal the prefix chosen by the previous levels.
-template <typename Src>
-__global__ __launch_bounds__(kHistThreads) void k_hist(Src src, int64_t n, const SelState *sel,
-                                                      Hist *hist, int level, const uint32_t *stop)
+// Histogram of the pattern bits of one radix level, restricted to values whose
+// higher bits equal the prefix chosen by the previous levels; then the pick.
+// per: values of a block.
+template <int LEVEL>
+__global__ __launch_bounds__(kHistThreads) void k_hist(const float *x, int64_t n, int per, const SelState *sel, Hist *hist)
 {
-    if (stop && *stop) return;
-    const int f = blockIdx.y;
-    if (sel[f].done || (int)sel[f].level != level) return;
-    __shared__ uint32_t cnt[kHistBins];
-    __shared__ unsigned long long ms[kHistBins];
-    const int bins = lvl_bins(level), shift = lvl_shift(level);
-    for (int b = threadIdx.x; b < bins; b += kHistThreads) {
-        cnt[b] = 0u;
-        ms[b] = 0ull;
+    constexpr int bins = LEVEL == 0 ? 2048 : 1024, shift = LEVEL == 0 ? 20 : (LEVEL == 1 ? 10 : 0);
+    constexpr int pshift = shift + (LEVEL == 0 ? 11 : 10);
+    __shared__ unsigned long long h[bins * kHistCopies];
+    // the first values are on their way before anything else is known
+    const int64_t q0 = (int64_t)blockIdx.x * per, q1 = q0 + per < n ? q0 + per : n;
+    int64_t q = q0 + 4 * threadIdx.x;
+    Quad v[kHistUnroll];
+    auto load = [&]() {
+#pragma unroll
+        for (int u = 0; u < kHistUnroll; ++u) v[u] = ld_quad(x, q + 4 * u * kHistThreads, q1);
+    };
+    load();
+    for (int b = threadIdx.x; b < bins * kHistCopies; b += kHistThreads) h[b] = 0ull;
+    if (sel->done || (int)sel->level != LEVEL) return;
+    const uint32_t prefix = sel->prefix;
+    __syncthreads();
+    const uint32_t copy = threadIdx.x & (kHistCopies - 1);
+    while (q < q1) {
+#pragma unroll
+        for (int u = 0; u < kHistUnroll; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t p = abs_bits(v[u].x[e]);
+                const bool in = q + 4 * u * kHistThreads + e < q1 && (LEVEL == 0 || (p >> pshift) == prefix);
+                if (in)
+                    atomicAdd(&h[((p >> shift) & (bins - 1)) * kHistCopies + copy], 1ull << 40 | significand(p));
+            }
+        q += 4 * kHistUnroll * kHistThreads;
+        load();
     }
     __syncthreads();
-    src.begin();
-    const uint32_t prefix = sel[f].prefix;
-    const int pshift = shift + (level == 0 ? 11 : 10);
-    const int64_t stride = (int64_t)gridDim.x * kHistThreads;
-    // kHistUnroll loads in flight per thread, then their bins
-    for (int64_t q0 = (int64_t)blockIdx.x * kHistThreads + threadIdx.x; q0 < n; q0 += kHistUnroll * stride) {
-        uint32_t pv[kHistUnroll];
+    constexpr int own = bins / kHistThreads;
 #pragma unroll
-        for (int u = 0; u < kHistUnroll; ++u) {
-            const int64_t q = q0 + u * stride;
-            pv[u] = q < n ? abs_bits(src.get(f, q)) : 0u;
-        }
+    for (int k = 0; k < own; ++k) {
+        const int b = threadIdx.x + k * kHistThreads;
+        unsigned long long m = 0ull;
+        uint32_t c = 0u;
 #pragma unroll
-        for (int u = 0; u < kHistUnroll; ++u) {
-            if (q0 + u * stride >= n) break;
-            const uint32_t p = pv[u];
-            if (level > 0 && (p >> pshift) != prefix) continue;
-            const uint32_t b = (p >> shift) & (uint32_t)(bins - 1);
-            atomicAdd(&cnt[b], 1u);
-            atomicAdd(&ms[b], (unsigned long long)significand(p));
+        for (int r = 0; r < kHistCopies; ++r) {
+            const unsigned long long w = h[b * kHistCopies + r];
+            c += (uint32_t)(w >> 40);
+            m += w & ((1ull << 40) - 1ull);
         }
-    }
-    __syncthreads();
-    for (int b = threadIdx.x; b < bins; b += kHistThreads) {
-        if (cnt[b]) {
-            atomicAdd(&hist[f].count[b], cnt[b]);
-            atomicAdd((unsigned long long *)&hist[f].msum[b], ms[b]);
+        if (c) {
+            atomicAdd(&hist->count[b], c);
+            atomicAdd((unsigned long long *)&hist->msum[b], m);
         }
     }
 }
 
-// One block per field: pick the bin that holds tau, or finish. The block
-// stages the level's bins in LDS and one wavefront makes the pick
-// (radix_level_wave, the same code as the solver's histogram passes).
-__global__ __launch_bounds__(kSelThreads) void k_select_level(SelState *sel, Hist *hist, int level,
-                                                              const uint32_t *stop)
+// The bin of a level that holds tau, or the end of the search: the block stages
+// the bins in LDS and one wavefront picks (radix_level_wave, the same code as
+// the solver's histogram passes).
+template <int LEVEL>
+__global__ __launch_bounds__(kHistThreads) void k_select_level(SelState *sel, Hist *hist)
 {
-    if (stop && *stop) return;
-    const int f = blockIdx.x;
-    __shared__ double bs[kHistBins];
-    __shared__ uint32_t bc[kHistBins];
-    __shared__ uint32_t fin;
-    const SelState s = sel[f];
-    if (s.done || (int)s.level != level) return;
-    const int nb = lvl_bins(level);
-    for (int b = threadIdx.x; b < nb; b += kSelThreads) {
-        bs[b] = (double)hist[f].msum[b] * bin_scale(lvl_exponent(level, s.prefix, b));
-        bc[b] = hist[f].count[b];
+    constexpr int bins = LEVEL == 0 ? 2048 : 1024, own = bins / kHistThreads;
+    __shared__ double bs[kHistStage];
+    __shared__ uint32_t bc[kHistStage];
+    unsigned long long m[own];
+    uint32_t c[own];
+#pragma unroll
+    for (int k = 0; k < own; ++k) {
+        m[k] = hist->msum[threadIdx.x + k * kHistThreads];
+        c[k] = hist->count[threadIdx.x + k * kHistThreads];
+    }
+    if (sel->done || (int)sel->level != LEVEL) return;
+    const uint32_t prefix = sel->prefix;
+#pragma unroll
+    for (int k = 0; k < own; ++k) {
+        const int b = threadIdx.x + k * kHistThreads;
+        bs[bin_at(b)] = (double)m[k] * bin_scale(lvl_exponent(LEVEL, prefix, b));
+        bc[bin_at(b)] = c[k];
+        // the next level accumulates into a clean histogram
+        hist->count[b] = 0u;
+        hist->msum[b] = 0ull;
     }
     __syncthreads();
     if (threadIdx.x < 64) {
-        RadixPick pk = {0.0, s.s_above, (double)s.c_above, 0.0, s.prefix, level, 0};
-        radix_level_wave(bs, bc, s.radius, pk);
+        RadixPick pk = {0.0, sel->s_above, (double)sel->c_above, 0.0, prefix, LEVEL, 0};
+        radix_level_wave(bs, bc, sel->radius, pk);
         if (threadIdx.x == 0) {
-            SelState o = s;
             if (pk.done) {
-                o.tau = pk.tau;
-                o.done = 1u;
-                set_window(o, true, 0.0);
+                sel->tau = pk.tau;
+                sel->done = 1u;
             } else {
-                o.prefix = pk.prefix;
-                o.s_above = pk.s_above;
-                o.c_above = (uint64_t)pk.c_above;
-                o.level = (uint32_t)(level + 1);
+                sel->prefix = pk.prefix;
+                sel->s_above = pk.s_above;
+                sel->c_above = (uint64_t)pk.c_above;
+                sel->level = (uint32_t)(LEVEL + 1);
             }
-            sel[f] = o;
-            fin = o.done;
         }
     }
-    __syncthreads();
-    // the next level accumulates into a clean histogram
-    if (!fin)
-        for (int q = threadIdx.x; q < kHistBins; q += kSelThreads) {
-            hist[f].count[q] = 0u;
-            hist[f].msum[q] = 0ull;
-        }
 }
 
 // Threshold search over the candidates of the predicted window (one block
@@ -723,58 +715,22 @@ __global__ __launch_bounds__(kWinThreads) void k_select_window(const char *table
         }
 }
 
-__global__ __launch_bounds__(kSelThreads) void k_soft(const float *x, int64_t n, const SelState *sel,
-                                                      float *out)
+__global__ __launch_bounds__(kSoftThreads) void k_soft(const float *x, int64_t n, const SelState *sel, float *out)
 {
+    const int64_t q0 = ((int64_t)blockIdx.x * kSoftUnroll * kSoftThreads + threadIdx.x) * 4;
+    Quad v[kSoftUnroll];
+#pragma unroll
+    for (int u = 0; u < kSoftUnroll; ++u) v[u] = ld_quad(x, q0 + 4 * u * kSoftThreads, n);
     const double tau = sel->tau;
-    const int64_t stride = (int64_t)gridDim.x * kSelThreads;
-    for (int64_t q = (int64_t)blockIdx.x * kSelThreads + threadIdx.x; q < n; q += stride) {
-        float z = x[q];
-        double m = fabs((double)z) - tau;
-        out[q] = m > 0.0 ? copysignf((float)m, z) : 0.0f;
+#pragma unroll
+    for (int u = 0; u < kSoftUnroll; ++u) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[u].x[e] = soft(v[u].x[e], tau);
+        st_quad_nt(out, q0 + 4 * u * kSoftThreads, n, v[u]);
     }
-}
-
-int hist_blocks(int64_t n)
-{
-    // 64 values per thread at most: the block histograms are flushed to
-    // global memory with atomics once per block
-    int b = ceil_div(n, (int64_t)kHistThreads * 64);
-    return b < 1 ? 1 : (b > 256 ? 256 : b);
-}
-
-int soft_blocks(int64_t n)
-{
-    int b = ceil_div(n, (int64_t)kSelThreads * 4);
-    return b < 1 ? 1 : (b > 8192 ? 8192 : b);
 }
 
 }  // namespace
-
-// stop may be null (standalone projection)
-hipError_t select_begin(SelState *sel, int nfields, double r0, double r1, Hist *hist,
-                        const uint32_t *stop, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_select_begin, dim3(nfields), dim3(kSelThreads), 0, st, sel, nfields, r0,
-                       r1, hist, stop);
-    return hipGetLastError();
-}
-
-hipError_t select_run(const float *z0, const float *z1, int nfields, int64_t n, SelState *sel,
-                      Hist *hist, const uint32_t *stop, hipStream_t st)
-{
-    ArraySrc zp;
-    zp.z[0] = z0;
-    zp.z[1] = z1;
-    const int hb = hist_blocks(n);
-    for (int level = 0; level < 3; ++level) {
-        hipLaunchKernelGGL(k_hist<ArraySrc>, dim3(hb, nfields), dim3(kHistThreads), 0, st, zp, n,
-                           (const SelState *)sel, hist, level, stop);
-        hipLaunchKernelGGL(k_select_level, dim3(nfields), dim3(kSelThreads), 0, st, sel, hist,
-                           level, stop);
-    }
-    return hipGetLastError();
-}
 
 hipError_t launch_select_window(const void *table, int stride, int ncubes, int prefetch_blocks,
                                 hipStream_t st)
@@ -784,17 +740,27 @@ hipError_t launch_select_window(const void *table, int stride, int ncubes, int p
     return hipGetLastError();
 }
 
-hipError_t launch_l1_threshold(const float *x, int64_t n, double radius, SelState *sel, Hist *hist,
-                               hipStream_t st)
+hipError_t launch_l1_threshold(const float *x, int64_t n, double radius, SelState *sel, Hist *hist, hipStream_t st)
 {
-    hipError_t e = select_begin(sel, 1, radius, 0.0, hist, nullptr, st);
-    if (e != hipSuccess) return e;
-    return select_run(x, nullptr, 1, n, sel, hist, nullptr, st);
+    hipLaunchKernelGGL(k_select_begin, dim3(1), dim3(kHistThreads), 0, st, sel, radius, hist);
+    // about one block per CU, of whole rounds of loads, at most 2^16 values each
+    constexpr int round = 4 * kHistThreads;
+    int64_t per = (n / 256 + round - 1) / round * round;
+    per = per < round ? round : per > kHistMost ? kHistMost : per;
+    const int blocks = n > 0 ? ceil_div(n, per) : 1;
+    hipLaunchKernelGGL(k_hist<0>, dim3(blocks), dim3(kHistThreads), 0, st, x, n, (int)per, sel, hist);
+    hipLaunchKernelGGL(k_select_level<0>, dim3(1), dim3(kHistThreads), 0, st, sel, hist);
+    hipLaunchKernelGGL(k_hist<1>, dim3(blocks), dim3(kHistThreads), 0, st, x, n, (int)per, sel, hist);
+    hipLaunchKernelGGL(k_select_level<1>, dim3(1), dim3(kHistThreads), 0, st, sel, hist);
+    hipLaunchKernelGGL(k_hist<2>, dim3(blocks), dim3(kHistThreads), 0, st, x, n, (int)per, sel, hist);
+    hipLaunchKernelGGL(k_select_level<2>, dim3(1), dim3(kHistThreads), 0, st, sel, hist);
+    return hipGetLastError();
 }
 
 hipError_t launch_soft(const float *x, int64_t n, const SelState *sel, float *out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_soft, dim3(soft_blocks(n)), dim3(kSelThreads), 0, st, x, n, sel, out);
+    hipLaunchKernelGGL(k_soft, dim3(ceil_div(n, 4 * kSoftUnroll * kSoftThreads)), dim3(kSoftThreads), 0, st, x, n, sel,
+                       out);
     return hipGetLastError();
 }
 

@@ -38,7 +38,7 @@ struct SelState {
                            // iteration (sizes the next window)
     double err;            // error of the last prediction of tau (FP32 duals)
     uint32_t calm;         // windows in a row that held tau
-    uint32_t pad_;
+    uint32_t finished;     // standalone projection: blocks of a pass that are done
 };
 
 constexpr int kHistBins = 2048;  // bins of radix level 0 (levels 1 and 2 use 1024)
@@ -536,11 +536,7 @@ hipError_t launch_apply_op(int op, int adjoint, const Dims &d, const float *in, 
                            hipStream_t st);
 int op_planes(int op, int adj, int *pin, int *pout);
 
-// Exact l1-ball threshold search (select.hip). stop may be null.
-hipError_t select_begin(SelState *sel, int nfields, double r0, double r1, Hist *hist,
-                        const uint32_t *stop, hipStream_t st);
-hipError_t select_run(const float *z0, const float *z1, int nfields, int64_t n, SelState *sel,
-                      Hist *hist, const uint32_t *stop, hipStream_t st);
+// Exact l1-ball threshold search (select.hip).
 hipError_t launch_l1_threshold(const float *x, int64_t n, double radius, SelState *sel,
                                Hist *hist, hipStream_t st);
 hipError_t launch_soft(const float *x, int64_t n, const SelState *sel, float *out, hipStream_t st);
