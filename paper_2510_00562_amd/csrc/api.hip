@@ -9,7 +9,7 @@
 #include <mutex>
 #include <vector>
 
-#include "solver.hpp"
+#include "host_box.hpp"
 
 namespace geo {
 
@@ -56,6 +56,43 @@ Layout make_layout(int n1, int n2, int n3, int dual_storage)
     }
     L.total = o;
     return L;
+}
+
+namespace {
+std::mutex g_box_mu;
+std::vector<void *> g_boxes;  // free boxes, kept until the process ends
+constexpr size_t kBoxesKept = 16;
+}  // namespace
+
+HostBox::HostBox()
+{
+    {
+        std::lock_guard<std::mutex> lock(g_box_mu);
+        if (!g_boxes.empty()) {
+            p_ = g_boxes.back();
+            g_boxes.pop_back();
+            return;
+        }
+    }
+    // (another thread may be capturing a graph)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    status_ = hipHostMalloc(&p_, kBytes, hipHostMallocPortable | hipHostMallocMapped);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (status_ != hipSuccess) p_ = nullptr;
+}
+
+HostBox::~HostBox()
+{
+    if (!p_) return;
+    {
+        std::lock_guard<std::mutex> lock(g_box_mu);
+        if (g_boxes.size() < kBoxesKept) {
+            g_boxes.push_back(p_);
+            return;
+        }
+    }
+    (void)hipHostFree(p_);
 }
 
 }  // namespace geo
@@ -177,10 +214,12 @@ int var_step_impl(geo_dims dims, const geo_params *p, const float *v, void *ws, 
 {
     int rc = check_var_ws(dims, p, ws, ws_bytes);
     if (rc) return rc;
-    DevScalars x;
+    HostBox box;
     int slots = 0;
-    rc = hip_status(var_step(to_dims(dims), p, v, ws, n_iter, st, &x, &slots, sweep_ms));
+    rc = hip_status(box.status());
+    if (!rc) rc = hip_status(var_step(to_dims(dims), p, v, ws, n_iter, st, box.as<DevScalars>(), &slots, sweep_ms));
     if (rc) return rc;
+    const DevScalars &x = *box.as<DevScalars>();
     const int own = x.nonfinite ? GEO_ENONFINITE : (p->tol > 0.0 && !x.stop ? GEO_MAXITER : GEO_OK);
     if (out) {
         memset(out, 0, sizeof *out);
@@ -198,14 +237,6 @@ int var_step_impl(geo_dims dims, const geo_params *p, const float *v, void *ws, 
         out->status = own;
     }
     return own;
-}
-
-int read_scalars(const void *ws, const Layout &L, DevScalars *out, hipStream_t st)
-{
-    hipError_t e = hipMemcpyAsync(out, (const char *)ws + L.scalars, sizeof(DevScalars),
-                                  hipMemcpyDeviceToHost, st);
-    if (e != hipSuccess) return hip_status(e);
-    return hip_status(hipStreamSynchronize(st));
 }
 
 }  // namespace
@@ -360,7 +391,9 @@ static int run_cubes(int n, const geo_dims *dims, const geo_params *p, const flo
         }
     }
 
-    std::vector<DevScalars> sc(n);
+    HostBox box;
+    if (!rc) rc = hip_status(box.status());
+    DevScalars *const sc = box.as<DevScalars>();
     std::vector<hipEvent_t> ev;
     int behind = n_iter;  // slots still needed by the furthest-behind busy cube
     while (!rc) {
@@ -385,9 +418,7 @@ static int run_cubes(int n, const geo_dims *dims, const geo_params *p, const flo
         }
         slots += batch;
         sampled += nsamp;
-        for (int c = 0; c < n && !rc; ++c)
-            rc = hip_status(hipMemcpyAsync(&sc[c], (const char *)ws[c] + L[c].scalars, sizeof(DevScalars),
-                                           hipMemcpyDeviceToHost, st));
+        if (!rc) rc = hip_status(launch_report(table, (int)sizeof(CubeEntry), n, sc, st));
         if (!rc) rc = hip_status(hipStreamSynchronize(st));
         if (!rc && phase_ms)
             for (int q = 0; q < nsamp && !rc; ++q)
@@ -399,7 +430,7 @@ static int run_cubes(int n, const geo_dims *dims, const geo_params *p, const flo
                     phase_ms[nph == 1 || ph == 2 || L[0].dual_bytes == 2 ? ph : 1 - ph] += ms;
                 }
         behind = 0;
-        for (int c = 0; c < n; ++c) {
+        for (int c = 0; c < n && !rc; ++c) {
             const int left = sc[c].stop ? 0 : n_iter - (int)sc[c].calls_iter;
             if (left > behind) behind = left;
         }
@@ -621,11 +652,11 @@ int geo_project_l1(const float *x, int64_t n, double radius, float *out, double 
     SelState *sel = (SelState *)ws;
     Hist *hist = (Hist *)((char *)ws + align256(sizeof(SelState)));
     int rc = hip_status(launch_l1_threshold(x, n, radius, sel, hist, st));
-    if (!rc && n > 0) rc = hip_status(launch_soft(x, n, sel, out, st));
-    SelState h;
-    if (!rc) rc = hip_status(hipMemcpyAsync(&h, sel, sizeof h, hipMemcpyDeviceToHost, st));
+    HostBox box;
+    if (!rc) rc = hip_status(box.status());
+    if (!rc) rc = hip_status(launch_soft(x, n, sel, out, box.as<double>(), st));
     if (!rc) rc = hip_status(hipStreamSynchronize(st));
-    if (!rc && tau) *tau = h.tau;
+    if (!rc && tau) *tau = *box.as<double>();
     return rc;
 }
 
@@ -645,12 +676,11 @@ int geo_project_l2(const float *x, const float *center, int64_t n, double eps, f
     if (!ws || ((uintptr_t)ws & 255u) || ws_bytes < need) return GEO_EWORKSPACE;
     const hipStream_t st = S(stream);
     double *part = (double *)ws;
-    double *rd = (double *)((char *)ws + align256(sizeof(double) * (size_t)l2_blocks(n)));
-    int rc = hip_status(launch_l2(x, center, n, eps, out, part, rd, st));
-    double h = 0.0;
-    if (!rc) rc = hip_status(hipMemcpyAsync(&h, rd, sizeof h, hipMemcpyDeviceToHost, st));
+    HostBox box;
+    int rc = hip_status(box.status());
+    if (!rc) rc = hip_status(launch_l2(x, center, n, eps, out, part, box.as<double>(), st));
     if (!rc) rc = hip_status(hipStreamSynchronize(st));
-    if (!rc && r) *r = h;
+    if (!rc && r) *r = *box.as<double>();
     return rc;
 }
 

@@ -49,11 +49,6 @@ void *device_scratch(hipError_t *err)
     return g_scratch[dev];
 }
 
-__global__ void k_tau_out(const SelState *sel, double *tau)
-{
-    if (threadIdx.x == 0) *tau = sel->tau;
-}
-
 }  // namespace
 }  // namespace geo
 
@@ -72,10 +67,6 @@ extern "C" int geo_project_l1_noalloc(const float *x, int64_t n, double radius, 
     SelState *sel = (SelState *)ws;
     Hist *hist = (Hist *)(ws + kL1StateBytes);
     e = launch_l1_threshold(x, n, radius, sel, hist, st);
-    if (e == hipSuccess && n > 0) e = launch_soft(x, n, sel, out, st);
-    if (e == hipSuccess && tau_dev) {
-        hipLaunchKernelGGL(k_tau_out, dim3(1), dim3(64), 0, st, (const SelState *)sel, tau_dev);
-        e = hipGetLastError();
-    }
+    if (e == hipSuccess && (n > 0 || tau_dev)) e = launch_soft(x, n, sel, out, tau_dev, st);
     return geo_hip_status(e);
 }

@@ -436,7 +436,7 @@ __global__ __launch_bounds__(NT) void k_l2_partial(const float *x, const float *
 }
 
 __global__ __launch_bounds__(NT) void k_l2_apply(const float *x, const float *cc, int64_t n, double eps,
-                                                 const double *part, int nb, double *r, float *out)
+                                                 const double *part, int nb, double *r_out, float *out)
 {
     __shared__ double red[NT / 64], norm;
     double acc = 0.0;
@@ -444,7 +444,7 @@ __global__ __launch_bounds__(NT) void k_l2_apply(const float *x, const float *cc
     acc = block_sum<NT>(acc, red);
     if (threadIdx.x == 0) {
         norm = sqrt(acc);
-        if (blockIdx.x == 0) *r = norm;
+        if (blockIdx.x == 0) *r_out = norm;
     }
     __syncthreads();
     const double rr = norm;
@@ -553,11 +553,11 @@ hipError_t launch_apply_op(int op, int adjoint, const Dims &d, const float *in, 
 int l2_blocks(int64_t n) { return grid_for(n) > 1024 ? 1024 : grid_for(n); }
 
 hipError_t launch_l2(const float *x, const float *c, int64_t n, double eps, float *out, double *partials,
-                     double *r_dev, hipStream_t st)
+                     double *r_out, hipStream_t st)
 {
     const int nb = l2_blocks(n);
     hipLaunchKernelGGL(k_l2_partial, dim3(nb), dim3(NT), 0, st, x, c, n, partials);
-    hipLaunchKernelGGL(k_l2_apply, dim3(nb), dim3(NT), 0, st, x, c, n, eps, partials, nb, r_dev, out);
+    hipLaunchKernelGGL(k_l2_apply, dim3(nb), dim3(NT), 0, st, x, c, n, eps, partials, nb, r_out, out);
     return hipGetLastError();
 }
 

@@ -524,6 +524,16 @@ __global__ __launch_bounds__(kBeginThreads) void k_loaded(DevScalars *sc, Hist *
     }
 }
 
+constexpr int kReportThreads = 64;
+static_assert(sizeof(DevScalars) % 8 == 0, "copied by words of 8 bytes");
+__global__ __launch_bounds__(kReportThreads) void k_report(const char *table, int stride, uint64_t *out)
+{
+    const CubeCommon &cc = *(const CubeCommon *)(table + (size_t)blockIdx.x * stride);
+    constexpr int words = sizeof(DevScalars) / 8;
+    for (int q = threadIdx.x; q < words; q += kReportThreads)
+        out[blockIdx.x * words + q] = reinterpret_cast<const uint64_t *>(cc.sc)[q];
+}
+
 }  // namespace
 
 hipError_t launch_search(const void *table, int stride, int ncubes, hipStream_t st)
@@ -535,6 +545,12 @@ hipError_t launch_search(const void *table, int stride, int ncubes, hipStream_t 
 hipError_t launch_begin(const void *table, int stride, int ncubes, hipStream_t st)
 {
     hipLaunchKernelGGL(k_begin, dim3(ncubes), dim3(kBeginThreads), 0, st, (const char *)table, stride, ncubes);
+    return hipGetLastError();
+}
+
+hipError_t launch_report(const void *table, int stride, int ncubes, DevScalars *out, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_report, dim3(ncubes), dim3(kReportThreads), 0, st, (const char *)table, stride, (uint64_t *)out);
     return hipGetLastError();
 }
 

@@ -715,13 +715,15 @@ __global__ __launch_bounds__(kWinThreads) void k_select_window(const char *table
         }
 }
 
-__global__ __launch_bounds__(kSoftThreads) void k_soft(const float *x, int64_t n, const SelState *sel, float *out)
+__global__ __launch_bounds__(kSoftThreads) void k_soft(const float *x, int64_t n, const SelState *sel, float *out,
+                                                       double *tau_out)
 {
     const int64_t q0 = ((int64_t)blockIdx.x * kSoftUnroll * kSoftThreads + threadIdx.x) * 4;
     Quad v[kSoftUnroll];
 #pragma unroll
     for (int u = 0; u < kSoftUnroll; ++u) v[u] = ld_quad(x, q0 + 4 * u * kSoftThreads, n);
     const double tau = sel->tau;
+    if (tau_out && blockIdx.x == 0 && threadIdx.x == 0) *tau_out = tau;
 #pragma unroll
     for (int u = 0; u < kSoftUnroll; ++u) {
 #pragma unroll
@@ -757,10 +759,11 @@ hipError_t launch_l1_threshold(const float *x, int64_t n, double radius, SelStat
     return hipGetLastError();
 }
 
-hipError_t launch_soft(const float *x, int64_t n, const SelState *sel, float *out, hipStream_t st)
+hipError_t launch_soft(const float *x, int64_t n, const SelState *sel, float *out, double *tau_out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_soft, dim3(ceil_div(n, 4 * kSoftUnroll * kSoftThreads)), dim3(kSoftThreads), 0, st, x, n, sel,
-                       out);
+    // (a block for the threshold, if for nothing else)
+    const int blocks = n > 0 ? ceil_div(n, 4 * kSoftUnroll * kSoftThreads) : 1;
+    hipLaunchKernelGGL(k_soft, dim3(blocks), dim3(kSoftThreads), 0, st, x, n, sel, out, tau_out);
     return hipGetLastError();
 }
 

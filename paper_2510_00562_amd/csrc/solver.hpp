@@ -529,6 +529,8 @@ hipError_t launch_slot(const void *table, int dual_bytes, const LaunchShape &sh,
 hipError_t launch_begin(const void *table, int stride, int ncubes, hipStream_t st);
 hipError_t launch_search(const void *table, int stride, int ncubes, hipStream_t st);
 hipError_t launch_loaded(DevScalars *sc, Hist *hist, int var, hipStream_t st);
+// The scalars of every cube of a table, in order, into out (host memory too).
+hipError_t launch_report(const void *table, int stride, int ncubes, DevScalars *out, hipStream_t st);
 // out != null: copy the variable out (FP32); otherwise load it from in.
 hipError_t launch_state_io(const Dims &d, void *ws, const Layout &L, int var, const float *v,
                            float *out, const float *in, hipStream_t st);
@@ -539,7 +541,8 @@ int op_planes(int op, int adj, int *pin, int *pout);
 // Exact l1-ball threshold search (select.hip).
 hipError_t launch_l1_threshold(const float *x, int64_t n, double radius, SelState *sel,
                                Hist *hist, hipStream_t st);
-hipError_t launch_soft(const float *x, int64_t n, const SelState *sel, float *out, hipStream_t st);
+// tau_out (may be null): where the threshold goes (device or host memory)
+hipError_t launch_soft(const float *x, int64_t n, const SelState *sel, float *out, double *tau_out, hipStream_t st);
 // The solver's per-iteration search over a table of cubes (entries of
 // `stride` bytes, CubeCommon first): one block per (cube, field).
 // Extra blocks of the same launch stream sweep B's inputs through the
@@ -563,7 +566,7 @@ size_t var_workspace_bytes(int n1, int n2, int n3, int regularizer);
 hipError_t var_state_init(const Dims &d, const geo_params *p, const float *v, void *ws,
                           hipStream_t st);
 // n_iter iterations or fewer once the rule of eq. (28) holds; blocking;
-// fills *out with the device scalars. sweep_ms (may be null): GPU time of the
+// fills *out (host memory that the device reaches) with the device scalars. sweep_ms (may be null): GPU time of the
 // sweep over the call, from events around a sample of launches.
 hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws, int n_iter,
                     hipStream_t st, DevScalars *out, int *slots, double *sweep_ms = nullptr);
@@ -583,7 +586,7 @@ int geo_hip_status(hipError_t e);
 // Standalone projections (ops.hip).
 int l2_blocks(int64_t n);
 hipError_t launch_l2(const float *x, const float *c, int64_t n, double eps, float *out,
-                     double *partials, double *r_dev, hipStream_t st);
+                     double *partials, double *r_out, hipStream_t st);
 hipError_t launch_prox_l12(const float *xa, const float *xb, int64_t n, float gamma, float *oa,
                            float *ob, hipStream_t st);
 hipError_t launch_box(const float *x, int64_t n, float lo, float hi, float *out, hipStream_t st);

@@ -699,13 +699,13 @@ hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws
             if (e == hipSuccess) e = launch_search(table, stride, 1, st);
         }
         issued += batch;
-        if (e == hipSuccess) e = hipMemcpyAsync(out, a.sc, sizeof(DevScalars), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = launch_report(table, stride, 1, out, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         synced = e == hipSuccess;
         if (synced && (out->stop || (int)out->calls_iter >= n_iter)) break;
     }
     if (!synced && e == hipSuccess) {  // n_iter = 0
-        e = hipMemcpyAsync(out, a.sc, sizeof(DevScalars), hipMemcpyDeviceToHost, st);
+        e = launch_report(table, stride, 1, out, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
     }
     *slots = issued;
