@@ -314,6 +314,40 @@ __device__ __forceinline__ double wave_sum(double x)
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
+// Two values in, their sums over pairs of lanes out: the lower half of the lanes
+// (SWAP 32: lanes 0..31; 16: the even rows of 16) the sums of a, the upper half
+// those of b.
+template <int SWAP>
+__device__ __forceinline__ double sum_halves(double a, double b)
+{
+    const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+    auto swap = [](uint32_t p, uint32_t q) {
+        if constexpr (SWAP == 32) return __builtin_amdgcn_permlane32_swap(p, q, false, false);
+        else return __builtin_amdgcn_permlane16_swap(p, q, false, false);
+    };
+    const auto lo = swap((uint32_t)x, (uint32_t)y), hi = swap((uint32_t)(x >> 32), (uint32_t)(y >> 32));
+    return __longlong_as_double((long long)((uint64_t)hi[0] << 32 | lo[0])) +
+           __longlong_as_double((long long)((uint64_t)hi[1] << 32 | lo[1]));
+}
+// Sum over each half row of 8 lanes, in all of them.
+__device__ __forceinline__ double sum_half_row(double x)
+{
+    x += dpp_double<0x141, 0xf>(x);  // row_half_mirror
+    x += dpp_double<0xb1, 0xf>(x);   // quad_perm 1 0 3 2
+    x += dpp_double<0x4e, 0xf>(x);   // quad_perm 2 3 0 1
+    return x;
+}
+// Wavefront-wide sums of eight values at once: the lanes halve with each step,
+// so it takes 10 additions where eight sums by themselves take 48. Lane 8 h + 16 r
+// and the 7 after it get the sum of value 4 h + (r & 1) * 2 + (r >> 1).
+__device__ __forceinline__ double wave_sums8(const double (&x)[8])
+{
+    const double a = sum_halves<16>(sum_halves<32>(x[0], x[1]), sum_halves<32>(x[2], x[3]));
+    const double b = sum_halves<16>(sum_halves<32>(x[4], x[5]), sum_halves<32>(x[6], x[7]));
+    const bool h = (__lane_id() & 8) != 0;
+    return sum_half_row((h ? b : a) + dpp_double<0x128, 0xf>(h ? a : b));  // row_ror:8
+}
+
 // Block-wide sum for blocks of up to 1024 threads; result valid in thread 0.
 template <int NT>
 __device__ __forceinline__ double block_sum(double x, double *lds /* NT/64 */)

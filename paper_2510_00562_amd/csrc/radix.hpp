@@ -188,6 +188,55 @@ __device__ __forceinline__ void block_sums(double (&x)[K], double *red /* K * NT
         }
 }
 
+// What a sweep sums for the search of the next thresholds (search.hip), by
+// field: |z| above the window at the interval's centre (its slope in a4, how
+// many) and the values inside it; counts are per wavefront, in scalar registers.
+struct Gathered {
+    double sum[2] = {0.0, 0.0};
+    float slope[2] = {0.f, 0.f};
+    uint32_t cnt[2] = {0u, 0u}, inside[2] = {0u, 0u};
+};
+
+// The end of a sweep tile: the sums over the block of NT threads of x (the
+// stopping rule's du2, u2, r2) and of what the next search needs, to the tile's
+// partials. red: 10 NT / 64 words of 8 bytes. Every thread calls; the caller
+// needs no barrier after it if several stand before it writes red again. (Eleven
+// wavefront sums one after another and one thread that added them over the
+// wavefronts took 9 us of a tile's 16 beside its bands.)
+template <int NT>
+__device__ __forceinline__ void tile_sums(double du2, double u2, double r2, const Gathered &ga, double *red,
+                                          double *part, double *win0, double *win1)
+{
+    constexpr int NW = NT / 64;
+    static_assert(NW <= 16, "a row of lanes adds over the wavefronts");
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(red + 8 * NW);
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // (nothing below is worth a register before)
+    const int lane = tid & 63, wid = tid >> 6, row = lane >> 4, col = lane & 15;
+    const double x[8] = {du2, u2, r2, ga.sum[0], (double)ga.slope[0], ga.sum[1], (double)ga.slope[1], 0.0};
+    const double s = wave_sums8(x);
+    if ((lane & 7) == 0) red[((col >> 1) + (row & 1) * 2 + (row >> 1)) * NW + wid] = s;  // col >> 1: 0 or 4
+    if (lane == 0) {
+        cnt[wid] = ga.cnt[0];
+        cnt[NW + wid] = ga.inside[0];
+        cnt[2 * NW + wid] = ga.cnt[1];
+        cnt[3 * NW + wid] = ga.inside[1];
+    }
+    __syncthreads();
+    if (tid >= 64) return;
+    // over the wavefronts: row r takes values r and 4 + r and count r
+    const bool in = col < NW;
+    double a = in ? red[row * NW + col] : 0.0, b = in ? red[(4 + row) * NW + col] : 0.0;
+    double c = in ? (double)cnt[row * NW + col] : 0.0;
+    a = sum_half_row(a + dpp_double<0x128, 0xf>(a));
+    b = sum_half_row(b + dpp_double<0x128, 0xf>(b));
+    c = sum_half_row(c + dpp_double<0x128, 0xf>(c));
+    // count above, sum above, its slope in a4, count inside
+    if (col == 0) *(row < 3 ? part + row : win0 + 1) = a;
+    if (col == 1 && row < 3) *(row == 0 ? win0 + 2 : win1 + row) = b;
+    if (col == 2) *((row < 2 ? win0 : win1) + 3 * (row & 1)) = c;
+}
+
 // The scalars of a state at the initial point.
 __device__ inline void init_scalars(DevScalars *sc, double eps, double tol, double alpha, double beta, double gy4)
 {
@@ -230,15 +279,6 @@ __device__ __forceinline__ void wave_append(bool want, const T &val, T *slice, u
     const uint32_t off = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
     if (want && base + off < (uint32_t)capb) slice[base + off] = val;
 }
-
-// What a sweep sums for the search of the next thresholds (search.hip), by
-// field: |z| above the window at the interval's centre (its slope in a4, how
-// many) and the values inside it; counts are per wavefront, in scalar registers.
-struct Gathered {
-    double sum[2] = {0.0, 0.0};
-    float slope[2] = {0.f, 0.f};
-    uint32_t cnt[2] = {0u, 0u}, inside[2] = {0u, 0u};
-};
 
 // One value of the next search, z = x - g (e + a4 q), over the interval of a4.
 // in: the lane has a value. Every lane of the wavefront takes part.

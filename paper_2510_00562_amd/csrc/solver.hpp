@@ -286,7 +286,7 @@ inline int max_tiles(int n1, int n2, int n3)
 // the library, the bands per tile that a model of the sweep's time prefers over
 // 8 x 128 of the nominal chunk, by 3% or more. One workgroup per CU marches at a
 // time, so a round of at most `blocks` tiles takes
-//   bands * sqrt(4.7^2 + (P / 36900)^2) + 16 us,
+//   bands * sqrt(4.7^2 + (P / 36900)^2) + 12 us,
 // P the pixels in flight: 4.7 us of instructions a band (measured on 8K pixels),
 // the state streamed at the card's rate (8.5 us at 262144), and the tile's start
 // and end. A row of a tile that ends within a row of the cube costs 15 pixels
@@ -310,10 +310,10 @@ inline SweepGrid fitted_grid(int n1, int n2, int n3, int requested, int blocks)
         const double miss = whole ? 0.0 : (n2 % 32 == 0 && g.cols % 32 == 0) ? 0.0 : (n2 % 16 == 0 && g.cols % 16 == 0) ? 8.0 : 15.0;
         const double px = ((double)n1 * n2 + miss * n1 * g.tj) / (g.ti * g.tj);  // pixels moved per tile and band
         const int full = T / blocks, left = T % blocks;
-        const double round = kc * step(px * blocks) + 16.0;  // of a full chip
+        const double round = kc * step(px * blocks) + 12.0;  // of a full chip
         const double share = (double)T / blocks * round;
         if (requested > 0) return share;
-        return full * round + (left ? kc * step(px * left) + 16.0 : 0.0) + share;
+        return full * round + (left ? kc * step(px * left) + 12.0 : 0.0) + share;
     };
     // (the form whose geometry the compiler knows, for the widths that fill it)
     auto form = [&](int rows, int cols) { return rows == kTileRows && cols == kTileCols && n2 % kTileCols == 0 ? 0 : 1; };

@@ -103,8 +103,8 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
     // phases of a band (t+, q+, y3, y3 of the row above)
     __shared__ float sT[FUSED ? ST : 1];
     __shared__ float4 keep[FUSED ? NT : 1];
-    constexpr int NS = FUSED ? 11 : 8;  // FP64 partials of a tile
-    __shared__ double red[NS * (NT / 64)];
+    constexpr int NS = 8;  // FP64 partials of a tile
+    __shared__ double red[(FUSED ? 10 : NS) * (NT / 64)];
     __shared__ uint32_t ncand[2];
     __shared__ int tile0[kMaxBatch + 1];
 
@@ -114,8 +114,19 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
     // full list, a batch in which a few cubes still run would leave most
     // blocks without work). Every block reads the same flags, written before
     // this launch.
+    // A single cube needs no list.
     static_assert(kMaxBatch <= 64, "one wavefront scans the cubes");
-    if (threadIdx.x < 64) {
+    const bool many = sh.ncubes > 1;
+    if (!many) {
+        const const4<CubeCommon> &cc = ((const4<CubeArgs<DT>> *)cubes)->c;
+        DevScalars *sc = cc.sc;
+        const bool idle_now = idle(sc);
+        if (FUSED && blockIdx.x == 0 && threadIdx.x == 0) {
+            sc->view = {sc->in.a_lo, sc->in.a_hi, sc->in.a_c, idle_now ? 1u : 0u};
+            *slot_flags(cubes, 1) = 0u;
+        }
+        if (idle_now) return;
+    } else if (threadIdx.x < 64) {
         const int c = threadIdx.x;
         int x = c < sh.ncubes && cubes[c].c.g.shape == S && !idle(cubes[c].c.sc) ? cubes[c].c.ntiles : 0;
 #pragma unroll
@@ -135,19 +146,20 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
             if (c == 0) *slot_flags(cubes, sh.ncubes) = 0u;
         }
     }
-    __syncthreads();
+    if (many) __syncthreads();
     const int tid = threadIdx.x;
 
     for (int r = 0;; ++r) {
         // (the working cubes' tile count is read from LDS at each tile rather
         // than kept live through the march)
-        const int t = tile_at(blockIdx.x, sh.shape_grid[S], tile0[sh.ncubes], r);
+        const int t = tile_at(blockIdx.x, sh.shape_grid[S], many ? tile0[sh.ncubes] : ((const4<CubeArgs<DT>> *)cubes)->c.ntiles, r);
         if (t < 0) break;
         int cube = 0;
-        while (tile0[cube + 1] <= t) ++cube;
+        if (many)
+            while (tile0[cube + 1] <= t) ++cube;
         // uniform across the block: the cube's entry is read with scalar loads
         cube = __builtin_amdgcn_readfirstlane(cube);
-        const int lt = __builtin_amdgcn_readfirstlane(t - tile0[cube]);  // tile within the cube
+        const int lt = __builtin_amdgcn_readfirstlane(many ? t - tile0[cube] : t);  // tile within the cube
         const4<CubeArgs<DT>> &a = ((const4<CubeArgs<DT>> *)cubes)[cube];
         const4<DevScalars> &sc = *(const4<DevScalars> *)a.c.sc;  // this launch does not write what it reads of it
         // Each phase reads the pointers and windows it needs with scalar loads
@@ -549,38 +561,28 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
 #undef DST
         // the tile's FP64 partials: stopping sums; the residual's norm and the
         // values above the windows, or the window statistics of the search
-        const bool one = (tid & 63) == 0;
-        const int nt = a.c.ntiles;
+        fresh();
+        const int nt = ent->c.ntiles;
         if constexpr (FUSED) {
-            double acc[NS] = {du2, u2, r2,
-                              one ? (double)ga.cnt[0] : 0.0, ga.sum[0], (double)ga.slope[0],
-                              one ? (double)ga.inside[0] : 0.0,
-                              one ? (double)ga.cnt[1] : 0.0, ga.sum[1], (double)ga.slope[1],
-                              one ? (double)ga.inside[1] : 0.0};
-            block_sums<NS, NT>(acc, red);
-            if (tid == 0) {
-                for (int q = 0; q < 3; ++q) a.c.part[3 * lt + q] = acc[q];
-                for (int q = 0; q < 4; ++q) {
-                    a.c.winpart[4 * lt + q] = acc[3 + q];
-                    a.c.winpart[4 * (nt + lt) + q] = acc[7 + q];
-                }
-            }
+            tile_sums<NT>(du2, u2, r2, ga, red, ent->c.part + 3 * lt, ent->c.winpart + 4 * lt,
+                          ent->c.winpart + 4 * (nt + lt));
         } else {
+            const bool one = (tid & 63) == 0;
             double acc[NS] = {du2, u2, one ? (double)cnt[0] : 0.0, sum[0], all[0],
                               one ? (double)cnt[1] : 0.0, sum[1], all[1]};
             block_sums<NS, NT>(acc, red);
             if (tid == 0) {
-                a.c.part[2 * lt] = acc[0];
-                a.c.part[2 * lt + 1] = acc[1];
+                ent->c.part[2 * lt] = acc[0];
+                ent->c.part[2 * lt + 1] = acc[1];
                 for (int f = 0; f < 2; ++f)
-                    for (int q = 0; q < 3; ++q) a.c.winpart[((int64_t)f * nt + lt) * 3 + q] = acc[2 + 3 * f + q];
+                    for (int q = 0; q < 3; ++q) ent->c.winpart[((int64_t)f * nt + lt) * 3 + q] = acc[2 + 3 * f + q];
             }
         }
         if (tid == 0) {
-            a.c.ccount[lt] = ncand[0];
-            a.c.ccount[nt + lt] = ncand[1];
+            ent->c.ccount[lt] = ncand[0];
+            ent->c.ccount[nt + lt] = ncand[1];
         }
-        __syncthreads();  // red and ncand are reused by the next tile
+        if constexpr (!FUSED) __syncthreads();  // red is reused by the next tile
     }
 }
 

@@ -123,7 +123,7 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
     __shared__ float sU[2 * SU];             // u' by band parity
     __shared__ float sT[(TI + 2) * TJ];      // t' with the rows above and below
     __shared__ float4 keep[NT];              // t+, q+, y3, y3 of the row above
-    __shared__ double red[11 * (NT / 64)];
+    __shared__ double red[10 * (NT / 64)];
     __shared__ uint32_t ncand[2];
     const int tid = threadIdx.x, lane = tid & 63;
     // Each phase reads the pointers and the window with scalar loads of its own
@@ -380,18 +380,8 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
         } while (++k < ke);
     }
 
-    // the slot's FP64 partials
-    const bool one = lane == 0;
-    double acc[11] = {du2, u2, r2,
-                      one ? (double)ga.cnt[0] : 0.0, ga.sum[0], (double)ga.slope[0], one ? (double)ga.inside[0] : 0.0,
-                      one ? (double)ga.cnt[1] : 0.0, ga.sum[1], (double)ga.slope[1], one ? (double)ga.inside[1] : 0.0};
-    block_sums<11, NT>(acc, red);
+    tile_sums<NT>(du2, u2, r2, ga, red, a.part + 3 * slot, a.winpart + 4 * slot, a.winpart + 4 * (a.slots + slot));
     if (tid == 0) {
-        for (int q = 0; q < 3; ++q) a.part[3 * slot + q] = acc[q];
-        for (int q = 0; q < 4; ++q) {
-            a.winpart[4 * slot + q] = acc[3 + q];
-            a.winpart[4 * (a.slots + slot) + q] = acc[7 + q];
-        }
         a.ccount[slot] = ncand[0];
         a.ccount[a.slots + slot] = ncand[1];
     }
