@@ -340,7 +340,7 @@ static int run_cubes(int n, const geo_dims *dims, const geo_params *p, const flo
     for (int q = 0; q < kTileShapes; ++q)
         sh.shape_grid[q] = sh.shape_tiles[q] > 0 ? sweep_a_grid(L[0].dual_bytes, sh.shape_tiles[q]) : 0;
     // the entries, then the launch flags zeroed
-    std::vector<unsigned char> img(table_bytes(n), 0);
+    std::vector<unsigned char> img(table_image_bytes(n), 0);
     memcpy(img.data(), ent.data(), (size_t)n * sizeof(CubeEntry));
     int rc = hip_status(hipMemcpyAsync(table, img.data(), img.size(), hipMemcpyHostToDevice, st));
     if (!rc) rc = hip_status(launch_begin(table, (int)sizeof(CubeEntry), n, st));

@@ -393,16 +393,20 @@ __device__ inline void set_window(SelState &o, bool missed, double budget, doubl
 // field whose window missed takes its threshold from the slot's histogram
 // passes, and the window of the iteration after it follows from that.
 __host__ __device__ inline double window_budget(int64_t n);
-__device__ inline SelState resolved(const SelState &s, const FbRec *rec, int f, int64_t n)
+// r0, r1: the field's records of levels 0 and 1; last: of the level that ended it.
+__device__ inline SelState resolved(const SelState &s, const FbRec &r0, const FbRec &r1, const FbRec &last, int64_t n)
 {
-    if (s.done) return s;
     SelState o = s;
-    o.tau = fb_final(rec, f).tau;
-    o.dens = !rec[f].done && rec[2 + f].dens > 0.0 ? rec[2 + f].dens : rec[f].dens;
+    o.tau = last.tau;
+    o.dens = !r0.done && r1.dens > 0.0 ? r1.dens : r0.dens;
     o.done = 1u;
     o.full = 0u;
     set_window(o, true, window_budget(n), kWindowFill, true);
     return o;
+}
+__device__ inline SelState resolved(const SelState &s, const FbRec *rec, int f, int64_t n)
+{
+    return s.done ? s : resolved(s, rec[f], rec[2 + f], fb_final(rec, f), n);
 }
 
 // The interval in which the next a4 (y4 = a4 q) is expected, after a4 of this

@@ -458,6 +458,8 @@ __global__ __launch_bounds__(kBeginThreads) void k_begin(const char *table, int 
     const const4<CubeCommon> &cc = *(const4<CubeCommon> *)(table + (size_t)blockIdx.x * stride);
     DevScalars *sc = cc.sc;
     const double rad[2] = {cc.alpha, cc.beta};
+    if (blockIdx.x == 0)
+        for (int q = threadIdx.x; q < 3 * kFbMost; q += kBeginThreads) slot_flags(table, ncubes)[kFbClaimWord + q] = 0u;
     if (!cc.ahead) {  // the thresholds are searched within each iteration
         if (threadIdx.x == 0) {
             sc->tol = cc.tol;

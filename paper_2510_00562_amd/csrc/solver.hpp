@@ -476,7 +476,7 @@ struct LaunchShape {
     int b_kinds;      // sweep B forms present: 1 one or two columns per thread, 2 four
     int shape_tiles[kTileShapes];  // sweep A tiles of the cubes of each tile shape
     int shape_grid[kTileShapes];   // persistent blocks of the sweep A launch of each shape
-    int fb_grid;      // blocks of each fallback histogram pass
+    int fb_grid;      // blocks of the fallback histogram passes
 };
 
 // Columns per sweep B thread for a row length: four when it is a multiple of
@@ -490,14 +490,17 @@ struct CubeEntry {
 };
 static_assert(sizeof(CubeArgs<float>) == sizeof(CubeArgs<bf16>), "one table entry size");
 
-// Launch-wide words of a table, in the 512 bytes after its entries (the
-// table upload zeroes them). Word 0: set by the window search when some
-// threshold of the slot missed its window, cleared by the finalize; the
-// histogram passes leave at once when it is 0. Words 64 + c (their own
-// cache lines, touched only by atomics of system scope): blocks of the
-// running histogram pass done with cube c.
-constexpr size_t kTableFlagBytes = 512;
-constexpr int kFbCounterWord = 64;
+// Launch-wide words of a table, after its entries (the table upload zeroes the
+// first 512 bytes of them, the start of a call the rest). Word 0: set by the
+// window search when some threshold missed its window; the histogram passes
+// leave at once when it is 0. Word 1: launches of the passes so far. Words 32 + l
+// and 64 + c (touched only by atomics of system scope while the passes run): cubes
+// read back at radix level l, chunks of the running level done of cube c. From
+// word 128 on: the launch that last claimed chunk j of level l, at l kFbMost + j.
+constexpr size_t kTableZeroBytes = 512;
+constexpr int kFbReadyWord = 32, kFbCounterWord = 64, kFbClaimWord = 128;
+constexpr int kFbMost = 512;  // chunks (blocks) of the passes at most
+constexpr size_t kTableFlagBytes = (kFbClaimWord + 3 * kFbMost) * sizeof(uint32_t);
 __host__ __device__ inline size_t table_flags_offset(int ncubes)
 {
     return ((size_t)ncubes * sizeof(CubeEntry) + 255) & ~(size_t)255;
@@ -507,6 +510,15 @@ __host__ __device__ inline uint32_t *slot_flags(const void *table, int ncubes)
     return (uint32_t *)((char *)table + table_flags_offset(ncubes));
 }
 __host__ __device__ inline size_t table_bytes(int ncubes) { return table_flags_offset(ncubes) + kTableFlagBytes; }
+// what of a table is uploaded
+inline size_t table_image_bytes(int ncubes) { return table_flags_offset(ncubes) + kTableZeroBytes; }
+// By one thread of a launch after the passes: they are over.
+__device__ inline void passes_over(uint32_t *flags)
+{
+    flags[0] = 0u;
+    flags[1] += 1u;
+    for (int l = 0; l < 3; ++l) flags[kFbReadyWord + l] = 0u;
+}
 
 // ---- launchers (kernels in sweep.hip / select.hip / ops.hip) ----
 hipError_t launch_init(const Dims &d, const float *v, void *ws, const Layout &L, double eps,
@@ -552,11 +564,10 @@ hipError_t launch_select_window(const void *table, int stride, int ncubes, int p
 // Sweep B of the two-sweep form (sweep_b.hip).
 hipError_t launch_sweep_b(const void *table, const LaunchShape &sh, hipStream_t st);
 
-// The histogram pass of radix level `level` (0..2) for the thresholds whose
-// window missed in this slot (fallback.hip); a no-op when none did.
+// The histogram passes for the thresholds whose window missed (fallback.hip); a
+// no-op when none did.
 int fallback_grid();
-hipError_t launch_fallback(const void *table, int dual_bytes, const LaunchShape &sh, int level,
-                           hipStream_t st);
+hipError_t launch_fallback(const void *table, int dual_bytes, const LaunchShape &sh, hipStream_t st);
 
 // The comparison regularizers (variants.hip): problem (15) with SSTV or
 // HSSTV in place of GeoSSTV, with the same device scalars, histogram passes

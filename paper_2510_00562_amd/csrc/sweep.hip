@@ -2,7 +2,7 @@
 //
 // FP32 duals:
 //   passes   (fallback.hip): the thresholds tau_s, tau_t of this iteration
-//            whose search missed at the end of the last one; no-ops otherwise.
+//            whose search missed at the end of the last one; a no-op otherwise.
 //   sweep    (LDS-tiled): steps 1-14, with the thresholds and the factor
 //            a4 of y4 known from the end of the last iteration; the FP64 partial
 //            sums of the stopping rule (eq. (28)) and of the l2-ball distance of
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
         const bool idle_now = idle(sc);
         if (FUSED && blockIdx.x == 0 && threadIdx.x == 0) {
             sc->view = {sc->in.a_lo, sc->in.a_hi, sc->in.a_c, idle_now ? 1u : 0u};
-            *slot_flags(cubes, 1) = 0u;
+            passes_over(slot_flags(cubes, 1));
         }
         if (idle_now) return;
     } else if (threadIdx.x < 64) {
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
                 DevScalars *sc = cubes[c].c.sc;
                 sc->view = {sc->in.a_lo, sc->in.a_hi, sc->in.a_c, idle(sc) ? 1u : 0u};
             }
-            if (c == 0) *slot_flags(cubes, sh.ncubes) = 0u;
+            if (c == 0) passes_over(slot_flags(cubes, sh.ncubes));
         }
     }
     if (many) __syncthreads();
@@ -812,18 +812,11 @@ void cube_entry_t(CubeArgs<DT> *a, const Dims &d, const float *v, void *ws, cons
 
 constexpr int kPrefetchBlocks = 240;  // cache prefetch beside the search (BF16)
 
-hipError_t passes(const void *table, int dual_bytes, const LaunchShape &sh, hipStream_t st)
-{
-    hipError_t e = hipSuccess;
-    for (int level = 0; level < 3 && e == hipSuccess; ++level) e = launch_fallback(table, dual_bytes, sh, level, st);
-    return e;
-}
-
 hipError_t slot_fused(const void *table, const LaunchShape &sh, hipStream_t st, hipEvent_t *ev, int nev)
 {
     const CubeArgs<float> *cubes = (const CubeArgs<float> *)table;
     if (nev >= 4) (void)hipEventRecord(ev[0], st);
-    hipError_t e = passes(table, 4, sh, st);
+    hipError_t e = launch_fallback(table, 4, sh, st);
     if (e != hipSuccess) return e;
     if (nev >= 2) (void)hipEventRecord(ev[nev >= 4 ? 1 : 0], st);
     // one persistent launch per form present (each takes the tiles of its cubes)
@@ -845,7 +838,7 @@ hipError_t slot_two(const void *table, const LaunchShape &sh, hipStream_t st, hi
     hipLaunchKernelGGL((k_sweep<bf16, 0, false>), dim3(sh.shape_grid[0]), dim3(NT), 0, st, cubes, sh);
     if (nev >= 2) (void)hipEventRecord(ev[1], st);
     hipError_t e = launch_select_window(table, stride, sh.ncubes, kPrefetchBlocks, st);
-    if (e == hipSuccess) e = passes(table, 2, sh, st);
+    if (e == hipSuccess) e = launch_fallback(table, 2, sh, st);
     if (e != hipSuccess) return e;
     if (nev >= 4) (void)hipEventRecord(ev[2], st);
     e = launch_sweep_b(table, sh, st);

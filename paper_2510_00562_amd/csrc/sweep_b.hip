@@ -280,7 +280,7 @@ __global__ __launch_bounds__(NPT) void k_finalize(const char *table, int stride)
         for (int k = 0; k < kFinUnroll; ++k)
             if (b0 + k * NPT < blocks_b) r2 += x2[k];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *slot_flags(table, (int)gridDim.x) = 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) passes_over(slot_flags(table, (int)gridDim.x));
     if (skip) return;
     // a threshold found by this slot's histogram passes becomes the field's
     // search state, with the window of the next iteration sized by the

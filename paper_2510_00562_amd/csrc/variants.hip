@@ -135,7 +135,7 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
         // what the search of this slot reads of the state it rewrites; the
         // histogram passes are over
         args.sc->view = {args.sc->in.a_lo, args.sc->in.a_hi, args.sc->in.a_c, idle_now ? 1u : 0u};
-        *args.flags = 0u;
+        passes_over(args.flags);
     }
     if (idle_now) return;
     const const4<DevScalars> &sc = *(const4<DevScalars> *)args.sc;
@@ -654,7 +654,7 @@ hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws
     sh.fb_grid = fallback_grid();
     const bool buf = (uint64_t)d.n1 * (uint64_t)d.n2 < kVarPixels;
     // the table image, with its launch-wide flags zeroed
-    std::vector<unsigned char> img(table_bytes(1), 0);
+    std::vector<unsigned char> img(table_image_bytes(1), 0);
     var_table_entry(reinterpret_cast<CubeEntry *>(img.data()), a, L, ws, p, n_iter);
     hipError_t e = hipMemcpyAsync(table, img.data(), img.size(), hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = launch_begin(table, stride, 1, st);
@@ -675,7 +675,7 @@ hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws
     while (issued < n_iter && e == hipSuccess) {
         const int batch = n_iter - issued < every ? n_iter - issued : every;
         for (int it = issued; it < issued + batch && e == hipSuccess; ++it) {
-            for (int level = 0; level < 3 && e == hipSuccess; ++level) e = launch_fallback(table, 4, sh, level, st);
+            e = launch_fallback(table, 4, sh, st);
             if (e != hipSuccess) break;
             const bool timed = sweep_ms && (all || it % kTimedEvery == kTimedEvery - 1) &&
                                ne + 2 <= ev.size();
