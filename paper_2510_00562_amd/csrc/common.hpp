@@ -8,6 +8,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace geo {
 
 constexpr float kStepU = 1.0f / 13.0f;  // step sizes printed after eq. (24)
@@ -346,6 +348,37 @@ __device__ __forceinline__ double wave_sums8(const double (&x)[8])
     const double b = sum_halves<16>(sum_halves<32>(x[4], x[5]), sum_halves<32>(x[6], x[7]));
     const bool h = (__lane_id() & 8) != 0;
     return sum_half_row((h ? b : a) + dpp_double<0x128, 0xf>(h ? a : b));  // row_ror:8
+}
+
+// Wavefront-wide sums of two values: a's in lanes 0..31, b's in the others.
+__device__ __forceinline__ double wave_pair(double a, double b)
+{
+    const double x = sum_halves<32>(a, b), y = sum_halves<16>(x, x);
+    return sum_half_row(y + dpp_double<0x128, 0xf>(y));  // row_ror:8
+}
+// Wavefront-wide minimum (no NaN among the lanes), in every lane.
+__device__ __forceinline__ float wave_min(float x)
+{
+    auto dpp = [](float v, auto ctrl) {
+        return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), decltype(ctrl)::value,
+                                                                     0xf, 0xf, true));
+    };
+    x = fminf(x, dpp(x, std::integral_constant<int, 0x128>()));  // row_ror:8
+    x = fminf(x, dpp(x, std::integral_constant<int, 0x141>()));  // row_half_mirror
+    x = fminf(x, dpp(x, std::integral_constant<int, 0xb1>()));   // quad_perm 1 0 3 2
+    x = fminf(x, dpp(x, std::integral_constant<int, 0x4e>()));   // quad_perm 2 3 0 1
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fminf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fminf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+// The value of one lane, uniform.
+__device__ __forceinline__ double lane_double(double x, int lane)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
 }
 
 // Block-wide sum for blocks of up to 1024 threads; result valid in thread 0.

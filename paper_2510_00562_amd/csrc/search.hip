@@ -17,6 +17,8 @@
 // then searches each field's threshold: f(x) = sum max(|z| - x, 0) = radius
 // within the window. A window or an interval that missed leaves the field
 // pending for the histogram passes of the next launch slot (fallback.hip).
+#include <type_traits>
+
 #include "radix.hpp"
 
 namespace geo {
@@ -24,16 +26,21 @@ namespace geo {
 namespace {
 
 // What bounds this kernel is latency: it works on a few hundred tile partials
-// and a few thousand candidates in one block per field. 256 x 256 x 128, 4.6K
-// candidates: with 1024 threads and cross-lane sums through LDS 22 us (the
-// moves of 16 wavefronts queue on one LDS unit: 3.2 us for the first sums);
-// with 256 threads, straight-line loads (no branch around one, so that a
-// thread's 16 are in flight together) and sums by vector-unit moves 12 us with
-// 2.5K candidates, 31 us at 512 x 512 x 224 (8.9K); with 512 threads 13 and
-// 26 us, and 37 instead of 54 us for the widest windows of the first iterations.
+// and a few thousand candidates in one block per field. 256 x 256 x 128: with
+// 1024 threads and cross-lane sums through LDS 22 us (4.6K candidates; the moves
+// of 16 wavefronts queue on one LDS unit); with 256 threads, straight-line loads
+// (no branch around one, so that a thread's batch is in flight together) and sums
+// by vector-unit moves 12 us with 2.5K candidates, 31 us at 512 x 512 x 224
+// (8.9K); with 512 threads 13 and 26 us, and 37 instead of 54 us for the widest
+// windows of the first iterations. Then the partials' sums eight at a time, over
+// the wavefronts by lanes, batches of six candidates when there are few, and no
+// pass to see that nothing changed: 10 us (its first loads 2.6, sums and scan 1.1,
+// candidates 2.3, passes 2.5, windows 0.8), an iteration of 64 x 64 x 16 28.9 ->
+// 26.3 us, of 120 x 120 x 198 126.3 -> 124.1.
 constexpr int kSrThreads = 512;
 constexpr int kSrWaves = kSrThreads / 64;
 constexpr int kSrList = 32768;  // candidates held in LDS
+constexpr int kSrFew = 6;       // candidates of a thread that calm windows stay below
 constexpr int kSrSplit = 4;     // parts a streamed window is split into per round
 constexpr int kBeginThreads = 1024;
 
@@ -43,8 +50,14 @@ struct PassSum {
     double cnt, sum;
 };
 
-// Block sums of N pairs. buf: alternates between two
-// calls, so that one barrier each is enough.
+// Count and sum of the listed values above some point, and the least of them.
+struct Pass {
+    double cnt, sum;
+    float least;
+};
+
+// Block sums of N pairs. buf: alternates between two calls, so that one barrier
+// each is enough.
 template <int N>
 __device__ __forceinline__ void block_pairs(PassSum (&x)[N], PassSum (*buf)[kSrWaves])
 {
@@ -77,16 +90,18 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
     DevScalars *sc = cc.sc;
     __shared__ SelState s;
     __shared__ uint32_t was_pending;
-    __shared__ double wsum[7][kSrWaves];
+    __shared__ double wsum[8 * kSrWaves];
     __shared__ uint32_t wcnt[kSrWaves], wovf[kSrWaves];
     __shared__ uint32_t pre[kMaxTiles + 1];
     __shared__ float list[kSrList];
     __shared__ uint32_t nlist;
     __shared__ PassSum pbuf[2][kSrSplit + 2][kSrWaves];
+    __shared__ Pass pass_buf[2][kSrWaves];
 
     // every first read goes out together; an idle cube has read a few KB for
     // nothing
-    const DevScalars::View view = sc->view;
+    const float view_lo = sc->view.a_lo, view_hi = sc->view.a_hi, view_c = sc->view.a_c;
+    const uint32_t view_idle = sc->view.idle;
     const int nt = cc.ntiles;
     const uint32_t capt = (uint32_t)cc.capt;
     const int per = (nt + kSrThreads - 1) / kSrThreads;  // consecutive tiles of a thread
@@ -129,7 +144,7 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
             }
         }
     }
-    if (view.idle) return;
+    if (view_idle) return;
     // sums (a butterfly in each wavefront, then the wavefronts in order) and
     // the scan of the tiles' candidate counts
     uint32_t inc = mine;
@@ -138,15 +153,13 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
         const uint32_t y = (uint32_t)__shfl_up((int)inc, o, 64);
         if (lane >= o) inc += y;
     }
-#pragma unroll
-    for (int q = 0; q < 7; ++q) acc[q] = wave_sum(acc[q]);
+    const double all[8] = {acc[0], acc[1], acc[2], acc[3], acc[4], acc[5], acc[6], 0.0};
+    const double s8 = wave_sums8(all);  // lanes 16 r + 8 h: value 4 h + 2 (r & 1) + (r >> 1)
+    const int v8 = ((lane >> 3) & 1) * 4 + ((lane >> 4) & 1) * 2 + (lane >> 5);
     const bool any_ovf = __ballot(ovf != 0u) != 0ull;
     if (lane == 63) wcnt[wv] = inc;
-    if (lane == 0) {
-#pragma unroll
-        for (int q = 0; q < 7; ++q) wsum[q][wv] = acc[q];
-        wovf[wv] = any_ovf ? 1u : 0u;
-    }
+    if ((lane & 7) == 0) wsum[v8 * kSrWaves + wv] = s8;
+    if (lane == 0) wovf[wv] = any_ovf ? 1u : 0u;
     __syncthreads();
     uint32_t total = 0u, before = 0u, overflow = 0u;
 #pragma unroll
@@ -155,12 +168,11 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
         total += wcnt[w];
         overflow |= wovf[w];
     }
+    // (eight wavefronts: value q over them in lanes 8 q .. 8 q + 7)
+    static_assert(kSrWaves == 8, "a half row of lanes adds over the wavefronts");
+    const double tot = sum_half_row(wsum[lane]);
 #pragma unroll
-    for (int q = 0; q < 7; ++q) {
-        acc[q] = wsum[q][0];
-#pragma unroll
-        for (int w = 1; w < kSrWaves; ++w) acc[q] += wsum[q][w];
-    }
+    for (int q = 0; q < 7; ++q) acc[q] = lane_double(tot, 8 * q);
     {
         uint32_t at = before + inc - mine;
         for (int k = 0; k < per; ++k) {
@@ -178,7 +190,7 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
     const double a4d = gy4 * c4;
     const float a4 = (float)a4d;
     const float g = f ? cc.zt_step : 1.f;  // z = x - g (e + a4 q); e = 0 for s
-    const bool in_iv = a4 >= view.a_lo && a4 <= view.a_hi;
+    const bool in_iv = a4 >= view_lo && a4 <= view_hi;
     const double radius = s.radius;
     const bool won = s.win_on != 0u;
     const double lo = (double)s.win_lo, hi = (double)s.win_hi;
@@ -191,8 +203,8 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
     } else if (!won) {
         // inside the ball so far: S and Q are sum |z| at the two ends of the
         // interval, and sum |z| is convex in a4, so the chord bounds it
-        const double wd = (double)view.a_hi - (double)view.a_lo;
-        const double x = wd > 0.0 ? ((double)a4 - (double)view.a_lo) / wd : 0.0;
+        const double wd = (double)view_hi - (double)view_lo;
+        const double x = wd > 0.0 ? ((double)a4 - (double)view_lo) / wd : 0.0;
         const double bound = (1.0 - x) * acc[4] + x * acc[5];
         verdict = in_iv && bound * (1.0 + 1e-5) <= radius ? 1 : 2;
     } else if (!in_iv || overflow || (double)total > fmax((double)kSrList, 2.0 * window_budget(cc.d.plane))) {
@@ -200,7 +212,7 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
     }
     __syncthreads();  // pre complete
     // sum and count of the values above the window, at this a4
-    double Sh = acc[4] - ((double)a4 - (double)view.a_c) * (double)g * acc[5], Ch = acc[3];
+    double Sh = acc[4] - ((double)a4 - (double)view_c) * (double)g * acc[5], Ch = acc[3];
     if (verdict == 0) {
         // the values, below zmax = 64 hi, rounded to multiples of a unit of which
         // total * zmax is less than 2^52: with few candidates finer than the
@@ -222,32 +234,40 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
             // positions tid, tid + 256, ... of the tiles' slices one after
             // another, a batch of loads in flight; a thread reads back only what
             // it staged
-            constexpr int U = 16;
-            for (uint32_t p0 = (uint32_t)tid; p0 < total; p0 += U * kSrThreads) {
-                // (straight-line: positions past the end repeat the last one)
-                float4 c[U];
-                uint32_t p[U];
-                int a[U];
-#pragma unroll
-                for (int e = 0; e < U; ++e) {
-                    p[e] = p0 + e * kSrThreads < total ? p0 + e * kSrThreads : total - 1u;
-                    a[e] = 0;
-                }
-                // the last tile whose slice starts at or before p
-                for (int step = 1 << (31 - __clz(nt)); step > 0; step >>= 1)
+            // (a batch no larger than what there is: 2K candidates in batches of
+            // 16 a thread took 1 us longer)
+            auto stage = [&](auto batch) {
+                constexpr int U = decltype(batch)::value;
+                for (uint32_t p0 = (uint32_t)tid; p0 < total; p0 += U * kSrThreads) {
+                    // (straight-line: positions past the end repeat the last one)
+                    float4 c[U];
+                    uint32_t p[U];
+                    int a[U];
 #pragma unroll
                     for (int e = 0; e < U; ++e) {
-                        const int m = a[e] + step < nt ? a[e] + step : nt;  // pre[nt] = total
-                        a[e] = pre[m] <= p[e] ? m : a[e];
+                        p[e] = p0 + e * kSrThreads < total ? p0 + e * kSrThreads : total - 1u;
+                        a[e] = 0;
                     }
+                    // the last tile whose slice starts at or before p
+                    for (int step = 1 << (31 - __clz(nt)); step > 0; step >>= 1)
 #pragma unroll
-                for (int e = 0; e < U; ++e) c[e] = cand[(uint32_t)a[e] * capt + (p[e] - pre[a[e]])];
+                        for (int e = 0; e < U; ++e) {
+                            const int m = a[e] + step < nt ? a[e] + step : nt;  // pre[nt] = total
+                            a[e] = pre[m] <= p[e] ? m : a[e];
+                        }
 #pragma unroll
-                for (int e = 0; e < U; ++e) {
-                    const float z = eval(c[e]);
-                    if (p0 + e * kSrThreads < total) list[p0 + e * kSrThreads] = z;
+                    for (int e = 0; e < U; ++e) c[e] = cand[(uint32_t)a[e] * capt + (p[e] - pre[a[e]])];
+#pragma unroll
+                    for (int e = 0; e < U; ++e) {
+                        const float z = eval(c[e]);
+                        if (p0 + e * kSrThreads < total) list[p0 + e * kSrThreads] = z;
+                    }
                 }
-            }
+            };
+            if (total <= kSrFew * kSrThreads)
+                stage(std::integral_constant<int, kSrFew>());
+            else
+                stage(std::integral_constant<int, 16>());
         } else {
             // every candidate once: wavefront w takes tiles w, w + 4, ..., four
             // at a time, the lanes their entries
@@ -340,30 +360,45 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
             if (verdict == -1) verdict = 0;
         }
         if (verdict == 0) {
-            // count and sum of the listed values above t
+            // count and sum of the listed values above t, and the least of them
             auto pass = [&](double t) {
                 const float tf = __double2float_rd(t);
-                PassSum x[1] = {{0.0, 0.0}};
-                float n = 0.f;
-                for (uint32_t p0 = (uint32_t)tid; p0 < total; p0 += 8 * kSrThreads) {
-                    float z[8];
+                double sum = 0.0;
+                float n = 0.f, least = __int_as_float(0x7f800000);
+                for (uint32_t p0 = (uint32_t)tid; p0 < total; p0 += kSrFew * kSrThreads) {
+                    float z[kSrFew];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
+                    for (int e = 0; e < kSrFew; ++e) {
                         const uint32_t p = p0 + e * kSrThreads;
                         z[e] = list[p < total ? p : total - 1u];
                         z[e] = p < total ? z[e] : -1.f;
                     }
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
+                    for (int e = 0; e < kSrFew; ++e) {
                         n += z[e] > tf ? 1.f : 0.f;
-                        x[0].sum += z[e] > tf ? fixed(z[e]) : 0.0;
+                        sum += z[e] > tf ? fixed(z[e]) : 0.0;
+                        least = fminf(least, z[e] > tf ? z[e] : least);
                     }
                 }
-                x[0].cnt = (double)n;
-                if (wild) x[0].sum = __longlong_as_double(0x7ff8000000000000ll);  // NaN: no verdict below
-                block_pairs(x, pbuf[buf]);
+                if (wild) sum = __longlong_as_double(0x7ff8000000000000ll);  // NaN: no verdict below
+                // over the wavefront, then over the eight of them; the two buffers
+                // alternate, so that one barrier each is enough
+                const double s2 = wave_pair(sum, (double)n);
+                least = wave_min(least);
+                Pass *o = &pass_buf[buf][wv];
+                if (lane == 0) {
+                    o->sum = s2;
+                    o->least = least;
+                }
+                if (lane == 32) o->cnt = s2;
+                __syncthreads();
+                const Pass w = pass_buf[buf][lane & 7];
                 buf ^= 1;
-                return x[0];
+                Pass y;
+                y.sum = lane_double(sum_half_row(w.sum), 0);
+                y.cnt = lane_double(sum_half_row(w.cnt), 0);
+                y.least = wave_min(w.least);  // (the lanes repeat the eight)
+                return y;
             };
             // Newton's iteration on the convex decreasing f from the centre of
             // the range (the predicted threshold when the whole window is
@@ -378,7 +413,7 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
             tau = 0.5 * (wlo + whi);
             verdict = 2;
             for (int it = 0; it < 64 && tau <= whi; ++it) {
-                const PassSum y = pass(tau);
+                const Pass y = pass(tau);
                 const double Cn = Ch + y.cnt, Sn = Sh + y.sum;
                 if (Cn == C) {
                     verdict = 1;
@@ -400,7 +435,13 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
                 }
                 at_lo = false;
                 C = Cn;
+                // no value between here and there: the set above does not change
+                const bool same = tn >= tau && tn <= whi && !((double)y.least <= tn);
                 tau = tn;
+                if (same) {
+                    verdict = 1;
+                    break;
+                }
             }
             if (!(tau >= lo && tau <= hi)) verdict = 2;
         }
