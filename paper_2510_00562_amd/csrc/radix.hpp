@@ -316,6 +316,12 @@ __device__ __forceinline__ void gather_ahead(Gathered &o, const4<DevScalars::Swe
 constexpr double kWindowFill = 16384.0;
 constexpr double kWindowFillCalm = 2048.0;
 constexpr uint32_t kCalmNarrow = 8;
+// FP32 duals (the search of search.hip, whose time follows the candidates): 8192,
+// narrow after 6. From the initial point, 16384 and 8 before: 30 iterations of
+// 64 x 64 x 16 1145 -> 1074 us, 60 of 128 x 128 x 64 4350 -> 4236, of 120 x 120 x
+// 198 8370 -> 8347 with one miss more, of 256 x 256 x 128 19520 -> 19635 with two.
+constexpr double kAheadFill = 8192.0;
+constexpr uint32_t kAheadCalm = 6;
 
 // Window of |z| that sweep A collects for the next iteration. tau is
 // extrapolated from the last levels: quadratically once four are known (the
@@ -401,7 +407,7 @@ __device__ inline SelState resolved(const SelState &s, const FbRec &r0, const Fb
     o.dens = !r0.done && r1.dens > 0.0 ? r1.dens : r0.dens;
     o.done = 1u;
     o.full = 0u;
-    set_window(o, true, window_budget(n), kWindowFill, true);
+    set_window(o, true, window_budget(n), kAheadFill, true);
     return o;
 }
 __device__ inline SelState resolved(const SelState &s, const FbRec *rec, int f, int64_t n)
