@@ -6,14 +6,19 @@
 // The launch is a no-op (its blocks read one flag and leave) unless a search left
 // a field of some working cube pending. That takes 1.5 us, and with a launch for
 // each level there were three of them: an iteration of 64 x 64 x 16 took 31.8 us,
-// now 28.9, of 120 x 120 x 198 128.0, now 126.3. What bounds a level that works
-// is the state (20 bytes a voxel), the atomics on the global bins, and the
-// counter: 100 x 100 x 360 90 us for all three.
+// now 28.9, of 120 x 120 x 198 128.0, now 126.3.
+// What bounds a level that works (256 x 256 x 128, one field, 88 us for the three):
+// the state once, at level 0 (23 us; the values found there are kept for the next
+// levels, which take 8 and 6 us over them), then a chain of round trips beyond the
+// L2: the work and the claims 3 us, the atomics on the global bins 1 to 6, the
+// bins read back 3, the pick 3 to 5. From the state at each level and with the
+// claims in front of the work, 512 x 512 x 224 took 1.25 ms more over its first 16
+// misses, and 60 iterations of 100 x 100 x 360 10512 instead of 10422 us.
 // The voxels of the cubes with a pending field are split evenly into chunks, one
 // per block of the launch. A block takes its own chunk and then those whose block
 // has not come yet, reads z_s and z_t where sweep A stored them in this
-// iteration, or else evaluates them from the state exactly as sweep A does
-// (the same rounding operations, so the values are bit-identical), keeps the
+// iteration (BF16), or else evaluates them from the state exactly as the sweep
+// does (the same rounding operations, so the values are bit-identical), takes the
 // values whose higher bits match the bins the earlier levels chose, and adds
 // them to LDS histograms that are flushed into the cube's global histogram
 // of the level with integer atomics (order-free, exact). The last block to
@@ -87,13 +92,23 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
     __shared__ unsigned long long hm[2][kHistStage];
     __shared__ int64_t seg0[kMaxBatch + 1];  // first work index of each cube
     __shared__ uint32_t fmask[kMaxBatch];    // fields of each cube at this level
+    __shared__ uint32_t prefix[2][kMaxBatch];  // and the bits their earlier levels fixed
     __shared__ int last, active, mine, next;
+    __shared__ uint32_t mine0[kFbMost / 32];  // chunks of level 0 whose z this block stored
     static_assert(kMaxBatch <= 64, "one wavefront scans the cubes");
     const int tid = threadIdx.x;
     const int G = (int)gridDim.x;  // chunks
+    int64_t W0 = 0;                // voxels at level 0: as many later means the same cubes
+    if (tid < kFbMost / 32) mine0[tid] = 0u;
     for (int level = 0; level < 3; ++level) {
         uint32_t *claims = flags + kFbClaimWord + level * kFbMost;
         __syncthreads();
+        if (tid == 64) {
+            // this block's own chunk
+            mine = __hip_atomic_exchange(&claims[blockIdx.x], run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != run ? 1 : 0;
+            next = G;
+            if (level == 0 && mine) mine0[blockIdx.x >> 5] |= 1u << (blockIdx.x & 31);
+        }
         if (tid < 64) {
             const int c = tid;
             uint32_t m = 0u;
@@ -104,11 +119,14 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
                 // earlier levels decided it (a record is of this launch only if
                 // no level before it ended the search)
                 const FbRec *rec = cubes[c].c.rec;
-                if (!idle(sc))
-                    for (int f = 0; f < 2; ++f)
-                        if (!sc->sel[f].done && (level < 1 || !word_load(&rec[f].done)) &&
-                            (level < 2 || !word_load(&rec[2 + f].done)))
-                            m |= 1u << f;
+                uint32_t over[2] = {sc->sel[0].done, sc->sel[1].done};
+                if (level > 0)
+                    for (int f = 0; f < 2; ++f) {
+                        over[f] |= word_load(&rec[f].done);
+                        if (level > 1) over[f] |= word_load(&rec[2 + f].done);
+                        prefix[f][c] = word_load(&rec[(level - 1) * 2 + f].prefix);
+                    }
+                if (!idle(sc)) m = (over[0] ? 0u : 1u) | (over[1] ? 0u : 2u);
                 if (m) n = cubes[c].c.d.plane;
             }
             const int busy = (int)__popcll(__ballot(n > 0));
@@ -130,14 +148,10 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
         __syncthreads();
         const int64_t W = seg0[sh.ncubes];
         if (W == 0) return;
+        if (level == 0) W0 = W;
         const int shift = lvl_shift(level), pshift = shift + (level == 0 ? 11 : 10);
         const uint32_t bmask = (uint32_t)lvl_bins(level) - 1u;
         for (int j = (int)blockIdx.x; j < G;) {
-            if (tid == 0) {
-                mine = __hip_atomic_exchange(&claims[j], run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != run ? 1 : 0;
-                next = G;
-            }
-            __syncthreads();
             const int64_t lo = W * (int64_t)j / G, hi = W * (int64_t)(j + 1) / G;
             for (int c = 0; mine && c < sh.ncubes; ++c) {
                 const int64_t c0 = seg0[c], c1 = seg0[c + 1];
@@ -147,8 +161,7 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
                 const uint32_t m = fmask[c];
                 const bool act0 = m & 1u, act1 = m & 2u;
                 FbRec *rec = a.c.rec;
-                const uint32_t pre0 = level ? word_load(&rec[(level - 1) * 2].prefix) : 0u;
-                const uint32_t pre1 = level ? word_load(&rec[(level - 1) * 2 + 1].prefix) : 0u;
+                const uint32_t pre0 = level ? prefix[0][c] : 0u, pre1 = level ? prefix[1][c] : 0u;
                 for (int b = tid; b < 2 * kHistBins; b += kFbThreads) {
                     hc[b / kHistBins][b % kHistBins] = 0u;
                     hm[b / kHistBins][b % kHistBins] = 0ull;
@@ -160,9 +173,20 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
                     const int par = (int)(sc->iter & 1u);
                     const Side<DT> src = a.side[par];
                     const float a4 = (float)sc->a4, gt = a.c.zt_step;
-                    // z as sweep A stored it in this iteration, or evaluated again
-                    const float *zb = sc->zstore ? a.c.zbuf : nullptr;
+                    // z as it was stored, by sweep A (BF16) or by this block at level
+                    // 0 (FP32: on the side of the state that the coming sweep writes
+                    // whole), or evaluated again. A level over the same cubes has the
+                    // same chunks, and each thread reads what it wrote.
                     const uint32_t N = (uint32_t)d.plane;
+                    const float *zs = nullptr, *zt = nullptr;
+                    float *ws = nullptr, *wt = nullptr;  // to be stored
+                    if constexpr (sizeof(DT) == 2) {
+                        if (sc->zstore) zs = a.c.zbuf, zt = zs + N;
+                    } else if (level == 0) {
+                        ws = a.side[par ^ 1].y4, wt = a.side[par ^ 1].t;
+                    } else if (W == W0 && (mine0[j >> 5] >> (j & 31) & 1u)) {
+                        zs = a.side[par ^ 1].y4, zt = a.side[par ^ 1].t;
+                    }
                     const uint32_t q0 = (uint32_t)((lo > c0 ? lo : c0) - c0), q1 = (uint32_t)((hi < c1 ? hi : c1) - c0);
                     auto add = [&](int f, uint32_t pre, float z) {
                         const uint32_t p = abs_bits(z);
@@ -171,7 +195,7 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
                         atomicAdd(&hc[f][b], 1u);
                         atomicAdd(&hm[f][b], (unsigned long long)significand(p));
                     };
-                    if (zb) {
+                    if (zs) {
                         for (uint32_t q = q0 + (uint32_t)tid; q < q1; q += kFbUnrollZ * kFbThreads) {
                             float z0[kFbUnrollZ], z1[kFbUnrollZ];
 #pragma unroll
@@ -179,8 +203,8 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
                                 const uint32_t x = q + (uint32_t)(u * kFbThreads);
                                 z0[u] = z1[u] = 0.f;
                                 if (x < q1) {
-                                    if (act0) z0[u] = zb[x];
-                                    if (act1) z1[u] = zb[N + x];
+                                    if (act0) z0[u] = zs[x];
+                                    if (act1) z1[u] = zt[x];
                                 }
                             }
 #pragma unroll
@@ -211,10 +235,19 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
                         }
 #pragma unroll
                         for (int u = 0; u < kFbUnroll; ++u) {
-                            if (q + (uint32_t)(u * kFbThreads) >= q1) break;
+                            const uint32_t x = q + (uint32_t)(u * kFbThreads);
+                            if (x >= q1) break;
                             const float y4 = y4_of(y4s[u], a4);
-                            if (act0) add(0, pre0, zs_of(sv[u], y4));
-                            if (act1) add(1, pre1, zt_of(tv[u], y3m[u], y3c[u], y4, gt));
+                            if (act0) {
+                                const float z = zs_of(sv[u], y4);
+                                if (ws) ws[x] = z;
+                                add(0, pre0, z);
+                            }
+                            if (act1) {
+                                const float z = zt_of(tv[u], y3m[u], y3c[u], y4, gt);
+                                if (wt) wt[x] = z;
+                                add(1, pre1, z);
+                            }
                         }
                     }
                 }
@@ -322,6 +355,12 @@ __global__ __launch_bounds__(kFbThreads) void k_fb_hist(const CubeArgs<DT> *__re
                 if (word_load(&claims[q]) != run) atomicMin(&next, q);
             __syncthreads();
             j = next;
+            __syncthreads();
+            if (tid == 0 && j < G) {
+                mine = __hip_atomic_exchange(&claims[j], run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != run ? 1 : 0;
+                next = G;
+                if (level == 0 && mine) mine0[j >> 5] |= 1u << (j & 31);
+            }
             __syncthreads();
         }
         // every chunk is taken: wait for the level

@@ -57,7 +57,7 @@ __device__ __forceinline__ void radix_level_wave(const double *bs, const uint32_
     const int btop = nb - 1 - per * lane;
     // this lane's bins, top down
     double ls = 0.0, lc = 0.0;
-#pragma unroll 8
+#pragma unroll 16
     for (int q = 0; q < per; ++q) {
         ls += bs[bin_at(btop - q)];
         lc += (double)bc[bin_at(btop - q)];
@@ -76,31 +76,34 @@ __device__ __forceinline__ void radix_level_wave(const double *bs, const uint32_
     double es = __shfl_up(xs, 1, 64), ec = __shfl_up(xc, 1, 64);
     if (lane == 0) es = ec = 0.0;
     double S = pk.s_above + es, C = pk.c_above + ec;
-    const double allS = pk.s_above + __shfl(xs, 63, 64), allC = pk.c_above + __shfl(xc, 63, 64);
-    int mine = -1;
-    double mS = 0.0, mC = 0.0, mbs = 0.0, mbc = 0.0, mfb = 0.0;
+    const double allS = pk.s_above + lane_double(xs, 63), allC = pk.c_above + lane_double(xc, 63);
+    // down to the highest bin whose lower edge has f >= radius: S and C stay at the
+    // sums strictly above it. (Without a way out of the loop, which left each
+    // bin's reads to wait for the bin before.)
+    int mine = btop;
+    bool found = false;
+#pragma unroll 16
     for (int q = 0; q < per; ++q) {
         const int b = btop - q;
         const double vs = bs[bin_at(b)], vc = (double)bc[bin_at(b)];
         const float eb = __uint_as_float(base | ((uint32_t)b << shift));
-        const double fb = (S + vs) - (double)eb * (C + vc);
-        if (fb >= radius) {
-            mine = b;
-            mS = S;  // strictly above bin b
-            mC = C;
-            mbs = vs;
-            mbc = vc;
-            mfb = fb;
-            break;
-        }
-        S += vs;
-        C += vc;
+        found = found || (S + vs) - (double)eb * (C + vc) >= radius;
+        mine = found ? mine : b - 1;
+        S = found ? S : S + vs;
+        C = found ? C : C + vc;
     }
     // the highest qualifying bin sits in the lowest lane that has one
-    const unsigned long long hit = __ballot(mine >= 0);
-    int src;
+    const unsigned long long hit = __ballot(found);
+    double mS, mC, mbs, mbc, mfb;
+    int b;
     if (hit) {
-        src = __ffsll((long long)hit) - 1;
+        const int src = __builtin_amdgcn_readfirstlane(__ffsll((long long)hit) - 1);
+        b = __builtin_amdgcn_readlane(mine, src);
+        mS = lane_double(S, src);
+        mC = lane_double(C, src);
+        mbs = bs[bin_at(b)];
+        mbc = (double)bc[bin_at(b)];
+        mfb = (mS + mbs) - (double)__uint_as_float(base | ((uint32_t)b << shift)) * (mC + mbc);
     } else {
         if (level == 0) {
             // f(0) = sum |z| < radius: inside the ball
@@ -110,23 +113,14 @@ __device__ __forceinline__ void radix_level_wave(const double *bs, const uint32_
             return;
         }
         // FP64 rounding at the lower edge of a deeper range (f there is >=
-        // radius by the choice of the range): take bin 0, from the last lane
-        src = 63;
-        if (lane == 63) {
-            mine = 0;
-            mbs = bs[0];
-            mbc = (double)bc[0];
-            mS = allS - mbs;
-            mC = allC - mbc;
-            mfb = allS - (double)__uint_as_float(base) * allC;
-        }
+        // radius by the choice of the range): take bin 0
+        b = 0;
+        mbs = bs[0];
+        mbc = (double)bc[0];
+        mS = allS - mbs;
+        mC = allC - mbc;
+        mfb = allS - (double)__uint_as_float(base) * allC;
     }
-    const int b = __shfl(mine, src, 64);
-    mS = __shfl(mS, src, 64);
-    mC = __shfl(mC, src, 64);
-    mbs = __shfl(mbs, src, 64);
-    mbc = __shfl(mbc, src, 64);
-    mfb = __shfl(mfb, src, 64);
     const float eb = __uint_as_float(base | ((uint32_t)b << shift));
     if (level == 0) {
         // density of values around tau (sizes the next window); the top bin
