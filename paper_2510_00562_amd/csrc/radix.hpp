@@ -389,10 +389,32 @@ __device__ inline void set_window(SelState &o, bool missed, double budget, doubl
     o.tau_prev = tau;
 }
 
+// Candidate budget of a cube's window: what LDS holds with room for the
+// error of the density estimate (20K of the 28K), or for large cubes N/256,
+// a streamed search that costs well under the three histogram passes over
+// the field that a miss costs.
+__host__ __device__ inline double window_budget(int64_t n)
+{
+    const double b = (double)n / 256.0;
+    return b > 20480.0 ? b : 20480.0;
+}
+
+// FP32 duals: N/512 where N/256 is more than the 32768 that search.hip holds in
+// LDS: it streams what does not fit, on one CU, and the passes over all of them
+// cost less than they did and go with those of the other field. With N/256, the
+// first 24 iterations of 512 x 512 x 224 took 55.5 ms (16 missed windows, now 21:
+// 53.2; N/1024 24: 53.4; N/2048 30: 54.4). Less than 20480 (12288, 8192): 64 x 64 x
+// 16 1100 and 1133 instead of 1090 us, 120 x 120 x 198 8345 instead of 8297.
+__host__ __device__ inline double ahead_budget(int64_t n)
+{
+    const double most = (double)n / 512.0 > 32768.0 ? (double)n / 512.0 : 32768.0;
+    const double b = window_budget(n);
+    return b < most ? b : most;
+}
+
 // The search state of field f as this slot's sweep and search use it: a
 // field whose window missed takes its threshold from the slot's histogram
 // passes, and the window of the iteration after it follows from that.
-__host__ __device__ inline double window_budget(int64_t n);
 // r0, r1: the field's records of levels 0 and 1; last: of the level that ended it.
 __device__ inline SelState resolved(const SelState &s, const FbRec &r0, const FbRec &r1, const FbRec &last, int64_t n)
 {
@@ -401,7 +423,7 @@ __device__ inline SelState resolved(const SelState &s, const FbRec &r0, const Fb
     o.dens = !r0.done && r1.dens > 0.0 ? r1.dens : r0.dens;
     o.done = 1u;
     o.full = 0u;
-    set_window(o, true, window_budget(n), kAheadFill, true);
+    set_window(o, true, ahead_budget(n), kAheadFill, true);
     return o;
 }
 __device__ inline SelState resolved(const SelState &s, const FbRec *rec, int f, int64_t n)
@@ -449,16 +471,6 @@ __device__ inline void predict_a4(DevScalars *sc, const A4History &h, double gy4
     sc->a_prev[1] = h.p1;
     sc->a_prev[0] = a;
     sc->a_n = h.n < 3u ? h.n + 1u : 3u;
-}
-
-// Candidate budget of a cube's window: what LDS holds with room for the
-// error of the density estimate (20K of the 28K), or for large cubes N/256,
-// a streamed search that costs well under the three histogram passes over
-// the field that a miss costs.
-__host__ __device__ inline double window_budget(int64_t n)
-{
-    const double b = (double)n / 256.0;
-    return b > 20480.0 ? b : 20480.0;
 }
 
 }  // namespace geo

@@ -457,7 +457,7 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
             o.tau = tau;
             const double wdt = hi - lo;
             o.dens = won && wdt > 0.0 ? (double)n_in / wdt : 0.0;
-            set_window(o, false, window_budget(cc.d.plane), s.calm >= kAheadCalm ? kWindowFillCalm : kAheadFill,
+            set_window(o, false, ahead_budget(cc.d.plane), s.calm >= kAheadCalm ? kWindowFillCalm : kAheadFill,
                        true);
             o.calm = s.calm + 1u;
         } else {

@@ -294,7 +294,8 @@ inline int max_tiles(int n1, int n2, int n3)
 // width and tile are multiples of 16 or 32). To the cube's time alone the model
 // adds its share of a chip filled by many cubes, which finer tiles raise; with a
 // chunk asked for (as a batch does) that share decides.
-// Measured (N1 x N2 x N3, sweep, us): nominal tiles against those chosen
+// Measured (N1 x N2 x N3, sweep, us; with a tile's sums still in 16 us instead of
+// 12): nominal tiles against those chosen
 //   64 x 64 x 16     16 x 64, 8 bands    53.6   16 x 64, 1 band      20.8
 //   128 x 128 x 64   8 x 128, 8 bands    69.3   8 x 128, 4 bands     51.5
 //   120 x 120 x 198  8 x 128, 12 bands  117.0   the same (8 x 120: 113.2)

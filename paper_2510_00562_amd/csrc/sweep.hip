@@ -13,11 +13,13 @@
 //            the next thresholds.
 //
 // Every state word is read and written once per iteration (172 bytes per
-// voxel with FP32 duals). What bounds the sweep is HBM streaming: 290 us for
-// 256 x 256 x 128 and 2040 us for 512 x 512 x 224 are 4.97 and 4.95 TB/s on those
-// bytes, 0.94 of what a plain copy reaches. In two sweeps with the search
+// voxel with FP32 duals). What bounds the sweep is HBM streaming: 287 us for
+// 256 x 256 x 128 and 1866 us for 512 x 512 x 224 are 5.03 and 5.41 TB/s on those
+// bytes, 0.94 and more of what a plain copy reaches. In two sweeps with the search
 // between them (the second read s, t, y3, y4 and an intermediate again, 36
-// bytes) the iteration took 354 and 2350 us, now 313 and 2080.
+// bytes) the iteration took 354 and 2350 us, now 301 and 1898. Cubes of few tiles
+// are bound by the instructions of a band (4.7 us) and a tile's start and end
+// instead: 64 x 64 x 16 17 us.
 //
 // Two things let the loads of a band stay in flight for a whole band. They go
 // through the buffer path (common.hpp: band_of), so no branch stands between a
