@@ -82,6 +82,30 @@ __device__ __forceinline__ int tile_at(int b, int G, int T, int r)
     return t < T ? t : -1;
 }
 
+// The tiles of many cubes in one launch: each cube's are dealt to the XCDs in
+// contiguous eighths, and an XCD's blocks take its parts of one cube after another
+// in turn. Of the tiles before number P of the list, XCD x has those whose number
+// is x modulo 8, as many as it would have in turn, so the XCDs' shares differ by
+// one at most. (With the list as a whole in eighths, the cubes of a mixed batch met
+// different XCDs, and the XCDs with the deep tiles of a large cube kept the
+// launch: an iteration of 512 x 512 x 224 and 256 x 256 x 128 took 3123 us, now 2165;
+// of 256 x 256 x 128 and six of 128 x 128 x 64 1361, now 527; of 32 uneven cubes
+// 5170, now 4690.)
+struct TileList {
+    int x, first, step;  // XCD (< 0: the list is not split), a block's first position, to its next
+    __device__ __forceinline__ TileList(int b, int G)
+    {
+        const bool split = G >= 8 && (G & 7) == 0;
+        x = split ? b & 7 : -1;
+        first = split ? b >> 3 : b;
+        step = split ? G >> 3 : G;
+    }
+    // positions of this XCD before tile P of the list
+    __device__ __forceinline__ int before(int P) const { return x < 0 ? P : (P >> 3) + ((P & 7) > x ? 1 : 0); }
+    // positions of the XCDs before this one
+    __device__ __forceinline__ int below(int P) const { return x < 0 ? 0 : (P >> 3) * x + min(P & 7, x); }
+};
+
 // FUSED (FP32 duals): the whole iteration, thresholds known beforehand.
 // Otherwise (BF16 duals) the first of two sweeps: steps 1, 4, 5, 11, 12 and the
 // u' part of step 14, the inputs z_s, z_t of steps 2 and 3 with their window
@@ -154,14 +178,20 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
     for (int r = 0;; ++r) {
         // (the working cubes' tile count is read from LDS at each tile rather
         // than kept live through the march)
-        const int t = tile_at(blockIdx.x, sh.shape_grid[S], many ? tile0[sh.ncubes] : ((const4<CubeArgs<DT>> *)cubes)->c.ntiles, r);
-        if (t < 0) break;
-        int cube = 0;
-        if (many)
-            while (tile0[cube + 1] <= t) ++cube;
+        int cube = 0, lt;  // tile within the cube
+        if (many) {
+            const TileList list(blockIdx.x, sh.shape_grid[S]);
+            const int p = list.first + r * list.step;
+            if (p >= list.before(tile0[sh.ncubes])) break;
+            while (list.before(tile0[cube + 1]) <= p) ++cube;
+            lt = p - list.before(tile0[cube]) + list.below(tile0[cube + 1]) - list.below(tile0[cube]);
+        } else {
+            lt = tile_at(blockIdx.x, sh.shape_grid[S], ((const4<CubeArgs<DT>> *)cubes)->c.ntiles, r);
+            if (lt < 0) break;
+        }
         // uniform across the block: the cube's entry is read with scalar loads
         cube = __builtin_amdgcn_readfirstlane(cube);
-        const int lt = __builtin_amdgcn_readfirstlane(many ? t - tile0[cube] : t);  // tile within the cube
+        lt = __builtin_amdgcn_readfirstlane(lt);
         const4<CubeArgs<DT>> &a = ((const4<CubeArgs<DT>> *)cubes)[cube];
         const4<DevScalars> &sc = *(const4<DevScalars> *)a.c.sc;  // this launch does not write what it reads of it
         // Each phase reads the pointers and windows it needs with scalar loads
