@@ -28,9 +28,9 @@
 // above and below; the next bands' loads are in flight meanwhile (the buffer
 // path, common.hpp: band_of). In two kernels with the search between them, each
 // reading s, t, y3, y4 and y1, an iteration of 256 x 256 x 128 took 182 us (SSTV)
-// and 226 us (HSSTV2), now 132 and 166; of 64 x 64 x 16 45 us, now 31; of
-// 512 x 512 x 224 1165 and 1435 us, now 790 and 991 (the sweep alone 732 and
-// 936: 4.8 TB/s).
+// and 226 us (HSSTV2), now 121 and 157 (the sweep 109 and 143: 4.6 and 4.5 TB/s);
+// of 64 x 64 x 16 45 us, now 20 (SSTV); of 512 x 512 x 224 1165 and 1435 us, now
+// 773 and 973 (the sweep 728 and 930: 4.8 TB/s).
 #include <math.h>
 #include <string.h>
 

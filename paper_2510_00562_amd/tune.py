@@ -7,6 +7,9 @@ give more tiles to spread over the 256 compute units. The best depth depends
 on the cube sizes, so this tuner times a few candidates on the caller's own
 states, in steady state, and returns the fastest one. It uses only the C
 ABI (geo_batch_step) and leaves every state back at Alg. 1's initial point.
+The model that ranks the candidates counts the nominal tiles of
+geo_sweep_geometry; the library may fit a tile's pixels to the cube, which
+the timing sees.
 """
 from __future__ import annotations
 
