@@ -399,15 +399,17 @@ __host__ __device__ inline double window_budget(int64_t n)
     return b > 20480.0 ? b : 20480.0;
 }
 
-// FP32 duals: N/512 where N/256 is more than the 32768 that search.hip holds in
-// LDS: it streams what does not fit, on one CU, and the passes over all of them
-// cost less than they did and go with those of the other field. With N/256, the
-// first 24 iterations of 512 x 512 x 224 took 55.5 ms (16 missed windows, now 21:
-// 53.2; N/1024 24: 53.4; N/2048 30: 54.4). Less than 20480 (12288, 8192): 64 x 64 x
-// 16 1100 and 1133 instead of 1090 us, 120 x 120 x 198 8345 instead of 8297.
+// FP32 duals: less where N/256 would overflow the 32768 that search.hip holds in
+// LDS: 24576, room for the error of the estimate, or N/1024. It streams what does
+// not fit, on one CU, and the passes over all of them cost less than they did and
+// go with those of the other field. With N/256 the first 24 iterations of
+// 512 x 512 x 224 took 55.5 ms (16 missed windows, now 24: 53.4; N/2048 30: 54.4),
+// with 32768 or N/512 the first 30 of 2048 x 2048 x 4 26.7 ms, now 24.9, 25 of
+// 256 x 256 x 128 9280 us, now 9207. Less than 20480 for small cubes (12288, 8192):
+// 64 x 64 x 16 1100 and 1133 instead of 1090 us, 120 x 120 x 198 8345 instead of 8297.
 __host__ __device__ inline double ahead_budget(int64_t n)
 {
-    const double most = (double)n / 512.0 > 32768.0 ? (double)n / 512.0 : 32768.0;
+    const double most = (double)n / 1024.0 > 24576.0 ? (double)n / 1024.0 : 24576.0;
     const double b = window_budget(n);
     return b < most ? b : most;
 }
