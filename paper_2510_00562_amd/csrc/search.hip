@@ -269,26 +269,38 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
             else
                 stage(std::integral_constant<int, 16>());
         } else {
-            // every candidate once: wavefront w takes tiles w, w + 4, ..., four
-            // at a time, the lanes their entries
-            auto each = [&](auto fn) {
-                for (int b0 = 4 * wv; b0 < nt; b0 += 4 * kSrWaves) {
-                    uint32_t n[4], nm = 0u;
+            // every candidate once: L lanes a tile's entries, U x 64 / L tiles of a
+            // wavefront at a time. Many tiles of few entries (4096 of 15 in 4 bands of
+            // 2048 x 2048) take 8 lanes each: with a wavefront to a tile, four at a
+            // time, an SSTV iteration of 610 x 340 x 103 with 60K candidates took
+            // 675 us, now 503 to 530 (445 with few).
+            auto tiles = [&](auto lanes, auto loads, auto fn) {
+                constexpr int L = decltype(lanes)::value, U = decltype(loads)::value, G = 64 / L;
+                const int grp = lane / L;
+                for (int b0 = G * U * wv; b0 < nt; b0 += G * U * kSrWaves) {
+                    uint32_t n[U], nm = 0u;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        n[q] = b0 + q < nt ? pre[b0 + q + 1] - pre[b0 + q] : 0u;
+                    for (int q = 0; q < U; ++q) {
+                        const int b = b0 + q * G + grp;
+                        n[q] = b < nt ? pre[b + 1] - pre[b] : 0u;
                         nm = n[q] > nm ? n[q] : nm;
                     }
-                    for (uint32_t i = (uint32_t)lane; i < nm; i += 64) {
-                        float4 c[4];
+                    for (uint32_t i = (uint32_t)(lane & (L - 1)); i < nm; i += L) {
+                        float4 c[U];
 #pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            c[q] = cand[i < n[q] ? (uint32_t)(b0 + q) * capt + i : 0u];
+                        for (int q = 0; q < U; ++q)
+                            c[q] = cand[i < n[q] ? (uint32_t)(b0 + q * G + grp) * capt + i : 0u];
 #pragma unroll
-                        for (int q = 0; q < 4; ++q)
+                        for (int q = 0; q < U; ++q)
                             if (i < n[q]) fn(eval(c[q]));
                     }
                 }
+            };
+            auto each = [&](auto fn) {
+                if (total > 64u * (uint32_t)nt)
+                    tiles(std::integral_constant<int, 64>(), std::integral_constant<int, 4>(), fn);
+                else
+                    tiles(std::integral_constant<int, 8>(), std::integral_constant<int, 8>(), fn);
             };
             // Streamed: each round sums the values above kSrSplit points of the
             // range and keeps the part that holds tau, until what lies in it
