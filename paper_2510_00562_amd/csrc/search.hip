@@ -309,9 +309,11 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
                 PassSum x[kSrSplit + 1];
                 double th[kSrSplit + 1];
                 float tf[kSrSplit + 1];  // z > th as FP32: z above the last float at or below it
+                uint32_t above[kSrSplit + 1];
 #pragma unroll
                 for (int k = 0; k <= kSrSplit; ++k) {
                     x[k] = {0.0, 0.0};
+                    above[k] = 0u;
                     th[k] = k == kSrSplit ? whi : wlo + (whi - wlo) * ((double)k / kSrSplit);
                     tf[k] = __double2float_rd(th[k]);
                 }
@@ -319,7 +321,7 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
                     const double v = fixed(z);
 #pragma unroll
                     for (int k = 0; k <= kSrSplit; ++k) {
-                        x[k].cnt += z > tf[k] ? 1.0 : 0.0;
+                        above[k] += z > tf[k] ? 1u : 0u;
                         x[k].sum += z > tf[k] ? v : 0.0;
                     }
                 });
@@ -327,6 +329,8 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
                     verdict = 2;
                     break;
                 }
+#pragma unroll
+                for (int k = 0; k <= kSrSplit; ++k) x[k].cnt = (double)above[k];
                 block_pairs(x, pbuf[buf]);
                 buf ^= 1;
                 int best = -1;
