@@ -59,6 +59,12 @@ constexpr int kVarMinWaves = 6;
 // Bands of fewer pixels go through the buffer path (an 8-byte pair of any pixel
 // lies below the offset of a missing one); larger ones by 64-bit addresses.
 constexpr uint32_t kVarPixels = 1u << 27;
+// The index of a missing pixel: kNoPix for the buffer path, and with 64-bit
+// addresses, where a large band has a pixel of that index, one that none has
+// (N < 2^31).
+template <bool BUF>
+constexpr uint32_t kNone = BUF ? kNoPix : 0xffffffffu;
+static_assert(kVarPixels <= kNone<true> && 1u << 31 <= kNone<false>, "no pixel has the index of a missing one");
 
 struct VarArgs {
     Dims d;
@@ -79,7 +85,7 @@ struct VarArgs {
     int slots, per, capt;               // slots of the search, consecutive tiles of one, candidates of one
 };
 
-// Loads and stores of one band of an array at a pixel (kNoPix: none): through
+// Loads and stores of one band of an array at a pixel (kNone: none): through
 // the buffer path, or (bands of kVarPixels pixels and more) by 64-bit addresses.
 template <bool BUF, typename T>
 struct Band {
@@ -100,19 +106,19 @@ template <bool BUF>
 __device__ __forceinline__ float bget(const Band<BUF, const float> &b, uint32_t pix)
 {
     if constexpr (BUF) return bld((const float *)nullptr, b.r, pix);
-    else return b.any && pix != kNoPix ? b.p[pix] : 0.f;
+    else return b.any && pix != kNone<BUF> ? b.p[pix] : 0.f;
 }
 template <bool BUF>
 __device__ __forceinline__ float2 bget(const Band<BUF, const float2> &b, uint32_t pix)
 {
     if constexpr (BUF) return pair_of(bld_raw((const float2 *)nullptr, b.r, pix));
-    else return b.any && pix != kNoPix ? b.p[pix] : make_float2(0.f, 0.f);
+    else return b.any && pix != kNone<BUF> ? b.p[pix] : make_float2(0.f, 0.f);
 }
 template <bool BUF, typename T>
 __device__ __forceinline__ void bput(const Band<BUF, T> &b, uint32_t pix, T x)
 {
     if constexpr (BUF) bst_nt((const T *)nullptr, b.r, pix, x);
-    else if (b.any && pix != kNoPix) b.p[pix] = x;
+    else if (b.any && pix != kNone<BUF>) b.p[pix] = x;
 }
 
 // P: planes of y1 (2 SSTV, 4 HSSTV)
@@ -175,23 +181,23 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
         const int j0 = (t % a.tj) * TJ, i0 = (rest % a.ti) * TI, kb = (rest / a.ti) * a.kc;
         const int ke = min(kb + a.kc, n3);
         auto pixel = [&](int i, int j) {
-            return i >= 0 && i < n1 && j >= 0 && j < n2 ? (uint32_t)i * (uint32_t)n2 + (uint32_t)j : kNoPix;
+            return i >= 0 && i < n1 && j >= 0 && j < n2 ? (uint32_t)i * (uint32_t)n2 + (uint32_t)j : kNone<BUF>;
         };
         // (the pixel of the row above: 64-bit addresses need its bound checked,
         // the buffer path drops a negative offset)
         auto row_above = [&](uint32_t p, int i) {
-            return BUF ? p - (uint32_t)n2 : (p != kNoPix && i >= 1 ? p - (uint32_t)n2 : kNoPix);
+            return BUF ? p - (uint32_t)n2 : (p != kNone<BUF> && i >= 1 ? p - (uint32_t)n2 : kNone<BUF>);
         };
         const int oi = i0 + oti, oj = j0 + otj;
         const uint32_t po = pixel(oi, oj), pom = row_above(po, oi);
-        const bool own_in = po != kNoPix;
+        const bool own_in = po != kNone<BUF>;
         const int ri = i0 + rui, rj = j0 + ruj;
-        const uint32_t pr = ring_u || wave_t ? pixel(ri, rj) : kNoPix, prm = row_above(pr, ri);
+        const uint32_t pr = ring_u || wave_t ? pixel(ri, rj) : kNone<BUF>, prm = row_above(pr, ri);
         uint32_t py[NY];
 #pragma unroll
         for (int n = 0; n < NY; ++n) {
             const int p = tid + NT * n;
-            py[n] = p < S2 ? pixel(i0 - 1 + p / W2, j0 - 1 + p % W2) : kNoPix;
+            py[n] = p < S2 ? pixel(i0 - 1 + p / W2, j0 - 1 + p % W2) : kNone<BUF>;
         }
         const bool ei = oi <= n1 - 2, ej = oj <= n2 - 2;
 
