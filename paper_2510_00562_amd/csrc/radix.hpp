@@ -183,12 +183,28 @@ __device__ __forceinline__ void block_sums(double (&x)[K], double *red /* K * NT
 }
 
 // What a sweep sums for the search of the next thresholds (search.hip), by
-// field: |z| above the window at the interval's centre (its slope in a4, how
-// many) and the values inside it; counts are per wavefront, in scalar registers.
+// field: |z| above the window at the interval's centre, its slope in a4, how
+// many, and how many values are inside it; without a window, |z| at the two ends
+// of the interval. The sums are FP64 (a tile has up to thousands of bands: in FP32
+// a sum of 4096 equal values was low by 3.4e-5, more than the search's margin
+// between inside the ball and outside), counts are per wavefront, in scalar
+// registers.
 struct Gathered {
     double sum[2] = {0.0, 0.0};
-    float slope[2] = {0.f, 0.f};
     uint32_t cnt[2] = {0u, 0u}, inside[2] = {0u, 0u};
+};
+// The slope's sums of a thread: in registers, or (SSTV's sweep, whose 80
+// registers are all taken) in LDS words of its own.
+struct SlopeRegs {
+    double x[2] = {0.0, 0.0};
+    __device__ __forceinline__ void add(int f, double v) { x[f] += v; }
+    __device__ __forceinline__ double get(int f) const { return x[f]; }
+};
+template <int NT>
+struct SlopeLds {
+    __attribute__((address_space(3))) double *x;  // [2][NT], this thread's first
+    __device__ __forceinline__ void add(int f, double v) const { __builtin_amdgcn_ds_atomic_fadd_f64(x + f * NT, v); }
+    __device__ __forceinline__ double get(int f) const { return x[f * NT]; }
 };
 
 // The end of a sweep tile: the sums over the block of NT threads of x (the
@@ -197,8 +213,8 @@ struct Gathered {
 // needs no barrier after it if several stand before it writes red again. (Eleven
 // wavefront sums one after another and one thread that added them over the
 // wavefronts took 9 us of a tile's 16 beside its bands.)
-template <int NT>
-__device__ __forceinline__ void tile_sums(double du2, double u2, double r2, const Gathered &ga, double *red,
+template <int NT, typename Slope>
+__device__ __forceinline__ void tile_sums(double du2, double u2, double r2, const Gathered &ga, const Slope &sl, double *red,
                                           double *part, double *win0, double *win1)
 {
     constexpr int NW = NT / 64;
@@ -207,7 +223,7 @@ __device__ __forceinline__ void tile_sums(double du2, double u2, double r2, cons
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));  // (nothing below is worth a register before)
     const int lane = tid & 63, wid = tid >> 6, row = lane >> 4, col = lane & 15;
-    const double x[8] = {du2, u2, r2, ga.sum[0], (double)ga.slope[0], ga.sum[1], (double)ga.slope[1], 0.0};
+    const double x[8] = {du2, u2, r2, ga.sum[0], sl.get(0), ga.sum[1], sl.get(1), 0.0};
     const double s = wave_sums8(x);
     if ((lane & 7) == 0) red[((col >> 1) + (row & 1) * 2 + (row >> 1)) * NW + wid] = s;  // col >> 1: 0 or 4
     if (lane == 0) {
@@ -276,14 +292,15 @@ __device__ __forceinline__ void wave_append(bool want, const T &val, T *slice, u
 
 // One value of the next search, z = x - g (e + a4 q), over the interval of a4.
 // in: the lane has a value. Every lane of the wavefront takes part.
-__device__ __forceinline__ void gather_ahead(Gathered &o, const4<DevScalars::SweepIn> &w, int f, bool in, float x,
+template <typename Slope>
+__device__ __forceinline__ void gather_ahead(Gathered &o, Slope &sl, const4<DevScalars::SweepIn> &w, int f, bool in, float x,
                                              float e, float g, float q, float4 *slice, uint32_t *lds_count, int capt)
 {
     const float zl = zt_of(x, e, y4_of(q, w.a_lo), g), zh = zt_of(x, e, y4_of(q, w.a_hi), g);
     if (!w.on[f]) {
         // inside the ball so far: sum |z| at both ends
         o.sum[f] += in ? (double)fabsf(zl) : 0.0;
-        o.slope[f] += in ? fabsf(zh) : 0.f;
+        sl.add(f, in ? (double)fabsf(zh) : 0.0);
         return;
     }
     const float lo = w.lo[f], hi = w.hi[f];
@@ -294,7 +311,7 @@ __device__ __forceinline__ void gather_ahead(Gathered &o, const4<DevScalars::Swe
     o.cnt[f] += (uint32_t)__popcll(__ballot(above));
     o.inside[f] += (uint32_t)__popcll(__ballot(in && fabsf(zc) >= lo && fabsf(zc) <= hi));
     o.sum[f] += above ? (double)fabsf(zc) : 0.0;
-    o.slope[f] += above ? copysignf(1.f, zc) * q : 0.f;
+    sl.add(f, above ? (double)(copysignf(1.f, zc) * q) : 0.0);
     wave_append(in && !above && !below, make_float4(x, e, q, 0.f), slice, lds_count, capt);
 }
 

@@ -257,6 +257,7 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
         const bool zst = !FUSED && sc.zstore != 0u;
         double du2 = 0.0, u2 = 0.0, r2 = 0.0;
         Gathered ga;
+        SlopeRegs sl;
         // otherwise (by field): |z| above the window, sum and count (of the
         // wavefront), and sum of all |z|
         double sum[2] = {0.0, 0.0}, all[2] = {0.0, 0.0};
@@ -371,7 +372,7 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
         };
         // FUSED: one value of the next search, z = x - g (e + a4 q)
         auto gather = [&](int f, bool in, float x, float e, float g, float q) {
-            gather_ahead(ga, scp->in, f, in, x, e, g, q, ent->c.cand + ((int64_t)f * ent->c.ntiles + lt) * ent->c.capt,
+            gather_ahead(ga, sl, scp->in, f, in, x, e, g, q, ent->c.cand + ((int64_t)f * ent->c.ntiles + lt) * ent->c.capt,
                          &ncand[f], ent->c.capt);
         };
         // otherwise: one value of this slot's search
@@ -596,7 +597,7 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
         fresh();
         const int nt = ent->c.ntiles;
         if constexpr (FUSED) {
-            tile_sums<NT>(du2, u2, r2, ga, red, ent->c.part + 3 * lt, ent->c.winpart + 4 * lt,
+            tile_sums<NT>(du2, u2, r2, ga, sl, red, ent->c.part + 3 * lt, ent->c.winpart + 4 * lt,
                           ent->c.winpart + 4 * (nt + lt));
         } else {
             const bool one = (tid & 63) == 0;

@@ -130,6 +130,10 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
     __shared__ float sT[(TI + 2) * TJ];      // t' with the rows above and below
     __shared__ float4 keep[NT];              // t+, q+, y3, y3 of the row above
     __shared__ double red[10 * (NT / 64)];
+    // (SSTV: with these sums in registers the sweep spills and takes 2.3% longer;
+    // HSSTV: 8 KB more would leave room for two blocks per CU)
+    constexpr bool slope_lds = P == 2;
+    __shared__ double sSlope[slope_lds ? 2 * NT : 1];
     __shared__ uint32_t ncand[2];
     const int tid = threadIdx.x, lane = tid & 63;
     // Each phase reads the pointers and the window with scalar loads of its own
@@ -174,6 +178,11 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
     }
     double du2 = 0.0, u2 = 0.0, r2 = 0.0;
     Gathered ga;
+    std::conditional_t<slope_lds, SlopeLds<NT>, SlopeRegs> sl;
+    if constexpr (slope_lds) {
+        sl.x = (__attribute__((address_space(3))) double *)sSlope + tid;
+        sSlope[tid] = sSlope[NT + tid] = 0.0;
+    }
 
     const int t1 = min((slot + 1) * a.per, a.ti * a.tj * a.tk);
     for (int t = slot * a.per; t < t1; ++t) {
@@ -299,7 +308,7 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
             }
             if (ring_u)
                 su[rui * WU + ruj] = 2.f * u_at(k, yc, yp, rui, ruj, ri <= n1 - 2, rj <= n2 - 2, xu, xq) - xu;
-            if (own) gather_ahead(ga, scp->in, 0, wr, sn, 0.f, 1.f, qn, slice(0), &ncand[0], ap->capt);
+            if (own) gather_ahead(ga, sl, scp->in, 0, wr, sn, 0.f, 1.f, qn, slice(0), &ncand[0], ap->capt);
         };
         // y1+ of band k at the own point
         auto yphase = [&](int k, const float *yc) {
@@ -337,7 +346,7 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
             const float yc = ei ? __builtin_fmaf(ap->gy, sT[2 * TJ + tid] - tp, o.z) : o.z;
             bput(Band<BUF, float>(ap->y3[par ^ 1], k, np, true), po, yc);
             const float ym = oi >= 1 ? __builtin_fmaf(ap->gy, tp - sT[tid], o.w) : 0.f;
-            gather_ahead(ga, scp->in, 1, own_in, o.x, ym - (ei ? yc : 0.f), ap->gt, o.y, slice(1), &ncand[1], ap->capt);
+            gather_ahead(ga, sl, scp->in, 1, own_in, o.x, ym - (ei ? yc : 0.f), ap->gt, o.y, slice(1), &ncand[1], ap->capt);
         };
 
         // ---------------- march ----------------
@@ -386,7 +395,7 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
         } while (++k < ke);
     }
 
-    tile_sums<NT>(du2, u2, r2, ga, red, a.part + 3 * slot, a.winpart + 4 * slot, a.winpart + 4 * (a.slots + slot));
+    tile_sums<NT>(du2, u2, r2, ga, sl, red, a.part + 3 * slot, a.winpart + 4 * slot, a.winpart + 4 * (a.slots + slot));
     if (tid == 0) {
         a.ccount[slot] = ncand[0];
         a.ccount[a.slots + slot] = ncand[1];
