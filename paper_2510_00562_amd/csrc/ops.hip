@@ -9,6 +9,9 @@ namespace geo {
 namespace {
 
 constexpr int NT = kPointThreads;
+// Blocks of one launch: the threads of a launch number less than 2^32.
+constexpr uint32_t kGridMost = 1u << 23;
+static_assert((uint64_t)kGridMost * NT < 1ull << 32, "a launch of kGridMost blocks is valid");
 
 struct Cube {
     Dims d;
@@ -394,7 +397,7 @@ void launch_op(int adjoint, const Dims &d, const float *in, float *out, hipStrea
     const int64_t np = (int64_t)d.n1 * d.n2;
     const uint32_t bx = (uint32_t)((np + NT - 1) / NT);
     const uint32_t blocks = bx * (uint32_t)d.n3;  // at most N / NT + n3 < 2^32
-    const dim3 grid(blocks < 1u << 30 ? blocks : 1u << 30);
+    const dim3 grid(blocks < kGridMost ? blocks : kGridMost);
     if (adjoint)
         hipLaunchKernelGGL((k_op<OP, true>), grid, dim3(NT), 0, st, d, in, out, bx, blocks);
     else
