@@ -124,11 +124,11 @@ __device__ float lt_comp(const Cube &c, const float *w, int64_t N, int gmask, in
 }
 
 __global__ __launch_bounds__(NT) void k_apply(int op, int adj, Dims d, const float *in, float *out,
-                                              int out_planes)
+                                              int out_planes, int64_t g0)
 {
     const Cube c{d};
     const int64_t N = d.plane;
-    const int64_t g = (int64_t)blockIdx.x * NT + threadIdx.x;
+    const int64_t g = g0 + (int64_t)blockIdx.x * NT + threadIdx.x;
     if (g >= N * out_planes) return;
     const int pl = (int)(g / N);
     const int64_t q = g - (int64_t)pl * N;
@@ -192,7 +192,8 @@ __global__ __launch_bounds__(NT) void k_apply(int op, int adj, Dims d, const flo
 }
 
 // One thread per voxel and all of its output planes, for bands that the buffer
-// path takes (common.hpp: band_of; below kOpsPixels pixels). What bounds an
+// path takes (common.hpp: band_of; below kOpsPixels pixels) and that fill enough
+// of their blocks (fills_lanes below). What bounds an
 // operator is HBM (K: 21 planes, 84 bytes per voxel): every plane is read from
 // HBM once, the neighbours come from the caches, and a thread's loads (37 for K)
 // are in flight together. k_apply above, one thread per output element, decodes
@@ -391,6 +392,23 @@ __global__ __launch_bounds__(NT) void k_op(Dims d, const float *in, float *out, 
     }
 }
 
+// Whether one thread per voxel is the faster form for bands of np pixels. A band
+// takes whole blocks of it, so bands of few pixels leave lanes idle, and k_apply
+// has none: it took K on 100000 bands of one pixel from 141 us to 10. The line is
+// the share of lanes filled where the two meet, over bands of 16 to 400 pixels of
+// 4M and 30M voxels; the more planes an operator writes, the more often k_apply
+// decodes an index and reads its inputs again. Time of a thread per voxel over
+// that of k_apply:
+//   one plane out: share 0.56 D_s 1.08 to 1.20, D^T 0.93 to 0.98; 0.77 0.87, 0.72
+//   two: 0.32 D 1.09 to 1.28, L_ud 0.97 to 1.08; 0.39 D 0.90 to 1.04, L_ud 0.79 to 0.89
+//   six: 0.14 K 1.30 to 1.80, L 0.83 to 0.96; 0.25 K 0.77 to 1.08, L 0.48 to 0.57
+//   fifteen: 0.06 K^T 1.5 to 1.9; 0.14 0.80 to 1.05
+bool fills_lanes(int64_t np, int pout)
+{
+    const int64_t lanes = (np + NT - 1) / NT * NT;
+    return 16 * np >= lanes * (pout == 1 ? 10 : pout == 2 ? 6 : pout == 6 ? 4 : 2);
+}
+
 template <int OP>
 void launch_op(int adjoint, const Dims &d, const float *in, float *out, hipStream_t st)
 {
@@ -532,7 +550,8 @@ hipError_t launch_apply_op(int op, int adjoint, const Dims &d, const float *in, 
 {
     int pin, pout;
     if (op_planes(op, adjoint, &pin, &pout)) return hipErrorInvalidValue;
-    if ((uint64_t)d.n1 * (uint64_t)d.n2 < kOpsPixels) {
+    const int64_t np = (int64_t)d.n1 * d.n2;
+    if (np < kOpsPixels && fills_lanes(np, pout)) {
         switch (op) {
         case GEO_OP_DV: launch_op<GEO_OP_DV>(adjoint, d, in, out, st); break;
         case GEO_OP_DH: launch_op<GEO_OP_DH>(adjoint, d, in, out, st); break;
@@ -547,9 +566,13 @@ hipError_t launch_apply_op(int op, int adjoint, const Dims &d, const float *in, 
         }
         return hipGetLastError();
     }
-    const int64_t total = d.plane * pout;
-    hipLaunchKernelGGL(k_apply, dim3((unsigned)((total + NT - 1) / NT)), dim3(NT), 0, st, op,
-                       adjoint, d, in, out, pout);
+    // (in launches of kGridMost blocks: a loop in the kernel made it 1.4 times slower)
+    const int64_t total = d.plane * pout, most = (int64_t)kGridMost * NT;
+    for (int64_t g0 = 0; g0 < total; g0 += most) {
+        const int64_t n = total - g0 < most ? total - g0 : most;
+        hipLaunchKernelGGL(k_apply, dim3((unsigned)((n + NT - 1) / NT)), dim3(NT), 0, st, op, adjoint, d, in, out, pout,
+                           g0);
+    }
     return hipGetLastError();
 }
 
