@@ -9,10 +9,6 @@ namespace geo {
 namespace {
 
 constexpr int NT = kPointThreads;
-// Blocks of one launch: the threads of a launch number less than 2^32.
-constexpr uint32_t kGridMost = 1u << 23;
-static_assert((uint64_t)kGridMost * NT < 1ull << 32, "a launch of kGridMost blocks is valid");
-
 struct Cube {
     Dims d;
     __device__ __forceinline__ bool in(int k, int i, int j) const
@@ -526,6 +522,8 @@ __global__ __launch_bounds__(NT) void k_box(const float *x, int64_t n, float lo,
     }
 }
 
+// One launch takes kPointMost values (kGridMost blocks' worth); more go in several.
+constexpr int64_t kPointMost = (int64_t)kGridMost * 4 * kPointUnroll * NT;
 unsigned point_grid(int64_t n) { return (unsigned)((n + 4 * kPointUnroll * NT - 1) / (4 * kPointUnroll * NT)); }
 
 int grid_for(int64_t n)
@@ -590,13 +588,19 @@ hipError_t launch_l2(const float *x, const float *c, int64_t n, double eps, floa
 hipError_t launch_prox_l12(const float *xa, const float *xb, int64_t n, float gamma, float *oa, float *ob,
                            hipStream_t st)
 {
-    hipLaunchKernelGGL(k_prox_l12, dim3(point_grid(n)), dim3(NT), 0, st, xa, xb, n, gamma, oa, ob);
+    for (int64_t q = 0; q < n; q += kPointMost) {
+        const int64_t m = n - q < kPointMost ? n - q : kPointMost;
+        hipLaunchKernelGGL(k_prox_l12, dim3(point_grid(m)), dim3(NT), 0, st, xa + q, xb + q, m, gamma, oa + q, ob + q);
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_box(const float *x, int64_t n, float lo, float hi, float *out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_box, dim3(point_grid(n)), dim3(NT), 0, st, x, n, lo, hi, out);
+    for (int64_t q = 0; q < n; q += kPointMost) {
+        const int64_t m = n - q < kPointMost ? n - q : kPointMost;
+        hipLaunchKernelGGL(k_box, dim3(point_grid(m)), dim3(NT), 0, st, x + q, m, lo, hi, out + q);
+    }
     return hipGetLastError();
 }
 

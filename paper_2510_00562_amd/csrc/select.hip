@@ -761,9 +761,15 @@ hipError_t launch_l1_threshold(const float *x, int64_t n, double radius, SelStat
 
 hipError_t launch_soft(const float *x, int64_t n, const SelState *sel, float *out, double *tau_out, hipStream_t st)
 {
-    // (a block for the threshold, if for nothing else)
-    const int blocks = n > 0 ? ceil_div(n, 4 * kSoftUnroll * kSoftThreads) : 1;
-    hipLaunchKernelGGL(k_soft, dim3(blocks), dim3(kSoftThreads), 0, st, x, n, sel, out, tau_out);
+    // (a block for the threshold, if for nothing else; more values than one launch
+    // takes go in several)
+    static_assert(kSoftThreads <= kPointThreads, "kGridMost blocks are a valid launch");
+    constexpr int64_t per = 4 * kSoftUnroll * kSoftThreads, most = kGridMost * per;
+    for (int64_t q = 0; q == 0 || q < n; q += most) {
+        const int64_t m = n - q < most ? n - q : most;
+        const int blocks = m > 0 ? ceil_div(m, per) : 1;
+        hipLaunchKernelGGL(k_soft, dim3(blocks), dim3(kSoftThreads), 0, st, x + q, m, sel, out + q, tau_out);
+    }
     return hipGetLastError();
 }
 

@@ -174,6 +174,9 @@ constexpr int kMaxTiles = 4096;      // tiles of one cube (slices of its search)
 constexpr int kFitTiles = 512;       // that any workspace has room for
 constexpr int kMaxBatch = 64;        // cubes of one batched launch
 constexpr int kPointThreads = 256;
+// Blocks of kPointThreads of one launch at most: its threads number less than 2^32.
+constexpr uint32_t kGridMost = 1u << 23;
+static_assert((uint64_t)kGridMost * kPointThreads < 1ull << 32, "a launch of kGridMost blocks is valid");
 constexpr int kSweepBBlocks = 2048;  // grid-stride blocks of sweep B per cube
 constexpr int kSweepBRows = 2;       // rows of a sweep B strip
 constexpr int kTimedEvery = 8;  // geo_step_timed: events around every 8th sweep A
