@@ -59,39 +59,53 @@ Layout make_layout(int n1, int n2, int n3, int dual_storage)
 }
 
 namespace {
-std::mutex g_box_mu;
-std::vector<void *> g_boxes;  // free boxes, kept until the process ends
 constexpr size_t kBoxesKept = 16;
+std::mutex g_box_mu;
+void *g_boxes[kBoxesKept];  // free boxes, kept until the process ends
+size_t g_nboxes = 0;
+
+// While one lives, allocations and frees of this thread disturb no capture (this
+// thread's or another's).
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
 }  // namespace
 
-HostBox::HostBox()
+HostBox::HostBox(hipStream_t st) : st_(st)
 {
     {
         std::lock_guard<std::mutex> lock(g_box_mu);
-        if (!g_boxes.empty()) {
-            p_ = g_boxes.back();
-            g_boxes.pop_back();
+        if (g_nboxes > 0) {
+            p_ = g_boxes[--g_nboxes];
             return;
         }
     }
-    // (another thread may be capturing a graph)
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    const RelaxedCapture relaxed;
     status_ = hipHostMalloc(&p_, kBytes, hipHostMallocPortable | hipHostMallocMapped);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
     if (status_ != hipSuccess) p_ = nullptr;
+}
+
+hipError_t HostBox::wait()
+{
+    const hipError_t e = hipStreamSynchronize(st_);
+    if (e == hipSuccess) used_ = false;
+    return e;
 }
 
 HostBox::~HostBox()
 {
     if (!p_) return;
-    {
+    // (where even the wait fails nothing runs any more: the memory is freed)
+    if (!used_ || wait() == hipSuccess) {
         std::lock_guard<std::mutex> lock(g_box_mu);
-        if (g_boxes.size() < kBoxesKept) {
-            g_boxes.push_back(p_);
+        if (g_nboxes < kBoxesKept) {
+            g_boxes[g_nboxes++] = p_;
             return;
         }
     }
+    const RelaxedCapture relaxed;
     (void)hipHostFree(p_);
 }
 
@@ -214,10 +228,10 @@ int var_step_impl(geo_dims dims, const geo_params *p, const float *v, void *ws, 
 {
     int rc = check_var_ws(dims, p, ws, ws_bytes);
     if (rc) return rc;
-    HostBox box;
+    HostBox box(st);
     int slots = 0;
     rc = hip_status(box.status());
-    if (!rc) rc = hip_status(var_step(to_dims(dims), p, v, ws, n_iter, st, box.as<DevScalars>(), &slots, sweep_ms));
+    if (!rc) rc = hip_status(var_step(to_dims(dims), p, v, ws, n_iter, st, box, &slots, sweep_ms));
     if (rc) return rc;
     const DevScalars &x = *box.as<DevScalars>();
     const int own = x.nonfinite ? GEO_ENONFINITE : (p->tol > 0.0 && !x.stop ? GEO_MAXITER : GEO_OK);
@@ -391,7 +405,7 @@ static int run_cubes(int n, const geo_dims *dims, const geo_params *p, const flo
         }
     }
 
-    HostBox box;
+    HostBox box(st);
     if (!rc) rc = hip_status(box.status());
     DevScalars *const sc = box.as<DevScalars>();
     std::vector<hipEvent_t> ev;
@@ -418,8 +432,11 @@ static int run_cubes(int n, const geo_dims *dims, const geo_params *p, const flo
         }
         slots += batch;
         sampled += nsamp;
-        if (!rc) rc = hip_status(launch_report(table, (int)sizeof(CubeEntry), n, sc, st));
-        if (!rc) rc = hip_status(hipStreamSynchronize(st));
+        if (!rc) {
+            box.use();
+            rc = hip_status(launch_report(table, (int)sizeof(CubeEntry), n, sc, st));
+        }
+        if (!rc) rc = hip_status(box.wait());
         if (!rc && phase_ms)
             for (int q = 0; q < nsamp && !rc; ++q)
                 for (int ph = 0; ph < nph && !rc; ++ph) {
@@ -652,10 +669,13 @@ int geo_project_l1(const float *x, int64_t n, double radius, float *out, double 
     SelState *sel = (SelState *)ws;
     Hist *hist = (Hist *)((char *)ws + align256(sizeof(SelState)));
     int rc = hip_status(launch_l1_threshold(x, n, radius, sel, hist, st));
-    HostBox box;
+    HostBox box(st);
     if (!rc) rc = hip_status(box.status());
-    if (!rc) rc = hip_status(launch_soft(x, n, sel, out, box.as<double>(), st));
-    if (!rc) rc = hip_status(hipStreamSynchronize(st));
+    if (!rc) {
+        box.use();
+        rc = hip_status(launch_soft(x, n, sel, out, box.as<double>(), st));
+    }
+    if (!rc) rc = hip_status(box.wait());
     if (!rc && tau) *tau = *box.as<double>();
     return rc;
 }
@@ -676,10 +696,13 @@ int geo_project_l2(const float *x, const float *center, int64_t n, double eps, f
     if (!ws || ((uintptr_t)ws & 255u) || ws_bytes < need) return GEO_EWORKSPACE;
     const hipStream_t st = S(stream);
     double *part = (double *)ws;
-    HostBox box;
+    HostBox box(st);
     int rc = hip_status(box.status());
-    if (!rc) rc = hip_status(launch_l2(x, center, n, eps, out, part, box.as<double>(), st));
-    if (!rc) rc = hip_status(hipStreamSynchronize(st));
+    if (!rc) {
+        box.use();
+        rc = hip_status(launch_l2(x, center, n, eps, out, part, box.as<double>(), st));
+    }
+    if (!rc) rc = hip_status(box.wait());
     if (!rc && r) *r = *box.as<double>();
     return rc;
 }

@@ -581,10 +581,11 @@ size_t var_workspace_bytes(int n1, int n2, int n3, int regularizer);
 hipError_t var_state_init(const Dims &d, const geo_params *p, const float *v, void *ws,
                           hipStream_t st);
 // n_iter iterations or fewer once the rule of eq. (28) holds; blocking;
-// fills *out (host memory that the device reaches) with the device scalars. sweep_ms (may be null): GPU time of the
+// fills the box with the device scalars. sweep_ms (may be null): GPU time of the
 // sweep over the call, from events around a sample of launches.
+class HostBox;  // host_box.hpp
 hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws, int n_iter,
-                    hipStream_t st, DevScalars *out, int *slots, double *sweep_ms = nullptr);
+                    hipStream_t st, HostBox &box, int *slots, double *sweep_ms = nullptr);
 // out != null: copy the variable out; otherwise load it from in.
 hipError_t var_state_io(const Dims &d, const geo_params *p, void *ws, int var, float *out,
                         const float *in, hipStream_t st);

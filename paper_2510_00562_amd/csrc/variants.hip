@@ -36,6 +36,7 @@
 
 #include <vector>
 
+#include "host_box.hpp"
 #include "radix.hpp"
 
 namespace geo {
@@ -657,8 +658,9 @@ hipError_t var_state_init(const Dims &d, const geo_params *p, const float *v, vo
 }
 
 hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws, int n_iter,
-                    hipStream_t st, DevScalars *out, int *slots, double *sweep_ms)
+                    hipStream_t st, HostBox &box, int *slots, double *sweep_ms)
 {
+    DevScalars *const out = box.as<DevScalars>();
     VarLayout L;
     const VarArgs a = var_args(d, p, v, ws, &L);
     void *table = (char *)ws + L.table;
@@ -704,14 +706,18 @@ hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws
             if (e == hipSuccess) e = launch_search(table, stride, 1, st);
         }
         issued += batch;
-        if (e == hipSuccess) e = launch_report(table, stride, 1, out, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e == hipSuccess) {
+            box.use();
+            e = launch_report(table, stride, 1, out, st);
+        }
+        if (e == hipSuccess) e = box.wait();
         synced = e == hipSuccess;
         if (synced && (out->stop || (int)out->calls_iter >= n_iter)) break;
     }
     if (!synced && e == hipSuccess) {  // n_iter = 0
+        box.use();
         e = launch_report(table, stride, 1, out, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e == hipSuccess) e = box.wait();
     }
     *slots = issued;
     if (e == hipSuccess && sweep_ms) {
