@@ -23,7 +23,7 @@
 //
 // What bounds the sweep is HBM: 60 bytes per voxel (SSTV: 7 state words each
 // way and v) or 76 (HSSTV). A workgroup owns an 8 x 64 pixel tile and marches
-// through a chunk of bands; y1 is staged in LDS with a 1-pixel halo, three bands
+// through a chunk of bands (narrow cubes: other tiles, or none, var_tiles); y1 is staged in LDS with a 1-pixel halo, three bands
 // in turn, u' with the row below and the column to the right, t' with the rows
 // above and below; the next bands' loads are in flight meanwhile (the buffer
 // path, common.hpp: band_of). In two kernels with the search between them, each
@@ -47,12 +47,17 @@ constexpr int VT = 1024;          // init and copy kernels
 constexpr int kVarBlocks = 8192;  // their blocks at most
 // The sweep's tile: 512 threads, one per point. Several blocks fit a CU, so one
 // block's barriers overlap another's loads, and 64 columns waste little of
-// ragged widths.
-constexpr int TI = 8, TJ = 64, NT = TI * TJ;
-constexpr int W2 = TJ + 2, S2 = (TI + 2) * W2, NY = (S2 + NT - 1) / NT;  // y1 with a 1-pixel halo
-constexpr int WU = TJ + 1, SU = (TI + 1) * WU, RINGU = SU - NT;           // u' with the (+1, +1) ring
-constexpr int T0 = NT / 2;                                               // first thread of the t' ring
-static_assert(T0 >= RINGU && T0 % 64 == 0 && T0 + 2 * TJ <= NT, "one ring role per wavefront");
+// ragged widths. Cubes that fill little of such tiles take others of as many points
+// and no larger halo (var_tiles below), or the form without tiles.
+constexpr int kTI = 8, kTJ = 64, NT = kTI * kTJ, kSpan = kTI + kTJ;
+// LDS planes of a tile of rows x cols <= NT points, rows + cols <= kSpan and cols <=
+// kTJ (8 x 64 fills them): y1 with a 1-pixel halo, u' with the (+1, +1) ring, t' with
+// the rows above and below. A tile of fewer points leaves the last word of the
+// last two free: idle threads write there.
+constexpr int S2 = NT + 2 * kSpan + 4, NY = (S2 + NT - 1) / NT;
+constexpr int SU = NT + kSpan + 1, ST = NT + 2 * kTJ;
+constexpr int T0 = NT / 2;  // first thread of the t' ring
+static_assert(T0 >= kSpan + 1 && T0 % 64 == 0 && T0 + 2 * kTJ <= NT, "one ring role per wavefront");
 // Wavefronts per SIMD asked of the compiler: three blocks per CU in 80 registers.
 // With two (128 registers allowed, 91 taken) the HSSTV2 sweep of 256 x 256 x 128
 // takes 140 instead of 143 us, the SSTV sweep of 145 x 141 x 103 50 instead of 43.
@@ -83,7 +88,8 @@ struct VarArgs {
     uint32_t *ccount;                   // [2][slots]
     uint32_t *flags;                    // of the launch table
     int ti, tj, tk, kc;                 // tiles along i, j, band chunks; bands per chunk
-    int slots, per, capt;               // slots of the search, consecutive tiles of one, candidates of one
+    int slots, per, capt;               // slots of the search, consecutive tiles (voxels) of one, candidates of one
+    int rows, cols;                     // points of a tile (0: k_var_flat)
 };
 
 // Loads and stores of one band of an array at a pixel (kNone: none): through
@@ -122,13 +128,27 @@ __device__ __forceinline__ void bput(const Band<BUF, T> &b, uint32_t pix, T x)
     else if (b.any && pix != kNone<BUF>) b.p[pix] = x;
 }
 
-// P: planes of y1 (2 SSTV, 4 HSSTV)
-template <int P, bool BUF>
+// The conjugate prox of the regularizer on one voxel's entries of y1.
+template <int P>
+__device__ __forceinline__ void dual_prox(int variant, float (&y)[P])
+{
+    if (P == 4 && variant == GEO_REG_HSSTV2) {
+        const float nr = sqrtf((y[0] * y[0] + y[1] * y[1]) + (y[P - 2] * y[P - 2] + y[P - 1] * y[P - 1]));
+#pragma unroll
+        for (int q = 0; q < P; ++q) y[q] = nr > 1.f ? y[q] / nr : y[q];
+    } else {
+#pragma unroll
+        for (int q = 0; q < P; ++q) y[q] = fminf(fmaxf(y[q], -1.f), 1.f);
+    }
+}
+
+// P: planes of y1 (2 SSTV, 4 HSSTV). FIT: tiles of a.rows x a.cols, else of 8 x 64.
+template <int P, bool BUF, bool FIT>
 __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
 {
     __shared__ float sY[3 * P * S2];         // three bands of y1, planes one after another
     __shared__ float sU[2 * SU];             // u' by band parity
-    __shared__ float sT[(TI + 2) * TJ];      // t' with the rows above and below
+    __shared__ float sT[ST];                 // t' with the rows above and below
     __shared__ float4 keep[NT];              // t+, q+, y3, y3 of the row above
     __shared__ double red[10 * (NT / 64)];
     // (SSTV: with these sums in registers the sweep spills and takes 2.3% longer;
@@ -163,19 +183,24 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
     const uint32_t pern = (uint32_t)a.slots >> 3, b0 = blockIdx.x;
     const int slot = (int)(b0 < 8u * pern ? (b0 & 7u) * pern + (b0 >> 3) : b0);
     if (tid < 2) ncand[tid] = 0u;  // published by the first barrier of a march
-    const int oti = tid / TJ, otj = tid % TJ;
-    // ring roles: u' (the first RINGU threads) and t' (T0 on), a wavefront has one
+    const int TI = FIT ? a.rows : kTI, TJ = FIT ? a.cols : kTJ;
+    const int W2 = TJ + 2, WU = TJ + 1;          // LDS row lengths
+    const bool act = !FIT || tid < TI * TJ;      // the thread has a point of the tile
+    const int oti = act ? tid / TJ : 0, otj = act ? tid % TJ : 0;
+    const int ou_w = act ? oti * WU + otj : SU - 1, ot_w = act ? TJ + tid : ST - 1;
+    // ring roles: u' (the first threads) and t' (T0 on), a wavefront has one
     int rui = 0, ruj = 0;
-    const bool ring_u = tid < RINGU;
+    const bool ring_u = tid < TI + TJ + 1;
     const int wave0 = __builtin_amdgcn_readfirstlane(tid);
     const bool wave_t = wave0 >= T0 && wave0 < T0 + 2 * TJ;
+    const bool ring_t = FIT ? tid >= T0 && tid < T0 + 2 * TJ : wave_t;
     if (ring_u) {
         rui = tid < WU ? TI : tid - WU;
         ruj = tid < WU ? tid : TJ;
     }
-    if (wave_t) {
+    if (ring_t) {
         rui = tid - T0 < TJ ? -1 : TI;
-        ruj = (tid - T0) % TJ;
+        ruj = FIT ? (tid - T0 < TJ ? tid - T0 : tid - T0 - TJ) : (tid - T0) % TJ;
     }
     double du2 = 0.0, u2 = 0.0, r2 = 0.0;
     Gathered ga;
@@ -199,15 +224,15 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
             return BUF ? p - (uint32_t)n2 : (p != kNone<BUF> && i >= 1 ? p - (uint32_t)n2 : kNone<BUF>);
         };
         const int oi = i0 + oti, oj = j0 + otj;
-        const uint32_t po = pixel(oi, oj), pom = row_above(po, oi);
+        const uint32_t po = act ? pixel(oi, oj) : kNone<BUF>, pom = row_above(po, oi);
         const bool own_in = po != kNone<BUF>;
         const int ri = i0 + rui, rj = j0 + ruj;
-        const uint32_t pr = ring_u || wave_t ? pixel(ri, rj) : kNone<BUF>, prm = row_above(pr, ri);
+        const uint32_t pr = ring_u || ring_t ? pixel(ri, rj) : kNone<BUF>, prm = row_above(pr, ri);
         uint32_t py[NY];
 #pragma unroll
         for (int n = 0; n < NY; ++n) {
             const int p = tid + NT * n;
-            py[n] = p < S2 ? pixel(i0 - 1 + p / W2, j0 - 1 + p % W2) : kNone<BUF>;
+            py[n] = p < (TI + 2) * W2 ? pixel(i0 - 1 + p / W2, j0 - 1 + p % W2) : kNone<BUF>;
         }
         const bool ei = oi <= n1 - 2, ej = oj <= n2 - 2;
 
@@ -283,7 +308,7 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
             float *su = sU + (k & 1) * SU;
             const float un = u_at(k, yc, yp, oti, otj, ei, ej, lu, lq);
             const float u0 = 2.f * un - lu;
-            su[oti * WU + otj] = u0;
+            su[ou_w] = u0;
             bput(Band<BUF, float>(ap->u[par ^ 1], k, np, own), po, un);
             const bool wr = own && own_in;
             const double dl = (double)un - (double)lu, ud = (double)lu;
@@ -301,9 +326,9 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
             const float qn = (a4 / ap->gy) * lq + ((u0 + sp) + tp) - lv;
             bput(Band<BUF, float>(ap->q[par ^ 1], k, np, own), po, qn);
             if (wr) r2 += (double)qn * (double)qn;
-            sT[TJ + tid] = tp;
+            sT[ot_w] = tp;
             keep[tid] = make_float4(tn, qn, l3c, l3m);
-            if (wave_t) {
+            if (ring_t) {
                 const float x = soft(zt_of(xu, x3m, ri <= n1 - 2 ? x3c : 0.f, y4_of(xq, a4), ap->gt), scp->in.tau[1]);
                 sT[(rui + 1) * TJ + ruj] = 2.f * x - xu;
             }
@@ -327,14 +352,7 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
             }
 #pragma unroll
             for (int q = 0; q < P; ++q) y[q] = __builtin_fmaf(ap->gy, av[q], yc[q * S2 + c]);
-            if (P == 4 && ap->variant == GEO_REG_HSSTV2) {
-                const float nr = sqrtf((y[0] * y[0] + y[1] * y[1]) + (y[P - 2] * y[P - 2] + y[P - 1] * y[P - 1]));
-#pragma unroll
-                for (int q = 0; q < P; ++q) y[q] = nr > 1.f ? y[q] / nr : y[q];
-            } else {
-#pragma unroll
-                for (int q = 0; q < P; ++q) y[q] = fminf(fmaxf(y[q], -1.f), 1.f);
-            }
+            dual_prox<P>(ap->variant, y);
             bput(Band<BUF, float2>(ap->ya[par ^ 1], k, np, true), po, make_float2(y[0], y[1]));
             if constexpr (P == 4)
                 bput(Band<BUF, float2>(ap->yb[par ^ 1], k, np, true), po, make_float2(y[2], y[3]));
@@ -398,6 +416,126 @@ __global__ __launch_bounds__(NT, kVarMinWaves) void k_var_sweep(VarArgs args)
 
     tile_sums<NT>(du2, u2, r2, ga, sl, red, a.part + 3 * slot, a.winpart + 4 * slot, a.winpart + 4 * (a.slots + slot));
     if (tid == 0) {
+        a.ccount[slot] = ncand[0];
+        a.ccount[a.slots + slot] = ncand[1];
+    }
+}
+
+// The same iteration for cubes whose bands fill little of any tile (single spectra,
+// single rows or columns of pixels): one thread per voxel, which evaluates the u'
+// and t' of the neighbours it needs again (6 and 3 points, some 90 loads from the
+// caches). What bounds it is those loads, 35 us (SSTV) and 51 us (HSSTV) per million
+// voxels, and below a few hundred thousand the search and the launches. A slot is a
+// run of `per` consecutive voxels. Every value comes from the operations of
+// k_var_sweep in their order.
+constexpr int FT = 256;
+template <int P>
+__global__ __launch_bounds__(FT) void k_var_flat(VarArgs a)
+{
+    __shared__ double red[10 * (FT / 64)];
+    __shared__ uint32_t ncand[2];
+    const int tid = threadIdx.x, slot = blockIdx.x;
+    DevScalars *sc = a.sc;
+    const bool idle_now = idle(sc);
+    if (slot == 0 && tid == 0) {
+        sc->view = {sc->in.a_lo, sc->in.a_hi, sc->in.a_c, idle_now ? 1u : 0u};
+        passes_over(a.flags);
+    }
+    if (idle_now) return;
+    if (tid < 2) ncand[tid] = 0u;
+    __syncthreads();
+    const const4<DevScalars> &scr = *(const4<DevScalars> *)sc;
+    const int par = (int)(scr.iter & 1u);
+    const uint32_t n1 = (uint32_t)a.d.n1, n2 = (uint32_t)a.d.n2, n3 = (uint32_t)a.d.n3, np = n1 * n2;
+    const float a4 = scr.in.a4;
+    const float *u = a.u[par], *t = a.t[par], *y3 = a.y3[par], *qv = a.q[par];
+    const float2 *ya = a.ya[par], *yb = a.yb[par];
+    double du2 = 0.0, u2 = 0.0, r2 = 0.0;
+    Gathered ga;
+    SlopeRegs sl;
+    const uint32_t N = (uint32_t)a.d.plane, q1 = min(N, (uint32_t)(slot + 1) * (uint32_t)a.per);
+    for (uint32_t q0 = (uint32_t)slot * (uint32_t)a.per; q0 < q1; q0 += FT) {
+        const bool in = q0 + tid < q1;  // (the others repeat the last voxel)
+        const uint32_t q = in ? q0 + tid : q1 - 1u;
+        const uint32_t row = q / n2, j = q - row * n2, k = row / n1, i = row - k * n1;
+        auto dT = [&](const float2 *y, uint32_t c, uint32_t ci, uint32_t cj) {
+            float x = ci >= 1u ? y[c - n2].x : 0.f;
+            x -= ci + 2u <= n1 ? y[c].x : 0.f;
+            x += cj >= 1u ? y[c - 1u].y : 0.f;
+            x -= cj + 2u <= n2 ? y[c].y : 0.f;
+            return x;
+        };
+        // u+ at one point, c its index
+        auto u_at = [&](uint32_t c, uint32_t ck, uint32_t ci, uint32_t cj, float uo) {
+            float g = 0.f;
+            if (ck >= 1u) g += dT(ya, c - np, ci, cj);
+            if (ck + 2u <= n3) g -= dT(ya, c, ci, cj);
+            if constexpr (P == 4) g = __builtin_fmaf(a.omega, dT(yb, c, ci, cj), g);
+            const float x = __builtin_fmaf(-a.gu, g + y4_of(qv[c], a4), uo);
+            return fminf(fmaxf(x, a.mu_lo), a.mu_hi);
+        };
+        auto up_at = [&](uint32_t c, uint32_t ck, uint32_t ci, uint32_t cj) {
+            const float uo = u[c];
+            return 2.f * u_at(c, ck, ci, cj, uo) - uo;
+        };
+        // t+ at one point of this band
+        auto t_at = [&](uint32_t c, uint32_t ci, float to) {
+            const float z = zt_of(to, ci >= 1u ? y3[c - n2] : 0.f, ci + 2u <= n1 ? y3[c] : 0.f, y4_of(qv[c], a4), a.gt);
+            return soft(z, scr.in.tau[1]);
+        };
+        auto tp_at = [&](uint32_t c, uint32_t ci) {
+            const float to = t[c];
+            return 2.f * t_at(c, ci, to) - to;
+        };
+        const bool ei = i + 2u <= n1, ej = j + 2u <= n2, ek = k + 2u <= n3;
+        const float uo = u[q], qo = qv[q], so = a.s[q], to = t[q], vo = a.v[q];
+        const float un = u_at(q, k, i, j, uo), up = 2.f * un - uo;
+        const float sn = soft(zs_of(so, y4_of(qo, a4)), scr.in.tau[0]), tn = t_at(q, i, to);
+        const float sp = 2.f * sn - so, tp = 2.f * tn - to;
+        const float qn = (a4 / a.gy) * qo + ((up + sp) + tp) - vo;
+        // y1+
+        const float ui = ei ? up_at(q + n2, k, i + 1u, j) : 0.f, uj = ej ? up_at(q + 1u, k, i, j + 1u) : 0.f;
+        float av[P], y[P];
+        av[0] = av[1] = 0.f;
+        if (ek) {
+            const float s0 = up_at(q + np, k + 1u, i, j) - up;
+            if (ei) av[0] = (up_at(q + np + n2, k + 1u, i + 1u, j) - ui) - s0;
+            if (ej) av[1] = (up_at(q + np + 1u, k + 1u, i, j + 1u) - uj) - s0;
+        }
+        const float2 yo = ya[q];
+        y[0] = __builtin_fmaf(a.gy, av[0], yo.x);
+        y[1] = __builtin_fmaf(a.gy, av[1], yo.y);
+        if constexpr (P == 4) {
+            const float2 bo = yb[q];
+            av[2] = ei ? a.omega * (ui - up) : 0.f;
+            av[3] = ej ? a.omega * (uj - up) : 0.f;
+            y[2] = __builtin_fmaf(a.gy, av[2], bo.x);
+            y[3] = __builtin_fmaf(a.gy, av[3], bo.y);
+        }
+        dual_prox<P>(a.variant, y);
+        // y3+ here and in the row above, for the t values of the next search
+        const float yc = ei ? __builtin_fmaf(a.gy, tp_at(q + n2, i + 1u) - tp, y3[q]) : y3[q];
+        const float ym = i >= 1u ? __builtin_fmaf(a.gy, tp - tp_at(q - n2, i - 1u), y3[q - n2]) : 0.f;
+        if (in) {
+            a.u[par ^ 1][q] = un;
+            a.s[q] = sn;
+            a.t[par ^ 1][q] = tn;
+            a.q[par ^ 1][q] = qn;
+            a.y3[par ^ 1][q] = yc;
+            a.ya[par ^ 1][q] = make_float2(y[0], y[1]);
+            if constexpr (P == 4) a.yb[par ^ 1][q] = make_float2(y[2], y[3]);
+            const double dl = (double)un - (double)uo, ud = (double)uo;
+            du2 += dl * dl;
+            u2 += ud * ud;
+            r2 += (double)qn * (double)qn;
+        }
+        float4 *cand = a.cand + (int64_t)slot * a.capt;
+        gather_ahead(ga, sl, scr.in, 0, in, sn, 0.f, 1.f, qn, cand, &ncand[0], a.capt);
+        gather_ahead(ga, sl, scr.in, 1, in, tn, ym - (ei ? yc : 0.f), a.gt, qn, cand + (int64_t)a.slots * a.capt, &ncand[1],
+                     a.capt);
+    }
+    tile_sums<FT>(du2, u2, r2, ga, sl, red, a.part + 3 * slot, a.winpart + 4 * slot, a.winpart + 4 * (a.slots + slot));
+    if (tid == 0) {  // (every append came before the barrier in the sums)
         a.ccount[slot] = ncand[0];
         a.ccount[a.slots + slot] = ncand[1];
     }
@@ -474,25 +612,57 @@ int resident_blocks()
             hipDeviceProp_t prop;
             if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
         }
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_var_sweep<P, true>, NT, 0) != hipSuccess || per < 1)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_var_sweep<P, true, false>, NT, 0) != hipSuccess || per < 1)
             per = 1;
         return cus * per;
     }();
     return cached;
 }
 
-// Tiles of a cube: the band chunk in 1..32 whose tiles the resident blocks
+// The split of a cube. A tile's points: 8 x 64, or rows x cols fitted to the cube
+// where that needs 3/5 of the tiles or less (narrow cubes; the loads of 8 x 64 tiles
+// come in full lines and their geometry is known to the compiler, so that between
+// 0.65 and 0.75 of the tiles the two take the same time: 300 x 90 x 90 67.9 us an
+// iteration of SSTV fitted, 64.9 not, 120 x 70 x 198 52.9 and 55.8, 1024 x 16 x 300 81
+// and 189). Where the tiles fill less than 3/10 of their threads, no tiles (rows = 0:
+// one thread per voxel, a slot a run of voxels), which takes 35 us per million
+// voxels once they fill the device: 1 x 1 x 100000 15 us, 355 in 8 x 64 tiles, 4096 x 2
+// x 300 93 us, 106 in fitted ones, 20 x 20 x 1000 36 and 28.
+// The band chunk: the depth in 1..32 whose tiles the resident blocks
 // finish first, a tile costing its bands and kTileFixedBands more (its first
 // loads, the halo bands, the partial sums); ties to the deeper chunk. A search
 // slot is one tile, or (bands of more than kMaxTiles tiles) several.
 struct VarTiles {
-    int ti, tj, tk, kc, slots, per;
+    int rows, cols, ti, tj, tk, kc, slots, per;
 };
 VarTiles var_tiles(const Dims &d, int blocks)
 {
-    VarTiles v;
-    v.ti = ceil_div(d.n1, TI);
-    v.tj = ceil_div(d.n2, TJ);
+    VarTiles v = {};
+    v.rows = kTI;
+    v.cols = kTJ;
+    auto per_band = [&](int rows, int cols) { return (int64_t)ceil_div(d.n1, rows) * ceil_div(d.n2, cols); };
+    const int64_t np = (int64_t)d.n1 * d.n2;
+    if (np < kVarPixels) {
+        int64_t best = per_band(kTI, kTJ) * 3 / 5;
+        for (int s = ceil_div(d.n2, kTJ), e = s + 4; s < e; ++s) {
+            const int cols = ceil_div(d.n2, s);
+            int rows = NT / cols < kSpan - cols ? NT / cols : kSpan - cols;
+            rows = ceil_div(d.n1, ceil_div(d.n1, rows));
+            if (per_band(rows, cols) <= best) {
+                best = per_band(rows, cols) - 1;
+                v.rows = rows;
+                v.cols = cols;
+            }
+        }
+    }
+    if (10 * np < 3 * NT * per_band(v.rows, v.cols)) {
+        v.rows = v.cols = 0;
+        v.per = ceil_div(ceil_div(d.plane, kMaxTiles), FT) * FT;
+        v.slots = ceil_div(d.plane, v.per);
+        return v;
+    }
+    v.ti = ceil_div(d.n1, v.rows);
+    v.tj = ceil_div(d.n2, v.cols);
     const int64_t pb = (int64_t)v.ti * v.tj;
     v.kc = d.n3 < 32 ? d.n3 : 32;
     double best = 0.0;
@@ -585,6 +755,8 @@ VarArgs var_args(const Dims &d, const geo_params *p, const float *v, void *ws, V
     a.s = (float *)(b + L.s);
     // (one tiling for all of them, so that HSSTV1 with omega = 0 sums as SSTV does)
     const VarTiles t = var_tiles(d, resident_blocks<4>());
+    a.rows = t.rows;
+    a.cols = t.cols;
     a.ti = t.ti;
     a.tj = t.tj;
     a.tk = t.tk;
@@ -630,13 +802,17 @@ void var_table_entry(CubeEntry *e, const VarArgs &a, const VarLayout &L, void *w
     c.ahead = 1u;
 }
 
-template <bool BUF>
+template <int P>
 void launch_var_sweep(const VarArgs &a, hipStream_t st)
 {
-    if (a.variant == GEO_REG_SSTV)
-        hipLaunchKernelGGL((k_var_sweep<2, BUF>), dim3(a.slots), dim3(NT), 0, st, a);
+    if (a.rows == 0)
+        hipLaunchKernelGGL(k_var_flat<P>, dim3(a.slots), dim3(FT), 0, st, a);
+    else if ((uint64_t)a.d.n1 * (uint64_t)a.d.n2 >= kVarPixels)
+        hipLaunchKernelGGL((k_var_sweep<P, false, false>), dim3(a.slots), dim3(NT), 0, st, a);
+    else if (a.rows == kTI && a.cols == kTJ)
+        hipLaunchKernelGGL((k_var_sweep<P, true, false>), dim3(a.slots), dim3(NT), 0, st, a);
     else
-        hipLaunchKernelGGL((k_var_sweep<4, BUF>), dim3(a.slots), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((k_var_sweep<P, true, true>), dim3(a.slots), dim3(NT), 0, st, a);
 }
 
 }  // namespace
@@ -669,7 +845,6 @@ hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws
     memset(&sh, 0, sizeof sh);
     sh.ncubes = 1;
     sh.fb_grid = fallback_grid();
-    const bool buf = (uint64_t)d.n1 * (uint64_t)d.n2 < kVarPixels;
     // the table image, with its launch-wide flags zeroed
     std::vector<unsigned char> img(table_image_bytes(1), 0);
     var_table_entry(reinterpret_cast<CubeEntry *>(img.data()), a, L, ws, p, n_iter);
@@ -697,10 +872,10 @@ hipError_t var_step(const Dims &d, const geo_params *p, const float *v, void *ws
             const bool timed = sweep_ms && (all || it % kTimedEvery == kTimedEvery - 1) &&
                                ne + 2 <= ev.size();
             if (timed) e = hipEventRecord(ev[ne], st);
-            if (buf)
-                launch_var_sweep<true>(a, st);
+            if (a.variant == GEO_REG_SSTV)
+                launch_var_sweep<2>(a, st);
             else
-                launch_var_sweep<false>(a, st);
+                launch_var_sweep<4>(a, st);
             if (timed && e == hipSuccess) e = hipEventRecord(ev[ne + 1], st);
             ne += timed ? 2 : 0;
             if (e == hipSuccess) e = launch_search(table, stride, 1, st);
