@@ -347,12 +347,11 @@ static int run_cubes(int n, const geo_dims *dims, const geo_params *p, const flo
         sh.total_tiles += nt;
         sh.total_b += nb;
         sh.b_kinds |= sweep_b_cpt(dims[c].n2) == 4 ? 2 : 1;
-        sh.shape_tiles[reinterpret_cast<const CubeCommon *>(ent[c].bytes)->g.shape] += nt;
+        sh.form_tiles[reinterpret_cast<const CubeCommon *>(ent[c].bytes)->g.form] += nt;
     }
-    sh.grid_a = sweep_a_grid(L[0].dual_bytes, sh.total_tiles);
     sh.fb_grid = fallback_grid();
-    for (int q = 0; q < kTileShapes; ++q)
-        sh.shape_grid[q] = sh.shape_tiles[q] > 0 ? sweep_a_grid(L[0].dual_bytes, sh.shape_tiles[q]) : 0;
+    for (int q = 0; q < kForms; ++q)
+        sh.form_grid[q] = sh.form_tiles[q] > 0 ? sweep_grid_of(L[0].dual_bytes, q, sh.form_tiles[q]) : 0;
     // the entries, then the launch flags zeroed
     std::vector<unsigned char> img(table_image_bytes(n), 0);
     memcpy(img.data(), ent.data(), (size_t)n * sizeof(CubeEntry));
@@ -588,7 +587,7 @@ int geo_sweep_blocks(int32_t dual_storage, int32_t *blocks)
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return GEO_EHIP;
     // the persistent grid of a launch with at least this many tiles
-    *blocks = sweep_a_grid(dual_storage == GEO_STORE_BF16 ? 2 : 4, 1 << 30);
+    *blocks = sweep_grid_of(dual_storage == GEO_STORE_BF16 ? 2 : 4, 0, 1 << 30);
     return GEO_OK;
 }
 

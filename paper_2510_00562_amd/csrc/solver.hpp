@@ -168,6 +168,12 @@ constexpr int kTileShapes = 2;
 constexpr int kShapeTI[kTileShapes] = {8, 16}, kShapeTJ[kTileShapes] = {128, 64};
 constexpr int kSweepThreads = 1024;
 constexpr int kTileRows = kShapeTI[0], kTileCols = kShapeTJ[0], kTileSpan = kTileRows + kTileCols;
+// Kernel forms of the sweep. The small one has workgroups of a quarter of the
+// threads, four to a compute unit, for cubes whose bands are one tile of at most
+// kSmallThreads pixels, kSmallSpan rows and columns together and kSmallCols columns:
+// in 1024 threads most wavefronts go through every instruction of a band for nothing.
+constexpr int kForms = 3, kSmallForm = 2;
+constexpr int kSmallThreads = 256, kSmallSpan = 40, kSmallCols = 32;
 constexpr int kDefaultKC = 32;       // deepest default chunk (the rule below picks 8..32)
 constexpr int kMinKC = 8;
 constexpr int kMaxTiles = 4096;      // tiles of one cube (slices of its search)
@@ -199,7 +205,7 @@ inline int tile_shape(int n1, int n2, int dual_bytes)
 }
 struct SweepGrid {
     int tj, ti, tk, kc;  // tiles along j, i, band chunks; bands per chunk
-    int shape;           // kernel form: 0 for tiles of 8 x 128, 1 for any others
+    int form;            // of the kernel: 0 for tiles of 8 x 128, 1 for any others, kSmallForm
     int rows, cols;      // pixels of a tile
     __host__ __device__ int blocks() const { return tj * ti * tk; }
 };
@@ -322,7 +328,7 @@ inline SweepGrid fitted_grid(int n1, int n2, int n3, int requested, int blocks)
     // (the form whose geometry the compiler knows, for the widths that fill it)
     auto form = [&](int rows, int cols) { return rows == kTileRows && cols == kTileCols && n2 % kTileCols == 0 ? 0 : 1; };
     SweepGrid best = sweep_grid(n1, n2, n3, band_chunk(n1, n2, n3, requested, blocks, 0), 0);
-    best.shape = form(best.rows, best.cols);
+    best.form = form(best.rows, best.cols);
     double best_time = 0.97 * time_of(best);
     const int most = max_tiles(n1, n2, n3), best_chunk = best.kc;
     const int s0 = ceil_div(n2, kTileCols);
@@ -353,10 +359,29 @@ inline SweepGrid fitted_grid(int n1, int n2, int n3, int requested, int blocks)
     }
     return best;
 }
+// One tile per band in the small form, for the cubes it takes: as many chunks as its
+// resident blocks, so that one round of them does (BF16: the nominal chunk, whose
+// tiles a query has promised; one nominal tile per band).
+inline bool small_grid(int n1, int n2, int n3, int requested, int blocks, int small_blocks, int dual_bytes, SweepGrid *g)
+{
+    if ((int64_t)n1 * n2 > kSmallThreads || n1 + n2 > kSmallSpan || n2 > kSmallCols) return false;
+    if (dual_bytes == 2 && n1 > kTileRows) return false;
+    int kc;
+    if (requested > 0 || dual_bytes == 2) {
+        kc = band_chunk(n1, n2, n3, requested, blocks, 0);
+    } else {
+        const int most = max_tiles(n1, n2, n3);
+        kc = ceil_div(n3, most < small_blocks ? most : small_blocks);
+    }
+    *g = SweepGrid{1, 1, ceil_div(n3, kc), kc, kSmallForm, n1, n2};
+    return true;
+}
 // The tiles of a cube: a function of its size and storage, the request and the
 // device only, so that a cube runs the same ones alone and in a batch.
-inline SweepGrid cube_grid(int n1, int n2, int n3, int requested, int blocks, int dual_bytes)
+inline SweepGrid cube_grid(int n1, int n2, int n3, int requested, int blocks, int small_blocks, int dual_bytes)
 {
+    SweepGrid g;
+    if (small_grid(n1, n2, n3, requested, blocks, small_blocks, dual_bytes, &g)) return g;
     if (dual_bytes == 4) return fitted_grid(n1, n2, n3, requested, blocks);
     const int shape = tile_shape(n1, n2, dual_bytes);
     return sweep_grid(n1, n2, n3, band_chunk(n1, n2, n3, requested, blocks, shape), shape);
@@ -478,8 +503,8 @@ struct LaunchShape {
     int grid_a;       // persistent sweep blocks
     int total_b;      // sweep B blocks over all cubes (BF16)
     int b_kinds;      // sweep B forms present: 1 one or two columns per thread, 2 four
-    int shape_tiles[kTileShapes];  // sweep A tiles of the cubes of each tile shape
-    int shape_grid[kTileShapes];   // persistent blocks of the sweep A launch of each shape
+    int form_tiles[kForms];  // sweep tiles of the cubes of each kernel form
+    int form_grid[kForms];   // persistent blocks of the sweep launch of each form
     int fb_grid;      // blocks of the fallback histogram passes
 };
 
@@ -532,7 +557,7 @@ hipError_t launch_init(const Dims &d, const float *v, void *ws, const Layout &L,
 // block counts.
 void cube_entry(CubeEntry *e, const Dims &d, const float *v, void *ws, const Layout &L, const geo_params *p,
                  int n_iter, int tile0, int b0, int *ntiles, int *nb);
-int sweep_a_grid(int dual_bytes, int total_tiles);
+int sweep_grid_of(int dual_bytes, int form, int tiles);
 // One launch slot over the table (device copy of the entries). ev (may be
 // null): nev = 4 events recorded at the phase boundaries (FP32: before and
 // after the histogram passes, after the sweep, after the search; BF16: before

@@ -44,24 +44,33 @@
 // remaining launches into no-ops, so iteration counts stay exact.
 #include <string.h>
 
+#include <type_traits>
+
 #include "radix.hpp"
 
 namespace geo {
 
 namespace {
 
-constexpr int NT = kSweepThreads;
-// LDS planes of a tile of TI x TJ pixels, TI * TJ <= NT and TI + TJ <= kTileSpan
-// (8 x 128 fills them): y with a 2-pixel halo, w' on a 1-pixel ring, u' with the
-// (+1, +1) ring, t' with the rows above and below. A tile of fewer than NT
-// pixels leaves the last word of each free: idle threads write there.
-constexpr int S2 = NT + 4 * kTileSpan + 16, S1 = NT + 2 * kTileSpan + 4, SU = NT + kTileSpan + 1;
-constexpr int ST = NT + 2 * kTileCols;
-constexpr int NY = (S2 + NT - 1) / NT;  // y points per thread
-constexpr int T0 = NT / 2;              // first thread of the t' ring
-static_assert(kTileRows * kTileCols == NT && kTileRows + kTileCols == kTileSpan, "the fixed tile fills the planes");
-static_assert(2 * kTileSpan + 4 <= NT && kTileSpan + 1 <= T0 && T0 + 2 * kTileCols <= NT && T0 % 64 == 0,
-              "at most one ring point of a kind per thread, one of u' and t' per wavefront");
+// LDS planes of a tile of TI x TJ pixels, TI * TJ <= NT, TI + TJ <= SPAN and TJ <=
+// COLS: y with a 2-pixel halo, w' on a 1-pixel ring, u' with the (+1, +1) ring, t'
+// with the rows above and below. A tile of fewer than NT pixels leaves the last word
+// of each free: idle threads write there.
+template <int THREADS, int SPAN, int COLS>
+struct Planes {
+    static constexpr int NT = THREADS;
+    static constexpr int S2 = NT + 4 * SPAN + 16, S1 = NT + 2 * SPAN + 4, SU = NT + SPAN + 1;
+    static constexpr int ST = NT + 2 * COLS;
+    static constexpr int NY = (S2 + NT - 1) / NT;  // y points per thread
+    static constexpr int T0 = NT / 2;              // first thread of the t' ring
+    static_assert(2 * SPAN + 4 <= NT && SPAN + 1 <= T0 && T0 + 2 * COLS <= NT && T0 % 64 == 0,
+                  "at most one ring point of a kind per thread, one of u' and t' per wavefront");
+};
+using Wide = Planes<kSweepThreads, kTileSpan, kTileCols>;  // 8 x 128 fills them
+using Small = Planes<kSmallThreads, kSmallSpan, kSmallCols>;
+static_assert(kTileRows * kTileCols == Wide::NT && kTileRows + kTileCols == kTileSpan, "the fixed tile fills the planes");
+template <int S>
+using PlanesOf = std::conditional_t<S == kSmallForm, Small, Wide>;
 constexpr int NPT = 256;  // threads of the pointwise kernels
 using lds_f = __attribute__((address_space(3))) float;
 
@@ -115,11 +124,14 @@ struct TileList {
 // iterations, so that storage keeps the form whose sums are over the values
 // themselves.
 // S 0: tiles of 8 x 128 pixels, the geometry known to the compiler (256 x 256 x
-// 128: 289 us, in the other form 293); 1: the cube's own rows x cols.
+// 128: 289 us, in the other form 293); 1: the cube's own rows x cols; kSmallForm: the
+// same in workgroups of kSmallThreads, for cubes whose bands are one such tile.
 template <typename DT, int S, bool FUSED>
-__global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh)
+__global__ __launch_bounds__(PlanesOf<S>::NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh)
 {
     using P = typename PairOf<DT>::type;
+    using PL = PlanesOf<S>;
+    constexpr int NT = PL::NT, S2 = PL::S2, S1 = PL::S1, SU = PL::SU, ST = PL::ST, NY = PL::NY, T0 = PL::T0;
     // three bands of masked [y1v, y1h, y2v, y2h] | u' by band parity | w1', w2'
     // planes read by neighbours (ud_h, lr_v, c_v, c_h)
     __shared__ __align__(16) float smem[3 * 4 * S2 + 2 * SU + 2 * 4 * S1];
@@ -154,7 +166,7 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
         if (idle_now) return;
     } else if (threadIdx.x < 64) {
         const int c = threadIdx.x;
-        int x = c < sh.ncubes && cubes[c].c.g.shape == S && !idle(cubes[c].c.sc) ? cubes[c].c.ntiles : 0;
+        int x = c < sh.ncubes && cubes[c].c.g.form == S && !idle(cubes[c].c.sc) ? cubes[c].c.ntiles : 0;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
             const int y = __shfl_up(x, o, 64);
@@ -180,13 +192,13 @@ __global__ __launch_bounds__(NT, 4) void k_sweep(Table<DT> cubes, LaunchShape sh
         // than kept live through the march)
         int cube = 0, lt;  // tile within the cube
         if (many) {
-            const TileList list(blockIdx.x, sh.shape_grid[S]);
+            const TileList list(blockIdx.x, sh.form_grid[S]);
             const int p = list.first + r * list.step;
             if (p >= list.before(tile0[sh.ncubes])) break;
             while (list.before(tile0[cube + 1]) <= p) ++cube;
             lt = p - list.before(tile0[cube]) + list.below(tile0[cube + 1]) - list.below(tile0[cube]);
         } else {
-            lt = tile_at(blockIdx.x, sh.shape_grid[S], ((const4<CubeArgs<DT>> *)cubes)->c.ntiles, r);
+            lt = tile_at(blockIdx.x, sh.form_grid[S], ((const4<CubeArgs<DT>> *)cubes)->c.ntiles, r);
             if (lt < 0) break;
         }
         // uniform across the block: the cube's entry is read with scalar loads
@@ -758,27 +770,30 @@ int grid_for(int64_t n)
     return (int)(b < 1 ? 1 : (b > 8192 ? 8192 : b));
 }
 
-// Resident blocks of sweep A on this device (queried once per process and
-// storage type).
-template <typename DT>
+// Resident blocks of the sweep on this device, of the forms in use (BF16: 8 x 128 and
+// the small one) the smaller number; queried once per process, storage and size.
+template <typename DT, bool SMALL>
 int resident_grid()
 {
-    // computed once per process (thread-safe initialisation of a local static)
+    // (thread-safe initialisation of a local static)
     static const int cached = [] {
-        int dev = 0, cus = 256, p0 = 1, p1 = 1;
+        int dev = 0, cus = 256;
         if (hipGetDevice(&dev) == hipSuccess) {
             hipDeviceProp_t prop;
             if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
         }
-        // the smaller occupancy of the forms in use (BF16: 8 x 128 only)
         constexpr bool fused = sizeof(DT) == 4;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&p0, k_sweep<DT, 0, fused>, NT, 0) != hipSuccess || p0 < 1)
-            p0 = 1;
-        p1 = p0;
-        if constexpr (fused)
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&p1, k_sweep<DT, 1, true>, NT, 0) != hipSuccess || p1 < 1)
-                p1 = 1;
-        return cus * (p0 < p1 ? p0 : p1);
+        auto per_cu = [](auto kernel, int threads) {
+            int p = 1;
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(&p, kernel, threads, 0) == hipSuccess && p >= 1 ? p : 1;
+        };
+        if constexpr (SMALL) return cus * per_cu(k_sweep<DT, kSmallForm, fused>, Small::NT);
+        int p = per_cu(k_sweep<DT, 0, fused>, Wide::NT);
+        if constexpr (fused) {
+            const int p1 = per_cu(k_sweep<DT, 1, true>, Wide::NT);
+            if (p1 < p) p = p1;
+        }
+        return cus * p;
     }();
     return cached;
 }
@@ -806,7 +821,8 @@ void cube_entry_t(CubeArgs<DT> *a, const Dims &d, const float *v, void *ws, cons
         c.zbuf = (float *)(b + L.zbuf);
     }
     c.ccount = (uint32_t *)(b + L.ccount);
-    c.g = cube_grid(d.n1, d.n2, d.n3, p->band_chunk, sweep_a_grid(sizeof(DT), 1 << 30), (int)sizeof(DT));
+    c.g = cube_grid(d.n1, d.n2, d.n3, p->band_chunk, sweep_grid_of(sizeof(DT), 0, 1 << 30),
+                    sweep_grid_of(sizeof(DT), kSmallForm, 1 << 30), (int)sizeof(DT));
     c.ntiles = c.g.blocks();
     c.capt = (int)(L.cap / c.ntiles);
     c.tile0 = tile0;
@@ -845,6 +861,13 @@ void cube_entry_t(CubeArgs<DT> *a, const Dims &d, const float *v, void *ws, cons
 
 constexpr int kPrefetchBlocks = 240;  // cache prefetch beside the search (BF16)
 
+template <typename DT, int S>
+void launch_sweep(const CubeArgs<DT> *cubes, const LaunchShape &sh, hipStream_t st)
+{
+    if (sh.form_tiles[S] > 0)
+        hipLaunchKernelGGL((k_sweep<DT, S, sizeof(DT) == 4>), dim3(sh.form_grid[S]), dim3(PlanesOf<S>::NT), 0, st, cubes, sh);
+}
+
 hipError_t slot_fused(const void *table, const LaunchShape &sh, hipStream_t st, hipEvent_t *ev, int nev)
 {
     const CubeArgs<float> *cubes = (const CubeArgs<float> *)table;
@@ -853,10 +876,9 @@ hipError_t slot_fused(const void *table, const LaunchShape &sh, hipStream_t st, 
     if (e != hipSuccess) return e;
     if (nev >= 2) (void)hipEventRecord(ev[nev >= 4 ? 1 : 0], st);
     // one persistent launch per form present (each takes the tiles of its cubes)
-    if (sh.shape_tiles[0] > 0)
-        hipLaunchKernelGGL((k_sweep<float, 0, true>), dim3(sh.shape_grid[0]), dim3(NT), 0, st, cubes, sh);
-    if (sh.shape_tiles[1] > 0)
-        hipLaunchKernelGGL((k_sweep<float, 1, true>), dim3(sh.shape_grid[1]), dim3(NT), 0, st, cubes, sh);
+    launch_sweep<float, 0>(cubes, sh, st);
+    launch_sweep<float, 1>(cubes, sh, st);
+    launch_sweep<float, kSmallForm>(cubes, sh, st);
     if (nev >= 2) (void)hipEventRecord(ev[nev >= 4 ? 2 : 1], st);
     e = launch_search(table, (int)sizeof(CubeEntry), sh.ncubes, st);
     if (nev >= 4) (void)hipEventRecord(ev[3], st);
@@ -868,7 +890,8 @@ hipError_t slot_two(const void *table, const LaunchShape &sh, hipStream_t st, hi
     const CubeArgs<bf16> *cubes = (const CubeArgs<bf16> *)table;
     const int stride = (int)sizeof(CubeEntry);
     if (nev >= 2) (void)hipEventRecord(ev[0], st);
-    hipLaunchKernelGGL((k_sweep<bf16, 0, false>), dim3(sh.shape_grid[0]), dim3(NT), 0, st, cubes, sh);
+    launch_sweep<bf16, 0>(cubes, sh, st);
+    launch_sweep<bf16, kSmallForm>(cubes, sh, st);
     if (nev >= 2) (void)hipEventRecord(ev[1], st);
     hipError_t e = launch_select_window(table, stride, sh.ncubes, kPrefetchBlocks, st);
     if (e == hipSuccess) e = launch_fallback(table, 2, sh, st);
@@ -891,12 +914,13 @@ void cube_entry(CubeEntry *e, const Dims &d, const float *v, void *ws, const Lay
         cube_entry_t<float>(reinterpret_cast<CubeArgs<float> *>(e->bytes), d, v, ws, L, p, n_iter, tile0, b0, ntiles, nb);
 }
 
-// Persistent sweep A grid: resident blocks, at most one per tile, a multiple
+// Persistent sweep grid of a form: resident blocks, at most one per tile, a multiple
 // of the 8 XCDs when it is smaller than the tile count.
-int sweep_a_grid(int dual_bytes, int total_tiles)
+int sweep_grid_of(int dual_bytes, int form, int tiles)
 {
-    int G = dual_bytes == 2 ? resident_grid<bf16>() : resident_grid<float>();
-    if (G >= total_tiles) return total_tiles;
+    const int G = form == kSmallForm ? (dual_bytes == 2 ? resident_grid<bf16, true>() : resident_grid<float, true>())
+                                     : (dual_bytes == 2 ? resident_grid<bf16, false>() : resident_grid<float, false>());
+    if (G >= tiles) return tiles;
     return G >= 8 ? (G & ~7) : G;
 }
 
