@@ -225,10 +225,11 @@ int geo_batch_step(int32_t n_cubes, const geo_dims *dims, const geo_params *p,
 
 /* Nominal launch geometry of the fused sweep, for callers that model load
  * balance, such as a band-chunk autotuner. Host-side only: no GPU work. With
- * BF16 duals it is the one used. With FP32 duals the sweep marches through the
- * bands asked for in tiles of up to 1024 pixels fitted to the cube's rows and
- * columns (idle lanes cost time), and chooses the bands as well when none are
- * asked for; the nominal tiles tell how requests compare.
+ * BF16 duals its chunks and tiles are the ones used. With FP32 duals the sweep
+ * marches through the bands asked for in tiles of up to 1024 pixels fitted to the
+ * cube's rows and columns (idle lanes cost time), and chooses the bands as well
+ * when none are asked for; the nominal tiles tell how requests compare, and
+ * geo_sweep_tiles gives the tiles that run.
  *   dual_storage: GEO_STORE_F32 or GEO_STORE_BF16 (as in geo_params). A
  *       tile is 8 x 128 pixels, or 16 x 64 when the cube's width fills a
  *       64-wide tile grid more than 3% better (FP32 duals only).
@@ -247,9 +248,20 @@ int geo_sweep_geometry(geo_dims dims, int32_t dual_storage, int32_t requested, i
                        int32_t *used_chunk, int32_t *tiles, int32_t *tile_rows,
                        int32_t *tile_cols);
 
+/* The tiles that the sweep runs for one cube, alone or in a batch. Host-side only:
+ * no GPU work. Arguments and outputs as in geo_sweep_geometry, except that blocks
+ * (geo_sweep_blocks on the device that will run the cube) is read for every
+ * request. Tiles cover the cube from pixel (0, 0) and band 0 on, the last ones of
+ * a row, column or run of bands cut off at its edge.
+ * Errors: GEO_EINVAL for bad dims or storage type, requested < 0, blocks < 1,
+ * or a NULL output. */
+int geo_sweep_tiles(geo_dims dims, int32_t dual_storage, int32_t requested, int32_t blocks,
+                    int32_t *used_chunk, int32_t *tiles, int32_t *tile_rows,
+                    int32_t *tile_cols);
+
 /* Tile capacity of a solver workspace for these dims and storage: the
- * most tiles any band chunk that geo_sweep_geometry can report (for every
- * request and block count) gives the cube. The per-tile regions of the
+ * most tiles any band chunk that geo_sweep_geometry or geo_sweep_tiles can
+ * report (for every request and block count) gives the cube. The per-tile regions of the
  * workspace (partial sums, window statistics, candidate counts) hold that
  * many tiles. Host-only; no device needed.
  * Errors: GEO_EINVAL for bad dims, storage type or a NULL output. */
@@ -257,7 +269,8 @@ int geo_workspace_tiles(geo_dims dims, int32_t dual_storage, int32_t *max_tiles)
 
 /* Persistent blocks of the fused sweep on the current device: a launch
  * runs min(blocks, tiles of all its cubes) blocks, and each block takes
- * tiles in turn. dual_storage: GEO_STORE_F32 or GEO_STORE_BF16.
+ * tiles in turn (cubes whose bands are one tile of at most 256 pixels: up to
+ * four times as many, smaller ones). dual_storage: GEO_STORE_F32 or GEO_STORE_BF16.
  * Errors: GEO_EINVAL for a bad storage type or NULL output; GEO_EHIP
  * without a usable device. */
 int geo_sweep_blocks(int32_t dual_storage, int32_t *blocks);

@@ -119,6 +119,7 @@ def lib():
             "geo_strerror": [ctypes.c_int],
             "geo_batch_table_size": [i32, ctypes.POINTER(_sz)],
             "geo_sweep_geometry": [geo_dims, i32, i32, i32] + [ctypes.POINTER(i32)] * 4,
+            "geo_sweep_tiles": [geo_dims, i32, i32, i32] + [ctypes.POINTER(i32)] * 4,
             "geo_sweep_blocks": [i32, ctypes.POINTER(i32)],
             "geo_workspace_tiles": [geo_dims, i32, ctypes.POINTER(i32)],
             "geo_batch_step": [i32, ctypes.POINTER(geo_dims), P, ctypes.POINTER(_vp),
@@ -265,11 +266,23 @@ def geo_batch_table_size(n_cubes: int) -> int:
 def geo_sweep_geometry(dims, requested: int = 0, blocks: int = 0,
                        dual_storage: int = GEO_STORE_F32):
     """(bands per tile used, tiles, tile rows, tile columns) of the fused
-    sweep for one cube at the requested band chunk (0 = the library's
-    default for `blocks` persistent blocks)."""
+    sweep's nominal geometry for one cube at the requested band chunk (0 = the
+    library's default for `blocks` persistent blocks). geo_sweep_tiles gives
+    the tiles that run."""
     out = [ctypes.c_int32() for _ in range(4)]
     _check(lib().geo_sweep_geometry(dims, int(dual_storage), int(requested), int(blocks),
                                     *[ctypes.byref(x) for x in out]), "geo_sweep_geometry")
+    return tuple(x.value for x in out)
+
+
+def geo_sweep_tiles(dims, requested: int = 0, blocks: int = 0,
+                    dual_storage: int = GEO_STORE_F32):
+    """(bands per tile, tiles, tile rows, tile columns) that the sweep runs for
+    one cube on a device of `blocks` persistent blocks (geo_sweep_blocks) at
+    the requested band chunk (0 = the library's choice)."""
+    out = [ctypes.c_int32() for _ in range(4)]
+    _check(lib().geo_sweep_tiles(dims, int(dual_storage), int(requested), int(blocks),
+                                 *[ctypes.byref(x) for x in out]), "geo_sweep_tiles")
     return tuple(x.value for x in out)
 
 

@@ -572,6 +572,20 @@ int geo_sweep_geometry(geo_dims dims, int32_t dual_storage, int32_t requested, i
     return GEO_OK;
 }
 
+int geo_sweep_tiles(geo_dims dims, int32_t dual_storage, int32_t requested, int32_t blocks,
+                    int32_t *used_chunk, int32_t *tiles, int32_t *tile_rows, int32_t *tile_cols)
+{
+    if (!solver_dims_ok(dims) || (dual_storage != GEO_STORE_F32 && dual_storage != GEO_STORE_BF16) ||
+        requested < 0 || blocks < 1 || !used_chunk || !tiles || !tile_rows || !tile_cols)
+        return GEO_EINVAL;
+    const SweepGrid g = cube_grid(dims.n1, dims.n2, dims.n3, requested, blocks, dual_storage == GEO_STORE_BF16 ? 2 : 4);
+    *used_chunk = g.kc;
+    *tiles = g.blocks();
+    *tile_rows = g.rows;
+    *tile_cols = g.cols;
+    return GEO_OK;
+}
+
 int geo_workspace_tiles(geo_dims dims, int32_t dual_storage, int32_t *max_tiles_out)
 {
     if (!solver_dims_ok(dims) || (dual_storage != GEO_STORE_F32 && dual_storage != GEO_STORE_BF16) ||

@@ -173,7 +173,7 @@ constexpr int kTileRows = kShapeTI[0], kTileCols = kShapeTJ[0], kTileSpan = kTil
 // kSmallThreads pixels, kSmallSpan rows and columns together and kSmallCols columns:
 // in 1024 threads most wavefronts go through every instruction of a band for nothing.
 constexpr int kForms = 3, kSmallForm = 2;
-constexpr int kSmallThreads = 256, kSmallSpan = 40, kSmallCols = 32;
+constexpr int kSmallThreads = 256, kSmallSpan = 40, kSmallCols = 32, kSmallPerWide = 4;
 constexpr int kDefaultKC = 32;       // deepest default chunk (the rule below picks 8..32)
 constexpr int kMinKC = 8;
 constexpr int kMaxTiles = 4096;      // tiles of one cube (slices of its search)
@@ -360,9 +360,9 @@ inline SweepGrid fitted_grid(int n1, int n2, int n3, int requested, int blocks)
     return best;
 }
 // One tile per band in the small form, for the cubes it takes: as many chunks as its
-// resident blocks, so that one round of them does (BF16: the nominal chunk, whose
-// tiles a query has promised; one nominal tile per band).
-inline bool small_grid(int n1, int n2, int n3, int requested, int blocks, int small_blocks, int dual_bytes, SweepGrid *g)
+// resident blocks (kSmallPerWide for each of the other forms), so that one round of
+// them does (BF16: the nominal chunk, one nominal tile per band).
+inline bool small_grid(int n1, int n2, int n3, int requested, int blocks, int dual_bytes, SweepGrid *g)
 {
     if ((int64_t)n1 * n2 > kSmallThreads || n1 + n2 > kSmallSpan || n2 > kSmallCols) return false;
     if (dual_bytes == 2 && n1 > kTileRows) return false;
@@ -370,7 +370,7 @@ inline bool small_grid(int n1, int n2, int n3, int requested, int blocks, int sm
     if (requested > 0 || dual_bytes == 2) {
         kc = band_chunk(n1, n2, n3, requested, blocks, 0);
     } else {
-        const int most = max_tiles(n1, n2, n3);
+        const int most = max_tiles(n1, n2, n3), small_blocks = kSmallPerWide * blocks;
         kc = ceil_div(n3, most < small_blocks ? most : small_blocks);
     }
     *g = SweepGrid{1, 1, ceil_div(n3, kc), kc, kSmallForm, n1, n2};
@@ -378,10 +378,10 @@ inline bool small_grid(int n1, int n2, int n3, int requested, int blocks, int sm
 }
 // The tiles of a cube: a function of its size and storage, the request and the
 // device only, so that a cube runs the same ones alone and in a batch.
-inline SweepGrid cube_grid(int n1, int n2, int n3, int requested, int blocks, int small_blocks, int dual_bytes)
+inline SweepGrid cube_grid(int n1, int n2, int n3, int requested, int blocks, int dual_bytes)
 {
     SweepGrid g;
-    if (small_grid(n1, n2, n3, requested, blocks, small_blocks, dual_bytes, &g)) return g;
+    if (small_grid(n1, n2, n3, requested, blocks, dual_bytes, &g)) return g;
     if (dual_bytes == 4) return fitted_grid(n1, n2, n3, requested, blocks);
     const int shape = tile_shape(n1, n2, dual_bytes);
     return sweep_grid(n1, n2, n3, band_chunk(n1, n2, n3, requested, blocks, shape), shape);

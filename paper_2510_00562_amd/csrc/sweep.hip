@@ -821,8 +821,7 @@ void cube_entry_t(CubeArgs<DT> *a, const Dims &d, const float *v, void *ws, cons
         c.zbuf = (float *)(b + L.zbuf);
     }
     c.ccount = (uint32_t *)(b + L.ccount);
-    c.g = cube_grid(d.n1, d.n2, d.n3, p->band_chunk, sweep_grid_of(sizeof(DT), 0, 1 << 30),
-                    sweep_grid_of(sizeof(DT), kSmallForm, 1 << 30), (int)sizeof(DT));
+    c.g = cube_grid(d.n1, d.n2, d.n3, p->band_chunk, sweep_grid_of(sizeof(DT), 0, 1 << 30), (int)sizeof(DT));
     c.ntiles = c.g.blocks();
     c.capt = (int)(L.cap / c.ntiles);
     c.tile0 = tile0;
