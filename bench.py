@@ -47,6 +47,8 @@ def phase_bytes(db):
 
 
 PHASE_BYTES = phase_bytes(4)
+# what the phases of geo_step_profiled are with FP32 duals
+FUSED_PHASES = {"sweep_a": "sweep", "l1_select": "missed_windows", "sweep_b": "search"}
 ALGO_BYTES_ITER = algo_bytes_iter(4)
 
 
@@ -265,7 +267,9 @@ def main():
                      "copy_ceiling": copy_bps / 1e9, "frac_of_copy": achieved / copy_bps,
                      "traffic_rate": None if traffic is None else traffic / avg_s / 1e9},
         "iteration_hbm_frac": algo_bytes_iter(db) * value / HBM_PEAK,
-        "phase_ms_per_step": {k: v_ / K for k, v_ in phase_ms.items()},
+        # (FP32 duals: the sweep, the passes of missed windows, the search)
+        "phase_ms_per_step": {(k if db == 2 else FUSED_PHASES[k]): v_ / K
+                              for k, v_ in phase_ms.items()},
         "last": {"rel_change": res.rel_change, "r": res.r, "tau_s": res.tau_s,
                  "tau_t": res.tau_t, "iters": res.total_iters},
         # the timed call: launch slots issued (one per iteration: a missed

@@ -223,12 +223,15 @@ def geo_step(dims, p, v, ws: Workspace, n_iter: int, stream=None) -> geo_result:
     return out
 
 
+# The phases of geo_step_profiled, named after the two-sweep form of an iteration,
+# which BF16 duals run. With FP32 duals: the fused sweep, the histogram passes of
+# missed windows, the end of the iteration with the search of the next thresholds.
 PHASES = ("sweep_a", "l1_select", "sweep_b")
 
 
 def geo_step_profiled(dims, p, v, ws: Workspace, n_iter: int, stream=None):
     """geo_step with per-phase GPU times (HIP events): returns
-    (geo_result, {phase: summed milliseconds})."""
+    (geo_result, {phase of PHASES: summed milliseconds})."""
     out = geo_result()
     ms = (ctypes.c_double * len(PHASES))()
     _check(lib().geo_step_profiled(dims, ctypes.byref(p), _f32(v), ws.ptr, ws.nbytes, int(n_iter),
