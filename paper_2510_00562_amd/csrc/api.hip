@@ -308,13 +308,14 @@ int geo_state_init(geo_dims dims, const geo_params *p, const float *v, void *ws,
 
 // One solver call over n cubes (n = 1: the single-cube entry points). The
 // launch table (host image `ent`, device copy at `table`) is written once;
-// each launch slot (the three histogram passes of a missed window, the sweep,
-// the search) completes one iteration of every busy cube.
+// each launch slot (the histogram passes of a missed window, the sweep, the search;
+// BF16 duals: sweep A, the search, the passes, sweep B, the finalize) completes one
+// iteration of every busy cube.
 // With a tolerance the host reads the stopping flags every check_every
 // slots; the device idles a cube once it has met its rule or done n_iter
 // iterations.
 // phase_ms (may be null): nph = GEO_NPHASE phase times (4 events in every
-// slot), or nph = 1 for sweep A alone: 2 events around it in every
+// slot), or nph = 1 for the (first) sweep alone: 2 events around it in every
 // kTimedEvery-th slot, from the kTimedEvery-th on (the first slot of a call
 // follows a host synchronisation and starts from an idle device), the
 // sampled times scaled to all slots (an event pair costs a few
@@ -340,11 +341,10 @@ static int run_cubes(int n, const geo_dims *dims, const geo_params *p, const flo
     sh.ncubes = n;
     for (int c = 0; c < n; ++c) {
         int nt = 0, nb = 0;
-        cube_entry(&ent[c], to_dims(dims[c]), v[c], ws[c], L[c], &p[c], n_iter, sh.total_tiles, sh.total_b, &nt, &nb);
+        cube_entry(&ent[c], to_dims(dims[c]), v[c], ws[c], L[c], &p[c], n_iter, sh.total_b, &nt, &nb);
         // the workspace's per-tile regions hold every chunk band_chunk gives
         // (make_layout); this only guards that invariant
         if (nt > L[c].max_tiles) return GEO_EWORKSPACE;
-        sh.total_tiles += nt;
         sh.total_b += nb;
         sh.b_kinds |= sweep_b_cpt(dims[c].n2) == 4 ? 2 : 1;
         sh.form_tiles[reinterpret_cast<const CubeCommon *>(ent[c].bytes)->g.form] += nt;

@@ -106,10 +106,6 @@ __device__ __forceinline__ void st2_nt(bf16x2 *p, float2 x)
     __builtin_nontemporal_store(bits, &p->bits);
 }
 
-// One component (c = 0 first, 1 second) of a stored pair, nontemporal.
-__device__ __forceinline__ void st_comp_nt(float2 *p, int c, float x) { st_nt(reinterpret_cast<float *>(p) + c, x); }
-__device__ __forceinline__ void st_comp_nt(bf16x2 *p, int c, float x) { st_nt(reinterpret_cast<bf16 *>(p) + c, x); }
-
 // Loads of values no other thread or tile reads (no halo reuse).
 __device__ __forceinline__ float ld_nt(const float *p)
 {
@@ -176,7 +172,16 @@ __device__ __forceinline__ float soft(float z, double tau)
 // element size, and the compiler knows exactly how many loads are in flight
 // when one of them is needed.
 using BandRsrc = __amdgpu_buffer_rsrc_t;
-constexpr uint32_t kNoPix = 0x0c000000u;  // times 2, 4, 8, 16: past any band (< 2^27 bytes)
+// The index of a missing pixel. Its byte offset, for elements of 2 to 16 bytes, lies
+// past every band that goes this way: fewer than 2^22 pixels of up to 16 bytes in
+// the solver's sweeps, 2^26 of 4 in the operators, 2^27 of up to 8 in the
+// regularizers' sweep. So does, in the first two, that of a missing pixel's
+// neighbours a row above or below, and everywhere that of a pixel above the first
+// row (negative, so near 2^32). (In a regularizer's band of one row of more than
+// 100M pixels a missing pixel's neighbour above may be a pixel: what it loads is
+// not used.)
+constexpr uint32_t kNoPix = 0x0c000000u;
+static_assert(kNoPix <= 0xffffffffu / 16, "offsets of missing pixels do not wrap");
 template <typename T>
 __device__ __forceinline__ BandRsrc band_of(const T *p, int64_t first, uint32_t count)
 {

@@ -196,6 +196,7 @@ __global__ __launch_bounds__(NT) void k_apply(int op, int adj, Dims d, const flo
 // its index with 64-bit divisions and reads a plane once per output plane that
 // needs it: K and its adjoint at 256 x 256 x 128 took 324 and 543 us.
 constexpr uint32_t kOpsPixels = 1u << 26;
+static_assert(kOpsPixels <= kNoPix - kOpsPixels, "a missing pixel and its neighbours lie past a band");
 
 struct OpView {
     const float *in;

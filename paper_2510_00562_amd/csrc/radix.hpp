@@ -272,7 +272,7 @@ __device__ inline void init_scalars(DevScalars *sc, double eps, double tol, doub
 }
 
 // Append val to this block's slice of a field's candidate list. The slot
-// comes from an LDS counter (wavefront-aggregated), so sweep A never waits on
+// comes from an LDS counter (wavefront-aggregated), so a sweep never waits on
 // a global atomic; entries past the slice's capacity are counted but
 // dropped, which the search detects as an overflow. Every lane of the
 // wavefront must call it.
@@ -334,7 +334,7 @@ constexpr uint32_t kCalmNarrow = 8;
 constexpr double kAheadFill = 8192.0;
 constexpr uint32_t kAheadCalm = 6;
 
-// Window of |z| that sweep A collects for the next iteration. tau is
+// Window of |z| that the sweep collects for the next iteration. tau is
 // extrapolated from the last levels: quadratically once four are known (the
 // levels follow a smooth path after the first iterations, and the quadratic
 // error is a fraction of the linear one there), linearly from two or three.

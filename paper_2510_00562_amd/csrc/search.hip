@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kSrThreads) void k_search(const char *table, int st
         int buf = 0;
         double wlo = lo, whi = hi;  // the range searched in LDS
         if (total <= (uint32_t)kSrList) {
-            // positions tid, tid + 256, ... of the tiles' slices one after
+            // positions tid, tid + kSrThreads, ... of the tiles' slices one after
             // another, a batch of loads in flight; a thread reads back only what
             // it staged
             // (a batch no larger than what there is: 2K candidates in batches of

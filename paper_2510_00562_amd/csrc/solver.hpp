@@ -13,32 +13,34 @@
 namespace geo {
 
 // Exact l1-ball threshold search state for one field. In steady state the
-// level tau moves little between iterations: sweep A collects the values of
-// |z| inside a window [win_lo, win_hi] predicted from the last two levels
+// level tau moves little between iterations: the sweep collects the values of
+// |z| inside a window [win_lo, win_hi] predicted from the last levels
 // (candidates) plus the count and sum of the values above it, and one block
-// finishes the search exactly over the candidates. When the window misses,
-// a radix search over the FP32 bit patterns of the whole field runs instead,
-// in the same launch slot (fallback.hip, radix.hpp).
+// finishes the search exactly over the candidates. With FP32 duals the sweep of an
+// iteration collects for the search of the next iteration's level, which follows it
+// (search.hip; tau is then the next iteration's from the search on), with BF16
+// duals sweep A collects for its own (select.hip). When the window misses, a radix
+// search over the FP32 bit patterns of the whole field runs instead (fallback.hip,
+// radix.hpp), before the sweep that needs the level.
 struct SelState {
     double radius;     // radius of the l1 ball
     double s_above;    // radix search: sum of |z| above the current bit range
-    double tau;        // soft-threshold level of this iteration
-    double tau_prev;   // level of the previous iteration (window prediction)
+    double tau;        // soft-threshold level
+    double tau_prev;   // level of the iteration before (window prediction)
     double tau_prev2;  // and of the one before
     double tau_prev3;  // and of the one before that
     uint64_t c_above;  // radix search: count of those values
     uint32_t prefix;   // radix search: pattern bits fixed so far
-    uint32_t done;     // tau final for this iteration
+    uint32_t done;     // tau final
     uint32_t level;    // next radix level (0, 1, 2)
     uint32_t full;     // 1 when the radix search over the full field runs
-    float win_lo, win_hi;  // window used by the next sweep A
+    float win_lo, win_hi;  // window of the next sweep
     uint32_t win_on;       // window valid
     uint32_t cand_count;   // candidates in the window (search bookkeeping)
     double dens;           // values of |z| per unit near tau in the last
                            // iteration (sizes the next window)
     double err;            // error of the last prediction of tau (FP32 duals)
     uint32_t calm;         // windows in a row that held tau
-    uint32_t finished;     // standalone projection: blocks of a pass that are done
 };
 
 constexpr int kHistBins = 2048;  // bins of radix level 0 (levels 1 and 2 use 1024)
@@ -51,8 +53,9 @@ struct Hist {
 };
 
 // Outcome of one radix level of a field whose window missed, written by the
-// histogram pass of that level (fallback.hip) and read by the next pass,
-// sweep B and the finalize of the same launch slot.
+// histogram pass of that level (fallback.hip) and read by the next pass and by
+// what follows the passes in the same launch slot: the search (FP32 duals) or sweep
+// B and the finalize (BF16).
 struct FbRec {
     double tau;      // the threshold, when the level ended the search
     double s_above;  // sum and count of the values above the chosen bin
@@ -149,7 +152,7 @@ struct Layout {
     size_t y1[2], y2[2], y3[2], y4[2];      // duals (FP32 or BF16), ping-pong
     size_t total;
     int dual_bytes;
-    int max_tiles;  // most sweep A tiles of any band chunk the library may use
+    int max_tiles;  // most sweep tiles of any band chunk the library may use
     int64_t cap;    // candidate capacity per field
 };
 
@@ -185,7 +188,7 @@ constexpr uint32_t kGridMost = 1u << 23;
 static_assert((uint64_t)kGridMost * kPointThreads < 1ull << 32, "a launch of kGridMost blocks is valid");
 constexpr int kSweepBBlocks = 2048;  // grid-stride blocks of sweep B per cube
 constexpr int kSweepBRows = 2;       // rows of a sweep B strip
-constexpr int kTimedEvery = 8;  // geo_step_timed: events around every 8th sweep A
+constexpr int kTimedEvery = 8;  // geo_step_timed: events around every 8th sweep
 
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
@@ -404,7 +407,7 @@ struct Side {
 
 // Layout of w1 and w2 (6N floats each): the ud and lr pairs of a voxel side
 // by side, [ud_v, ud_h, lr_v, lr_h] (N float4), then the c pairs (N float2),
-// so that sweep A moves one field of a voxel in a 16-byte and an 8-byte
+// so that the sweep moves one field of a voxel in a 16-byte and an 8-byte
 // access.
 __host__ __device__ inline float4 *w_udlr(float2 *w) { return reinterpret_cast<float4 *>(w); }
 __host__ __device__ inline const float4 *w_udlr(const float2 *w) { return reinterpret_cast<const float4 *>(w); }
@@ -418,10 +421,9 @@ __host__ __device__ inline float2 *w_pair(float2 *w, int64_t n, int g, int64_t q
 
 // Everything the iteration kernels need about one cube. A launch covers a
 // table of these in device memory (one entry for a single cube, up to
-// kMaxBatch for a batch): sweep A walks the concatenated tile list of the
-// cubes still working, the search takes one block per (cube, field), sweep B
-// a block range per cube and the finalize one block per cube. Stopped cubes
-// are skipped.
+// kMaxBatch for a batch): the sweep walks the tiles of the cubes still working, the
+// search takes one block per (cube, field), with BF16 duals sweep B a block range
+// per cube and the finalize one block per cube. Stopped cubes are skipped.
 struct CubeCommon {
     Dims d;
     const float *v;
@@ -441,7 +443,6 @@ struct CubeCommon {
     int capt;           // candidate capacity of one tile slice
     int ntiles;
     SweepGrid g;
-    int tile0;          // first tile of this cube in the launch's full tile list
     int b0, nb;         // sweep B blocks of this cube (BF16): first, count
     float thr1;         // omega * step of w1
     float zt_step;      // step size of t in z_t (the histogram passes evaluate z_t)
@@ -471,36 +472,9 @@ struct CubeArgs {
 template <typename T>
 using const4 = const __attribute__((address_space(4))) T;
 
-template <typename DT>
-__device__ __forceinline__ Side<DT> load_side(const4<Side<DT>> &s)
-{
-    Side<DT> o;
-    o.u = s.u;
-    o.s = s.s;
-    o.t = s.t;
-    o.w1 = s.w1;
-    o.w2 = s.w2;
-    o.y1 = s.y1;
-    o.y2 = s.y2;
-    o.y3 = s.y3;
-    o.y4 = s.y4;
-    return o;
-}
-__device__ __forceinline__ Dims load_dims(const4<Dims> &d)
-{
-    Dims o;
-    o.n1 = d.n1;
-    o.n2 = d.n2;
-    o.n3 = d.n3;
-    o.plane = d.plane;
-    return o;
-}
-
 // Shape of one launch slot over a table of cubes.
 struct LaunchShape {
     int ncubes;
-    int total_tiles;  // sweep A tiles over all cubes
-    int grid_a;       // persistent sweep blocks
     int total_b;      // sweep B blocks over all cubes (BF16)
     int b_kinds;      // sweep B forms present: 1 one or two columns per thread, 2 four
     int form_tiles[kForms];  // sweep tiles of the cubes of each kernel form
@@ -552,11 +526,10 @@ __device__ inline void passes_over(uint32_t *flags)
 // ---- launchers (kernels in sweep.hip / select.hip / ops.hip) ----
 hipError_t launch_init(const Dims &d, const float *v, void *ws, const Layout &L, double eps,
                        double tol, double alpha, double beta, hipStream_t st);
-// Fill e for the cube (d, v, ws) with band chunk kc and the call's
-// parameters; tile0/b0 place it in the launch; returns its tile and sweep B
-// block counts.
+// Fill e for the cube (d, v, ws) with the call's parameters; b0 places it in the
+// launch of sweep B; returns its tile and sweep B block counts.
 void cube_entry(CubeEntry *e, const Dims &d, const float *v, void *ws, const Layout &L, const geo_params *p,
-                 int n_iter, int tile0, int b0, int *ntiles, int *nb);
+                int n_iter, int b0, int *ntiles, int *nb);
 int sweep_grid_of(int dual_bytes, int form, int tiles);
 // One launch slot over the table (device copy of the entries). ev (may be
 // null): nev = 4 events recorded at the phase boundaries (FP32: before and

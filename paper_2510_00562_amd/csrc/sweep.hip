@@ -34,8 +34,8 @@
 // a 2-pixel halo in LDS, recomputes w' on a 1-pixel ring, u' on the
 // (i+1, j+1) ring and t' on the rows above and below, and updates y1, y2, y3
 // from LDS; the D_s coupling of neighbouring bands is carried in LDS. Global
-// loads of band k+1 (w) and k+2 (y, u, v, y4, s, t, y3) are issued while band
-// k is computed, so the memory latency overlaps the arithmetic.
+// loads of bands k+1 (w), k+2 (u, v, y4, s, t, y3) and k+3 (y) are issued while
+// band k is computed, so the memory latency overlaps the arithmetic.
 //
 // Every state array is ping-ponged: iteration k reads side (k & 1) and writes
 // side ((k + 1) & 1), so halo reads never race with writes. The side comes
@@ -68,6 +68,8 @@ struct Planes {
 };
 using Wide = Planes<kSweepThreads, kTileSpan, kTileCols>;  // 8 x 128 fills them
 using Small = Planes<kSmallThreads, kSmallSpan, kSmallCols>;
+static_assert((uint64_t)kMaxTiles * kSweepThreads <= 1u << 22 && 1u << 22 <= kNoPix - (1u << 22),
+              "a missing pixel and its neighbours lie past a band");
 static_assert(kTileRows * kTileCols == Wide::NT && kTileRows + kTileCols == kTileSpan, "the fixed tile fills the planes");
 template <int S>
 using PlanesOf = std::conditional_t<S == kSmallForm, Small, Wide>;
@@ -714,7 +716,7 @@ __global__ __launch_bounds__(NPT) void k_state_io(Dims d, Side<DT> s0, Side<DT> 
                 break;
             case GEO_VAR_Y1:
             case GEO_VAR_Y2:
-                // both sides: sweep A never rewrites the masked entries
+                // both sides: the sweep never rewrites the masked entries
                 if (pl == 0) {
                     const float2 y = make_float2(in[q], in[q + N]);
                     st2((var == GEO_VAR_Y1 ? s0.y1 : s0.y2) + q, y);
@@ -800,7 +802,7 @@ int resident_grid()
 
 template <typename DT>
 void cube_entry_t(CubeArgs<DT> *a, const Dims &d, const float *v, void *ws, const Layout &L, const geo_params *p,
-                  int n_iter, int tile0, int b0, int *ntiles, int *nb)
+                  int n_iter, int b0, int *ntiles, int *nb)
 {
     char *b = (char *)ws;
     memset(a, 0, sizeof *a);
@@ -824,7 +826,6 @@ void cube_entry_t(CubeArgs<DT> *a, const Dims &d, const float *v, void *ws, cons
     c.g = cube_grid(d.n1, d.n2, d.n3, p->band_chunk, sweep_grid_of(sizeof(DT), 0, 1 << 30), (int)sizeof(DT));
     c.ntiles = c.g.blocks();
     c.capt = (int)(L.cap / c.ntiles);
-    c.tile0 = tile0;
     c.thr1 = (float)(p->omega * 0.25);
     c.zt_step = kStepT;
     c.mu_lo = (float)p->mu_lo;
@@ -905,12 +906,12 @@ hipError_t slot_two(const void *table, const LaunchShape &sh, hipStream_t st, hi
 }  // namespace
 
 void cube_entry(CubeEntry *e, const Dims &d, const float *v, void *ws, const Layout &L, const geo_params *p,
-                int n_iter, int tile0, int b0, int *ntiles, int *nb)
+                int n_iter, int b0, int *ntiles, int *nb)
 {
     if (L.dual_bytes == 2)
-        cube_entry_t<bf16>(reinterpret_cast<CubeArgs<bf16> *>(e->bytes), d, v, ws, L, p, n_iter, tile0, b0, ntiles, nb);
+        cube_entry_t<bf16>(reinterpret_cast<CubeArgs<bf16> *>(e->bytes), d, v, ws, L, p, n_iter, b0, ntiles, nb);
     else
-        cube_entry_t<float>(reinterpret_cast<CubeArgs<float> *>(e->bytes), d, v, ws, L, p, n_iter, tile0, b0, ntiles, nb);
+        cube_entry_t<float>(reinterpret_cast<CubeArgs<float> *>(e->bytes), d, v, ws, L, p, n_iter, b0, ntiles, nb);
 }
 
 // Persistent sweep grid of a form: resident blocks, at most one per tile, a multiple

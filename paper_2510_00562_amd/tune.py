@@ -8,8 +8,9 @@ on the cube sizes, so this tuner times a few candidates on the caller's own
 states, in steady state, and returns the fastest one. It uses only the C
 ABI (geo_batch_step) and leaves every state back at Alg. 1's initial point.
 The model that ranks the candidates counts the nominal tiles of
-geo_sweep_geometry; the library may fit a tile's pixels to the cube, which
-the timing sees.
+geo_sweep_geometry, dealt to the XCDs as one list; with FP32 duals the library
+fits a tile's pixels to the cube (geo_sweep_tiles), and it deals each cube's tiles
+over all XCDs. The ranking only chooses what is timed.
 """
 from __future__ import annotations
 
@@ -20,8 +21,8 @@ CANDIDATES = (16, 32, 64)
 
 def _busiest_block(cost, G):
     """Longest per-block total when G persistent blocks take the tiles of
-    `cost` (in the sweep's order) as the sweep hands them out: each of the 8
-    XCDs a contiguous eighth of the list, its blocks every (G/8)-th tile."""
+    `cost` (in the sweep's order) as the sweep hands out those of one cube: each
+    of the 8 XCDs a contiguous eighth of the list, its blocks every (G/8)-th tile."""
     import numpy as np
     T = cost.size
     if T == 0:
@@ -46,7 +47,7 @@ def model_candidates(dims, dual_storage=0, n=4, c0=2.0, lo=8, hi=64):
     A tile costs its bands plus c0 band-equivalents of fixed work (its halo
     band, the pipeline fill, its partial sums). The model lays the tiles of
     the cubes out in the sweep's order, hands them to the G persistent
-    blocks as the sweep does, and takes the busiest block's total as the
+    blocks as one list, and takes the busiest block's total as the
     sweep's length; cubes of the two tile shapes run in two launches one
     after the other, so their lengths add. Deep chunks leave blocks idle
     when there are few tiles, shallow ones pay the fixed work more often,

@@ -12,7 +12,14 @@ N = (1 << 35) + 5
 MARKS = (0, 1 << 34, (1 << 34) - 1, (1 << 35) - 1, 1 << 35, N - 1)
 
 
+@pytest.fixture(autouse=True)
+def give_back():
+    yield
+    torch_cuda().cuda.empty_cache()
+
+
 def buffer(torch):
+    torch.cuda.empty_cache()
     free, _ = torch.cuda.mem_get_info()
     if free < 4 * N + (8 << 30):
         pytest.skip("needs 136 GiB of device memory")
