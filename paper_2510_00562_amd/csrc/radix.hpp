@@ -417,13 +417,24 @@ __host__ __device__ inline double window_budget(int64_t n)
 }
 
 // FP32 duals: less where N/256 would overflow the 32768 that search.hip holds in
-// LDS: 24576, room for the error of the estimate, or N/1024. It streams what does
-// not fit, on one CU, and the passes over all of them cost less than they did and
-// go with those of the other field. With N/256 the first 24 iterations of
-// 512 x 512 x 224 took 55.5 ms (16 missed windows, now 24: 53.4; N/2048 30: 54.4),
-// with 32768 or N/512 the first 30 of 2048 x 2048 x 4 26.7 ms, now 24.9, 25 of
-// 256 x 256 x 128 9280 us, now 9207. Less than 20480 for small cubes (12288, 8192):
-// 64 x 64 x 16 1100 and 1133 instead of 1090 us, 120 x 120 x 198 8345 instead of 8297.
+// LDS: 24576, room for the error of the estimate, or N/1024. A wide window pays while
+// its search costs less than the miss that a narrow one risks. Of one field, in us:
+//   a search   9 and 2 for each thousand candidates held in LDS (256 x 256 x 128: 22 with
+//              8.1K, 57 to 67 with 24.5K); streamed, on one CU, 1 to 3 for each thousand
+//              (512 x 512 x 224: 75 to 120 with 56K, 160 to 230 in the first ones); with
+//              4096 tiles 30 more (2048 x 2048 x 4)
+//   a miss     50 and 5 for each million voxels, over all CUs (64 x 64 x 16 55, 256 x 256
+//              x 128 90, 2048 x 2048 x 4 124, 512 x 512 x 224 330; the other field of the
+//              same slot adds a third to two thirds)
+// so that a search at the budget takes two thirds of a miss at 8M voxels, half at 17M
+// and a quarter to a third at 59M: more values than that would have to save almost
+// every miss they cover, and windows grow by less than half from one iteration to
+// the next while they miss. Whole solves move by 0.5 to 4% over the range (with
+// N/256 the first 24 iterations of 512 x 512 x 224 took 55.5 ms, now 53.4, with N/2048
+// 54.4; with 32768 or N/512 the first 30 of 2048 x 2048 x 4 26.7 ms, now 24.9; 25 of
+// 256 x 256 x 128 9280 and 9207 us), a miss more or less among it. Less than 20480 for
+// small cubes (12288, 8192): 64 x 64 x 16 1100 and 1133 instead of 1090 us, 120 x 120 x
+// 198 8345 instead of 8297.
 __host__ __device__ inline double ahead_budget(int64_t n)
 {
     const double most = (double)n / 1024.0 > 24576.0 ? (double)n / 1024.0 : 24576.0;
