@@ -349,6 +349,14 @@ static int run_cubes(int n, const geo_dims *dims, const geo_params *p, const flo
         sh.b_kinds |= sweep_b_cpt(dims[c].n2) == 4 ? 2 : 1;
         sh.form_tiles[reinterpret_cast<const CubeCommon *>(ent[c].bytes)->g.form] += nt;
     }
+    if (L[0].dual_bytes == 4 && sh.form_tiles[0] + sh.form_tiles[1] > 0 && sh.form_tiles[kSmallForm] <= kSmallMerge) {
+        sh.form_tiles[1] += sh.form_tiles[kSmallForm];
+        sh.form_tiles[kSmallForm] = 0;
+        for (CubeEntry &e : ent) {
+            SweepGrid &g = reinterpret_cast<CubeCommon *>(e.bytes)->g;
+            if (g.form == kSmallForm) g.form = 1;
+        }
+    }
     sh.fb_grid = fallback_grid();
     for (int q = 0; q < kForms; ++q)
         sh.form_grid[q] = sh.form_tiles[q] > 0 ? sweep_grid_of(L[0].dual_bytes, q, sh.form_tiles[q]) : 0;

@@ -175,8 +175,14 @@ constexpr int kTileRows = kShapeTI[0], kTileCols = kShapeTJ[0], kTileSpan = kTil
 // threads, four to a compute unit, for cubes whose bands are one tile of at most
 // kSmallThreads pixels, kSmallSpan rows and columns together and kSmallCols columns:
 // in 1024 threads most wavefronts go through every instruction of a band for nothing.
+// Form 1 gives the same bits for the same tiles: a thread has the same pixel, and the
+// sums over a tile add zeros for the other wavefronts. A batch with a few tiles of
+// such cubes among others (kSmallMerge or fewer, FP32 duals) runs them in form 1 with
+// the rest, without a launch of their own (577 us an iteration against 603 with one
+// cube of 8 x 8 x 8 among five images).
 constexpr int kForms = 3, kSmallForm = 2;
 constexpr int kSmallThreads = 256, kSmallSpan = 40, kSmallCols = 32, kSmallPerWide = 4;
+constexpr int kSmallMerge = 256;
 constexpr int kDefaultKC = 32;       // deepest default chunk (the rule below picks 8..32)
 constexpr int kMinKC = 8;
 constexpr int kMaxTiles = 4096;      // tiles of one cube (slices of its search)
@@ -362,13 +368,16 @@ inline SweepGrid fitted_grid(int n1, int n2, int n3, int requested, int blocks)
     }
     return best;
 }
-// One tile per band in the small form, for the cubes it takes: as many chunks as its
+// One tile per band, for the cubes that the small form takes: as many chunks as its
 // resident blocks (kSmallPerWide for each of the other forms), so that one round of
-// them does (BF16: the nominal chunk, one nominal tile per band).
+// them does. BF16 duals: the nominal chunk, one nominal tile per band, and only
+// cubes of more bands than the other forms have blocks (of fewer, every band gets a
+// workgroup anyway, and the launch of its own would cost a batch more: 612 -> 647 us
+// an iteration with one cube of 8 x 8 x 8 among five images).
 inline bool small_grid(int n1, int n2, int n3, int requested, int blocks, int dual_bytes, SweepGrid *g)
 {
     if ((int64_t)n1 * n2 > kSmallThreads || n1 + n2 > kSmallSpan || n2 > kSmallCols) return false;
-    if (dual_bytes == 2 && n1 > kTileRows) return false;
+    if (dual_bytes == 2 && (n1 > kTileRows || n3 <= blocks)) return false;
     int kc;
     if (requested > 0 || dual_bytes == 2) {
         kc = band_chunk(n1, n2, n3, requested, blocks, 0);

@@ -1,9 +1,10 @@
 """The sweep's small form (256 threads, cubes whose bands are one tile of at most 256
-pixels, 40 rows and columns together and 32 columns; BF16 duals: 8 rows): its largest
-tiles, single pixels, rows and columns, and the first sizes past each limit, with
-FP32 and BF16 duals; many chunks of bands, one band each and bands left over; all
-forms in one batch. Tolerances are those of the tests whose checks are used. And the
-time of an iteration over single spectra beside that of as many voxels in larger
+pixels, 40 rows and columns together and 32 columns; BF16 duals: 8 rows and more than
+256 bands): its largest tiles, single pixels, rows and columns, and the first sizes
+past each limit, with FP32 and BF16 duals; many chunks of bands, one band each and
+bands left over; with cubes of the other forms in one batch, in a launch of its own
+and among their tiles. Tolerances are those of the tests whose checks are used. And
+the time of an iteration over single spectra beside that of as many voxels in larger
 bands."""
 import time
 
@@ -29,7 +30,8 @@ def test_one_step(ora, shape):
     one_step(ora, shape)
 
 
-@pytest.mark.parametrize("shape", [(5, 8, 32), (3, 9, 16), (6, 1, 32), (40, 1, 1), (7, 8, 19), (300, 3, 3), (5, 16, 16)])
+@pytest.mark.parametrize("shape", [(260, 8, 32), (257, 9, 16), (270, 1, 32), (400, 1, 1), (256, 8, 19), (300, 3, 3),
+                                   (40, 8, 5)])
 def test_one_step_bf16(ora, shape):
     bf16_one_step(ora, shape)
 
@@ -40,12 +42,18 @@ def test_many_chunks(ora, shape, chunk):
     follow_the_oracle(ora, shape, chunk)
 
 
-def test_every_form_in_one_batch():
+@pytest.mark.parametrize("shapes", [
+    # 743 small tiles: a launch of their own
+    [(40, 9, 11), (5, 33, 33), (9, 24, 128), (700, 1, 2), (3, 16, 16), (12, 16, 256)],
+    # 43 and 256: with the others, in 1024 threads (alone in 256)
+    [(40, 9, 11), (5, 33, 33), (9, 24, 128), (3, 16, 16), (12, 16, 256)],
+    [(250, 16, 16), (6, 7, 30), (9, 24, 128)],
+])
+def test_every_form_in_one_batch(shapes):
     """Small tiles, fitted ones and 8 x 128: the bits of each cube alone."""
-    announce("small, fitted and fixed tiles in one batch")
+    announce(f"small, fitted and fixed tiles in one batch: {shapes}")
     torch_cuda()
     import paper_2510_00562_amd as geo
-    shapes = [(40, 9, 11), (5, 33, 33), (9, 24, 128), (700, 1, 2), (3, 16, 16), (12, 16, 256)]
     st = [setup(s, 0) for s in shapes]
     table = geo.Workspace(geo.geo_batch_table_size(len(st)))
     geo.geo_batch_step([x[2] for x in st], [x[4] for x in st], [x[3] for x in st], [x[5] for x in st], table, 20,
